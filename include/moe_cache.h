@@ -239,7 +239,8 @@ int moe_cache_prefill_pins(moe_cache_t* cache, int32_t layer, const int32_t* exp
  * is executed as consecutive waves of tokens (the batch is halved until every wave
  * fits; one token always fits); routing, hits, misses, evictions and outputs are the
  * same as for the unsplit call, only slower.
- * Host waits: none for batch 1, or for a cache that holds every expert (C >= E), on bf16 experts in the tiled
+ * Host waits: none on a layer all of whose experts are known to be resident (C >= E and loaded by earlier calls); none
+ * for batch 1, or for a cache that holds every expert (C >= E), on bf16 experts in the tiled
  * layout with in-kernel fetch (router, gating, lookups and the expert FFN are then one launch, the combine a
  * second one); every other call waits for the device to report the miss list (copy-engine fetch) or whether
  * it has to be split (batched calls on a constrained cache).

@@ -7,7 +7,7 @@
 //   route_cache kernel (router, gating, cache lookups, grouping; leaves the miss list and the call's counters in a
 //   pinned mailbox) -> expert FFN -> combine.
 // Copy-engine fetch: the FFN over the groups whose expert was already resident is enqueued before the host looks
-// at the miss list; the host then reads the mailbox, issues one hipMemcpyAsync per miss (pinned pool -> device
+// at the miss list; the host then polls the mailbox (no event: see wait_mailbox), issues one hipMemcpyAsync per miss (pinned pool -> device
 // buffer) on the copy stream, makes the caller's stream wait for them and enqueues the FFN over the fetched
 // groups.  The host round trip and the PCIe copies overlap the resident experts' compute: the additive model of
 // Eq. 4 (compute + N_miss * transfer) is the worst case.
@@ -127,11 +127,13 @@ struct moe_cache {
   int max_miss = 0;
 
   hipStream_t copy_stream = nullptr;
-  hipEvent_t ev_mail = nullptr, ev_copy = nullptr, ev_order = nullptr;
+  hipEvent_t ev_copy = nullptr;
   uint32_t seq = 0;
   bool copies_pending = false;    // copies issued that no stream has been ordered after yet
 
   std::vector<moe_cache_stats_t> stats;
+  std::vector<uint8_t> full;      // [L] 1: the host knows that all E experts of the layer are resident (C >= E; nothing is
+                                  // ever evicted then), so its calls cannot miss and need no answer from the device
 
   bool profiling = false;
   std::vector<ProfSlot> prof;
@@ -229,9 +231,7 @@ void free_all(moe_cache* c) {
     if (p.c0) (void)hipEventDestroy(p.c0);
     if (p.c1) (void)hipEventDestroy(p.c1);
   }
-  if (c->ev_mail) (void)hipEventDestroy(c->ev_mail);
   if (c->ev_copy) (void)hipEventDestroy(c->ev_copy);
-  if (c->ev_order) (void)hipEventDestroy(c->ev_order);
   if (c->copy_stream) (void)hipStreamDestroy(c->copy_stream);
   if (c->buffers) (void)hipFree(c->buffers);
   if (c->table_mem) (void)hipFree(c->table_mem);
@@ -244,12 +244,22 @@ void free_all(moe_cache* c) {
   delete c;
 }
 
-// Wait until the cache kernel of call `seq` has filled the mailbox.
-int wait_mailbox(moe_cache* c, hipStream_t s, uint32_t seq) {
-  HIPCHK(hipEventRecord(c->ev_mail, s));
-  HIPCHK(hipEventSynchronize(c->ev_mail));
-  const uint32_t got = __atomic_load_n(&c->mailbox->seq, __ATOMIC_ACQUIRE);
-  if (got != seq) return fail(MOE_ERR_TIMEOUT, "miss list of call %u not delivered (mailbox holds %u)", seq, got);
+// Wait until the cache kernel of call `seq`, enqueued on `s`, has filled the mailbox: polls the record in pinned memory
+// (publish_record, gating.hpp).  Every few thousand polls the stream is asked whether it still runs, so a call that
+// failed on the device, or ended without a record, ends the wait.
+int wait_mailbox(moe_cache* c, int layer, hipStream_t s, uint32_t seq) {
+  const auto there = [&] { return __atomic_load_n(&c->mailbox->seq, __ATOMIC_ACQUIRE) == seq; };
+  for (unsigned n = 1; !there(); ++n) {
+    __builtin_ia32_pause();
+    if (n % 8192 != 0) continue;
+    const hipError_t e = hipStreamQuery(s);
+    if (e == hipErrorNotReady) continue;
+    if (e != hipSuccess) return fail(MOE_ERR_HIP, "waiting for the miss list: %s", hipGetErrorString(e));
+    if (!there())
+      return fail(MOE_ERR_TIMEOUT, "miss list of call %u not delivered (mailbox holds %u)", seq, c->mailbox->seq);
+    break;
+  }
+  c->full[layer] = c->mailbox->status == MOE_OK && c->C >= c->cfg.n_experts && c->mailbox->n_res >= c->cfg.n_experts;
   return MOE_OK;
 }
 
@@ -465,6 +475,7 @@ int moe_cache_create(const moe_cache_config_t* cfg, const moe_weights_t* weights
   c->G = (int)std::min<size_t>((size_t)Bm * K, (size_t)std::max(P, E)) + cfg->n_shared;   // buffers, or experts when streaming a prompt
   c->max_miss = (int)std::max<size_t>((size_t)Bm * K, (size_t)C);
   c->stats.assign(L, moe_cache_stats_t{});
+  c->full.assign(L, 0);
 
   if (route_cache_lds_bytes(E, C, P, cfg->n_shared, (int)std::min<size_t>(Bm, kStageMaxPairs / KS), K, KS) > 64 * 1024 ||
       route_cache_lds_bytes(E, C, P, cfg->n_shared, 1, C, C) > 64 * 1024) {
@@ -609,9 +620,7 @@ int moe_cache_create(const moe_cache_config_t* cfg, const moe_weights_t* weights
     CREATE_CHK(launch_pack_router(nullptr, weights->router_w, c->router_packed, E, cfg->d_model, L), MOE_ERR_HIP);
   }
   CREATE_CHK(hipStreamCreateWithFlags(&c->copy_stream, hipStreamNonBlocking), MOE_ERR_HIP);
-  CREATE_CHK(hipEventCreateWithFlags(&c->ev_mail, hipEventDisableTiming), MOE_ERR_HIP);
   CREATE_CHK(hipEventCreateWithFlags(&c->ev_copy, hipEventDisableTiming), MOE_ERR_HIP);
-  CREATE_CHK(hipEventCreateWithFlags(&c->ev_order, hipEventDisableTiming), MOE_ERR_HIP);
 
   for (int l = 0; l < L; ++l) CREATE_CHK(launch_reset(nullptr, state_of(c, l), E, C, P, 1, nullptr), MOE_ERR_HIP);
   CREATE_CHK(hipStreamSynchronize(nullptr), MOE_ERR_HIP);
@@ -640,6 +649,7 @@ int moe_cache_reset(moe_cache_t* c, int32_t layer, int32_t clear_stats, void* hi
     unsigned long long* ds = reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(c->dev_stats) + c->layer_stride * l);
     HIPCHK(launch_reset(s, state_of(c, l), c->cfg.n_experts, c->C, c->P, clear_stats ? 1 : 0, clear_stats ? ds : nullptr));
     if (clear_stats) c->stats[l] = moe_cache_stats_t{};
+    c->full[l] = 0;
   }
   return MOE_OK;
 }
@@ -668,7 +678,7 @@ int moe_cache_prefill_pins(moe_cache_t* c, int32_t layer, const int32_t* expert_
   a.mailbox = c->mailbox; a.miss_list = c->miss_list; a.max_miss = c->max_miss;
   if (c->copies_pending) { HIPCHK(hipStreamWaitEvent(s, c->ev_copy, 0)); c->copies_pending = false; }
   HIPCHK(launch_pin(s, state_of(c, layer), c->t, a));
-  int rc = wait_mailbox(c, s, a.seq);
+  int rc = wait_mailbox(c, layer, s, a.seq);
   if (rc != MOE_OK) return rc;
   const Mailbox mb = *c->mailbox;
   if (mb.status != MOE_OK) return fail(mb.status, "prefill_pins ran out of expert buffers");
@@ -758,7 +768,6 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   a.policy = cf.policy; a.gamma = cf.gamma; a.trace_cap = cf.trace_capacity; a.seq = ++c->seq;
   a.pin_ids = nullptr; a.mailbox = c->mailbox; a.miss_list = c->miss_list; a.max_miss = c->max_miss;
   HIPCHK(launch_route_cache(s, cf.dtype, ra, state_of(c, layer), c->t, a, ps ? ps->route : KernelEvents{}));
-  HIPCHK(hipEventRecord(c->ev_mail, s));
 
   FfnArgs fa{};
   fa.x = x_dev;
@@ -784,10 +793,14 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   fa.pass = in_kernel ? 2 : 0;
   HIPCHK(launch_ffn(s, cf.dtype, plan, fa, ke1, ke2));
 
-  HIPCHK(hipEventSynchronize(c->ev_mail));
-  const uint32_t got = __atomic_load_n(&c->mailbox->seq, __ATOMIC_ACQUIRE);
-  if (got != a.seq) return fail(MOE_ERR_TIMEOUT, "miss list of call %u not delivered (mailbox holds %u)", a.seq, got);
-  const Mailbox mb = *c->mailbox;
+  Mailbox mb{};
+  if (c->full[layer]) {
+    mb.n_hits = batch * K;        // every lookup hits: nothing to learn from the device
+  } else {
+    const int rc = wait_mailbox(c, layer, s, a.seq);
+    if (rc != MOE_OK) return rc;
+    mb = *c->mailbox;
+  }
   if (mb.status != MOE_OK)
     return fail(mb.status, "call needs more spare expert buffers than staging_buffers=%d (batch %d)",
                 cf.staging_buffers, batch);
@@ -895,7 +908,6 @@ int moe_layer_prefill(moe_cache_t* c, int32_t layer, const void* x_dev, const fl
   a.policy = cf.policy; a.gamma = cf.gamma; a.trace_cap = 0; a.seq = ++c->seq;
   a.pin_ids = nullptr; a.mailbox = c->mailbox; a.miss_list = c->miss_list; a.max_miss = c->max_miss;
   HIPCHK(launch_route_cache(s, cf.dtype, ra, state_of(c, layer), c->t, a, KernelEvents{}));
-  HIPCHK(hipEventRecord(c->ev_mail, s));
 
   FfnArgs fa{};
   fa.x = x_dev;
@@ -913,10 +925,12 @@ int moe_layer_prefill(moe_cache_t* c, int32_t layer, const void* x_dev, const fl
   HIPCHK(cf.pool_layout == MOE_LAYOUT_TILED_INT4 ? launch_ffn_gemm_q4(s, fa, KernelEvents{}, KernelEvents{})
                                                   : launch_ffn_gemm(s, fa, KernelEvents{}, KernelEvents{}));
 
-  HIPCHK(hipEventSynchronize(c->ev_mail));
-  const uint32_t got = __atomic_load_n(&c->mailbox->seq, __ATOMIC_ACQUIRE);
-  if (got != a.seq) return fail(MOE_ERR_TIMEOUT, "group list of call %u not delivered (mailbox holds %u)", a.seq, got);
-  const Mailbox mb = *c->mailbox;
+  Mailbox mb{};
+  if (!c->full[layer]) {          // with every expert resident nothing is streamed
+    const int rc = wait_mailbox(c, layer, s, a.seq);
+    if (rc != MOE_OK) return rc;
+    mb = *c->mailbox;
+  }
   HIPCHK(launch_combine(s, cf.dtype, c->o, c->t.wpair, c->t.pos_of, n_tokens, KS, d, y_dev));
   moe_cache_stats_t& st = c->stats[layer];
   st.stream_loads += (uint64_t)mb.n_miss;

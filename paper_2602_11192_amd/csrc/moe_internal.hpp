@@ -36,7 +36,8 @@ struct Mailbox {
   int32_t n_evict;
   int32_t n_groups;    // distinct expert buffers used by the call (incl. shared experts)
   int32_t n_hits;
-  int32_t pad[2];
+  int32_t n_res;       // experts resident after the call
+  int32_t pad;
 };
 
 // One group = the (token, expert) pairs of a call that read the same expert buffer.  A single 32-byte record so
@@ -70,7 +71,7 @@ struct CacheCallArgs {
   int32_t trace_cap;
   uint32_t seq;
   const int32_t* pin_ids; // mode 1: host-mapped list of K ids (B = 1)
-  Mailbox* mailbox;       // host-mapped
+  Mailbox* mailbox;       // host-mapped; null: nobody reads the call record
   MissEntry* miss_list;   // host-mapped, [max_miss]
   int32_t max_miss;
   int32_t row0;           // row of the caller's batch at which this wave of tokens starts (trace records)

@@ -99,7 +99,7 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
 
   // ---- carve the array ----
   size_t o_tick, o_score, o_scal, o_ein, o_bos, o_free, o_zom, o_used, o_idx, o_wp, o_pb, o_sp, o_po, o_gd, o_ng,
-      o_arr, o_mail, o_miss, o_h, o_o;
+      o_arr, o_miss, o_h, o_o;
   auto carve = [&]() {
     size_t o = 0;
     o_tick = o; o += up((size_t)E * 8);
@@ -118,7 +118,6 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
     o_gd = o; o += up((size_t)G * sizeof(GroupDesc));
     o_ng = o; o += 256;
     o_arr = o; o += 256;
-    o_mail = o; o += up(sizeof(Mailbox));
     o_miss = o; o += up(max_miss * sizeof(MissEntry));
     o_h = o; o += plan.fused ? 0 : up(NP * (size_t)f * 4);
     o_o = o;
@@ -190,7 +189,7 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
   CacheCallArgs a{};
   a.mode = 0; a.B = batch; a.K = K; a.KS = KS; a.E = E; a.C = E; a.P = E; a.n_shared = ns;
   a.policy = MOE_POLICY_LRU; a.gamma = 0.0; a.trace_cap = 0; a.seq = seq;
-  a.mailbox = reinterpret_cast<Mailbox*>(base + o_mail);
+  a.mailbox = nullptr;
   a.miss_list = reinterpret_cast<MissEntry*>(base + o_miss);
   a.max_miss = (int32_t)max_miss;
   HIPCHK(launch_route_cache(s, L->dtype, ra, st, t, a, KernelEvents{}));

@@ -210,13 +210,7 @@ __device__ void prefill_phase(unsigned char* smem, const LdsLayout& L, const int
   for (int gi = lane; gi < n_groups; gi += kWave) t.grp[gi].pair0 = t.sorted_pair[t.grp[gi].begin];
   if (lane == 0) {
     *t.n_groups = n_groups;
-    Mailbox* mb = a.mailbox;
-    mb->status = MOE_OK;
-    mb->n_miss = n_stream;
-    mb->n_evict = 0;
-    mb->n_groups = n_groups;
-    mb->n_hits = 0;
-    mb->seq = a.seq;
+    publish_record(a.mailbox, MOE_OK, n_stream, 0, n_groups, 0, (int)st.scalars[SC_NRES], a.seq);
   }
 }
 
@@ -388,15 +382,7 @@ __device__ void cache_phase_general(unsigned char* smem, const LdsLayout& L, con
       st.scalars[SC_TRACE_N] = trace_n + trace_added;
     }
   }
-  if (lane == 0) {
-    Mailbox* mb = a.mailbox;
-    mb->status = status;
-    mb->n_miss = n_miss;
-    mb->n_evict = n_evict;
-    mb->n_groups = n_groups;
-    mb->n_hits = n_hits;
-    mb->seq = seq;   // read by the host only after the kernel has completed
-  }
+  if (lane == 0) publish_record(a.mailbox, status, n_miss, n_evict, n_groups, n_hits, n_res, seq);
 }
 
 // Runs in ONE wave.  idx_src: the experts to look up, in order (decode: [B][K]; pin: the list);
@@ -620,15 +606,7 @@ __device__ void cache_phase_fast(FastTable f, unsigned char* smem, const LdsLayo
       st.scalars[SC_TRACE_N] = f.trace_n + (a.mode == 0 ? n_lookups : 0);
     }
   }
-  if (lane == 0) {
-    Mailbox* mb = a.mailbox;
-    mb->status = status;
-    mb->n_miss = n_miss;
-    mb->n_evict = n_evict;
-    mb->n_groups = n_groups;
-    mb->n_hits = n_hits;
-    mb->seq = seq;   // read by the host only after the kernel has completed
-  }
+  if (lane == 0) publish_record(a.mailbox, status, n_miss, n_evict, n_groups, n_hits, f.n_res, seq);
 }
 
 // ---------------------------------------------------------------- the decode launch
@@ -855,15 +833,7 @@ __device__ void cache_phase_fast_wide(unsigned char* smem, const LdsLayout& L, c
   __syncthreads();
   // a group's first pair: the smallest position belongs to whichever pair claimed it; read it back
   for (int gi = tid; gi < s_n_groups; gi += nthr) t.grp[gi].pair0 = t.sorted_pair[t.grp[gi].begin];
-  if (tid == 0) {
-    Mailbox* mb = a.mailbox;
-    mb->status = MOE_OK;
-    mb->n_miss = 0;
-    mb->n_evict = 0;
-    mb->n_groups = s_n_groups;
-    mb->n_hits = n_lookups;
-    mb->seq = a.seq;
-  }
+  if (tid == 0) publish_record(a.mailbox, MOE_OK, 0, 0, s_n_groups, n_lookups, f.n_res, a.seq);
 }
 
 // Phases 1 and 2 for calls of many bf16 tokens: a workgroup (eight waves) routes a tile of 16 tokens.  The
