@@ -123,7 +123,7 @@ __device__ __forceinline__ void fused_q4_body(const FfnArgs& a, const RoutedArgs
   const uint16_t* xrow = nullptr;
   if (n < cnt) {
     int p;
-    if constexpr (ROUTED) p = rl_store.sorted_pair[begin + n];
+    if constexpr (ROUTED) p = a.max_count == 1 ? begin : rl_store.sorted_pair[begin + n];   // one token: pairs in order
     else p = n == 0 ? pair0 : a.t.sorted_pair[begin + n];
     xrow = reinterpret_cast<const uint16_t*>(a.x) + (size_t)(p / a.KS) * d + (size_t)ks * 128 + q * 8;
   }

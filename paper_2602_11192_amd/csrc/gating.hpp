@@ -41,6 +41,48 @@ __host__ __device__ inline bool fast_table(int policy, int C, int P, int n_share
 }
 
 // ---------------------------------------------------------------- phase 2
+// The K largest of E values held by one wave (value e in z[e / 64] of lane e % 64), as one lane mask per register;
+// equal values go to the lower id.  Exactly K bits are set whatever the values are (K <= E).
+// The K-th largest is found bit by bit from the top of its order-preserving integer key: one compare, one ballot and
+// a scalar population count per bit, and it ends as soon as a threshold separates exactly K values - after the sign,
+// the exponent and a few mantissa bits on router logits.  K rounds of wave-wide arg-max instead take ~250
+// cycles each: 1.2 us of a one-token call at K = 8 against 0.3 us.
+template <int EPL>
+__device__ __forceinline__ void top_select(const float (&z)[EPL], int E, int K, uint64_t (&mask)[EPL]) {
+  const int lane = threadIdx.x & 63;
+  uint32_t key[EPL];
+  uint64_t valid[EPL];
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) {
+    const uint32_t u = __builtin_bit_cast(uint32_t, z[i] + 0.0f);      // -0 counts as +0
+    key[i] = u ^ ((u >> 31) ? 0xffffffffu : 0x80000000u);
+    valid[i] = __ballot(lane + i * kWave < E);
+  }
+  uint32_t t = 0;          // largest threshold so far that at least K keys reach
+#pragma unroll 1
+  for (int bit = 31; bit >= 0; --bit) {
+    const uint32_t cand = t | (1u << bit);
+    int n = 0;
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) n += __popcll(__ballot(key[i] >= cand) & valid[i]);
+    if (n >= K) t = cand;
+    if (n == K) break;
+  }
+  int ties = K;            // entries equal to the threshold that still belong to the K
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) {
+    mask[i] = __ballot(key[i] > t) & valid[i];
+    ties -= __popcll(mask[i]);
+  }
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) {
+    const uint64_t eq = __ballot(key[i] == t) & valid[i];
+    const int before = __popcll(eq & ((1ull << lane) - 1ull));
+    mask[i] |= __ballot(((eq >> lane) & 1) != 0 && before < ties);
+    ties -= __popcll(eq);
+  }
+}
+
 // One wave gates one token from the logits in LDS (zs[E]).  kWeights = false: only the selected set (idx_g) is
 // formed - same selection, no softmax - for callers that need to know which experts run, not their weights.
 template <int EPL, bool kWeights = true>
@@ -59,43 +101,10 @@ __device__ __forceinline__ void gate_token(const float* zs, int b, int E, int K,
     zmax = fmaxf(zmax, z[i]);
   }
   zmax = wave_max(zmax);
-  if (K <= 16) {
-    // K rounds of arg-max; a taken entry is masked out; ties resolve to the lowest id
-    float zc[EPL];
+  uint64_t top[EPL];
+  top_select<EPL>(z, E, K, top);
 #pragma unroll
-    for (int i = 0; i < EPL; ++i) zc[i] = z[i];
-    for (int k = 0; k < K; ++k) {
-      float m = zc[0];
-#pragma unroll
-      for (int i = 1; i < EPL; ++i) m = fmaxf(m, zc[i]);
-      m = wave_max(m);
-      bool done = false;
-#pragma unroll
-      for (int i = 0; i < EPL; ++i) {
-        const uint64_t cand = __ballot(zc[i] == m && (lane + i * kWave) < E);
-        if (!done && cand != 0) {          // uniform
-          const int first = __ffsll((unsigned long long)cand) - 1;
-          if (lane == first) { sel[i] = true; zc[i] = -INFINITY; }
-          done = true;
-        }
-      }
-    }
-  } else {
-    // rank every logit against all others (ties to the lower id)
-    int rank[EPL];
-#pragma unroll
-    for (int i = 0; i < EPL; ++i) rank[i] = 0;
-    for (int j = 0; j < E; ++j) {
-      const float zj = zs[j];  // same address in every lane: LDS broadcast
-#pragma unroll
-      for (int i = 0; i < EPL; ++i) {
-        const int e = lane + i * kWave;
-        rank[i] += (zj > z[i] || (zj == z[i] && j < e)) ? 1 : 0;
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < EPL; ++i) sel[i] = (lane + i * kWave) < E && rank[i] < K;
-  }
+  for (int i = 0; i < EPL; ++i) sel[i] = (top[i] >> lane) & 1;
   if constexpr (!kWeights) {
     int base = 0;
 #pragma unroll

@@ -213,7 +213,7 @@ __device__ inline void lookup_small(FastTable f, RoutedLds& rl, const RoutedArgs
 // tiles and, when there are more waves than tiles, the contraction; the slices meet in LDS (pz, WAVES x 2 x 256
 // floats).
 template <int WAVES>
-__device__ __forceinline__ void route_logits(const RoutedArgs& ra, float* pz, RoutedLds& rl) {
+__device__ __forceinline__ void route_logits(const RoutedArgs& ra, float* pz, RoutedLds& rl, int tb_exp, int tb_buf) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 15, q = lane >> 4;
   const int B = ra.a.B, E = ra.a.E, d = ra.r.d;
@@ -281,6 +281,7 @@ __device__ __forceinline__ void route_logits(const RoutedArgs& ra, float* pz, Ro
     }
     if (have) load_batch();
   }
+  if (tb_exp >= 0) rl.buf_of[tb_exp] = tb_buf;       // (the waves that hold no entry of the table pass -1)
   __syncthreads();
   for (int i = threadIdx.x; i < B * E; i += 64 * WAVES) {
     const int b = i / E, e = i - b * E;
@@ -296,6 +297,38 @@ __device__ __forceinline__ void route_logits(const RoutedArgs& ra, float* pz, Ro
 
 // The group a workgroup of the expert phase works on.
 struct GroupView { int buf, begin, count, miss, expert; };
+
+// Group g of a one-token call all of whose selected experts are resident: every wave selects the experts and reads
+// the buffer off the map by itself, which takes neither a barrier nor the lookup routine.  False (for the whole
+// workgroup alike) when an expert is missing: the lookups then decide where it goes and what it replaces.
+template <int EPL>
+__device__ __forceinline__ bool resident_group(const RoutedLds& rl, int g, const CacheCallArgs& a, GroupView& gd) {
+  const int lane = threadIdx.x & 63;
+  float z[EPL];
+  int buf[EPL];
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) {
+    const int e = lane + i * kWave;
+    z[i] = e < a.E ? rl.zs[0][e] : -INFINITY;
+    buf[i] = e < a.E ? rl.buf_of[e] : -1;
+  }
+  uint64_t top[EPL], missing = 0;
+  top_select<EPL>(z, a.E, a.K, top);
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) missing |= top[i] & __ballot(buf[i] < 0);
+  if (missing != 0) return false;
+  gd.begin = g; gd.count = 1; gd.miss = 0; gd.expert = -1;
+  gd.buf = a.P + (g - a.K);                // shared experts come behind the K selected
+  int base = 0;
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) {
+    const int rank = base + __popcll(top[i] & ((1ull << lane) - 1ull));
+    const uint64_t at = __ballot(((top[i] >> lane) & 1) != 0 && rank == g);
+    if (at != 0) gd.buf = readlane_i(buf[i], __ffsll((unsigned long long)at) - 1);
+    base += __popcll(top[i]);
+  }
+  return true;
+}
 
 // Runs the prologue in the calling workgroup (all waves must call it).  pz: LDS scratch of WAVES x 2 x 256 floats.
 // g_max: number of group rows of the grid; the row behind them keeps the books (its first workgroup does what the
@@ -313,8 +346,11 @@ __device__ __forceinline__ bool routed_prologue(const FfnArgs& a, const RoutedAr
   if (wave == 0) ft = fast_load(ra.st_in, ra.a.C, ra.a.P);     // in flight while the logits are formed
   int tb_exp = -1, tb_buf = -1;     // the last wave inverts the table: expert -> buffer
   if (wave == WAVES - 1 && lane < ra.a.C) { tb_exp = ra.st_in.expert_in[lane]; tb_buf = ra.st_in.buf_of_slot[lane]; }
-  route_logits<WAVES>(ra, pz, rl);
-  if (wave == WAVES - 1 && tb_exp >= 0) rl.buf_of[tb_exp] = tb_buf;
+  route_logits<WAVES>(ra, pz, rl, tb_exp, tb_buf);
+  if (ra.a.B == 1 && !keeper) {
+    if (g >= ra.a.KS) return false;
+    if (ra.a.E <= 64 ? resident_group<1>(rl, g, ra.a, gd) : resident_group<kRoutedMaxE / 64>(rl, g, ra.a, gd)) return true;
+  }
   for (int b = wave; b < ra.a.B; b += WAVES) {
     if (keeper) {
       if (ra.a.E <= 64) gate_token<1>(rl.zs[b], b, ra.a.E, ra.a.K, ra.a.KS, ra.r.norm_topk, rl.idx, rl.wpair, ra.r.user_idx, ra.r.user_w, nullptr);
