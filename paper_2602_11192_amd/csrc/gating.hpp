@@ -85,7 +85,8 @@ __device__ __forceinline__ void top_select(const float (&z)[EPL], int E, int K, 
 
 // One wave gates one token from the logits in LDS (zs[E]).  kWeights = false: only the selected set (idx_g) is
 // formed - same selection, no softmax - for callers that need to know which experts run, not their weights.
-template <int EPL, bool kWeights = true>
+// kPublish: idx_g is written at device scope, for another workgroup of the same launch to read.
+template <int EPL, bool kWeights = true, bool kPublish = false>
 __device__ __forceinline__ void gate_token(const float* zs, int b, int E, int K, int KS, int norm_topk,
                                            int32_t* idx_g, float* wpair_g, int32_t* user_idx, float* user_w,
                                            int32_t* idx_stage) {
@@ -138,7 +139,10 @@ __device__ __forceinline__ void gate_token(const float* zs, int b, int E, int K,
     if (sel[i]) {
       const int pos = base + __popcll(m & ((1ull << lane) - 1ull));   // ascending expert id
       const float w = norm_topk ? p[i] / selsum : p[i];
-      idx_g[(size_t)b * K + pos] = e;
+      if constexpr (kPublish)
+        __hip_atomic_store(&idx_g[(size_t)b * K + pos], e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      else
+        idx_g[(size_t)b * K + pos] = e;
       wpair_g[(size_t)b * KS + pos] = w;
       if (idx_stage) idx_stage[(size_t)b * K + pos] = e;
       if (user_idx) user_idx[(size_t)b * K + pos] = e;

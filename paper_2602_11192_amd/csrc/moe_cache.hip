@@ -106,7 +106,7 @@ struct moe_cache {
   unsigned long long* dev_stats = nullptr;   // [L][4] hits, misses, evictions counted on the device by calls without a host wait
   bool dev_stats_used = false;
   size_t layer_stride = 0;             // bytes between the tables (and device counters) of consecutive layers
-  char* router_packed = nullptr;       // [L] router matrices in operand order, for the single-launch decode
+  char* router_packed = nullptr;       // [L] router matrices in operand order: in-kernel fetch, shapes of the single-launch decode
   bool single_ok = false;              // the single-launch decode kernel covers this cache's shape and policy
   int single_max_batch = 0;
   int n_cu = 0;                        // compute units of the device
@@ -720,6 +720,7 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   ra.d = d; ra.norm_topk = cf.norm_topk;
   ra.user_idx = topk_idx_dev; ra.user_w = topk_w_dev;
   ra.arrive = c->arrive;
+  ra.router_packed = c->router_packed ? c->router_packed + router_packed_bytes(E, d) * layer : nullptr;
 
   // One launch up to the combine, and no host wait: batch 1 (a single token's experts always fit), or a cache
   // that holds every expert (nothing is ever evicted) - the two cases in which a call cannot run out of spare
@@ -727,7 +728,6 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   if (c->single_ok && batch <= c->single_max_batch && (batch == 1 || c->C >= E)) {
     RoutedArgs q{};
     q.r = ra;
-    q.router_packed = c->router_packed + router_packed_bytes(E, d) * layer;
     q.st_in = state_of(c, layer);
     q.st_out = c->layers[(size_t)layer * 2 + (c->cur[layer] ^ 1)];
     CacheCallArgs& a = q.a;
@@ -766,7 +766,8 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   a.mode = 0; a.B = batch; a.K = K; a.KS = KS; a.E = E; a.C = c->C; a.P = c->P; a.n_shared = cf.n_shared;
   a.row0 = row0;
   a.policy = cf.policy; a.gamma = cf.gamma; a.trace_cap = cf.trace_capacity; a.seq = ++c->seq;
-  a.pin_ids = nullptr; a.mailbox = c->mailbox; a.miss_list = c->miss_list; a.max_miss = c->max_miss;
+  a.pin_ids = nullptr; a.miss_list = c->miss_list; a.max_miss = c->max_miss;
+  a.mailbox = c->full[layer] ? nullptr : c->mailbox;       // (every lookup hits: nobody reads the record)
   HIPCHK(launch_route_cache(s, cf.dtype, ra, state_of(c, layer), c->t, a, ps ? ps->route : KernelEvents{}));
 
   FfnArgs fa{};
@@ -902,11 +903,13 @@ int moe_layer_prefill(moe_cache_t* c, int32_t layer, const void* x_dev, const fl
   ra.d = d; ra.norm_topk = cf.norm_topk;
   ra.user_idx = topk_idx_dev; ra.user_w = topk_w_dev;
   ra.arrive = c->arrive;
+  ra.router_packed = c->router_packed ? c->router_packed + router_packed_bytes(E, d) * layer : nullptr;
 
   CacheCallArgs a{};
   a.mode = 2; a.B = n_tokens; a.K = K; a.KS = KS; a.E = E; a.C = c->C; a.P = c->P; a.n_shared = cf.n_shared;
   a.policy = cf.policy; a.gamma = cf.gamma; a.trace_cap = 0; a.seq = ++c->seq;
-  a.pin_ids = nullptr; a.mailbox = c->mailbox; a.miss_list = c->miss_list; a.max_miss = c->max_miss;
+  a.pin_ids = nullptr; a.miss_list = c->miss_list; a.max_miss = c->max_miss;
+  a.mailbox = c->full[layer] ? nullptr : c->mailbox;
   HIPCHK(launch_route_cache(s, cf.dtype, ra, state_of(c, layer), c->t, a, KernelEvents{}));
 
   FfnArgs fa{};

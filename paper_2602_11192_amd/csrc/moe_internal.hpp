@@ -74,6 +74,7 @@ struct CacheCallArgs {
   Mailbox* mailbox;       // host-mapped; null: nobody reads the call record
   MissEntry* miss_list;   // host-mapped, [max_miss]
   int32_t max_miss;
+  int32_t resident;       // 1: every expert sits in memory in the order of the ids (register-table case); no table is read
   int32_t row0;           // row of the caller's batch at which this wave of tokens starts (trace records)
 };
 
@@ -101,6 +102,7 @@ struct RouteArgs {
   const void* x;          // [B][d]
   const void* router_w;   // [E][d] of this layer
   const float* bias;      // [B][E] or null
+  const void* router_packed;  // the same matrix in matrix-core operand order (launch_pack_router), or null
   int32_t d, norm_topk;
   int32_t* user_idx;      // optional copies of the routing result for the caller
   float* user_w;
@@ -114,7 +116,6 @@ struct RouteArgs {
 // launch.
 struct RoutedArgs {
   RouteArgs r;               // x, router_w, bias, d, norm_topk, user_idx, user_w (arrive unused)
-  const void* router_packed; // this layer's router matrix in matrix-core operand order (launch_pack_router)
   LayerState st_in, st_out;
   CacheCallArgs a;
   unsigned long long* dev_stats;  // [3] hits, misses, evictions of the layer, accumulated on the device

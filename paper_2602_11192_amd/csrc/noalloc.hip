@@ -11,6 +11,7 @@
 // state, so calls on one GPU must not overlap (different streams without ordering race).
 #include <mutex>
 
+#include "gating.hpp"
 #include "moe_internal.hpp"
 
 using namespace moe;
@@ -30,7 +31,7 @@ uint32_t g_seq[kMaxDevices] = {};
 size_t up(size_t v) { return (v + 255) / 256 * 256; }
 
 // The table of a cache that already holds every expert: expert e in slot e and buffer e, no free buffer.
-__global__ void resident_table_kernel(LayerState st, int E, int32_t* arrive, int32_t* n_groups) {
+__global__ void resident_table_kernel(LayerState st, int E) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < E) {
     st.expert_in[i] = i;
@@ -48,8 +49,6 @@ __global__ void resident_table_kernel(LayerState st, int E, int32_t* arrive, int
     st.scalars[SC_NZOMBIE] = 0;
     st.scalars[SC_CALLSEQ] = 0;
     st.scalars[SC_TRACE_N] = 0;
-    *arrive = 0;
-    *n_groups = 0;
   }
 }
 
@@ -102,6 +101,7 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
       o_arr, o_miss, o_h, o_o;
   auto carve = [&]() {
     size_t o = 0;
+    o_arr = o; o += 256;        // the same place whatever the shape: zero before the first launch and after every one
     o_tick = o; o += up((size_t)E * 8);
     o_score = o; o += up((size_t)E * 8);
     o_scal = o; o += up((size_t)SC_COUNT * 8);
@@ -117,7 +117,6 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
     o_po = o; o += up(NP * 4);
     o_gd = o; o += up((size_t)G * sizeof(GroupDesc));
     o_ng = o; o += 256;
-    o_arr = o; o += 256;
     o_miss = o; o += up(max_miss * sizeof(MissEntry));
     o_h = o; o += plan.fused ? 0 : up(NP * (size_t)f * 4);
     o_o = o;
@@ -178,8 +177,11 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
   int32_t* arrive = reinterpret_cast<int32_t*>(base + o_arr);
 
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  hipLaunchKernelGGL(resident_table_kernel, dim3((E + 255) / 256), dim3(256), 0, s, st, E, arrive, t.n_groups);
-  HIPCHK(hipGetLastError());
+  const bool resident = fast_table(MOE_POLICY_LRU, E, E, ns);     // the router kernel knows this table by itself
+  if (!resident) {
+    hipLaunchKernelGGL(resident_table_kernel, dim3((E + 255) / 256), dim3(256), 0, s, st, E);
+    HIPCHK(hipGetLastError());
+  }
 
   RouteArgs ra{};
   ra.x = x_dev; ra.router_w = L->router_w; ra.bias = logit_bias_dev;
@@ -189,6 +191,7 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
   CacheCallArgs a{};
   a.mode = 0; a.B = batch; a.K = K; a.KS = KS; a.E = E; a.C = E; a.P = E; a.n_shared = ns;
   a.policy = MOE_POLICY_LRU; a.gamma = 0.0; a.trace_cap = 0; a.seq = seq;
+  a.resident = resident ? 1 : 0;
   a.mailbox = nullptr;
   a.miss_list = reinterpret_cast<MissEntry*>(base + o_miss);
   a.max_miss = (int32_t)max_miss;

@@ -25,6 +25,8 @@
 //     miss list in pinned host memory for the copy scheduler.
 // Nothing is committed when the call runs out of spare buffers, so a failed call
 // leaves the cache unchanged.
+#include <algorithm>
+
 #include "device_utils.hpp"
 #include "gating.hpp"
 #include "moe_internal.hpp"
@@ -609,11 +611,47 @@ __device__ void cache_phase_fast(FastTable f, unsigned char* smem, const LdsLayo
   if (lane == 0) publish_record(a.mailbox, status, n_miss, n_evict, n_groups, n_hits, f.n_res, seq);
 }
 
+// One layer's table as loaded: lane i < SC_COUNT holds scalar i (turned into the uniform values of FastTable by
+// `table_of`, once they are needed: the loads stay in flight while the logits are formed).
+struct RawTable { int64_t sc; int exp, buf, free_b, zomb; uint64_t tick; uint32_t used; };
+
+__device__ __forceinline__ RawTable raw_load(const LayerState& st, const CacheCallArgs& a) {
+  const int lane = threadIdx.x & 63;
+  RawTable f;
+  if (a.resident) {       // a layer all of whose experts are in memory in the order of their ids: nothing to read
+    f.sc = lane == SC_NRES ? a.E : 0;
+    f.exp = f.buf = lane < a.E ? lane : -2;
+    f.tick = 0; f.used = 0; f.free_b = f.zomb = -1;
+    return f;
+  }
+  f.sc = lane < SC_COUNT ? st.scalars[lane] : 0;
+  f.exp = lane < a.C ? st.expert_in[lane] : -2;
+  f.tick = lane < a.C ? st.tick[lane] : ~0ull;
+  f.buf = lane < a.C ? st.buf_of_slot[lane] : -1;
+  f.used = lane < a.P ? st.used_stamp[lane] : 0u;
+  f.free_b = lane < a.P ? st.free_buf[lane] : -1;
+  f.zomb = lane < a.P ? st.zombie[lane] : -1;
+  return f;
+}
+
+__device__ __forceinline__ FastTable table_of(const RawTable& r) {
+  const auto scalar = [&](int i) {
+    const uint32_t lo = (uint32_t)readlane_i((int)(uint32_t)r.sc, i);
+    const uint32_t hi = (uint32_t)readlane_i((int)(uint32_t)((uint64_t)r.sc >> 32), i);
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+  };
+  FastTable f;
+  f.clock = scalar(SC_CLOCK); f.trace_n = scalar(SC_TRACE_N);
+  f.n_res = (int)scalar(SC_NRES); f.n_free = (int)scalar(SC_NFREE); f.n_zombie = (int)scalar(SC_NZOMBIE);
+  f.exp = r.exp; f.buf = r.buf; f.free_b = r.free_b; f.zomb = r.zomb; f.tick = r.tick; f.used = r.used;
+  return f;
+}
+
 // ---------------------------------------------------------------- the decode launch
 // EB: router rows a wave handles at a time (1 when there are at least as many waves as experts: no spare loads).
 template <typename T, int EB>
 __global__ void __launch_bounds__(1024) route_cache_kernel(RouteArgs r, LayerState st, CallTables t, CacheCallArgs a) {
-  extern __shared__ __align__(8) unsigned char smem[];
+  extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int s_last;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -624,8 +662,8 @@ __global__ void __launch_bounds__(1024) route_cache_kernel(RouteArgs r, LayerSta
   const bool fast = a.mode != 2 && fast_table(a.policy, a.C, a.P, a.n_shared);
 
   // With one workgroup the cache table can be fetched while the router GEMV runs.
-  FastTable ft{};
-  if (single && fast && wave == 0) ft = fast_load(st, a.C, a.P);
+  RawTable raw{};
+  if (single && fast && wave == 0) raw = raw_load(st, a);
 
   const LdsLayout L = lds_layout(E, a.C, a.P, a.n_shared, a.B, K, KS);
   float* zs = reinterpret_cast<float*>(smem + L.logit);
@@ -697,7 +735,7 @@ __global__ void __launch_bounds__(1024) route_cache_kernel(RouteArgs r, LayerSta
     if (stage)
       for (int i = lane; i < a.B * K; i += kWave)
         idx_stage[i] = __hip_atomic_load(&t.idx[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (fast) ft = fast_load(st, a.C, a.P);
+    if (fast) raw = raw_load(st, a);
   }
   wave_sync();
 
@@ -705,93 +743,93 @@ __global__ void __launch_bounds__(1024) route_cache_kernel(RouteArgs r, LayerSta
   if (a.mode == 2) {
     prefill_phase(smem, L, stage ? idx_stage : t.idx, pair_stage, st, t, a);
   } else if (fast) {
-    cache_phase_fast(ft, smem, L, stage ? idx_stage : t.idx, pair_stage, st, t, a);
+    cache_phase_fast(table_of(raw), smem, L, stage ? idx_stage : t.idx, pair_stage, st, t, a);
   } else {
     cache_phase_general(smem, L, stage ? idx_stage : t.idx, pair_stage, st, t, a);
   }
 }
 
 
-// ---------------------------------------------------------------- many tokens per call
-// Phase 3 for a large call, run by ALL waves of the last workgroup (register-table case, LRU).  The common case of
-// such a call - every lookup hits - is embarrassingly parallel: residency does not change, a slot's new tick is
-// the position of its last lookup (LDS atomic max), and the pairs are grouped by a counting sort with the
-// counters in LDS.  A call with at least one miss hands over to the in-order routine in wave 0.
-__device__ void cache_phase_fast_wide(unsigned char* smem, const LdsLayout& L, const int32_t* idx, int32_t* pair_buf,
-                                      const LayerState& st, const CallTables& t, const CacheCallArgs& a) {
-  __shared__ int s_buf_of_slot[kWave];
-  __shared__ int s_any_miss, s_n_groups;
-  int32_t* lds_slot_of = reinterpret_cast<int32_t*>(smem + L.slot_of);
-  int32_t* lds_last = reinterpret_cast<int32_t*>(smem + L.free_buf);
-  int32_t* lds_touch = reinterpret_cast<int32_t*>(smem + L.zombie);
-  int32_t* lds_count = reinterpret_cast<int32_t*>(smem + L.count);
-  int32_t* lds_cursor = reinterpret_cast<int32_t*>(smem + L.start);
-  const int tid = threadIdx.x, nthr = blockDim.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int C = a.C, P = a.P, K = a.K, KS = a.KS;
-  const int n_lookups = a.B * K, NP = a.B * KS, NB = P + a.n_shared;
-  FastTable f{};
-  if (wave == 0) {
-    f = fast_load(st, C, P);
-    if (lane < C) s_buf_of_slot[lane] = f.buf;
-    if (lane == 0) { s_any_miss = f.n_res > 0 ? 0 : 1; s_n_groups = 0; }
+// ---------------------------------------------------------------- several tokens per call
+constexpr int kTileWaves = 16, kTileThreads = 64 * kTileWaves, kTileTokens = 16;
+constexpr int kMaxKeys = 2 * kWave; // buffer ids of the register-table case, shared experts included
+
+// What the grouping phase of the tile kernel keeps in LDS.
+struct TileLds {
+  int map[kTileMaxE];          // expert -> buffer << 8 | slot, -1 when it is not resident
+  int count[kMaxKeys], start[kMaxKeys], group[kMaxKeys];
+  int last[kWave], touched[kWave];
+  int any_miss, n_groups, last_arrived;
+};
+
+// Phase 3 of the tile kernel on the register table (LRU), run by ALL waves of the last workgroup.  The common case -
+// every lookup hits - is embarrassingly parallel: residency does not change, a slot's new tick is the position of its
+// last lookup (LDS atomic max), and the pairs are grouped by a counting sort whose counters sit in LDS; the rank a pair
+// draws from its counter is kept in a register until the group's first position is known, so that nothing goes through
+// memory.  A call with at least one miss hands over to the in-order routine in wave 0.
+// H: lookups a thread keeps in registers (the code of this phase runs once per launch and is fetched cold, so a small
+// call takes the variant that holds one).  idx_at(l): expert of lookup l; copy_to: where the lookups are copied on the
+// way (or null); in_order: where the in-order routine finds them.
+template <int H, typename IdxAt>
+__device__ __forceinline__ void group_hits(unsigned char* smem, const LdsLayout& L, TileLds& tl, const RawTable& raw,
+                                           IdxAt idx_at, int32_t* copy_to, const int32_t* in_order, int32_t* pair_buf,
+                                           const LayerState& st, const CallTables& t, const CacheCallArgs& a) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int C = a.C, P = a.P, K = a.K, KS = a.KS, ns = a.n_shared;
+  const int n_lookups = a.B * K, NB = P + ns;
+  const auto pair_of = [&](int l) { return ns == 0 ? l : l + (l / K) * ns; };
+  int m[H], rank[H];
+  bool miss = false;
+#pragma unroll
+  for (int i = 0; i < H; ++i) {
+    const int l = tid + i * kTileThreads;
+    const int e = l < n_lookups ? idx_at(l) : -1;
+    if (e >= 0 && copy_to) copy_to[l] = e;
+    m[i] = e;
   }
-  for (int e = tid; e < a.E; e += nthr) lds_slot_of[e] = -1;
-  for (int i = tid; i < P; i += nthr) { lds_last[i] = 0; lds_touch[i] = 0; }
-  for (int i = tid; i < NB; i += nthr) lds_count[i] = 0;
-  __syncthreads();
-  if (wave == 0 && lane < C && f.exp >= 0) lds_slot_of[f.exp] = lane;
-  __syncthreads();
-  {
-    bool miss = false;
-    for (int l = tid; l < n_lookups; l += nthr) miss |= lds_slot_of[idx[l]] < 0;
-    if (miss) s_any_miss = 1;
+#pragma unroll
+  for (int i = 0; i < H; ++i) {
+    if (m[i] < 0) continue;
+    m[i] = tl.map[m[i]];
+    miss |= m[i] < 0;
   }
+  if constexpr (H > 1)
+    for (int l = tid + H * kTileThreads; l < n_lookups; l += kTileThreads) miss |= tl.map[idx_at(l)] < 0;
+  if (miss) tl.any_miss = 1;
   __syncthreads();
-  if (s_any_miss != 0) {                      // uniform: in-order routine, one wave
-    if (wave == 0) cache_phase_fast(f, smem, L, idx, pair_buf, st, t, a);
+  if (tl.any_miss) {                          // in-order routine, one wave
+    if (wave != 0) return;
+    if (in_order == t.idx) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");     // reads the other workgroups' results directly
+    cache_phase_fast(table_of(raw), smem, L, in_order, pair_buf, st, t, a);
     return;
   }
-  // ---- every lookup hits ----
-  const int64_t trace_n = st.scalars[SC_TRACE_N];
-  for (int l = tid; l < n_lookups; l += nthr) {
-    const int e = idx[l];
-    const int slot = lds_slot_of[e];
-    atomicMax(&lds_last[slot], l + 1);
-    const int b = l / K;
-    const int buf = s_buf_of_slot[slot];
-    pair_buf[(size_t)b * KS + (l - b * K)] = buf;
-    atomicAdd(&lds_count[buf], 1);
-    if (trace_n + l < a.trace_cap) st.trace[trace_n + l] = moe_trace_rec_t{a.row0 + b, e, 1, -1};
+  // the last lookup of a slot and the position of a pair in its group
+  const auto look_up = [&](int l, int v) {
+    atomicMax(&tl.last[v & 255], l + 1);
+    return atomicAdd(&tl.count[v >> 8], 1);
+  };
+#pragma unroll
+  for (int i = 0; i < H; ++i) {
+    const int l = tid + i * kTileThreads;
+    rank[i] = l < n_lookups ? look_up(l, m[i]) : 0;
   }
-  for (int p = tid; p < a.B * a.n_shared; p += nthr) {
-    const int b = p / a.n_shared, sidx = p - b * a.n_shared;
-    pair_buf[(size_t)b * KS + K + sidx] = P + sidx;
-    atomicAdd(&lds_count[P + sidx], 1);
+  if constexpr (H > 1)
+    for (int l = tid + H * kTileThreads; l < n_lookups; l += kTileThreads)      // beyond the registers: parked in pos_of
+      t.pos_of[pair_of(l)] = look_up(l, tl.map[idx_at(l)]);
+  if (a.trace_cap > 0) {
+    const int64_t trace_n = st.scalars[SC_TRACE_N];
+    for (int l = tid; l < n_lookups && trace_n + l < a.trace_cap; l += kTileThreads)
+      st.trace[trace_n + l] = moe_trace_rec_t{a.row0 + l / K, idx_at(l), 1, -1};
   }
   __syncthreads();
   if (wave == 0) {
-    // recency of the slots, buffers in use, group descriptors in ascending buffer id
-    const int last = lane < C ? lds_last[lane] : 0;
-    if (last > 0) {
-      f.tick = (uint64_t)(f.clock + last);
-      lds_touch[f.buf] = 1;
-    }
-    wave_sync();
-    if (lane < P && lds_touch[lane]) f.used = a.seq;
-    {   // buffers released by the previous call become free again (as in the in-order routine)
-      const int src = lane - f.n_free;
-      const int z = __shfl(f.zomb, src < 0 ? 0 : src);
-      if (src >= 0 && src < f.n_zombie) f.free_b = z;
-      f.n_free += f.n_zombie;
-      f.n_zombie = 0;
-    }
-    f.clock += n_lookups;
+    // group descriptors in ascending buffer id (every token is in the group of every shared expert)
     const uint64_t lt_mask = (1ull << lane) - 1ull;
     int n_groups = 0, offset = 0;
+#pragma unroll 1
     for (int base = 0; base < NB; base += kWave) {
       const int id = base + lane;
-      const int c = id < NB ? lds_count[id] : 0;
+      const int c = id < P ? tl.count[id] : id < NB ? a.B : 0;
       int incl = c;
 #pragma unroll
       for (int dlt = 1; dlt < kWave; dlt <<= 1) {
@@ -800,115 +838,219 @@ __device__ void cache_phase_fast_wide(unsigned char* smem, const LdsLayout& L, c
       }
       const int begin = offset + incl - c;
       const uint64_t gm = __ballot(c > 0);
+      const int gi = n_groups + __popcll(gm & lt_mask);
       if (c > 0) {
-        GroupDesc gd;
-        gd.buf = id; gd.begin = begin; gd.count = c; gd.miss = 0;
-        gd.pair0 = 0; gd.expert = -1; gd.pad[0] = gd.pad[1] = 0;
-        t.grp[n_groups + __popcll(gm & lt_mask)] = gd;
+        GroupDesc* gd = &t.grp[gi];
+        *reinterpret_cast<int4*>(gd) = int4{id, begin, c, 0};       // pair0: whoever drew rank 0, below
+        gd->expert = -1;
       }
-      if (id < NB) lds_cursor[id] = begin;
+      if (id < NB) { tl.start[id] = begin; tl.group[id] = gi; }
       n_groups += __popcll(gm);
       offset += __shfl(incl, kWave - 1);
     }
-    if (lane == 0) { s_n_groups = n_groups; *t.n_groups = n_groups; }
-    // commit the table
-    if (lane < C) { st.tick[lane] = f.tick; st.expert_in[lane] = f.exp; st.buf_of_slot[lane] = f.buf; }
-    if (lane < P) { st.used_stamp[lane] = f.used; st.free_buf[lane] = f.free_b; st.zombie[lane] = f.zomb; }
-    if (lane == 0) {
-      st.scalars[SC_CLOCK] = f.clock;
-      st.scalars[SC_NRES] = f.n_res;
-      st.scalars[SC_NFREE] = f.n_free;
-      st.scalars[SC_NZOMBIE] = f.n_zombie;
-      st.scalars[SC_CALLSEQ] = a.seq;
-      st.scalars[SC_TRACE_N] = trace_n + n_lookups;
-    }
+    if (lane == 0) { *t.n_groups = n_groups; tl.n_groups = n_groups; }
   }
   __syncthreads();
-  for (int p = tid; p < NP; p += nthr) {
-    const int pos = atomicAdd(&lds_cursor[pair_buf[p]], 1);
+  const auto place = [&](int p, int key, int r) {
+    const int pos = tl.start[key] + r;
     t.sorted_pair[pos] = p;
     t.pos_of[p] = pos;
+    if (r == 0) t.grp[tl.group[key]].pair0 = p;
+  };
+#pragma unroll
+  for (int i = 0; i < H; ++i) {
+    const int l = tid + i * kTileThreads;
+    if (l < n_lookups) place(pair_of(l), m[i] >> 8, rank[i]);
   }
-  __threadfence_block();
-  __syncthreads();
-  // a group's first pair: the smallest position belongs to whichever pair claimed it; read it back
-  for (int gi = tid; gi < s_n_groups; gi += nthr) t.grp[gi].pair0 = t.sorted_pair[t.grp[gi].begin];
-  if (tid == 0) publish_record(a.mailbox, MOE_OK, 0, 0, s_n_groups, n_lookups, f.n_res, a.seq);
+  if constexpr (H > 1)
+    for (int l = tid + H * kTileThreads; l < n_lookups; l += kTileThreads) {
+      const int p = pair_of(l);
+      place(p, tl.map[idx_at(l)] >> 8, t.pos_of[p]);
+    }
+  for (int p = tid; p < a.B * ns; p += kTileThreads) {
+    const int b = p / ns, sidx = p - b * ns;
+    place(b * KS + K + sidx, P + sidx, b);
+  }
+  if (a.resident || wave != 0) return;
+  // ---- the table after the call: recency of the slots, buffers in use, released buffers free again ----
+  FastTable f = table_of(raw);
+  const int last = lane < C ? tl.last[lane] : 0;
+  if (last > 0) {
+    f.tick = (uint64_t)(f.clock + last);
+    tl.touched[f.buf] = 1;
+  }
+  wave_sync();
+  if (lane < P && tl.touched[lane]) f.used = a.seq;
+  const int src = lane - f.n_free;
+  const int z = __shfl(f.zomb, src < 0 ? 0 : src);
+  if (src >= 0 && src < f.n_zombie) f.free_b = z;
+  if (lane < C) { st.tick[lane] = f.tick; st.expert_in[lane] = f.exp; st.buf_of_slot[lane] = f.buf; }
+  if (lane < P) { st.used_stamp[lane] = f.used; st.free_buf[lane] = f.free_b; st.zombie[lane] = f.zomb; }
+  if (lane == 0) {
+    st.scalars[SC_CLOCK] = f.clock + n_lookups;
+    st.scalars[SC_NRES] = f.n_res;
+    st.scalars[SC_NFREE] = f.n_free + f.n_zombie;
+    st.scalars[SC_NZOMBIE] = 0;
+    st.scalars[SC_CALLSEQ] = a.seq;
+    st.scalars[SC_TRACE_N] = f.trace_n + n_lookups;
+    publish_record(a.mailbox, MOE_OK, 0, 0, tl.n_groups, n_lookups, f.n_res, a.seq);
+  }
 }
 
-// Phases 1 and 2 for calls of many bf16 tokens: a workgroup (eight waves) routes a tile of 16 tokens.  The
-// router logits of the tile are one small matrix product (experts x tokens) on the matrix cores: the rows of W_r
-// are the A operand and the tokens the B operand of v_mfma_f32_16x16x32_bf16, both read straight from global
-// memory in operand order, so W_r is read once per 16 tokens instead of once per token.  The waves then gate
-// the 16 tokens between them.  The last workgroup to arrive runs phase 3 with all its waves.
-__global__ void __launch_bounds__(1024) route_tile_kernel(RouteArgs r, LayerState st, CallTables t, CacheCallArgs a) {
+// Phases 1 to 3 for calls of two and more bf16 tokens: a workgroup of sixteen waves routes a tile of 16 tokens.  The
+// router logits of the tile are one small matrix product (experts x tokens) on the matrix cores: rows of W_r are the
+// A operand, the tokens the B operand of v_mfma_f32_16x16x32_bf16.  The waves split the contraction - a wave takes pairs
+// of adjacent k-blocks and multiplies them with NT expert tiles, so that every byte of x and of W_r reaches the
+// workgroup once and all loads of a wave are in flight together - and their partial tiles meet in LDS.  Then a
+// wave gates a token.  A call of at most 16 tokens is one workgroup, which goes straight on to the lookups; of a larger
+// call the workgroup that arrives last does (nobody waits).  What the others must see of a workgroup are its selected
+// experts only, written past the caches with device-scope stores, so the arrival needs no cache write-back: a
+// write-back in every wave, logits by half of the waves and the grouping through memory made this launch take 53 us at
+// 1024 tokens, 23 us at 64 and 13 us at 16 (64 experts, d = 2048); now 21, 12 and 11.5 us.
+// PACKED: W_r comes from the library's copy in operand order (pack_router_kernel), where a cache has one: a wave-wide load
+// is then one contiguous KiB instead of 16 pieces of 64 bytes (64 x 2048 experts: 11.5 against 17.8 us per launch).
+template <bool PACKED, int NT>
+__global__ void __launch_bounds__(kTileThreads) route_tile_kernel(RouteArgs r, LayerState st, CallTables t, CacheCallArgs a) {
   typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
   typedef float f32x4 __attribute__((ext_vector_type(4)));
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-  extern __shared__ __align__(8) unsigned char smem[];
-  __shared__ float zs_tile[16][kTileMaxE];
-  __shared__ int s_last;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
+  extern __shared__ __align__(16) unsigned char smem[];     // partial tiles of the logits, then phase 3's scratch
+  __shared__ float zs_tile[kTileTokens][kTileMaxE + 4];     // (+ 4: the 16 tokens of a column fall on different banks)
+  __shared__ TileLds tl;
+  float* pz = reinterpret_cast<float*>(smem);               // [8 waves][NT][256]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 15, q = lane >> 4;
   const int E = a.E, K = a.K, KS = a.KS, d = r.d;
-  const int t0 = blockIdx.x * 16;
+  const int t0 = blockIdx.x * kTileTokens;
   const int nkb = d >> 5;
-  const uint16_t* xrow = (t0 + n < a.B) ? static_cast<const uint16_t*>(r.x) + (size_t)(t0 + n) * d + q * 8 : nullptr;
-  for (int e0 = wave * 16; e0 < E; e0 += 16 * n_waves) {          // expert tiles of this wave
-    const int er = e0 + n < E ? e0 + n : E - 1;         // clamped: in bounds, dropped below
-    const uint16_t* wrow = static_cast<const uint16_t*>(r.router_w) + (size_t)er * d + q * 8;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    constexpr int U = 8;
-    for (int kb0 = 0; kb0 < nkb; kb0 += U) {
-      u32x4 wa[U], xb[U];
+  const bool single = gridDim.x == 1;
+  const bool fast = a.mode == 0 && fast_table(a.policy, a.C, a.P, a.n_shared);
+  // nobody changes the table before the last workgroup of this launch does: every workgroup may fetch it now
+  RawTable raw{};
+  if (fast && wave == 0) raw = raw_load(st, a);
+  for (int e = tid; e < E; e += kTileThreads) tl.map[e] = -1;
+  if (tid < kMaxKeys) tl.count[tid] = 0;
+  if (tid < kWave) { tl.last[tid] = 0; tl.touched[tid] = 0; }
+  if (tid == 0) tl.any_miss = 0;
+
+  const int tok = t0 + n < a.B ? t0 + n : a.B - 1;          // clamped: in bounds, the column is dropped below
+  const uint16_t* xrow = static_cast<const uint16_t*>(r.x) + (size_t)tok * d + q * 8;
+  for (int eg = 0; eg < E; eg += 16 * NT) {
+    float bias[(NT * 256 + kTileThreads - 1) / kTileThreads];
+#pragma unroll
+    for (int i = 0; i < (NT * 256 + kTileThreads - 1) / kTileThreads; ++i) {
+      const int el = tid + i * kTileThreads, ln = (el & 255) >> 2;
+      const int e = eg + (el >> 8) * 16 + (ln >> 4) * 4 + (el & 3), tb = t0 + (ln & 15);
+      bias[i] = (r.bias && el < NT * 256 && e < E && tb < a.B) ? r.bias[(size_t)tb * E + e] : 0.f;
+    }
+    const u32x4* wt[NT];                                    // this lane's piece of k-block 0 of every tile
+    constexpr int w_step = PACKED ? 64 : 4;
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      if constexpr (PACKED) {
+        const int tile = min((eg >> 4) + i, (E - 1) >> 4);
+        wt[i] = static_cast<const u32x4*>(r.router_packed) + (size_t)tile * nkb * 64 + lane;
+      } else {
+        const int er = min(eg + i * 16 + n, E - 1);
+        wt[i] = reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(r.router_w) + (size_t)er * d + q * 8);
+      }
+    }
+    f32x4 acc[NT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    constexpr int U = NT == 1 ? 8 : 4;                      // k-blocks in flight (two adjacent ones at a time)
+    for (int kb0 = 2 * wave; kb0 < nkb; kb0 += U * kTileWaves) {
+      u32x4 xb[U], wa[U][NT];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int kb = kb0 + u < nkb ? kb0 + u : nkb - 1;
-        wa[u] = *reinterpret_cast<const u32x4*>(wrow + (size_t)kb * 32);
-        xb[u] = xrow ? *reinterpret_cast<const u32x4*>(xrow + (size_t)kb * 32) : u32x4{0, 0, 0, 0};
+        const int kb = min(kb0 + (u >> 1) * 2 * kTileWaves + (u & 1), nkb - 1);
+        xb[u] = *reinterpret_cast<const u32x4*>(xrow + (size_t)kb * 32);
+#pragma unroll
+        for (int i = 0; i < NT; ++i) wa[u][i] = wt[i][(size_t)kb * w_step];
       }
 #pragma unroll
       for (int u = 0; u < U; ++u)
-        if (kb0 + u < nkb)      // uniform
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wa[u]),
-                                                        __builtin_bit_cast(bf16x8, xb[u]), acc, 0, 0, 0);
-    }
-    // lane holds experts e0 + 4q + i of token t0 + n
+        if (kb0 + (u >> 1) * 2 * kTileWaves + (u & 1) < nkb) {      // uniform
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int e = e0 + q * 4 + i;
-      if (e < E && t0 + n < a.B) zs_tile[n][e] = acc[i] + (r.bias ? r.bias[(size_t)(t0 + n) * E + e] : 0.f);
+          for (int i = 0; i < NT; ++i)
+            acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wa[u][i]),
+                                                             __builtin_bit_cast(bf16x8, xb[u]), acc[i], 0, 0, 0);
+        }
     }
+    // the upper eight waves hand their partial tiles to the lower eight, whose sums are then added up per element
+    if (wave >= kTileWaves / 2) {
+#pragma unroll
+      for (int i = 0; i < NT; ++i)
+        *reinterpret_cast<f32x4*>(pz + ((wave - kTileWaves / 2) * NT + i) * 256 + lane * 4) = acc[i];
+    }
+    __syncthreads();
+    if (wave < kTileWaves / 2) {
+#pragma unroll
+      for (int i = 0; i < NT; ++i) {
+        f32x4* slot = reinterpret_cast<f32x4*>(pz + (wave * NT + i) * 256 + lane * 4);
+        *slot = acc[i] + *slot;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < (NT * 256 + kTileThreads - 1) / kTileThreads; ++i) {
+      const int el = tid + i * kTileThreads;
+      if (el < NT * 256) {
+        float v = 0.f;
+#pragma unroll
+        for (int w = 0; w < kTileWaves / 2; ++w) v += pz[w * NT * 256 + el];
+        const int ln = (el & 255) >> 2;                     // the MFMA left rows 4 (ln / 16) + el % 4, token ln % 16
+        const int e = eg + (el >> 8) * 16 + (ln >> 4) * 4 + (el & 3);
+        if (e < E) zs_tile[ln & 15][e] = v + bias[i];
+      }
+    }
+    __syncthreads();
   }
-  __syncthreads();
-  for (int tt = wave; tt < 16 && t0 + tt < a.B; tt += n_waves) {
-    if (E <= 64) gate_token<1>(zs_tile[tt], t0 + tt, E, K, KS, r.norm_topk, t.idx, t.wpair, r.user_idx, r.user_w, nullptr);
-    else gate_token<kTileMaxE / 64>(zs_tile[tt], t0 + tt, E, K, KS, r.norm_topk, t.idx, t.wpair, r.user_idx, r.user_w,
-                                    nullptr);
-  }
-  __threadfence();
-  __syncthreads();
-  if (threadIdx.x == 0) s_last = atomicAdd(r.arrive, 1) == (int)gridDim.x - 1;
-  __syncthreads();
-  if (!s_last) return;
-  if (threadIdx.x == 0) __hip_atomic_store(r.arrive, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch on this stream
-  __threadfence();
+  if (fast && wave == 0 && lane < a.C && raw.exp >= 0) tl.map[raw.exp] = raw.buf << 8 | lane;
+
   const LdsLayout L = lds_layout(E, a.C, a.P, a.n_shared, a.B, K, KS);
   const bool stage = stage_in_lds(a.B, KS);
+  int32_t* idx_stage = stage ? reinterpret_cast<int32_t*>(smem + L.idx_stage) : nullptr;
   int32_t* pair_stage = stage ? reinterpret_cast<int32_t*>(smem + L.pair_stage) : t.pair_buf;
-  if (a.mode == 0 && fast_table(a.policy, a.C, a.P, a.n_shared)) {
-    cache_phase_fast_wide(smem, L, t.idx, pair_stage, st, t, a);
+  if (t0 + wave < a.B) {
+    int32_t* lds_idx = single ? idx_stage : nullptr;
+    if (E <= 64) gate_token<1, true, true>(zs_tile[wave], t0 + wave, E, K, KS, r.norm_topk, t.idx, t.wpair, r.user_idx, r.user_w, lds_idx);
+    else gate_token<kTileMaxE / 64, true, true>(zs_tile[wave], t0 + wave, E, K, KS, r.norm_topk, t.idx, t.wpair, r.user_idx,
+                                                r.user_w, lds_idx);
+  }
+  if (!single) {
+    // the selected experts went past the caches; once every wave's stores have arrived the workgroup is announced
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0)
+      tl.last_arrived = __hip_atomic_fetch_add(r.arrive, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+    __syncthreads();
+    if (!tl.last_arrived) return;
+    if (tid == 0) __hip_atomic_store(r.arrive, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch on this stream
+  } else {
+    __syncthreads();
+  }
+  // (a single workgroup's lookups always fit the LDS copy: 16 tokens of at most 128 pairs)
+  const auto published = [&](int l) { return __hip_atomic_load(&t.idx[l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  const int32_t* in_order = stage ? idx_stage : t.idx;
+  if (fast) {
+    if (single) group_hits<1>(smem, L, tl, raw, [&](int l) { return idx_stage[l]; }, nullptr, in_order, pair_stage, st, t, a);
+    else if (a.B * K <= kTileThreads) group_hits<1>(smem, L, tl, raw, published, idx_stage, in_order, pair_stage, st, t, a);
+    else group_hits<8>(smem, L, tl, raw, published, idx_stage, in_order, pair_stage, st, t, a);
     return;
   }
+  if (!single && stage)
+    for (int i = tid; i < a.B * K; i += kTileThreads) idx_stage[i] = published(i);
+  __syncthreads();
   if (wave != 0) return;
-  if (a.mode == 2) prefill_phase(smem, L, t.idx, pair_stage, st, t, a);
-  else if (fast_table(a.policy, a.C, a.P, a.n_shared))
-    cache_phase_fast(fast_load(st, a.C, a.P), smem, L, t.idx, pair_stage, st, t, a);
-  else cache_phase_general(smem, L, t.idx, pair_stage, st, t, a);
+  if (!stage) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  if (a.mode == 2) prefill_phase(smem, L, in_order, pair_stage, st, t, a);
+  else cache_phase_general(smem, L, in_order, pair_stage, st, t, a);
 }
 
 __global__ void __launch_bounds__(64) pin_kernel(LayerState st, CallTables t, CacheCallArgs a) {
-  extern __shared__ __align__(8) unsigned char smem[];
+  extern __shared__ __align__(16) unsigned char smem[];
   if (fast_table(a.policy, a.C, a.P, a.n_shared)) {
     const LdsLayout L = lds_layout(a.E, a.C, a.P, a.n_shared, 1, a.K, a.KS);
     cache_phase_fast(fast_load(st, a.C, a.P), smem, L, a.pin_ids, nullptr, st, t, a);
@@ -947,12 +1089,25 @@ hipError_t launch_route_cache(hipStream_t s, int dtype, const RouteArgs& r, cons
   if (waves > a.E) waves = a.E;
   dim3 grid(a.B), block(64 * waves);
   const size_t lds = route_cache_lds_bytes(a.E, a.C, a.P, a.n_shared, a.B, a.K, a.KS);
-  // from about a hundred tokens on, routing 16 tokens per workgroup on the matrix cores and running the cache
-  // phase on all waves of the last workgroup wins (measured: 31 against 48 us at 256 tokens, 49 against 182 us at 1024;
-  // 28.6 against 26.6 at 96, 29.3 against 31.6 at 127)
-  if (dtype == MOE_DTYPE_BF16 && a.B >= 112 && a.E <= kTileMaxE && r.d % 32 == 0) {
-    constexpr int kTileWaves = 8;   // measured: 49 us at 1024 tokens against 61 with four waves and 54 with sixteen
-    launch_timed(route_tile_kernel, dim3((a.B + 15) / 16), dim3(64 * kTileWaves), lds, s, ev, r, st, t, a);
+  // Tiles of 16 tokens: from two tokens on with the packed router matrix.  Reading it row-major the tile kernel needs 6 us
+  // more on 64 x 2048 (a layer call of 16 tokens 82.5 against 79.1 us, of 24 86.3 against 86.5, of 48 89.5 against 92.2, of
+  // 64 90.6 against 111.4); with few experts a workgroup per token keeps up for longer (16 x 4096, 64 tokens: 96.0 against
+  // 93.7 us).
+  const int tile_min = r.router_packed ? 2 : a.E > 32 ? 32 : 112;
+  if (dtype == MOE_DTYPE_BF16 && a.B >= tile_min && a.E <= kTileMaxE && r.d % 32 == 0) {
+    const int nt = a.E <= 16 ? 1 : a.E <= 32 ? 2 : 4;
+    const size_t bytes = std::max(lds, (size_t)(kTileWaves / 2) * nt * 256 * sizeof(float));
+    const dim3 tiles((a.B + kTileTokens - 1) / kTileTokens), threads(kTileThreads);
+    const auto launch = [&](auto kernel) { launch_timed(kernel, tiles, threads, bytes, s, ev, r, st, t, a); };
+    if (r.router_packed) {
+      if (nt == 1) launch(route_tile_kernel<true, 1>);
+      else if (nt == 2) launch(route_tile_kernel<true, 2>);
+      else launch(route_tile_kernel<true, 4>);
+    } else {
+      if (nt == 1) launch(route_tile_kernel<false, 1>);
+      else if (nt == 2) launch(route_tile_kernel<false, 2>);
+      else launch(route_tile_kernel<false, 4>);
+    }
     return hipGetLastError();
   }
   const bool one_row = a.E <= waves;

@@ -241,7 +241,7 @@ __device__ __forceinline__ void route_logits(const RoutedArgs& ra, float* pz, Ro
   bool have = item < n_items;
   rp_u32x4 wa[U];
   auto load_batch = [&]() {
-    const rp_u32x4* wfrag = static_cast<const rp_u32x4*>(ra.router_packed) + (size_t)(item % tiles) * nkb * 64 + lane;
+    const rp_u32x4* wfrag = static_cast<const rp_u32x4*>(ra.r.router_packed) + (size_t)(item % tiles) * nkb * 64 + lane;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int kb = kb0 + u * S < nkb ? kb0 + u * S : nkb - 1;    // clamped: in bounds, not used below

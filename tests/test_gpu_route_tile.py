@@ -1,0 +1,104 @@
+"""Routing of several tokens per launch (tiles of 16 tokens, the grouping in the workgroup that arrives last) at the edges
+of its tiles: token and expert counts around 16 and 64, more lookups than the grouping phase keeps in registers,
+shared experts; through a cache (router matrix in operand order) and through the entry point that allocates nothing
+(row-major), against the layer in 64 bits."""
+import numpy as np
+import pytest
+
+from tests.helpers import TOL
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    assert t.cuda.is_available(), "these tests need the MI355X"
+    return t
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2602_11192_amd import binding
+    return binding
+
+
+def layer64(torch, x, router, bias, blocks, shared, K, d, f):
+    z = x.double() @ router.double().t() + bias.double()
+    top = torch.topk(z, K, dim=-1)
+    gap = top.values[:, -1] - z.masked_fill(torch.zeros_like(z).scatter(1, top.indices, 1.0) > 0, -1e30).max(-1).values
+    idx = top.indices.sort(-1).values
+    w = torch.softmax(z.gather(1, idx), -1)
+    y = torch.zeros(x.shape[0], d, dtype=torch.float64)
+    every = torch.arange(x.shape[0])
+
+    def ffn(block, rows):
+        g, u, dn = (m.double() for m in block.split(d * f))
+        xr = x[rows].double()
+        return (torch.nn.functional.silu(xr @ g.view(f, d).t()) * (xr @ u.view(f, d).t())) @ dn.view(d, f).t()
+    for e in range(router.shape[0]):
+        rows, k = (idx == e).nonzero(as_tuple=True)
+        if len(rows):
+            y[rows] += w[rows, k, None] * ffn(blocks[e], rows)
+    for s in shared:
+        y += ffn(s, every)
+    return idx, w, y, gap
+
+
+@pytest.mark.parametrize("batch,E,K,ns,d", [(2, 8, 2, 0, 64), (15, 16, 4, 1, 32), (16, 17, 3, 0, 96), (17, 60, 8, 2, 160),
+                                            (129, 64, 8, 0, 64), (40, 100, 5, 1, 64), (33, 256, 2, 0, 64), (1100, 64, 8, 1, 64),
+                                            (5, 8, 2, 0, 256), (16, 24, 3, 0, 256), (17, 64, 8, 0, 256), (150, 60, 4, 0, 256),
+                                            (1030, 64, 8, 0, 256)])
+def test_routing_of_a_batch(torch, B, batch, E, K, ns, d):
+    f = 32
+    gen = torch.Generator().manual_seed(batch * 1000 + E)
+    rnd = lambda *s: torch.randn(*s, generator=gen)
+    router, x, bias = (rnd(E, d) * 0.3).bfloat16(), rnd(batch, d).bfloat16(), rnd(batch, E)
+    blocks, shared = (rnd(E, 3 * d * f) * 0.1).bfloat16(), (rnd(ns, 3 * d * f) * 0.1).bfloat16()
+    idx, w, y, gap = layer64(torch, x, router, bias, blocks, shared, K, d, f)
+    # fp32 logits of a few units are off by under 1e-5: tokens whose rank K is closer than that have no fixed set
+    sure = gap > 1e-5
+    assert sure.float().mean() > 0.9
+    dev = lambda t: t.cuda() if t.numel() else None
+    xd, bd, rd, sd = x.cuda(), bias.cuda(), router.cuda(), dev(shared.reshape(-1))
+
+    def check(run):
+        yd = torch.full((batch, d), 7.0, dtype=torch.bfloat16, device="cuda:0")
+        i = torch.full((batch, K), -1, dtype=torch.int32, device="cuda:0")
+        wd = torch.full((batch, K), -1.0, device="cuda:0")
+        run(yd, i, wd)
+        torch.cuda.synchronize()
+        i, wd, yd = i.cpu().long(), wd.cpu().double(), yd.cpu().double()
+        assert torch.equal(i[sure], idx[sure])
+        assert float((wd - w)[sure].abs().max()) < 1e-5
+        err = (yd - y).abs().max(-1).values / y.abs().max(-1).values
+        assert float(err[sure].max()) <= TOL["bf16"]
+        return i
+
+    for _ in range(2):
+        check(lambda yd, i, wd: B.moe_layer_decode_resident_noalloc(
+            n_experts=E, n_shared=ns, top_k=K, d_model=d, d_ff=f, dtype=B.MOE_DTYPE_BF16, pool_layout=B.MOE_LAYOUT_ROWMAJOR,
+            router_w=rd, experts=blocks.reshape(-1).cuda(), shared_w=sd, x=xd, y=yd, logit_bias=bd, topk_idx=i, topk_w=wd))
+    # (in-kernel fetch goes with the tiled layout and the router matrix in operand order)
+    packed = d == 256
+    pool = blocks.reshape(-1).clone()
+    if packed:
+        for src, dst in zip(blocks, pool.view(E, -1)):
+            B.moe_pack_expert(src.view(torch.int16).numpy().view(np.uint16), dst.view(torch.int16).numpy().view(np.uint16), d, f)
+    # the cache starts with all experts but one: the first call takes the in-order lookups, the second finds everything
+    cache = B.MoECache(n_layers=1, n_experts=E, n_shared=ns, top_k=K, d_model=d, d_ff=f, capacity=E, dtype=B.MOE_DTYPE_BF16,
+                       router_w=rd, expert_pool=pool.pin_memory(), max_batch=batch,
+                       shared_w=sd, trace_capacity=2 * batch * K,
+                       pool_layout=B.MOE_LAYOUT_TILED if packed else B.MOE_LAYOUT_ROWMAJOR,
+                       fetch_mode=B.MOE_FETCH_IN_KERNEL if packed else B.MOE_FETCH_COPY_ENGINE)
+    cache.moe_cache_prefill_pins(0, [e for e in range(E) if e != int(idx[0, 0])])
+    got = [check(lambda yd, i, wd: cache.moe_layer_decode(0, xd, yd, bd, i, wd)) for _ in range(2)]
+    rec, total = cache.moe_cache_read_trace(0)
+    assert total == 2 * batch * K
+    assert rec[:, 1].tolist() == np.concatenate([g.reshape(-1).numpy() for g in got]).tolist()
+    assert rec[:, 0].tolist() == 2 * np.repeat(np.arange(batch), K).tolist()
+    miss = np.flatnonzero(rec[:, 2] == 0)
+    assert miss.tolist() == [0] and int(rec[0, 1]) == int(idx[0, 0])
+    st = cache.moe_cache_stats(0)
+    assert st["hits"] == 2 * batch * K - 1 and st["misses"] == 1 and st["evictions"] == 0
+    cache.close()
