@@ -540,6 +540,7 @@ int moe_cache_create(const moe_cache_config_t* cfg, const moe_weights_t* weights
   const size_t o_po = cm; cm += align_up(NP * 4, 16);
   cm = align_up(cm, 32);
   const size_t o_gd = cm; cm += (size_t)c->G * sizeof(GroupDesc);
+  const size_t o_work = cm; cm += (1 + work_capacity(c->G, NP)) * sizeof(int4);
   const size_t o_ng = cm; cm += 16;
   const size_t o_arr = cm; cm += 16;
   CREATE_CHK(hipMalloc(&c->call_mem, cm), MOE_ERR_HIP);
@@ -550,6 +551,7 @@ int moe_cache_create(const moe_cache_config_t* cfg, const moe_weights_t* weights
   c->t.sorted_pair = reinterpret_cast<int32_t*>(c->call_mem + o_sp);
   c->t.pos_of = reinterpret_cast<int32_t*>(c->call_mem + o_po);
   c->t.grp = reinterpret_cast<GroupDesc*>(c->call_mem + o_gd);
+  c->t.work = reinterpret_cast<int4*>(c->call_mem + o_work);
   c->t.n_groups = reinterpret_cast<int32_t*>(c->call_mem + o_ng);
   c->arrive = reinterpret_cast<int32_t*>(c->call_mem + o_arr);
   CREATE_CHK(hipMalloc(&c->h, NP * cfg->d_ff * 4), MOE_ERR_HIP);
@@ -768,6 +770,9 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   a.policy = cf.policy; a.gamma = cf.gamma; a.trace_cap = cf.trace_capacity; a.seq = ++c->seq;
   a.pin_ids = nullptr; a.miss_list = c->miss_list; a.max_miss = c->max_miss;
   a.mailbox = c->full[layer] ? nullptr : c->mailbox;       // (every lookup hits: nobody reads the record)
+  const FfnPlan plan = plan_ffn(cf.pool_layout, d, cf.d_ff, batch);
+  const int g_max = (int)std::min<size_t>((size_t)batch * K, (size_t)c->P) + cf.n_shared;
+  if (plan.gemm) a.work = plan_ffn_gemm(batch, KS, g_max, false);
   HIPCHK(launch_route_cache(s, cf.dtype, ra, state_of(c, layer), c->t, a, ps ? ps->route : KernelEvents{}));
 
   FfnArgs fa{};
@@ -777,10 +782,10 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
                           : nullptr;
   fa.expert_bytes = c->expert_bytes;
   fa.P = c->P; fa.d = d; fa.f = cf.d_ff; fa.KS = KS;
-  fa.g_max = (int)std::min<size_t>((size_t)batch * K, (size_t)c->P) + cf.n_shared;
+  fa.g_max = g_max;
   fa.max_count = batch;
+  fa.work = a.work;
   fa.t = c->t; fa.h = c->h; fa.o = c->o;
-  const FfnPlan plan = plan_ffn(cf.pool_layout, d, cf.d_ff, batch);
   const bool fused = plan.fused;
   fa.fused = fused ? 1 : 0;
   const KernelEvents ke1 = ps ? ps->gate_up : KernelEvents{}, ke2 = ps ? ps->down : KernelEvents{};
@@ -910,6 +915,9 @@ int moe_layer_prefill(moe_cache_t* c, int32_t layer, const void* x_dev, const fl
   a.policy = cf.policy; a.gamma = cf.gamma; a.trace_cap = 0; a.seq = ++c->seq;
   a.pin_ids = nullptr; a.miss_list = c->miss_list; a.max_miss = c->max_miss;
   a.mailbox = c->full[layer] ? nullptr : c->mailbox;
+  const int g_max = (int)std::min<size_t>((size_t)n_tokens * K, (size_t)E) + cf.n_shared;   // groups are experts here
+  const bool q4 = cf.pool_layout == MOE_LAYOUT_TILED_INT4;
+  if (!q4) a.work = plan_ffn_gemm(n_tokens, KS, g_max, true);
   HIPCHK(launch_route_cache(s, cf.dtype, ra, state_of(c, layer), c->t, a, KernelEvents{}));
 
   FfnArgs fa{};
@@ -919,14 +927,14 @@ int moe_layer_prefill(moe_cache_t* c, int32_t layer, const void* x_dev, const fl
                           : nullptr;
   fa.expert_bytes = c->expert_bytes;
   fa.P = c->P; fa.d = d; fa.f = cf.d_ff; fa.KS = KS;
-  fa.g_max = (int)std::min<size_t>((size_t)n_tokens * K, (size_t)E) + cf.n_shared;   // groups are experts here
+  fa.g_max = g_max;
+  fa.work = a.work;
   fa.max_count = n_tokens;
   fa.t = c->t; fa.h = c->h; fa.o = c->o;
   fa.pass = 2; fa.fused = 0;
   fa.pool = c->pool_dev[layer];
   fa.fetch = 1;
-  HIPCHK(cf.pool_layout == MOE_LAYOUT_TILED_INT4 ? launch_ffn_gemm_q4(s, fa, KernelEvents{}, KernelEvents{})
-                                                  : launch_ffn_gemm(s, fa, KernelEvents{}, KernelEvents{}));
+  HIPCHK(q4 ? launch_ffn_gemm_q4(s, fa, KernelEvents{}, KernelEvents{}) : launch_ffn_gemm(s, fa, KernelEvents{}, KernelEvents{}));
 
   Mailbox mb{};
   if (!c->full[layer]) {          // with every expert resident nothing is streamed

@@ -61,7 +61,19 @@ struct CallTables {
   int32_t* pos_of;       // [B*KS]  inverse of sorted_pair
   GroupDesc* grp;        // [G]     one record per distinct expert buffer of the call
   int32_t* n_groups;     // [1]     number of groups of the call (0 if the call failed)
+  int4* work;            // [1 + work_capacity()] work list of the grouped GEMM
 };
+
+// Work list of the grouped GEMM, written by the routing launch: one item per (group, token tile) that exists, so that no
+// workgroup is launched for a tile that does not.  work[0] = (number of items, 0, 0, 0), then the items: (first token of the tile, buffer, first pair of
+// the group, its pairs | miss << 30), a group streamed from the host with its expert in place of the buffer: all a
+// workgroup needs of its group.
+struct WorkPlan {
+  int32_t shift;   // log2 of the tokens per tile (at least 6)
+  int32_t cap;     // items the list can hold; 0: no list
+};
+// tiles of 64 tokens at the smallest
+inline size_t work_capacity(size_t groups, size_t pairs) { return groups + pairs / 64; }
 
 struct CacheCallArgs {
   int32_t mode;          // 0 decode, 1 pin, 2 prompt streaming (cache read-only)
@@ -74,6 +86,7 @@ struct CacheCallArgs {
   Mailbox* mailbox;       // host-mapped; null: nobody reads the call record
   MissEntry* miss_list;   // host-mapped, [max_miss]
   int32_t max_miss;
+  WorkPlan work;          // work list to write for the grouped GEMM
   int32_t resident;       // 1: every expert sits in memory in the order of the ids (register-table case); no table is read
   int32_t row0;           // row of the caller's batch at which this wave of tokens starts (trace records)
 };
@@ -94,7 +107,8 @@ struct FfnArgs {
   const char* pool;        // in-kernel fetch: this layer's expert blocks in pinned host memory (device-visible)
   int32_t fetch;           // 1: groups with miss == 1 read their weights from `pool` and fill their buffer
   int32_t n_parts;         // tile kernel: workgroups (= partial rows in o) per group
-  int32_t work_down;       // grouped GEMM with a work list: offset of the down pass's items in the list (0: no list)
+  WorkPlan work;           // grouped GEMM: its work list
+  int32_t by_die;          // ... and its order: all row blocks of an item on one die
 };
 
 // Router inputs of one call.
@@ -140,6 +154,8 @@ hipError_t launch_reset(hipStream_t s, const LayerState& st, int E, int C, int P
                         unsigned long long* dev_stats);
 hipError_t launch_ffn_rowmajor(hipStream_t s, int dtype, const FfnArgs& a, KernelEvents gate_up, KernelEvents down);
 hipError_t launch_ffn_tiled(hipStream_t s, const FfnArgs& a, KernelEvents gate_up, KernelEvents down);
+// The tiles of a call of `batch` tokens, KS experts each, in at most g_max groups (streamed: experts read from the host).
+WorkPlan plan_ffn_gemm(int batch, int KS, int g_max, bool streamed);
 hipError_t launch_ffn_gemm(hipStream_t s, const FfnArgs& a, KernelEvents gate_up, KernelEvents down);
 // Most tokens per call for which the single-launch bf16 decode kernel is used (it can take 16 per expert; the
 // whole call is faster with the grouped GEMM from about 6 tokens on: 109 against 110 us at 6, 119 against 133 us

@@ -97,7 +97,7 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
   FfnPlan plan = plan_ffn(L->pool_layout, d, f, batch);
 
   // ---- carve the array ----
-  size_t o_tick, o_score, o_scal, o_ein, o_bos, o_free, o_zom, o_used, o_idx, o_wp, o_pb, o_sp, o_po, o_gd, o_ng,
+  size_t o_tick, o_score, o_scal, o_ein, o_bos, o_free, o_zom, o_used, o_idx, o_wp, o_pb, o_sp, o_po, o_gd, o_work, o_ng,
       o_arr, o_miss, o_h, o_o;
   auto carve = [&]() {
     size_t o = 0;
@@ -116,6 +116,7 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
     o_sp = o; o += up(NP * 4);
     o_po = o; o += up(NP * 4);
     o_gd = o; o += up((size_t)G * sizeof(GroupDesc));
+    o_work = o; o += up((1 + work_capacity(G, NP)) * sizeof(int4));
     o_ng = o; o += 256;
     o_miss = o; o += up(max_miss * sizeof(MissEntry));
     o_h = o; o += plan.fused ? 0 : up(NP * (size_t)f * 4);
@@ -173,6 +174,7 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
   t.sorted_pair = reinterpret_cast<int32_t*>(base + o_sp);
   t.pos_of = reinterpret_cast<int32_t*>(base + o_po);
   t.grp = reinterpret_cast<GroupDesc*>(base + o_gd);
+  t.work = reinterpret_cast<int4*>(base + o_work);
   t.n_groups = reinterpret_cast<int32_t*>(base + o_ng);
   int32_t* arrive = reinterpret_cast<int32_t*>(base + o_arr);
 
@@ -195,6 +197,7 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
   a.mailbox = nullptr;
   a.miss_list = reinterpret_cast<MissEntry*>(base + o_miss);
   a.max_miss = (int32_t)max_miss;
+  if (plan.gemm) a.work = plan_ffn_gemm(batch, KS, G, false);
   HIPCHK(launch_route_cache(s, L->dtype, ra, st, t, a, KernelEvents{}));
 
   FfnArgs fa{};
@@ -205,6 +208,7 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
   fa.P = E; fa.d = d; fa.f = f; fa.KS = KS;
   fa.g_max = G;
   fa.max_count = batch;
+  fa.work = a.work;
   fa.t = t;
   fa.h = base + o_h;
   fa.o = reinterpret_cast<float*>(base + o_o);

@@ -101,7 +101,7 @@ __host__ __device__ inline LdsLayout lds_layout(int E, int C, int P, int n_share
 // pair_buf[B*KS] must hold the buffer of every routed pair; shared-expert pairs are filled in here.
 // The order of the pairs inside a group is whatever order the LDS atomics resolve in; every pair's arithmetic is
 // independent of its position, so the layer output does not depend on it.
-__device__ int group_pairs_lds(int32_t* count, int32_t* cursor, const int32_t* filled, int32_t* pair_buf,
+__device__ __forceinline__ int group_pairs_lds(int32_t* count, int32_t* cursor, const int32_t* filled, int32_t* pair_buf,
                                const CallTables& t, const CacheCallArgs& a) {
   const int lane = threadIdx.x & 63;
   const uint64_t lt_mask = (1ull << lane) - 1ull;
@@ -149,12 +149,43 @@ __device__ int group_pairs_lds(int32_t* count, int32_t* cursor, const int32_t* f
   return n_groups;
 }
 
+// ---------------------------------------------------------------- work list of the grouped GEMM
+__device__ __forceinline__ int4 work_item(int tok0, int buf, int begin, int count, int miss) {
+  return int4{tok0, buf, begin, count | (miss ? 1 << 30 : 0)};
+}
+
+__device__ __forceinline__ int tiles_of(int count, const WorkPlan& w) { return (count + (1 << w.shift) - 1) >> w.shift; }
+
+// The list in the order of the groups, from the descriptors just written; ONE wave.
+__device__ __forceinline__ void write_work_list(const CallTables& t, const CacheCallArgs& a, int n_groups) {
+  if (a.work.cap == 0) return;
+  const int lane = threadIdx.x & 63;
+  wave_sync();
+  int base = 0;
+  for (int g0 = 0; g0 < n_groups; g0 += kWave) {
+    GroupDesc gd{};
+    if (g0 + lane < n_groups) gd = t.grp[g0 + lane];
+    const int buf = a.mode == 2 && gd.miss ? gd.expert : gd.buf;
+    const int n = tiles_of(gd.count, a.work);
+    int incl = n;
+#pragma unroll
+    for (int dlt = 1; dlt < kWave; dlt <<= 1) {
+      const int v = __shfl_up(incl, dlt);
+      if (lane >= dlt) incl += v;
+    }
+    int4* items = t.work + 1 + base + incl - n;
+    for (int i = 0; i < n; ++i) items[i] = work_item(i << a.work.shift, buf, gd.begin, gd.count, gd.miss);
+    base += __shfl(incl, kWave - 1);
+  }
+  if (lane == 0) t.work[0] = int4{base, 0, 0, 0};
+}
+
 // ---------------------------------------------------------------- prompt streaming
 // Phase 3 of a prefill call: the cache is only READ.  Pairs are grouped by expert; a group whose expert is
 // resident reads its buffer, any other group streams its expert from the pinned host pool (miss = 1) and
 // nothing is inserted or refreshed, so a one-off scan over a long prompt leaves the cache as the prefetch set
 // it.  Runs in ONE wave; idx [B][K] routed experts (LDS or global), keys [B*KS] scratch.
-__device__ void prefill_phase(unsigned char* smem, const LdsLayout& L, const int32_t* idx, int32_t* keys,
+__device__ __forceinline__ void prefill_phase(unsigned char* smem, const LdsLayout& L, const int32_t* idx, int32_t* keys,
                               const LayerState& st, const CallTables& t, const CacheCallArgs& a) {
   int32_t* slot_of = reinterpret_cast<int32_t*>(smem + L.slot_of);
   int32_t* count = reinterpret_cast<int32_t*>(smem + L.count);
@@ -210,6 +241,7 @@ __device__ void prefill_phase(unsigned char* smem, const LdsLayout& L, const int
   }
   wave_sync();
   for (int gi = lane; gi < n_groups; gi += kWave) t.grp[gi].pair0 = t.sorted_pair[t.grp[gi].begin];
+  write_work_list(t, a, n_groups);
   if (lane == 0) {
     *t.n_groups = n_groups;
     publish_record(a.mailbox, MOE_OK, n_stream, 0, n_groups, 0, (int)st.scalars[SC_NRES], a.seq);
@@ -219,7 +251,7 @@ __device__ void prefill_phase(unsigned char* smem, const LdsLayout& L, const int
 // ---------------------------------------------------------------- phase 3
 // General path (any C, P, batch; both policies): the table lives in LDS.
 // Runs in ONE wave.  idx: selected experts [B][K] (LDS or global); pair_buf: scratch [B*KS].
-__device__ void cache_phase_general(unsigned char* smem, const LdsLayout& L, const int32_t* idx, int32_t* pair_buf,
+__device__ __forceinline__ void cache_phase_general(unsigned char* smem, const LdsLayout& L, const int32_t* idx, int32_t* pair_buf,
                             const LayerState& st, const CallTables& t, const CacheCallArgs& a) {
   uint64_t* tick = reinterpret_cast<uint64_t*>(smem + L.tick);
   double* score = reinterpret_cast<double*>(smem + L.score);
@@ -362,7 +394,10 @@ __device__ void cache_phase_general(unsigned char* smem, const LdsLayout& L, con
   if (status == MOE_OK && a.mode == 0) {
     n_groups = group_pairs_lds(count, start, filled, pair_buf, t, a);
   }
-  if (a.mode == 0 && lane == 0) *t.n_groups = n_groups;
+  if (a.mode == 0) {
+    if (lane == 0) *t.n_groups = n_groups;
+    write_work_list(t, a, n_groups);
+  }
 
   if (status == MOE_OK) {
     // ---- commit ----
@@ -389,7 +424,7 @@ __device__ void cache_phase_general(unsigned char* smem, const LdsLayout& L, con
 
 // Runs in ONE wave.  idx_src: the experts to look up, in order (decode: [B][K]; pin: the list);
 // pair_buf: scratch [B*KS] (LDS or global), used when the call has more than 64 pairs.
-__device__ void cache_phase_fast(FastTable f, unsigned char* smem, const LdsLayout& L, const int32_t* idx_src,
+__device__ __forceinline__ void cache_phase_fast(FastTable f, unsigned char* smem, const LdsLayout& L, const int32_t* idx_src,
                                  int32_t* pair_buf, const LayerState& st, const CallTables& t,
                                  const CacheCallArgs& a) {
   const int lane = threadIdx.x & 63;
@@ -593,7 +628,10 @@ __device__ void cache_phase_fast(FastTable f, unsigned char* smem, const LdsLayo
       n_groups = group_pairs_lds(lds_count, lds_cursor, lds_filled, pair_buf, t, a);
     }
   }
-  if (a.mode == 0 && lane == 0) *t.n_groups = n_groups;
+  if (a.mode == 0) {
+    if (lane == 0) *t.n_groups = n_groups;
+    write_work_list(t, a, n_groups);
+  }
 
   if (status == MOE_OK) {
     // ---- commit ----
@@ -757,7 +795,7 @@ constexpr int kMaxKeys = 2 * kWave; // buffer ids of the register-table case, sh
 // What the grouping phase of the tile kernel keeps in LDS.
 struct TileLds {
   int map[kTileMaxE];          // expert -> buffer << 8 | slot, -1 when it is not resident
-  int count[kMaxKeys], start[kMaxKeys], group[kMaxKeys];
+  int count[kMaxKeys], start[kMaxKeys], group[kMaxKeys], first[kMaxKeys];
   int last[kWave], touched[kWave];
   int any_miss, n_groups, last_arrived;
 };
@@ -822,14 +860,28 @@ __device__ __forceinline__ void group_hits(unsigned char* smem, const LdsLayout&
       st.trace[trace_n + l] = moe_trace_rec_t{a.row0 + l / K, idx_at(l), 1, -1};
   }
   __syncthreads();
+  if (a.work.cap > 0) {
+    // work list, groups with the most tokens first: a group's items come behind those of all larger ones (ties by id)
+    constexpr int kParts = kTileThreads / kMaxKeys;
+    const int key = tid % kMaxKeys, part = tid / kMaxKeys;
+    const int c = key < P ? tl.count[key] : key < NB ? a.B : 0;
+    int before = 0;
+    for (int j = part; j < NB; j += kParts) {
+      const int cj = j < P ? tl.count[j] : a.B;
+      before += cj > c || (cj == c && j < key) ? tiles_of(cj, a.work) : 0;
+    }
+    atomicAdd(&tl.first[key], before);
+  }
   if (wave == 0) {
     // group descriptors in ascending buffer id (every token is in the group of every shared expert)
     const uint64_t lt_mask = (1ull << lane) - 1ull;
     int n_groups = 0, offset = 0;
+    float n_tiles = 0.f;
 #pragma unroll 1
     for (int base = 0; base < NB; base += kWave) {
       const int id = base + lane;
       const int c = id < P ? tl.count[id] : id < NB ? a.B : 0;
+      n_tiles += (float)tiles_of(c, a.work);
       int incl = c;
 #pragma unroll
       for (int dlt = 1; dlt < kWave; dlt <<= 1) {
@@ -848,9 +900,18 @@ __device__ __forceinline__ void group_hits(unsigned char* smem, const LdsLayout&
       n_groups += __popcll(gm);
       offset += __shfl(incl, kWave - 1);
     }
+    if (a.work.cap > 0) {       // (whole numbers below 2^24: the float sum is exact)
+      n_tiles = wave_sum(n_tiles);
+      if (lane == 0) t.work[0] = int4{(int)n_tiles, 0, 0, 0};
+    }
     if (lane == 0) { *t.n_groups = n_groups; tl.n_groups = n_groups; }
   }
   __syncthreads();
+  if (a.work.cap > 0 && tid < NB) {
+    const int c = tid < P ? tl.count[tid] : a.B;
+    int4* items = t.work + 1 + tl.first[tid];
+    for (int i = 0; i < tiles_of(c, a.work); ++i) items[i] = work_item(i << a.work.shift, tid, tl.start[tid], c, 0);
+  }
   const auto place = [&](int p, int key, int r) {
     const int pos = tl.start[key] + r;
     t.sorted_pair[pos] = p;
@@ -930,7 +991,7 @@ __global__ void __launch_bounds__(kTileThreads) route_tile_kernel(RouteArgs r, L
   RawTable raw{};
   if (fast && wave == 0) raw = raw_load(st, a);
   for (int e = tid; e < E; e += kTileThreads) tl.map[e] = -1;
-  if (tid < kMaxKeys) tl.count[tid] = 0;
+  if (tid < kMaxKeys) tl.count[tid] = tl.first[tid] = 0;
   if (tid < kWave) { tl.last[tid] = 0; tl.touched[tid] = 0; }
   if (tid == 0) tl.any_miss = 0;
 
