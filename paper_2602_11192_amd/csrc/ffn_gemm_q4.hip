@@ -2,9 +2,9 @@
 // (section 3.2) as a grouped GEMM, for calls in which an expert sees many
 // tokens: batched decode beyond 16 tokens and prompt processing.
 //
-// One workgroup = 4 waves x a tile of up to 64 of one expert's tokens.  Tokens
+// One workgroup = 4 waves x a tile of up to TOK of one expert's tokens.  Tokens
 // are the A operand of v_mfma_f32_16x16x32_bf16, staged through LDS in fragment
-// order, four k-blocks (128 columns) per step, double buffered; weights are the
+// order, four k-blocks (128 columns) per step of the gate/up pass and two per step of the down pass, double buffered; weights are the
 // B operand, unpacked from 4-bit codes in registers (see ffn_fused_q4.hip for
 // the 128 + q mantissa trick and the -136 correction fed through the C input).
 // A lane holds one weight row for four tokens, so the per-group scale is one
@@ -14,8 +14,11 @@
 //     the eight scales.  h = silu(g) * u is written as bf16, rows in group order.
 //   down pass: wave w owns the block of 64 rows 4 bx + w of W_d; per k-block one
 //     16-byte load per lane brings the codes of its four row tiles.
-// Every weight byte is read by exactly one wave, so a group whose expert is not
+// Codes and tokens are requested R - 1 steps ahead of their use into a ring of fixed register slots.
+// Every weight byte is read by exactly one wave of a token tile, so a group whose expert is not
 // resident can stream it from the pinned host pool (prompt streaming).
+#include <type_traits>
+
 #include "device_utils.hpp"
 #include "moe_internal.hpp"
 #include "q4_layout.hpp"
@@ -30,7 +33,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kWaves = 4;
-constexpr int kSkb = 4;             // k-blocks staged per step
 
 template <typename V>
 __device__ __forceinline__ V ldnt(const void* p) {
@@ -57,165 +59,173 @@ __device__ __forceinline__ const char* group_weights(const FfnArgs& a, int id) {
                   : a.shared + (size_t)(id - a.P) * a.expert_bytes;
 }
 
-// kTok: tokens per workgroup (64 or 128).  An expert streamed from the host is read once per token tile, so prompt
-// streaming takes the large tile; the small one needs half the accumulators and serves every resident call.
-template <int NMAT, int kTok>
-__global__ void __launch_bounds__(64 * kWaves) ffn_gemm_q4_kernel(FfnArgs a) {
-  constexpr int kCb = kTok / 16;      // column blocks of 16 tokens
-  constexpr int kPieces = kTok / 16;  // 16-byte pieces of the token tile each thread stages per step
+// TOK: tokens per workgroup.  R: steps in flight.  MINW: waves per SIMD the registers have to leave room for.
+// STREAM: experts may have to be read over the link: nothing is requested beyond the contraction (a branch around the
+// loads; without it the last requests of a wave repeat its last step).
+template <int NMAT, int TOK, int R, int MINW, bool STREAM>
+__global__ void __launch_bounds__(64 * kWaves, MINW) ffn_gemm_q4_kernel(FfnArgs a) {
+  constexpr int CB = TOK / 16;        // column blocks of 16 tokens
+  constexpr int kSkb = NMAT == 2 ? 4 : 2;                   // k-blocks per step
+  constexpr int PIECES = TOK * kSkb * 4 / (64 * kWaves);    // 16-byte pieces of the token tile each thread stages per step
   // [buffer][k-block of the step][column block][lane] x 16 bytes
-  __shared__ u32x4 xs[2][kSkb][kCb][64];
-  const int g = blockIdx.y;
-  const int ng = *a.t.n_groups;
-  const GroupDesc gd = a.t.grp[g];
-  if (g >= ng || (a.pass != 2 && gd.miss != a.pass)) return;
-  const int tok0 = blockIdx.z * kTok;
-  const int cnt = gd.count;
-  if (tok0 >= cnt) return;
-  const int n_tok = min(kTok, cnt - tok0);
+  __shared__ u32x4 xs[2][kSkb][CB][64];
+  const int d = a.d, f = a.f;
+  const int n_units = NMAT == 2 ? (f >> 4) : (d >> 6);         // row tiles of 16 / row blocks of 64
+  const int n_rb = (n_units + kWaves - 1) / kWaves;
+  const int item_id = blockIdx.x / n_rb, rb = blockIdx.x % n_rb;
+  const int n_items = a.t.work[0].x;
+  const int4 item = a.t.work[1 + min(item_id, a.work.cap - 1)];
+  if (item_id >= n_items) return;
+  const int tok0 = item.x, begin = item.z, cnt = item.w & 0x3fffffff, miss = (item.w >> 30) & 1;
+  if (a.pass != 2 && miss != a.pass) return;
+  const int n_tok = min(TOK, cnt - tok0);
   const int n_cb = (n_tok + 15) >> 4;
 
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 15, q = lane >> 4;
-  const int d = a.d, f = a.f;
-  const int kdim = NMAT == 2 ? d : f;
-  const int nkb = kdim >> 5;                                   // k-blocks of the contraction
-  const int n_units = NMAT == 2 ? (f >> 4) : (d >> 6);         // row tiles of 16 / row blocks of 64
-  const int unit = blockIdx.x * kWaves + wave;                 // this wave's row tile / row block
+  const int nkb = (NMAT == 2 ? d : f) >> 5;                    // k-blocks of the contraction
+  const int n_steps = (nkb + kSkb - 1) / kSkb;
+  const int unit = rb * kWaves + wave;                         // this wave's row tile / row block
   const bool has_rows = unit < n_units;
   const int uc = has_rows ? unit : n_units - 1;                // clamped: loads stay in bounds, results are dropped
 
-  const char* wsrc = (a.fetch != 0 && gd.miss != 0) ? a.pool + (size_t)gd.expert * a.expert_bytes
-                                                    : group_weights(a, gd.buf);
+  const char* wsrc = (a.fetch != 0 && miss != 0) ? a.pool + (size_t)item.y * a.expert_bytes : group_weights(a, item.y);
   // gate/up: records [row tile][super-block of 4 k-blocks]; down: records [k-block][row block]
   const int nsb = d >> 7, n_dq = d >> 6;
   const char* wrec = NMAT == 2 ? wsrc + (size_t)uc * nsb * q4::kGateUpRecord
                                : wsrc + q4::gate_up_bytes(d, f) + (size_t)uc * q4::kDownRecord;
-
-  // ---- token staging: 256 threads x kPieces pieces of 16 bytes = kTok rows x 256 bytes (4 k-blocks) ----
-  const uint16_t* src[kPieces];
-  int dst[kPieces];
-#pragma unroll
-  for (int i = 0; i < kPieces; ++i) {
-    const int idx = threadIdx.x + 256 * i;
-    const int r = idx >> 4, sg = idx & 15;                     // token row of the tile, 16-byte segment of its 256 bytes
-    const int kbl = sg >> 2, qq = sg & 3;
-    // the 16 lanes that write together hold one row's 16 (k-block, slice) pieces: the XOR spreads them over the banks
-    dst[i] = (kbl * kCb + (r >> 4)) * 64 + qq * 16 + ((r & 15) ^ (qq + 4 * kbl));
-    if (r < n_tok) {
-      if (NMAT == 2) {
-        const int p = a.t.sorted_pair[gd.begin + tok0 + r];
-        src[i] = reinterpret_cast<const uint16_t*>(a.x) + (size_t)(p / a.KS) * d + sg * 8;
-      } else {
-        src[i] = reinterpret_cast<const uint16_t*>(a.h) + (size_t)(gd.begin + tok0 + r) * f + sg * 8;
-      }
-    } else {
-      src[i] = nullptr;
-    }
-  }
-  auto load_x = [&](u32x4 (&xr)[kPieces], int kb) {
-#pragma unroll
-    for (int i = 0; i < kPieces; ++i) {
-      const int kbi = kb + ((threadIdx.x + 256 * i) & 15) / 4;   // k-block this piece belongs to
-      xr[i] = (src[i] != nullptr && kbi < nkb) ? *reinterpret_cast<const u32x4*>(src[i] + (size_t)kb * 32)
-                                                : u32x4{0, 0, 0, 0};
-    }
-  };
   // weights of one step: gate/up = codes of W_g, W_u and 8 scales of one super-block;
-  //                      down    = codes of 4 row tiles and 4 scales for each of up to 4 k-blocks
-  constexpr int NW = NMAT == 2 ? 3 : 6;
-  auto load_w = [&](u32x4 (&wr)[NW], int kb) {
+  //                      down    = codes of 4 row tiles and 4 scales for each of 2 k-blocks
+  constexpr int NW = 3;
+  u32x4 wr[R][NW];
+  auto req_w = [&](int slot, int step) {
     if (NMAT == 2) {
-      const char* rec = wrec + (size_t)(kb >> 2) * q4::kGateUpRecord;
-      wr[0] = ldnt<u32x4>(rec + lane * 16);
-      wr[1] = ldnt<u32x4>(rec + 1024 + lane * 16);
-      wr[2] = ldnt<u32x4>(rec + 2048 + n * 16);
+      const char* rec = wrec + (size_t)step * q4::kGateUpRecord;
+      wr[slot][0] = ldnt<u32x4>(rec + lane * 16);
+      wr[slot][1] = ldnt<u32x4>(rec + 1024 + lane * 16);
+      wr[slot][2] = ldnt<u32x4>(rec + 2048 + n * 16);
     } else {
 #pragma unroll
       for (int j = 0; j < kSkb; ++j) {
-        const int kbj = kb + j < nkb ? kb + j : nkb - 1;         // clamped; the surplus k-blocks are skipped below
-        const char* rec = wrec + (size_t)kbj * n_dq * q4::kDownRecord;
-        wr[j] = ldnt<u32x4>(rec + lane * 16);
+        const int kb = min(step * kSkb + j, nkb - 1);          // clamped; the surplus k-blocks are skipped below
+        const char* rec = wrec + (size_t)kb * n_dq * q4::kDownRecord;
+        wr[slot][j] = ldnt<u32x4>(rec + lane * 16);
         const u32x2 s2 = ldnt<u32x2>(rec + 1024 + n * 8);
-        wr[4 + (j >> 1)][(j & 1) * 2] = s2[0];
-        wr[4 + (j >> 1)][(j & 1) * 2 + 1] = s2[1];
+        wr[slot][2][j * 2] = s2[0];
+        wr[slot][2][j * 2 + 1] = s2[1];
       }
     }
+  };
+#pragma unroll
+  for (int u = 0; u < R - 1; ++u) req_w(u, min(u, n_steps - 1));
+
+  // ---- token staging: 256 threads x PIECES pieces of 16 bytes = TOK rows x kSkb k-blocks of 64 bytes; rows beyond the
+  //      tile repeat its last token, their results are dropped at the end ----
+  const uint16_t* src[PIECES];
+  int dst[PIECES];
+  constexpr int SEGS = 4 * kSkb;                                 // 16-byte segments of a row's step
+  const int sg = threadIdx.x % SEGS, kbl = sg >> 2, qq = sg & 3;
+  // the lanes that write together hold the (k-block, slice) pieces of one or two rows: the XOR spreads them over the
+  // banks, and keeps the rows of neighbouring slices of a k-block apart for the reader
+  const auto swz = [](int kb, int slice) { return (slice + 4 * kb) * (kSkb == 4 ? 1 : 2); };
+#pragma unroll
+  for (int i = 0; i < PIECES; ++i) {
+    const int r = threadIdx.x / SEGS + 64 * kWaves / SEGS * i;   // token row of the tile
+    dst[i] = (kbl * CB + (r >> 4)) * 64 + qq * 16 + ((r & 15) ^ swz(kbl, qq));
+    const int pos = begin + tok0 + min(r, n_tok - 1);
+    src[i] = NMAT == 2 ? reinterpret_cast<const uint16_t*>(a.x) + (size_t)(a.t.sorted_pair[pos] / a.KS) * d + qq * 8
+                       : reinterpret_cast<const uint16_t*>(a.h) + (size_t)pos * f + qq * 8;
+  }
+  u32x4 xq[R][PIECES];
+  auto req_x = [&](int slot, int step) {
+    const int kb = min(step * kSkb + kbl, nkb - 1);
+#pragma unroll
+    for (int i = 0; i < PIECES; ++i) xq[slot][i] = *reinterpret_cast<const u32x4*>(src[i] + (size_t)kb * 32);
+  };
+  auto put_x = [&](int b, int slot) {
+#pragma unroll
+    for (int i = 0; i < PIECES; ++i) (&xs[b][0][0][0])[dst[i]] = xq[slot][i];
   };
 
   const bf16x8 minus136 = __builtin_bit_cast(bf16x8, u32x4{0xC308C308u, 0xC308C308u, 0xC308C308u, 0xC308C308u});
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
   // gate/up: acc[cb][0] gate, acc[cb][1] up; down: acc[cb][j] row tile j of the block
   constexpr int NA = NMAT == 2 ? 2 : 4;
-  f32x4 acc[kCb][NA];
+  f32x4 acc[CB][NA];
 #pragma unroll
-  for (int cb = 0; cb < kCb; ++cb)
+  for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
     for (int m = 0; m < NA; ++m) acc[cb][m] = zero;
 
-  u32x4 xr[kPieces], wc[NW], wn[NW];
-  load_x(xr, 0);
-  load_w(wc, 0);
 #pragma unroll
-  for (int i = 0; i < kPieces; ++i) (&xs[0][0][0][0])[dst[i]] = xr[i];
+  for (int u = 0; u < R - 1; ++u) req_x(u, min(u, n_steps - 1));
+  put_x(0, 0);
   __syncthreads();
-
-  int buf = 0;
-  for (int kb = 0; kb < nkb; kb += kSkb) {
-    const bool more = kb + kSkb < nkb;
-    if (more) {
-      load_x(xr, kb + kSkb);
-      load_w(wn, kb + kSkb);
-    }
+  // the column blocks in use, rounded up to a quarter or half of the tile, as a compile-time count
+  auto run = [&](auto ncb_tag) {
+    constexpr int NCB = decltype(ncb_tag)::value;
+    auto multiply = [&](int u, int b, int n_kb) {
+      u32x4 fr[2][NCB];               // token fragments of a k-block, those of the next one on their way
 #pragma unroll
-    for (int j = 0; j < kSkb; ++j) {
-      if (kb + j < nkb) {       // uniform
-        bf16x8 wb[NA];
-        float sc[NA];
-        if (NMAT == 2) {
-          wb[0] = codes_to_bf16(wc[0][j]);
-          wb[1] = codes_to_bf16(wc[1][j]);
-          sc[0] = scale_at(wc[2], j);
-          sc[1] = scale_at(wc[2], 4 + j);
-        } else {
+      for (int cb = 0; cb < NCB; ++cb) fr[0][cb] = xs[b][0][cb][lane ^ swz(0, q)];
 #pragma unroll
-          for (int m = 0; m < 4; ++m) {
-            wb[m] = codes_to_bf16(wc[j][m]);
-            sc[m] = scale_at(wc[4 + (j >> 1)], (j & 1) * 4 + m);
-          }
+      for (int j = 0; j < kSkb; ++j) {
+        if (j + 1 < kSkb) {
+#pragma unroll
+          for (int cb = 0; cb < NCB; ++cb) fr[(j + 1) & 1][cb] = xs[b][j + 1][cb][lane ^ swz(j + 1, q)];
         }
+        __builtin_amdgcn_sched_barrier(0);
+        if (j < n_kb) {      // uniform
+          bf16x8 wb[NA];
+          float sc[NA];
 #pragma unroll
-        for (int cb = 0; cb < kCb; ++cb) {
-          if (cb < n_cb) {      // uniform
-            const bf16x8 xa = __builtin_bit_cast(bf16x8, xs[buf][j][cb][lane ^ (q + 4 * j)]);
+          for (int m = 0; m < NA; ++m) {
+            wb[m] = codes_to_bf16(NMAT == 2 ? wr[u][m][j] : wr[u][j][m]);
+            sc[m] = scale_at(wr[u][2], NMAT == 2 ? 4 * m + j : 4 * j + m);
+          }
+#pragma unroll
+          for (int cb = 0; cb < NCB; ++cb) {
+            const bf16x8 xa = __builtin_bit_cast(bf16x8, fr[j & 1][cb]);
             const f32x4 off = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, minus136, zero, 0, 0, 0);
 #pragma unroll
             for (int m = 0; m < NA; ++m)
               acc[cb][m] += sc[m] * __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, wb[m], off, 0, 0, 0);
           }
         }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    // (as in ffn_gemm.hip: no branch around a load, tokens requested ahead of the weights of the same step)
+#pragma unroll 1
+    for (int s0 = 0; s0 < n_steps; s0 += R) {
+#pragma unroll
+      for (int u = 0; u < R; ++u) {
+        const int ahead = s0 + u + R - 1;
+        if (!STREAM || ahead < n_steps) {
+          req_x((u + R - 1) % R, min(ahead, n_steps - 1));
+          req_w((u + R - 1) % R, min(ahead, n_steps - 1));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (s0 + u < n_steps) multiply(u, (s0 + u) & 1, nkb - (s0 + u) * kSkb);
+        put_x((s0 + u + 1) & 1, (u + 1) % R);
+        __syncthreads();
       }
     }
-    if (more) {
-#pragma unroll
-      for (int i = 0; i < kPieces; ++i) (&xs[buf ^ 1][0][0][0])[dst[i]] = xr[i];
-#pragma unroll
-      for (int m = 0; m < NW; ++m) wc[m] = wn[m];
-    }
-    __syncthreads();
-    buf ^= 1;
-  }
+  };
+  if (CB >= 4 && n_cb <= CB / 4) run(std::integral_constant<int, CB / 4 ? CB / 4 : 1>{});
+  else if (n_cb <= CB / 2) run(std::integral_constant<int, CB / 2>{});
+  else run(std::integral_constant<int, CB>{});
 
   // ---- epilogue: lane holds weight row n of its tile(s) for tokens 16 cb + 4 q + i ----
   if (!has_rows) return;
 #pragma unroll
-  for (int cb = 0; cb < kCb; ++cb) {
+  for (int cb = 0; cb < CB; ++cb) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int tk = cb * 16 + q * 4 + i;
-      if (cb < n_cb && tk < n_tok) {
-        const size_t pos = (size_t)(gd.begin + tok0 + tk);
+      if (tk < n_tok) {
+        const size_t pos = (size_t)(begin + tok0 + tk);
         if (NMAT == 2) {
           reinterpret_cast<uint16_t*>(a.h)[pos * f + unit * 16 + n] =
               f32_to_bf16(silu(acc[cb][0][i]) * acc[cb][NA - 1][i]);
@@ -229,26 +239,38 @@ __global__ void __launch_bounds__(64 * kWaves) ffn_gemm_q4_kernel(FfnArgs a) {
   }
 }
 
+constexpr int kSmallTile = 5, kLargeTile = 6, kStreamedTile = 7;     // log2 of the tokens per tile
+
 }  // namespace
+
+// What bounds it: the vector arithmetic of unpacking and scaling and the exchange through LDS as much as the codes, so
+// occupancy beats depth: one step ahead at four waves per SIMD takes 61.6 us per layer call of 64 OLMoE-like tokens, two
+// steps ahead at three waves 68.3, three at two 67.1; the former loop on 64-token tiles 83 (gate/up 43.5 us for 151 MB, down
+// 27 us for 75 MB).  Tiles of 32 tokens win up to a mean of ~64 pairs per expert: 57 / 61.6 / 74 / 95.5 / 145 / 237 us at 17 /
+// 64 / 128 / 256 / 512 / 1024 tokens against 65 / 70 / 79 / 104 / 142 / 229 with tiles of 64.  Experts streamed from the host
+// cross the link once per tile: 128 tokens.
+WorkPlan plan_ffn_gemm_q4(int batch, int KS, int g_max, bool streamed) {
+  const int64_t load = (int64_t)batch * KS;
+  WorkPlan w{};
+  w.shift = streamed ? kStreamedTile : load <= (int64_t)56 * g_max ? kSmallTile : kLargeTile;
+  w.cap = (int)work_capacity(g_max, load);
+  return w;
+}
 
 hipError_t launch_ffn_gemm_q4(hipStream_t s, const FfnArgs& a, KernelEvents e1, KernelEvents e2) {
   if (a.g_max <= 0) return hipSuccess;
-  // 128-token tiles only when experts stream in from the host (each tile reads the expert over the link once).
-  // On resident experts the 64-token tile is faster at every call size measured (OLMoE-like layer: 71 against
-  // 127 us at 64 tokens per call, 280 against 413 us at 1024, 505 against 717 us at 2048): half the accumulators,
-  // twice the workgroups per compute unit.
-  const bool large_tile = a.fetch != 0;
-  const int tok = large_tile ? 128 : 64;
-  const int tiles = (a.max_count + tok - 1) / tok;
-  dim3 block(64 * kWaves);
-  dim3 g1((a.f / 16 + kWaves - 1) / kWaves, a.g_max, tiles);
-  dim3 g2((a.d / 64 + kWaves - 1) / kWaves, a.g_max, tiles);
-  if (large_tile) {
-    launch_timed(ffn_gemm_q4_kernel<2, 128>, g1, block, 0, s, e1, a);
-    launch_timed(ffn_gemm_q4_kernel<1, 128>, g2, block, 0, s, e2, a);
+  const int items = a.g_max + (int)(((int64_t)a.max_count * a.KS) >> a.work.shift);     // upper bound
+  const auto blocks = [&](int units) { return dim3(items * ((units + kWaves - 1) / kWaves)); };
+  const dim3 block(64 * kWaves);
+  if (a.work.shift == kStreamedTile) {
+    launch_timed(ffn_gemm_q4_kernel<2, 128, 2, 1, true>, blocks(a.f / 16), block, 0, s, e1, a);
+    launch_timed(ffn_gemm_q4_kernel<1, 128, 2, 1, true>, blocks(a.d / 64), block, 0, s, e2, a);
+  } else if (a.work.shift == kSmallTile) {
+    launch_timed(ffn_gemm_q4_kernel<2, 32, 2, 4, false>, blocks(a.f / 16), block, 0, s, e1, a);
+    launch_timed(ffn_gemm_q4_kernel<1, 32, 2, 4, false>, blocks(a.d / 64), block, 0, s, e2, a);
   } else {
-    launch_timed(ffn_gemm_q4_kernel<2, 64>, g1, block, 0, s, e1, a);
-    launch_timed(ffn_gemm_q4_kernel<1, 64>, g2, block, 0, s, e2, a);
+    launch_timed(ffn_gemm_q4_kernel<2, 64, 2, 3, false>, blocks(a.f / 16), block, 0, s, e1, a);
+    launch_timed(ffn_gemm_q4_kernel<1, 64, 2, 2, false>, blocks(a.d / 64), block, 0, s, e2, a);
   }
   return hipGetLastError();
 }

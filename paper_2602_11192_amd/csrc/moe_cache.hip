@@ -50,8 +50,12 @@ FfnPlan plan_ffn(int pool_layout, int d, int f, int batch) {
   p.tiled = pool_layout == MOE_LAYOUT_TILED;
   p.q4 = pool_layout == MOE_LAYOUT_TILED_INT4;
   p.fused = p.q4 ? batch <= 16 : (p.tiled && ffn_fused_supported(d, f, batch));
-  p.gemm = p.tiled && !p.fused && batch > fused_max_tokens(f);
+  p.gemm = !p.fused && (p.q4 || (p.tiled && batch > fused_max_tokens(f)));
   return p;
+}
+
+WorkPlan plan_work(const FfnPlan& p, int batch, int KS, int g_max) {
+  return !p.gemm ? WorkPlan{} : p.q4 ? plan_ffn_gemm_q4(batch, KS, g_max, false) : plan_ffn_gemm(batch, KS, g_max, false);
 }
 
 hipError_t launch_ffn(hipStream_t s, int dtype, const FfnPlan& p, const FfnArgs& a, KernelEvents ke1, KernelEvents ke2) {
@@ -772,7 +776,7 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   a.mailbox = c->full[layer] ? nullptr : c->mailbox;       // (every lookup hits: nobody reads the record)
   const FfnPlan plan = plan_ffn(cf.pool_layout, d, cf.d_ff, batch);
   const int g_max = (int)std::min<size_t>((size_t)batch * K, (size_t)c->P) + cf.n_shared;
-  if (plan.gemm) a.work = plan_ffn_gemm(batch, KS, g_max, false);
+  a.work = plan_work(plan, batch, KS, g_max);
   HIPCHK(launch_route_cache(s, cf.dtype, ra, state_of(c, layer), c->t, a, ps ? ps->route : KernelEvents{}));
 
   FfnArgs fa{};
@@ -917,7 +921,7 @@ int moe_layer_prefill(moe_cache_t* c, int32_t layer, const void* x_dev, const fl
   a.mailbox = c->full[layer] ? nullptr : c->mailbox;
   const int g_max = (int)std::min<size_t>((size_t)n_tokens * K, (size_t)E) + cf.n_shared;   // groups are experts here
   const bool q4 = cf.pool_layout == MOE_LAYOUT_TILED_INT4;
-  if (!q4) a.work = plan_ffn_gemm(n_tokens, KS, g_max, true);
+  a.work = q4 ? plan_ffn_gemm_q4(n_tokens, KS, g_max, true) : plan_ffn_gemm(n_tokens, KS, g_max, true);
   HIPCHK(launch_route_cache(s, cf.dtype, ra, state_of(c, layer), c->t, a, KernelEvents{}));
 
   FfnArgs fa{};

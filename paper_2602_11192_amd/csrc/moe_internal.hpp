@@ -69,11 +69,11 @@ struct CallTables {
 // the group, its pairs | miss << 30), a group streamed from the host with its expert in place of the buffer: all a
 // workgroup needs of its group.
 struct WorkPlan {
-  int32_t shift;   // log2 of the tokens per tile (at least 6)
+  int32_t shift;   // log2 of the tokens per tile (at least 5)
   int32_t cap;     // items the list can hold; 0: no list
 };
-// tiles of 64 tokens at the smallest
-inline size_t work_capacity(size_t groups, size_t pairs) { return groups + pairs / 64; }
+// tiles of 32 tokens at the smallest
+inline size_t work_capacity(size_t groups, size_t pairs) { return groups + pairs / 32; }
 
 struct CacheCallArgs {
   int32_t mode;          // 0 decode, 1 pin, 2 prompt streaming (cache read-only)
@@ -182,10 +182,12 @@ hipError_t launch_decode_tiles(hipStream_t s, const FfnArgs& a, const RoutedArgs
 int fused_q4_waves(int d);
 bool ffn_fused_q4_supported(int d, int f, int max_count);
 hipError_t launch_ffn_fused_q4(hipStream_t s, const FfnArgs& a, KernelEvents ev);
+WorkPlan plan_ffn_gemm_q4(int batch, int KS, int g_max, bool streamed);
 hipError_t launch_ffn_gemm_q4(hipStream_t s, const FfnArgs& a, KernelEvents gate_up, KernelEvents down);
 // Which expert-FFN kernels run a call of `batch` tokens on experts of the given layout and shape.
-struct FfnPlan { bool fused, gemm, tiled, q4; };
+struct FfnPlan { bool fused, gemm, tiled, q4; };      // gemm: a grouped GEMM, which needs a work list
 FfnPlan plan_ffn(int pool_layout, int d, int f, int batch);
+WorkPlan plan_work(const FfnPlan& p, int batch, int KS, int g_max);      // no list unless a GEMM runs
 hipError_t launch_ffn(hipStream_t s, int dtype, const FfnPlan& p, const FfnArgs& a, KernelEvents ke1, KernelEvents ke2);
 // identity: pair (b, j) has partial row b * KS + j (pos_of is not read)
 hipError_t launch_combine_chunks(hipStream_t s, const float* o_part, const float* wpair, const int32_t* pos_of,

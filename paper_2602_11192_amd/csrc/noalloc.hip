@@ -129,7 +129,7 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
     // the single-launch kernels keep one partial row per 32 rows of d_ff; when those do not fit, the two-pass
     // grouped GEMM (one row per pair) does the same work in a fraction of the scratch
     plan.fused = false;
-    plan.gemm = plan.tiled;
+    plan.gemm = true;
     o = carve();
   }
   if (o > kScratchBytes)
@@ -197,7 +197,7 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
   a.mailbox = nullptr;
   a.miss_list = reinterpret_cast<MissEntry*>(base + o_miss);
   a.max_miss = (int32_t)max_miss;
-  if (plan.gemm) a.work = plan_ffn_gemm(batch, KS, G, false);
+  a.work = plan_work(plan, batch, KS, G);
   HIPCHK(launch_route_cache(s, L->dtype, ra, st, t, a, KernelEvents{}));
 
   FfnArgs fa{};
