@@ -1,6 +1,6 @@
 // Expert SwiGLU FFN (paper section 2, Eq. 3) on INT4 group-quantised experts
 // (section 3.2) as a grouped GEMM, for calls in which an expert sees many
-// tokens: batched decode beyond 16 tokens and prompt processing.
+// tokens: batched decode and prompt processing.
 //
 // One workgroup = 4 waves x a tile of up to TOK of one expert's tokens.  Tokens
 // are the A operand of v_mfma_f32_16x16x32_bf16, staged through LDS in fragment

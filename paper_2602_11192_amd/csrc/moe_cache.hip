@@ -41,16 +41,21 @@ int fail(int code, const char* fmt, ...) {
   return code;
 }
 
-// Larger calls: the LDS-staged grouped GEMM (measured faster than the split-K streaming pair from 17 tokens
-// on: 119 against 139 us at 17 tokens, 138 against 190 us at 128 on the OLMoE-like layer, and faster than the
-// single-launch kernel from about 6 tokens: 90 against 96 us at 8, 123 against 136 us at 16).  The split-K
-// pair remains for small calls on shapes the single-launch kernel does not cover.
-FfnPlan plan_ffn(int pool_layout, int d, int f, int batch) {
+// The single-launch FFN kernels (one partial row per 32 rows of d_ff) for a few tokens, the grouped GEMM beyond.  On a layer
+// whose experts are all resident the line lies at 3 tokens in bf16 (4 tokens, the kernel / the GEMM: OLMoE-like 72.4 / 67.8
+// us per call, Phi-3.5-MoE-like 182 / 172, Mixtral-like 275 / 266; 3 tokens 59.0 / 63.6, 149 / 144, 214 / 224), in INT4 at 4
+// (OLMoE-like, 5 tokens: 44.0 / 42.1 us), or at 8 on experts so large that the kernel has workgroups enough without
+// more tokens (Phi-3.5-MoE-like, 8 tokens: 126 / 135 us, 10: 149 / 140).  A call that may have to fetch experts stays with
+// the kernel that reads them from the pool itself for longer.  The split-K pair (ffn_tiled.hip) remains for small calls on
+// shapes the single-launch kernel does not cover.
+FfnPlan plan_ffn(int pool_layout, int d, int f, int batch, bool resident) {
   FfnPlan p{};
   p.tiled = pool_layout == MOE_LAYOUT_TILED;
   p.q4 = pool_layout == MOE_LAYOUT_TILED_INT4;
-  p.fused = p.q4 ? batch <= 16 : (p.tiled && ffn_fused_supported(d, f, batch));
-  p.gemm = !p.fused && (p.q4 || (p.tiled && batch > fused_max_tokens(f)));
+  const bool shape = p.q4 || (p.tiled && ffn_fused_supported(d, f, 1));
+  const int most = p.q4 ? (resident ? (f >= 4096 ? 8 : 4) : 16) : resident ? 3 : fused_max_tokens(f);
+  p.fused = shape && batch <= most;
+  p.gemm = !p.fused && (shape || (p.tiled && batch > fused_max_tokens(f)));
   return p;
 }
 
@@ -729,9 +734,12 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   ra.router_packed = c->router_packed ? c->router_packed + router_packed_bytes(E, d) * layer : nullptr;
 
   // One launch up to the combine, and no host wait: batch 1 (a single token's experts always fit), or a cache
-  // that holds every expert (nothing is ever evicted) - the two cases in which a call cannot run out of spare
-  // buffers - on the shapes the single-launch kernel covers.
-  if (c->single_ok && batch <= c->single_max_batch && (batch == 1 || c->C >= E)) {
+  // that can hold every expert (nothing is ever evicted) - the two cases in which a call cannot run out of spare
+  // buffers - on the shapes the single-launch kernel covers.  Of several tokens only as long as the host does not know
+  // that all experts are there: then the other path does not wait either, and routing once instead of in every
+  // workgroup is faster (2 / 3 / 4 tokens: OLMoE-like 47.8 / 61.9 / 77.4 against 45.6 / 59.0 / 67.8 us, INT4 35.5 / 44.9 /
+  // 56.5 against 28.6 / 34.8 / 40.1; Phi-3.5-MoE-like 98.6 against 99.8 at 2 tokens).
+  if (c->single_ok && (batch == 1 || (c->C >= E && !c->full[layer] && batch <= c->single_max_batch))) {
     RoutedArgs q{};
     q.r = ra;
     q.st_in = state_of(c, layer);
@@ -774,7 +782,7 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   a.policy = cf.policy; a.gamma = cf.gamma; a.trace_cap = cf.trace_capacity; a.seq = ++c->seq;
   a.pin_ids = nullptr; a.miss_list = c->miss_list; a.max_miss = c->max_miss;
   a.mailbox = c->full[layer] ? nullptr : c->mailbox;       // (every lookup hits: nobody reads the record)
-  const FfnPlan plan = plan_ffn(cf.pool_layout, d, cf.d_ff, batch);
+  const FfnPlan plan = plan_ffn(cf.pool_layout, d, cf.d_ff, batch, c->full[layer] != 0);
   const int g_max = (int)std::min<size_t>((size_t)batch * K, (size_t)c->P) + cf.n_shared;
   a.work = plan_work(plan, batch, KS, g_max);
   HIPCHK(launch_route_cache(s, cf.dtype, ra, state_of(c, layer), c->t, a, ps ? ps->route : KernelEvents{}));

@@ -157,13 +157,9 @@ hipError_t launch_ffn_tiled(hipStream_t s, const FfnArgs& a, KernelEvents gate_u
 // The tiles of a call of `batch` tokens, KS experts each, in at most g_max groups (streamed: experts read from the host).
 WorkPlan plan_ffn_gemm(int batch, int KS, int g_max, bool streamed);
 hipError_t launch_ffn_gemm(hipStream_t s, const FfnArgs& a, KernelEvents gate_up, KernelEvents down);
-// Most tokens per call for which the single-launch bf16 decode kernel is used (it can take 16 per expert; the
-// whole call is faster with the grouped GEMM from about 6 tokens on: 109 against 110 us at 6, 119 against 133 us
-// at 8 on the OLMoE-like layer).
+// Most tokens per call for which a call that may have to fetch experts uses the single-launch bf16 decode kernel (it can
+// take 16 per expert); large experts (d_ff >= 4096) give it workgroups enough for longer.
 constexpr int kFusedMaxTokens = 6;
-// Shapes with a long contraction in the down pass (d_ff >= 4096) keep the single-launch kernel up to 8 tokens: the
-// grouped GEMM's down pass is the weaker one there (Phi-like layer: 286 against 337 us at 7 tokens, 312 against 332 us
-// at 8; Mixtral-like: 488 against 510 us at 7, level at 8; from 12 tokens on the GEMM wins on both).
 inline int fused_max_tokens(int d_ff) { return d_ff >= 4096 ? 8 : kFusedMaxTokens; }
 bool ffn_fused_supported(int d, int f, int max_count);
 hipError_t launch_ffn_fused(hipStream_t s, const FfnArgs& a, KernelEvents ev);
@@ -186,7 +182,7 @@ WorkPlan plan_ffn_gemm_q4(int batch, int KS, int g_max, bool streamed);
 hipError_t launch_ffn_gemm_q4(hipStream_t s, const FfnArgs& a, KernelEvents gate_up, KernelEvents down);
 // Which expert-FFN kernels run a call of `batch` tokens on experts of the given layout and shape.
 struct FfnPlan { bool fused, gemm, tiled, q4; };      // gemm: a grouped GEMM, which needs a work list
-FfnPlan plan_ffn(int pool_layout, int d, int f, int batch);
+FfnPlan plan_ffn(int pool_layout, int d, int f, int batch, bool resident);
 WorkPlan plan_work(const FfnPlan& p, int batch, int KS, int g_max);      // no list unless a GEMM runs
 hipError_t launch_ffn(hipStream_t s, int dtype, const FfnPlan& p, const FfnArgs& a, KernelEvents ke1, KernelEvents ke2);
 // identity: pair (b, j) has partial row b * KS + j (pos_of is not read)
