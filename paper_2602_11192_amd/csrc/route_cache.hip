@@ -26,6 +26,7 @@
 // Nothing is committed when the call runs out of spare buffers, so a failed call
 // leaves the cache unchanged.
 #include <algorithm>
+#include <type_traits>
 
 #include "device_utils.hpp"
 #include "gating.hpp"
@@ -790,6 +791,11 @@ __global__ void __launch_bounds__(1024) route_cache_kernel(RouteArgs r, LayerSta
 
 // ---------------------------------------------------------------- several tokens per call
 constexpr int kTileWaves = 16, kTileThreads = 64 * kTileWaves, kTileTokens = 16;
+// Router products and bytes of an fp32 call of 2 to 8 tokens up to which one workgroup routes them all, instead of one per
+// token that then meet (layer calls, 4 tokens: 8 experts of 64 columns 18.2 -> 16.9 us, 16 of 128 20.0 -> 18.6, 32 of 256
+// 20.4 -> 19.8; 16 tokens x 8 experts 25.2 -> 26.7, 8 tokens x 64 experts of 512 columns 24.8 -> 28.0: not taken).
+constexpr int kSmallRouterItems = 128;
+constexpr size_t kSmallRouterBytes = 128 << 10;
 constexpr int kMaxKeys = 2 * kWave; // buffer ids of the register-table case, shared experts included
 
 // What the grouping phase of the tile kernel keeps in LDS.
@@ -970,7 +976,9 @@ __device__ __forceinline__ void group_hits(unsigned char* smem, const LdsLayout&
 // 1024 tokens, 23 us at 64 and 13 us at 16 (64 experts, d = 2048); now 21, 12 and 11.5 us.
 // PACKED: W_r comes from the library's copy in operand order (pack_router_kernel), where a cache has one: a wave-wide load
 // is then one contiguous KiB instead of 16 pieces of 64 bytes (64 x 2048 experts: 11.5 against 17.8 us per launch).
-template <bool PACKED, int NT>
+// T = float: the router rows as dot products, one wave per (token, expert); for calls so small that one workgroup does it
+// sooner than several meet (kSmallRouterBytes).
+template <typename T, bool PACKED, int NT>
 __global__ void __launch_bounds__(kTileThreads) route_tile_kernel(RouteArgs r, LayerState st, CallTables t, CacheCallArgs a) {
   typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
   typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -995,6 +1003,37 @@ __global__ void __launch_bounds__(kTileThreads) route_tile_kernel(RouteArgs r, L
   if (tid < kWave) { tl.last[tid] = 0; tl.touched[tid] = 0; }
   if (tid == 0) tl.any_miss = 0;
 
+  if constexpr (std::is_same<T, float>::value) {
+    const int n_vec = d / 4, n_items = min(kTileTokens, a.B - t0) * E;
+    constexpr int U = 4;                                    // products of a wave in flight together
+    for (int it0 = wave; it0 < n_items; it0 += U * kTileWaves) {
+      float acc[U], bias[U];
+      const float4 *xv[U], *wv[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int it = min(it0 + u * kTileWaves, n_items - 1);       // clamped: in bounds, formed again
+        const int b = it / E, e = it - b * E;
+        xv[u] = reinterpret_cast<const float4*>(static_cast<const float*>(r.x) + (size_t)(t0 + b) * d);
+        wv[u] = reinterpret_cast<const float4*>(static_cast<const float*>(r.router_w) + (size_t)e * d);
+        bias[u] = r.bias ? r.bias[(size_t)(t0 + b) * E + e] : 0.f;
+        acc[u] = 0.f;
+      }
+      for (int c = lane; c < n_vec; c += kWave) {
+        float4 xc[U], wc[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) { xc[u] = xv[u][c]; wc[u] = wv[u][c]; }
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc[u] = Vec<float>::dot(wc[u], xc[u], acc[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int it = min(it0 + u * kTileWaves, n_items - 1);
+        const float sum = wave_sum(acc[u]);
+        if (lane == 0) zs_tile[it / E][it % E] = sum + bias[u];
+      }
+    }
+    __syncthreads();
+  } else {
   const int tok = t0 + n < a.B ? t0 + n : a.B - 1;          // clamped: in bounds, the column is dropped below
   const uint16_t* xrow = static_cast<const uint16_t*>(r.x) + (size_t)tok * d + q * 8;
   for (int eg = 0; eg < E; eg += 16 * NT) {
@@ -1067,6 +1106,7 @@ __global__ void __launch_bounds__(kTileThreads) route_tile_kernel(RouteArgs r, L
       }
     }
     __syncthreads();
+  }
   }
   if (fast && wave == 0 && lane < a.C && raw.exp >= 0) tl.map[raw.exp] = raw.buf << 8 | lane;
 
@@ -1161,14 +1201,19 @@ hipError_t launch_route_cache(hipStream_t s, int dtype, const RouteArgs& r, cons
     const dim3 tiles((a.B + kTileTokens - 1) / kTileTokens), threads(kTileThreads);
     const auto launch = [&](auto kernel) { launch_timed(kernel, tiles, threads, bytes, s, ev, r, st, t, a); };
     if (r.router_packed) {
-      if (nt == 1) launch(route_tile_kernel<true, 1>);
-      else if (nt == 2) launch(route_tile_kernel<true, 2>);
-      else launch(route_tile_kernel<true, 4>);
+      if (nt == 1) launch(route_tile_kernel<uint16_t, true, 1>);
+      else if (nt == 2) launch(route_tile_kernel<uint16_t, true, 2>);
+      else launch(route_tile_kernel<uint16_t, true, 4>);
     } else {
-      if (nt == 1) launch(route_tile_kernel<false, 1>);
-      else if (nt == 2) launch(route_tile_kernel<false, 2>);
-      else launch(route_tile_kernel<false, 4>);
+      if (nt == 1) launch(route_tile_kernel<uint16_t, false, 1>);
+      else if (nt == 2) launch(route_tile_kernel<uint16_t, false, 2>);
+      else launch(route_tile_kernel<uint16_t, false, 4>);
     }
+    return hipGetLastError();
+  }
+  if (dtype == MOE_DTYPE_FP32 && a.B >= 2 && a.B <= 8 && a.B * a.E <= kSmallRouterItems &&
+      (size_t)a.B * a.E * r.d * sizeof(float) <= kSmallRouterBytes) {
+    launch_timed(route_tile_kernel<float, false, 1>, dim3(1), dim3(kTileThreads), lds, s, ev, r, st, t, a);
     return hipGetLastError();
   }
   const bool one_row = a.E <= waves;
