@@ -2,6 +2,8 @@
 // expert blocks kept in the plain row-major layout W_g | W_u | W_d, fp32 or
 // bf16.  This is the layout-agnostic path (one wavefront per output row, four tokens at a time, DPP
 // reduction over the contraction); the bf16 production path is ffn_tiled.hip.
+#include <type_traits>
+
 #include "device_utils.hpp"
 #include "moe_internal.hpp"
 
@@ -36,6 +38,14 @@ __device__ __forceinline__ void load_vec(const uint16_t* p, float (&v)[8]) {
 // launch saved 2 us on the smallest experts with 16 tokens and lost 3 to 20 elsewhere.)
 constexpr int kTok = 4;
 
+// Calls f with the number of tokens a wave takes at a time: no more than the group has.
+template <typename F>
+__device__ __forceinline__ void by_count(int cnt, F f) {
+  if (cnt == 1) f(std::integral_constant<int, 1>{});
+  else if (cnt == 2) f(std::integral_constant<int, 2>{});
+  else f(std::integral_constant<int, kTok>{});
+}
+
 // h[pos][j] = silu(W_g[j,:].x) * (W_u[j,:].x)
 template <typename T>
 __global__ void __launch_bounds__(64 * kRowsPerBlock) gate_up_rowmajor(FfnArgs a) {
@@ -52,11 +62,13 @@ __global__ void __launch_bounds__(64 * kRowsPerBlock) gate_up_rowmajor(FfnArgs a
   const T* wu = w + (size_t)a.f * a.d + (size_t)j * a.d;
   const int begin = gd.begin, cnt = gd.count;
   float* h = reinterpret_cast<float*>(a.h);
-  for (int t0 = 0; t0 < cnt; t0 += kTok) {
-    const T* xr[kTok];
-    float sg[kTok], su[kTok];
+  by_count(cnt, [&](auto n_tok) {
+  constexpr int N = decltype(n_tok)::value;
+  for (int t0 = 0; t0 < cnt; t0 += N) {
+    const T* xr[N];
+    float sg[N], su[N];
 #pragma unroll
-    for (int t = 0; t < kTok; ++t) {
+    for (int t = 0; t < N; ++t) {
       const int p = a.t.sorted_pair[begin + min(t0 + t, cnt - 1)];       // clamped: formed again, dropped below
       xr[t] = reinterpret_cast<const T*>(a.x) + (size_t)(p / a.KS) * a.d;
       sg[t] = su[t] = 0.f;
@@ -66,7 +78,7 @@ __global__ void __launch_bounds__(64 * kRowsPerBlock) gate_up_rowmajor(FfnArgs a
       load_vec(wg + i, vg);
       load_vec(wu + i, vu);
 #pragma unroll
-      for (int t = 0; t < kTok; ++t) {
+      for (int t = 0; t < N; ++t) {
         float x[V];
         load_vec(xr[t] + i, x);
 #pragma unroll
@@ -74,11 +86,12 @@ __global__ void __launch_bounds__(64 * kRowsPerBlock) gate_up_rowmajor(FfnArgs a
       }
     }
 #pragma unroll
-    for (int t = 0; t < kTok; ++t) {
+    for (int t = 0; t < N; ++t) {
       const float vg = wave_sum(sg[t]), vu = wave_sum(su[t]);
       if (lane == 0 && t0 + t < cnt) h[(size_t)(begin + t0 + t) * a.f + j] = silu(vg) * vu;
     }
   }
+  });
 }
 
 // o[pos][i] = W_d[i,:].h[pos,:].  VEC: rows of W_d are whole multiples of 16 bytes (f % V == 0).
@@ -94,11 +107,13 @@ __global__ void __launch_bounds__(64 * kRowsPerBlock) down_rowmajor(FfnArgs a) {
   if (i >= a.d) return;
   const T* wd = reinterpret_cast<const T*>(group_weights(a, gd.buf)) + (size_t)2 * a.f * a.d + (size_t)i * a.f;
   const int begin = gd.begin, cnt = gd.count;
-  for (int t0 = 0; t0 < cnt; t0 += kTok) {
-    const float* hr[kTok];
-    float s[kTok];
+  by_count(cnt, [&](auto n_tok) {
+  constexpr int N = decltype(n_tok)::value;
+  for (int t0 = 0; t0 < cnt; t0 += N) {
+    const float* hr[N];
+    float s[N];
 #pragma unroll
-    for (int t = 0; t < kTok; ++t) {
+    for (int t = 0; t < N; ++t) {
       hr[t] = reinterpret_cast<const float*>(a.h) + (size_t)(begin + min(t0 + t, cnt - 1)) * a.f;
       s[t] = 0.f;
     }
@@ -107,7 +122,7 @@ __global__ void __launch_bounds__(64 * kRowsPerBlock) down_rowmajor(FfnArgs a) {
       if constexpr (VEC) load_vec(wd + j, w);
       else w[0] = Elem<T>::load(wd + j);
 #pragma unroll
-      for (int t = 0; t < kTok; ++t) {
+      for (int t = 0; t < N; ++t) {
         float x[V];
         if constexpr (VEC) {
 #pragma unroll
@@ -125,11 +140,12 @@ __global__ void __launch_bounds__(64 * kRowsPerBlock) down_rowmajor(FfnArgs a) {
       }
     }
 #pragma unroll
-    for (int t = 0; t < kTok; ++t) {
+    for (int t = 0; t < N; ++t) {
       const float v = wave_sum(s[t]);
       if (lane == 0 && t0 + t < cnt) a.o[(size_t)(begin + t0 + t) * a.d + i] = v;
     }
   }
+  });
 }
 
 // y[b][i] = sum_j wpair[b][j] * o[pos_of[b][j]][i], j over the K selected then the shared experts.

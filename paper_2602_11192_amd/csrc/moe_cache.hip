@@ -42,18 +42,20 @@ int fail(int code, const char* fmt, ...) {
 }
 
 // The single-launch FFN kernels (one partial row per 32 rows of d_ff) for a few tokens, the grouped GEMM beyond.  On a layer
-// whose experts are all resident the line lies at 3 tokens in bf16 (4 tokens, the kernel / the GEMM: OLMoE-like 72.4 / 67.8
-// us per call, Phi-3.5-MoE-like 182 / 172, Mixtral-like 275 / 266; 3 tokens 59.0 / 63.6, 149 / 144, 214 / 224), in INT4 at 4
-// (OLMoE-like, 5 tokens: 44.0 / 42.1 us), or at 8 on experts so large that the kernel has workgroups enough without
-// more tokens (Phi-3.5-MoE-like, 8 tokens: 126 / 135 us, 10: 149 / 140).  A call that may have to fetch experts stays with
-// the kernel that reads them from the pool itself for longer.  The split-K pair (ffn_tiled.hip) remains for small calls on
-// shapes the single-launch kernel does not cover.
-FfnPlan plan_ffn(int pool_layout, int d, int f, int batch, bool resident) {
+// whose experts are all resident, once the call reads enough weights (largest_bytes: every pair on an expert of its own)
+// to outweigh the GEMM's second launch, the line lies at 3 tokens in bf16 (4 tokens, the kernel / the GEMM: OLMoE-like
+// 72.4 / 67.8 us per call, Phi-3.5-MoE-like 182 / 172, Mixtral-like 275 / 266; 3 tokens 59.0 / 63.6, 149 / 144, 214 / 224; but
+// 8 experts of 1024 x 4096, 201 MB: 32 / 59, and 32 of 2048 x 512, 100 MB: 27 / 38), in INT4 at 4 (OLMoE-like, 5 tokens, 141
+// MB: 44.0 / 42.1 us), or at 8 on experts so large that the kernel has workgroups enough without more tokens
+// (Phi-3.5-MoE-like, 8 tokens: 126 / 135 us, 10: 149 / 140).  Smaller layers, and calls that may have to fetch experts, stay
+// with the kernel for longer.  The split-K pair (ffn_tiled.hip) remains for small calls on shapes the kernel does not cover.
+FfnPlan plan_ffn(int pool_layout, int d, int f, int batch, bool resident, uint64_t largest_bytes) {
   FfnPlan p{};
   p.tiled = pool_layout == MOE_LAYOUT_TILED;
   p.q4 = pool_layout == MOE_LAYOUT_TILED_INT4;
   const bool shape = p.q4 || (p.tiled && ffn_fused_supported(d, f, 1));
-  const int most = p.q4 ? (resident ? (f >= 4096 ? 8 : 4) : 16) : resident ? 3 : fused_max_tokens(f);
+  const bool heavy = resident && largest_bytes >= (p.q4 ? 120ull : 350ull) * 1000000;
+  const int most = p.q4 ? (heavy ? (f >= 4096 ? 8 : 4) : 16) : heavy ? 3 : fused_max_tokens(f);
   p.fused = shape && batch <= most;
   p.gemm = !p.fused && (shape || (p.tiled && batch > fused_max_tokens(f)));
   return p;
@@ -81,6 +83,7 @@ namespace {
   } while (0)
 
 constexpr int kProfSlots = 512;
+constexpr int64_t kSingleRouting = 50 << 20;     // see decode_wave
 
 struct ProfSlot {
   KernelEvents route, gate_up, down;   // attached to the dispatches of the three main kernels of a call
@@ -735,11 +738,14 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
 
   // One launch up to the combine, and no host wait: batch 1 (a single token's experts always fit), or a cache
   // that can hold every expert (nothing is ever evicted) - the two cases in which a call cannot run out of spare
-  // buffers - on the shapes the single-launch kernel covers.  Of several tokens only as long as the host does not know
-  // that all experts are there: then the other path does not wait either, and routing once instead of in every
-  // workgroup is faster (2 / 3 / 4 tokens: OLMoE-like 47.8 / 61.9 / 77.4 against 45.6 / 59.0 / 67.8 us, INT4 35.5 / 44.9 /
-  // 56.5 against 28.6 / 34.8 / 40.1; Phi-3.5-MoE-like 98.6 against 99.8 at 2 tokens).
-  if (c->single_ok && (batch == 1 || (c->C >= E && !c->full[layer] && batch <= c->single_max_batch))) {
+  // buffers - on the shapes the single-launch kernel covers.  When the host knows that all experts are there the other
+  // path does not wait either, and with several tokens routing once is faster than in every workgroup as soon as the
+  // workgroups and the router matrix are many and large (2 / 3 / 4 tokens, workgroups x E x d = 67 M and more: OLMoE-like 47.8
+  // / 61.9 / 77.4 against 45.6 / 59.0 / 67.8 us, INT4 35.5 / 44.9 / 56.5 against 28.6 / 34.8 / 40.1; at 52 M, 2 Phi-3.5-MoE-like
+  // tokens, 98.6 against 99.8, INT4 54 / 51; at 17 M, 4 tokens on 32 experts of 2048 x 512, 26.6 against 38.4).
+  const int64_t single_wgs = (int64_t)(cf.d_ff / 32) * (std::min<int64_t>((int64_t)batch * K, c->P) + cf.n_shared);
+  const bool route_once = c->full[layer] && single_wgs * E * d > kSingleRouting;
+  if (c->single_ok && (batch == 1 || (c->C >= E && !route_once && batch <= c->single_max_batch))) {
     RoutedArgs q{};
     q.r = ra;
     q.st_in = state_of(c, layer);
@@ -782,8 +788,8 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   a.policy = cf.policy; a.gamma = cf.gamma; a.trace_cap = cf.trace_capacity; a.seq = ++c->seq;
   a.pin_ids = nullptr; a.miss_list = c->miss_list; a.max_miss = c->max_miss;
   a.mailbox = c->full[layer] ? nullptr : c->mailbox;       // (every lookup hits: nobody reads the record)
-  const FfnPlan plan = plan_ffn(cf.pool_layout, d, cf.d_ff, batch, c->full[layer] != 0);
   const int g_max = (int)std::min<size_t>((size_t)batch * K, (size_t)c->P) + cf.n_shared;
+  const FfnPlan plan = plan_ffn(cf.pool_layout, d, cf.d_ff, batch, c->full[layer] != 0, g_max * c->expert_bytes);
   a.work = plan_work(plan, batch, KS, g_max);
   HIPCHK(launch_route_cache(s, cf.dtype, ra, state_of(c, layer), c->t, a, ps ? ps->route : KernelEvents{}));
 
