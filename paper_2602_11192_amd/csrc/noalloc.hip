@@ -116,7 +116,10 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
     o_sp = o; o += up(NP * 4);
     o_po = o; o += up(NP * 4);
     o_gd = o; o += up((size_t)G * sizeof(GroupDesc));
-    o_work = o; o += up((1 + work_capacity(G, NP)) * sizeof(int4));
+    // the work list takes the place of the pairs' buffer ids, which nothing reads once the pairs are grouped, where it fits
+    const size_t work = plan.gemm ? (1 + work_capacity(G, NP)) * sizeof(int4) : 0;
+    o_work = work <= NP * 4 ? o_pb : o;
+    o += work <= NP * 4 ? 0 : up(work);
     o_ng = o; o += 256;
     o_miss = o; o += up(max_miss * sizeof(MissEntry));
     o_h = o; o += plan.fused ? 0 : up(NP * (size_t)f * 4);
