@@ -116,8 +116,9 @@ typedef struct {
  *                          d_ff % 32 == 0.  Statistics count bytes of this block size.
  */
 typedef struct {
-  const void* router_w;    /* device, [L][E][d] row-major, dtype.  A cache with in-kernel fetch may read a copy
-                              that moe_cache_create made                                    */
+  const void* router_w;    /* device, [L][E][d] row-major, dtype.  With in-kernel fetch, decode calls of one token,
+                              and of up to four where capacity >= E, may read a copy that moe_cache_create
+                              made; every other call reads router_w itself                  */
   const void* expert_pool; /* pinned host, [L][E] expert blocks in one allocation; or NULL  */
   const void* shared_w;    /* device, [L][n_shared] expert blocks; NULL iff n_shared == 0   */
   const void* const* expert_pool_layers; /* or: host array of L pointers, each to one layer's

@@ -118,7 +118,7 @@ struct moe_cache {
   unsigned long long* dev_stats = nullptr;   // [L][4] hits, misses, evictions counted on the device by calls without a host wait
   bool dev_stats_used = false;
   size_t layer_stride = 0;             // bytes between the tables (and device counters) of consecutive layers
-  char* router_packed = nullptr;       // [L] router matrices in operand order: in-kernel fetch, shapes of the single-launch decode
+  char* router_packed = nullptr;       // [L] router matrices in operand order, for the calls that the single-launch decode covers
   bool single_ok = false;              // the single-launch decode kernel covers this cache's shape and policy
   int single_max_batch = 0;
   int n_cu = 0;                        // compute units of the device
@@ -734,18 +734,20 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   ra.d = d; ra.norm_topk = cf.norm_topk;
   ra.user_idx = topk_idx_dev; ra.user_w = topk_w_dev;
   ra.arrive = c->arrive;
-  ra.router_packed = c->router_packed ? c->router_packed + router_packed_bytes(E, d) * layer : nullptr;
 
   // One launch up to the combine, and no host wait: batch 1 (a single token's experts always fit), or a cache
   // that can hold every expert (nothing is ever evicted) - the two cases in which a call cannot run out of spare
-  // buffers - on the shapes the single-launch kernel covers.  When the host knows that all experts are there the other
+  // buffers - on the shapes the single-launch kernel covers.  These calls alone read the copy of W_r that create made,
+  // whichever path they take; all others read the caller's matrix, as the allocation-free entry point does.  When the host knows that all experts are there the other
   // path does not wait either, and with several tokens routing once is faster than in every workgroup as soon as the
   // workgroups and the router matrix are many and large (2 / 3 / 4 tokens, workgroups x E x d = 67 M and more: OLMoE-like 47.8
   // / 61.9 / 77.4 against 45.6 / 59.0 / 67.8 us, INT4 35.5 / 44.9 / 56.5 against 28.6 / 34.8 / 40.1; at 52 M, 2 Phi-3.5-MoE-like
   // tokens, 98.6 against 99.8, INT4 54 / 51; at 17 M, 4 tokens on 32 experts of 2048 x 512, 26.6 against 38.4).
+  const bool small = c->single_ok && (batch == 1 || (c->C >= E && batch <= c->single_max_batch));
+  if (small) ra.router_packed = c->router_packed + router_packed_bytes(E, d) * layer;
   const int64_t single_wgs = (int64_t)(cf.d_ff / 32) * (std::min<int64_t>((int64_t)batch * K, c->P) + cf.n_shared);
-  const bool route_once = c->full[layer] && single_wgs * E * d > kSingleRouting;
-  if (c->single_ok && (batch == 1 || (c->C >= E && !route_once && batch <= c->single_max_batch))) {
+  const bool route_once = batch > 1 && c->full[layer] && single_wgs * E * d > kSingleRouting;
+  if (small && !route_once) {
     RoutedArgs q{};
     q.r = ra;
     q.st_in = state_of(c, layer);
@@ -926,7 +928,6 @@ int moe_layer_prefill(moe_cache_t* c, int32_t layer, const void* x_dev, const fl
   ra.d = d; ra.norm_topk = cf.norm_topk;
   ra.user_idx = topk_idx_dev; ra.user_w = topk_w_dev;
   ra.arrive = c->arrive;
-  ra.router_packed = c->router_packed ? c->router_packed + router_packed_bytes(E, d) * layer : nullptr;
 
   CacheCallArgs a{};
   a.mode = 2; a.B = n_tokens; a.K = K; a.KS = KS; a.E = E; a.C = c->C; a.P = c->P; a.n_shared = cf.n_shared;

@@ -1190,10 +1190,10 @@ hipError_t launch_route_cache(hipStream_t s, int dtype, const RouteArgs& r, cons
   if (waves > a.E) waves = a.E;
   dim3 grid(a.B), block(64 * waves);
   const size_t lds = route_cache_lds_bytes(a.E, a.C, a.P, a.n_shared, a.B, a.K, a.KS);
-  // Tiles of 16 tokens: from two tokens on with the packed router matrix.  Reading it row-major the tile kernel needs 6 us
-  // more on 64 x 2048 (a layer call of 16 tokens 82.5 against 79.1 us, of 24 86.3 against 86.5, of 48 89.5 against 92.2, of
-  // 64 90.6 against 111.4); with few experts a workgroup per token keeps up for longer (16 x 4096, 64 tokens: 96.0 against
-  // 93.7 us).
+  // Tiles of 16 tokens: from two tokens on with the packed router matrix (calls of up to four tokens have one).  Reading it
+  // row-major the tile kernel needs 6 us more on 64 x 2048 (a layer call of 16 tokens 82.5 against 79.1 us, of 24 86.3
+  // against 86.5, of 48 89.5 against 92.2, of 64 90.6 against 111.4); with few experts a workgroup per token keeps up for
+  // longer (16 x 4096, 64 tokens: 96.0 against 93.7 us).
   const int tile_min = r.router_packed ? 2 : a.E > 32 ? 32 : 112;
   if (dtype == MOE_DTYPE_BF16 && a.B >= tile_min && a.E <= kTileMaxE && r.d % 32 == 0) {
     const int nt = a.E <= 16 ? 1 : a.E <= 32 ? 2 : 4;
