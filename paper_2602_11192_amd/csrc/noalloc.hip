@@ -116,13 +116,12 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
     o_sp = o; o += up(NP * 4);
     o_po = o; o += up(NP * 4);
     o_gd = o; o += up((size_t)G * sizeof(GroupDesc));
-    // the work list takes the place of the pairs' buffer ids, which nothing reads once the pairs are grouped, where it fits
-    const size_t work = plan.gemm ? (1 + work_capacity(G, NP)) * sizeof(int4) : 0;
-    o_work = work <= NP * 4 ? o_pb : o;
-    o += work <= NP * 4 ? 0 : up(work);
     o_ng = o; o += 256;
     o_miss = o; o += up(max_miss * sizeof(MissEntry));
     o_h = o; o += plan.fused ? 0 : up(NP * (size_t)f * 4);
+    // The grouped GEMMs keep h in bf16, half of what is set aside; their work list sits in the other half, so it takes no
+    // space from the batch.  It always fits: f >= 32 leaves 64 bytes a pair, the list needs at most 16 + 16.5.
+    o_work = o_h + NP * (size_t)f * 2;
     o_o = o;
     o += up(plan.fused ? NP * (size_t)(f / 32) * d * 4 : NP * (size_t)d * 4);
     return o;
