@@ -133,6 +133,14 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
     plan.fused = false;
     plan.gemm = true;
     o = carve();
+  } else if (o > kScratchBytes && plan.gemm) {
+    // with so few rows of d_ff that a pair's partial rows are smaller than its h and GEMM row together, a few tokens may
+    // fit the single-launch kernel alone
+    const FfnPlan few = plan_ffn(L->pool_layout, d, f, batch, false, 0);
+    if (few.fused) {
+      plan = few;
+      o = carve();
+    }
   }
   if (o > kScratchBytes)
     return fail(MOE_ERR_UNSUPPORTED,

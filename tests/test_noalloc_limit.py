@@ -64,3 +64,16 @@ def test_results_at_the_limit():
         assert float((wd.cpu().double() - w)[sure].abs().max()) < 1e-5
         err = (yd.cpu().double() - y).abs().max(-1).values / y.abs().max(-1).values
         assert float(err[sure].max()) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("int4,batch,E,K,ns,d,f", [(1, 15, 400, 35, 64, 5632, 32), (0, 4, 128, 62, 0, 33792, 32)])
+def test_a_batch_that_fits_the_one_launch_kernel_alone_is_accepted(int4, batch, E, K, ns, d, f):
+    """Heavy layers take the GEMM from a few tokens on; where only the one-launch kernel's partial sums,
+    NP (d_ff / 32) d_model floats, fit the array, that kernel runs."""
+    import torch
+    from paper_2602_11192_amd import binding as B
+    if torch.cuda.is_available():
+        pytest.skip("an accepted call would run on these addresses")
+    kw = dict(n_experts=E, top_k=K, n_shared=ns, d_model=d, d_ff=f,
+              pool_layout=B.MOE_LAYOUT_TILED_INT4 if int4 else B.MOE_LAYOUT_TILED)
+    assert not scratch_refused(B, batch, **kw), B.moe_last_error()
