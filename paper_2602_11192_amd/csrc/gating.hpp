@@ -42,7 +42,8 @@ __host__ __device__ inline bool fast_table(int policy, int C, int P, int n_share
 
 // ---------------------------------------------------------------- phase 2
 // The K largest of E values held by one wave (value e in z[e / 64] of lane e % 64), as one lane mask per register;
-// equal values go to the lower id.  Exactly K bits are set whatever the values are (K <= E).
+// equal values go to the lower id, NaN counts as less than everything.  Exactly K bits are set whatever the values are
+// (K <= E).
 // The K-th largest is found bit by bit from the top of its order-preserving integer key: one compare, one ballot and
 // a scalar population count per bit, and it ends as soon as a threshold separates exactly K values - after the sign,
 // the exponent and a few mantissa bits on router logits.  K rounds of wave-wide arg-max instead take ~250
@@ -55,7 +56,7 @@ __device__ __forceinline__ void top_select(const float (&z)[EPL], int E, int K, 
 #pragma unroll
   for (int i = 0; i < EPL; ++i) {
     const uint32_t u = __builtin_bit_cast(uint32_t, z[i] + 0.0f);      // -0 counts as +0
-    key[i] = u ^ ((u >> 31) ? 0xffffffffu : 0x80000000u);
+    key[i] = z[i] != z[i] ? 0u : u ^ ((u >> 31) ? 0xffffffffu : 0x80000000u);
     valid[i] = __ballot(lane + i * kWave < E);
   }
   uint32_t t = 0;          // largest threshold so far that at least K keys reach
