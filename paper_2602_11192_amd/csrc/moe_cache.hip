@@ -83,7 +83,8 @@ namespace {
   } while (0)
 
 constexpr int kProfSlots = 512;
-constexpr int64_t kSingleRouting = 50 << 20;     // see decode_wave
+// Lines between the single launch and routing once, see decode_wave.
+constexpr int64_t kSingleWork = 53000000, kSingleWorkQ4 = 60000000, kSingleWgsQ4 = 512;
 
 struct ProfSlot {
   KernelEvents route, gate_up, down;   // attached to the dispatches of the three main kernels of a call
@@ -740,13 +741,18 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   // buffers - on the shapes the single-launch kernel covers.  These calls alone read the copy of W_r that create made,
   // whichever path they take; all others read the caller's matrix, as the allocation-free entry point does.  When the host knows that all experts are there the other
   // path does not wait either, and with several tokens routing once is faster than in every workgroup as soon as the
-  // workgroups and the router matrix are many and large (2 / 3 / 4 tokens, workgroups x E x d = 67 M and more: OLMoE-like 47.8
-  // / 61.9 / 77.4 against 45.6 / 59.0 / 67.8 us, INT4 35.5 / 44.9 / 56.5 against 28.6 / 34.8 / 40.1; at 52 M, 2 Phi-3.5-MoE-like
-  // tokens, 98.6 against 99.8, INT4 54 / 51; at 17 M, 4 tokens on 32 experts of 2048 x 512, 26.6 against 38.4).
+  // workgroups and the router matrix are many and large.  Single launch / routing once, us per call, by workgroups x E x d:
+  // bf16 at 50 M 43.1 / 40.4 (OLMoE-like with d_ff 512, 3 tokens) but 57.9 / 58.0, at 52 M (2 Phi-3.5-MoE-like tokens) 99.2 /
+  // 101.3, at 55 M 42.7 / 41.6, at 57 M 43.4 / 41.2, at 67 M (2 OLMoE-like tokens) 45.8 / 43.8, at 134 M (4) 78.7 / 72.3; at 17 M,
+  // 4 tokens on 32 experts of 2048 x 512, 27.1 / 28.6.  In INT4 a call is short enough that more than two workgroups per compute
+  // unit decide as well: with 576 of them at 42 M 30.4 / 25.2, 800 at 52 M 52.9 / 50.3, 768 at 6 M 25.7 / 25.1, with 512 at 4 M
+  // 20.8 / 21.5; at 55 M with 416 27.3 / 28.1, at 67 M with 512 30.4 / 27.8, at 134 M with 1024 56.1 / 40.2.
   const bool small = c->single_ok && (batch == 1 || (c->C >= E && batch <= c->single_max_batch));
   if (small) ra.router_packed = c->router_packed + router_packed_bytes(E, d) * layer;
   const int64_t single_wgs = (int64_t)(cf.d_ff / 32) * (std::min<int64_t>((int64_t)batch * K, c->P) + cf.n_shared);
-  const bool route_once = batch > 1 && c->full[layer] && single_wgs * E * d > kSingleRouting;
+  const bool q4 = cf.pool_layout == MOE_LAYOUT_TILED_INT4;
+  const bool route_once = batch > 1 && c->full[layer] &&
+                          (single_wgs * E * d > (q4 ? kSingleWorkQ4 : kSingleWork) || (q4 && single_wgs > kSingleWgsQ4));
   if (small && !route_once) {
     RoutedArgs q{};
     q.r = ra;
