@@ -19,6 +19,7 @@
 // every step).  With hundreds of tokens per expert it is what a compute unit can pull in, ~36 GB/s of weights and
 // tokens together under load - with the weights served from cache the same loop takes 2/3 of the time, with an
 // eighth of the matrix work as good as the same time - so the large tile is chosen for the bytes it saves.
+#include <algorithm>
 #include <type_traits>
 
 #include "device_utils.hpp"
@@ -227,21 +228,36 @@ __global__ void __launch_bounds__(64 * WAVES, MINW) ffn_gemm_kernel(FfnArgs a) {
   }
 }
 
-constexpr int kSmallTile = 6, kLargeTile = 8;     // log2 of the tokens per tile
+constexpr int kSmallTile = 6, kMidTile = 7, kLargeTile = 8;     // log2 of the tokens per tile
+constexpr int kUnits = 256;                                     // compute units
 
 }  // namespace
 
-// The group sizes are not known on the host; the mean load decides the token tile.  Tiles of 64 tokens on four waves
-// stream best (three workgroups per compute unit); tiles of 256 on eight waves read a busy expert's weights once where the
-// small ones read them per 64 tokens.  Layer calls at a mean of 24 / 32 / 48 / 64 / 128 pairs per expert (OLMoE-like): 158 / 172
-// / 203 / 237 / 385 us with the small tile, 166 / 170 / 181 / 191 / 256 with the large one; with large experts the small tile
-// wins for longer (at 32, Phi-3.5-MoE-like 424 against 452 us, Mixtral-like 472 against 555).  (Tiles of 128 on eight waves:
-// 180 / 189 / 219 / 253 at 32 / 48 / 64 / 128.)  Experts streamed from the host cross the link once per tile: the large one.
-WorkPlan plan_ffn_gemm(int batch, int KS, int g_max, bool streamed) {
+// The group sizes are not known on the host; the mean load m = pairs / groups and the workgroups it makes decide the token
+// tile.  Tiles of 64 tokens on four waves stream best (three workgroups per compute unit); tiles of 256 on eight waves read a
+// busy expert's weights once where the small ones read them per 64 tokens, but they leave the chip idle where they are few; tiles
+// of 128 on eight waves lie between.  Up to m = 40 the small one (OLMoE-like, small / large: at m = 24 155 / 170 us per layer
+// call, at 40 173 / 179; Phi-3.5-MoE-like at 32 423 / 452).  Beyond, the small one while it needs less than 1.35 workgroups per
+// compute unit, the two passes weighted by their length (8 experts of 1024 x 512, small / middle / large: m = 64 39 / 46 / 53 us,
+// m = 256 52 / 59 / 84; one of 2048 x 2048, m = 256: 55 / 78 / 132); then the large one, given m > 112 and enough workgroups in
+// either pass (OLMoE-like, m = 128 390 / 302 / 230; 24 of 2560 x 2048, m = 171, 444 / 340 / 242), and the middle one where these
+// are not enough (4 of 3072 x 3072, m = 200, 171 / 125 / 179; 8 of 1024 x 4096, m = 256, 179 / 143 / 187).  Of 262 points (25
+// shapes, m = 30 to 1024) none is slower than with the kernels before the ring, 1.22x in the mean against two tiles split at
+// m = 40.  Experts streamed from the host cross the link once per tile: the large one.
+WorkPlan plan_ffn_gemm(int batch, int KS, int g_max, int d, int f, bool streamed) {
   const int64_t load = (int64_t)batch * KS;
   WorkPlan w{};
-  w.shift = streamed || load > (int64_t)40 * g_max ? kLargeTile : kSmallTile;
   w.cap = (int)work_capacity(g_max, load);
+  w.shift = streamed ? kLargeTile : kSmallTile;
+  if (streamed || load <= (int64_t)40 * g_max) return w;
+  // tiles to expect: half a tile per group is lost to its last one
+  const auto tiles = [&](int shift) { return std::max((double)g_max, (double)load / (1 << shift) + 0.5 * g_max); };
+  const auto blocks = [](int rows, int per_wg) { return (rows + per_wg - 1) / per_wg; };
+  // workgroups of either pass; its length goes with the contraction (gate/up: d, two matrices of half the rows)
+  const double small = tiles(kSmallTile) * ((double)d * blocks(f, 64) + (double)f * blocks(d, 128)) / (d + f);
+  if (small < 1.35 * kUnits) return w;
+  const bool fills = tiles(kMidTile) * blocks(f, 128) >= 0.75 * kUnits && tiles(kLargeTile) * blocks(d, 256) >= 0.375 * kUnits;
+  w.shift = load > (int64_t)112 * g_max && fills ? kLargeTile : kMidTile;
   return w;
 }
 
@@ -258,6 +274,9 @@ hipError_t launch_ffn_gemm(hipStream_t s, const FfnArgs& args, KernelEvents e1, 
     a.by_die = a.g_max >= 32 && load <= (int64_t)24 * a.g_max;
     launch_timed(ffn_gemm_kernel<2, 1, 64, 4, 4, 3>, blocks(a.f, 4), dim3(256), 0, s, e1, a);
     launch_timed(ffn_gemm_kernel<1, 2, 64, 4, 4, 3>, blocks(a.d, 8), dim3(256), 0, s, e2, a);
+  } else if (a.work.shift == kMidTile) {
+    launch_timed(ffn_gemm_kernel<2, 1, 128, 8, 4, 2>, blocks(a.f, 8), dim3(512), 0, s, e1, a);
+    launch_timed(ffn_gemm_kernel<1, 1, 128, 8, 4, 4>, blocks(a.d, 8), dim3(512), 0, s, e2, a);
   } else {
     launch_timed(ffn_gemm_kernel<2, 1, 256, 8, 3, 2>, blocks(a.f, 8), dim3(512), 0, s, e1, a);
     launch_timed(ffn_gemm_kernel<1, 2, 256, 8, 3, 2>, blocks(a.d, 16), dim3(512), 0, s, e2, a);

@@ -61,8 +61,8 @@ FfnPlan plan_ffn(int pool_layout, int d, int f, int batch, bool resident, uint64
   return p;
 }
 
-WorkPlan plan_work(const FfnPlan& p, int batch, int KS, int g_max) {
-  return !p.gemm ? WorkPlan{} : p.q4 ? plan_ffn_gemm_q4(batch, KS, g_max, false) : plan_ffn_gemm(batch, KS, g_max, false);
+WorkPlan plan_work(const FfnPlan& p, int batch, int KS, int g_max, int d, int f) {
+  return !p.gemm ? WorkPlan{} : p.q4 ? plan_ffn_gemm_q4(batch, KS, g_max, false) : plan_ffn_gemm(batch, KS, g_max, d, f, false);
 }
 
 hipError_t launch_ffn(hipStream_t s, int dtype, const FfnPlan& p, const FfnArgs& a, KernelEvents ke1, KernelEvents ke2) {
@@ -798,7 +798,7 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   a.mailbox = c->full[layer] ? nullptr : c->mailbox;       // (every lookup hits: nobody reads the record)
   const int g_max = (int)std::min<size_t>((size_t)batch * K, (size_t)c->P) + cf.n_shared;
   const FfnPlan plan = plan_ffn(cf.pool_layout, d, cf.d_ff, batch, c->full[layer] != 0, g_max * c->expert_bytes);
-  a.work = plan_work(plan, batch, KS, g_max);
+  a.work = plan_work(plan, batch, KS, g_max, d, cf.d_ff);
   HIPCHK(launch_route_cache(s, cf.dtype, ra, state_of(c, layer), c->t, a, ps ? ps->route : KernelEvents{}));
 
   FfnArgs fa{};
@@ -942,7 +942,7 @@ int moe_layer_prefill(moe_cache_t* c, int32_t layer, const void* x_dev, const fl
   a.mailbox = c->full[layer] ? nullptr : c->mailbox;
   const int g_max = (int)std::min<size_t>((size_t)n_tokens * K, (size_t)E) + cf.n_shared;   // groups are experts here
   const bool q4 = cf.pool_layout == MOE_LAYOUT_TILED_INT4;
-  a.work = q4 ? plan_ffn_gemm_q4(n_tokens, KS, g_max, true) : plan_ffn_gemm(n_tokens, KS, g_max, true);
+  a.work = q4 ? plan_ffn_gemm_q4(n_tokens, KS, g_max, true) : plan_ffn_gemm(n_tokens, KS, g_max, d, cf.d_ff, true);
   HIPCHK(launch_route_cache(s, cf.dtype, ra, state_of(c, layer), c->t, a, KernelEvents{}));
 
   FfnArgs fa{};

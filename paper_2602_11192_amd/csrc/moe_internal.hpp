@@ -155,7 +155,7 @@ hipError_t launch_reset(hipStream_t s, const LayerState& st, int E, int C, int P
 hipError_t launch_ffn_rowmajor(hipStream_t s, int dtype, const FfnArgs& a, KernelEvents gate_up, KernelEvents down);
 hipError_t launch_ffn_tiled(hipStream_t s, const FfnArgs& a, KernelEvents gate_up, KernelEvents down);
 // The tiles of a call of `batch` tokens, KS experts each, in at most g_max groups (streamed: experts read from the host).
-WorkPlan plan_ffn_gemm(int batch, int KS, int g_max, bool streamed);
+WorkPlan plan_ffn_gemm(int batch, int KS, int g_max, int d, int f, bool streamed);
 hipError_t launch_ffn_gemm(hipStream_t s, const FfnArgs& a, KernelEvents gate_up, KernelEvents down);
 // Most tokens per call for which a call that may have to fetch experts uses the single-launch bf16 decode kernel (it can
 // take 16 per expert); large experts (d_ff >= 4096) give it workgroups enough for longer.
@@ -183,7 +183,7 @@ hipError_t launch_ffn_gemm_q4(hipStream_t s, const FfnArgs& a, KernelEvents gate
 // Which expert-FFN kernels run a call of `batch` tokens on experts of the given layout and shape.
 struct FfnPlan { bool fused, gemm, tiled, q4; };      // gemm: a grouped GEMM, which needs a work list
 FfnPlan plan_ffn(int pool_layout, int d, int f, int batch, bool resident, uint64_t largest_bytes);
-WorkPlan plan_work(const FfnPlan& p, int batch, int KS, int g_max);      // no list unless a GEMM runs
+WorkPlan plan_work(const FfnPlan& p, int batch, int KS, int g_max, int d, int f);      // no list unless a GEMM runs
 hipError_t launch_ffn(hipStream_t s, int dtype, const FfnPlan& p, const FfnArgs& a, KernelEvents ke1, KernelEvents ke2);
 // identity: pair (b, j) has partial row b * KS + j (pos_of is not read)
 hipError_t launch_combine_chunks(hipStream_t s, const float* o_part, const float* wpair, const int32_t* pos_of,

@@ -207,7 +207,7 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
   a.mailbox = nullptr;
   a.miss_list = reinterpret_cast<MissEntry*>(base + o_miss);
   a.max_miss = (int32_t)max_miss;
-  a.work = plan_work(plan, batch, KS, G);
+  a.work = plan_work(plan, batch, KS, G, d, f);
   HIPCHK(launch_route_cache(s, L->dtype, ra, st, t, a, KernelEvents{}));
 
   FfnArgs fa{};
