@@ -1193,8 +1193,11 @@ hipError_t launch_route_cache(hipStream_t s, int dtype, const RouteArgs& r, cons
   // Tiles of 16 tokens: from two tokens on with the packed router matrix (calls of up to four tokens have one).  Reading it
   // row-major the tile kernel needs 6 us more on 64 x 2048 (a layer call of 16 tokens 82.5 against 79.1 us, of 24 86.3
   // against 86.5, of 48 89.5 against 92.2, of 64 90.6 against 111.4); with few experts a workgroup per token keeps up for
-  // longer (16 x 4096, 64 tokens: 96.0 against 93.7 us).
-  const int tile_min = r.router_packed ? 2 : a.E > 32 ? 32 : 112;
+  // longer (16 x 4096, 64 tokens: 96.0 against 93.7 us), and so it does where the tile's logits take several passes (200
+  // experts of 1024 columns, launch of 33 tokens 104 against 79 us, of 64 155 against 125) or one wave looks up in order
+  // whatever routes (64 experts under discounted counts, layer call of 64 tokens 149 against 144 us).
+  const bool in_order = a.mode == 0 && !fast_table(a.policy, a.C, a.P, a.n_shared);
+  const int tile_min = r.router_packed ? 2 : a.E > 32 && a.E <= 64 && !in_order ? 32 : 112;
   if (dtype == MOE_DTYPE_BF16 && a.B >= tile_min && a.E <= kTileMaxE && r.d % 32 == 0) {
     const int nt = a.E <= 16 ? 1 : a.E <= 32 ? 2 : 4;
     const size_t bytes = std::max(lds, (size_t)(kTileWaves / 2) * nt * 256 * sizeof(float));
