@@ -63,6 +63,17 @@ __device__ __forceinline__ float wave_max(float v) {
   return fmaxf(fmaxf(r0, r1), fmaxf(r2, r3));
 }
 
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  const auto step = [](uint32_t a, int o) { return a > (uint32_t)o ? a : (uint32_t)o; };
+  v = step(v, __builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true));
+  v = step(v, __builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, true));
+  v = step(v, __builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true));
+  v = step(v, __builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, true));
+  uint32_t best = (uint32_t)__builtin_amdgcn_readlane((int)v, 0);
+  for (int r = 1; r < 4; ++r) best = step(best, __builtin_amdgcn_readlane((int)v, r * 16));
+  return best;
+}
+
 __device__ __forceinline__ float readlane_f(float v, int lane) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
 }

@@ -41,7 +41,8 @@ def expected(bias, K):
 
 # one wave per token in fp32; sixteen tokens a workgroup in bf16 (32 tokens and more on over 32 experts, 112 on fewer)
 @pytest.mark.parametrize("dtype,E,K,batch", [("fp32", 8, 2, 16), ("fp32", 8, 2, 8), ("fp32", 64, 8, 8), ("fp32", 256, 17, 8),
-                                             ("fp32", 1024, 8, 8), ("bf16", 63, 7, 40), ("bf16", 200, 20, 40),
+                                             ("fp32", 1024, 8, 8), ("fp32", 100, 3, 8), ("fp32", 1024, 2, 8),
+                                             ("bf16", 63, 7, 40), ("bf16", 200, 20, 120), ("bf16", 200, 4, 120),
                                              ("bf16", 16, 4, 120)])
 def test_special_values_in_the_router_kernels(torch, B, dtype, E, K, batch):
     d, f = 64, 32
