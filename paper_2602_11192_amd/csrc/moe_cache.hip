@@ -42,20 +42,26 @@ int fail(int code, const char* fmt, ...) {
 }
 
 // The single-launch FFN kernels (one partial row per 32 rows of d_ff) for a few tokens, the grouped GEMM beyond.  On a layer
-// whose experts are all resident, once the call reads enough weights (largest_bytes: every pair on an expert of its own)
-// to outweigh the GEMM's second launch, the line lies at 3 tokens in bf16 (4 tokens, the kernel / the GEMM: OLMoE-like
-// 72.4 / 67.8 us per call, Phi-3.5-MoE-like 182 / 172, Mixtral-like 275 / 266; 3 tokens 59.0 / 63.6, 149 / 144, 214 / 224; but
-// 8 experts of 1024 x 4096, 201 MB: 32 / 59, and 32 of 2048 x 512, 100 MB: 27 / 38), in INT4 at 4 (OLMoE-like, 5 tokens, 141
-// MB: 44.0 / 42.1 us), or at 8 on experts so large that the kernel has workgroups enough without more tokens
-// (Phi-3.5-MoE-like, 8 tokens: 126 / 135 us, 10: 149 / 140).  Smaller layers, and calls that may have to fetch experts, stay
-// with the kernel for longer.  The split-K pair (ffn_tiled.hip) remains for small calls on shapes the kernel does not cover.
-FfnPlan plan_ffn(int pool_layout, int d, int f, int batch, bool resident, uint64_t largest_bytes) {
+// whose experts are all resident the GEMM may take over earlier, from 4 tokens (INT4: 5), where
+//   - the call reads enough weights (every pair on an expert of its own) to outweigh the second launch: 350 MB, INT4 120 MB (4
+//     tokens, the kernel / the GEMM: 8 experts of 1024 x 4096, 201 MB, 32 / 59 us, 32 of 2048 x 512, 100 MB, 27 / 38); and
+//   - its down pass has workgroups enough - groups x blocks of 128 (INT4: 256) rows - to fill the units, each of them working
+//     through all of d_ff, in proportion to what more tokens cost the other kernel: 160 and 1000 / tokens of them (INT4 192 and
+//     1500 / tokens).  Kernel / GEMM, bf16: 4 Phi-3.5-MoE-like tokens (256 workgroups) 182 / 172, 4 Mixtral-like (256) 275 / 266, 6 on 16
+//     of 1536 x 4096 (192) 112 / 104, but 4 on 16 of 512 x 12288 (64) 81 / 137, 4 on 8 of 1536 x 6144 (96) 71 / 95; INT4: 6
+//     OLMoE-like tokens (384) 57 / 55, 16 (512) 77 / 61, 12 Phi-3.5-MoE-like (256) 156 / 145, but 10 on 16 of 512 x 12288 (32) 72 / 144,
+//     10 on 8 of 2048 x 8192 (64) 76 / 113.
+// Smaller layers, and calls that may have to fetch experts, stay with the kernel for longer.  The split-K pair (ffn_tiled.hip)
+// remains for small calls on shapes the kernel does not cover.
+FfnPlan plan_ffn(int pool_layout, int d, int f, int batch, bool resident, int groups, uint64_t expert_bytes) {
   FfnPlan p{};
   p.tiled = pool_layout == MOE_LAYOUT_TILED;
   p.q4 = pool_layout == MOE_LAYOUT_TILED_INT4;
   const bool shape = p.q4 || (p.tiled && ffn_fused_supported(d, f, 1));
-  const bool heavy = resident && largest_bytes >= (p.q4 ? 120ull : 350ull) * 1000000;
-  const int most = p.q4 ? (heavy ? (f >= 4096 ? 8 : 4) : 16) : heavy ? 3 : fused_max_tokens(f);
+  const int64_t down_wgs = (int64_t)groups * (p.q4 ? (d + 255) / 256 : (d + 127) / 128);
+  const bool heavy = resident && groups * expert_bytes >= (p.q4 ? 120ull : 350ull) * 1000000 &&
+                     down_wgs >= (p.q4 ? 192 : 160) && down_wgs * batch >= (p.q4 ? 1500 : 1000);
+  const int most = heavy ? (p.q4 ? 4 : 3) : p.q4 ? 16 : fused_max_tokens(f);
   p.fused = shape && batch <= most;
   p.gemm = !p.fused && (shape || (p.tiled && batch > fused_max_tokens(f)));
   return p;
@@ -797,7 +803,7 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   a.pin_ids = nullptr; a.miss_list = c->miss_list; a.max_miss = c->max_miss;
   a.mailbox = c->full[layer] ? nullptr : c->mailbox;       // (every lookup hits: nobody reads the record)
   const int g_max = (int)std::min<size_t>((size_t)batch * K, (size_t)c->P) + cf.n_shared;
-  const FfnPlan plan = plan_ffn(cf.pool_layout, d, cf.d_ff, batch, c->full[layer] != 0, g_max * c->expert_bytes);
+  const FfnPlan plan = plan_ffn(cf.pool_layout, d, cf.d_ff, batch, c->full[layer] != 0, g_max, c->expert_bytes);
   a.work = plan_work(plan, batch, KS, g_max, d, cf.d_ff);
   HIPCHK(launch_route_cache(s, cf.dtype, ra, state_of(c, layer), c->t, a, ps ? ps->route : KernelEvents{}));
 
