@@ -688,7 +688,9 @@ __device__ __forceinline__ FastTable table_of(const RawTable& r) {
 
 // ---------------------------------------------------------------- the decode launch
 // EB: router rows a wave handles at a time (1 when there are at least as many waves as experts: no spare loads).
-template <typename T, int EB>
+// EPL: logits a lane holds while it gates (a kernel of its own for each: code that a launch jumps over costs it as well, 0.5 us
+// with the selection for many experts beside the one for up to 64).
+template <typename T, int EB, int EPL>
 __global__ void __launch_bounds__(1024) route_cache_kernel(RouteArgs r, LayerState st, CallTables t, CacheCallArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int s_last;
@@ -757,9 +759,7 @@ __global__ void __launch_bounds__(1024) route_cache_kernel(RouteArgs r, LayerSta
 
   // ---- phase 2: gating of token b by wave 0 ----
   if (wave != 0) return;
-  if (E <= 64) gate_token<1>(zs, b, E, K, KS, r.norm_topk, t.idx, t.wpair, r.user_idx, r.user_w, idx_stage);
-  else if (E <= 256) gate_token<4>(zs, b, E, K, KS, r.norm_topk, t.idx, t.wpair, r.user_idx, r.user_w, idx_stage);
-  else gate_token<16>(zs, b, E, K, KS, r.norm_topk, t.idx, t.wpair, r.user_idx, r.user_w, idx_stage);
+  gate_token<EPL>(zs, b, E, K, KS, r.norm_topk, t.idx, t.wpair, r.user_idx, r.user_w, idx_stage);
 
   if (!single) {
     // ---- the last workgroup to arrive carries on (no waiting anywhere) ----
@@ -1219,14 +1219,15 @@ hipError_t launch_route_cache(hipStream_t s, int dtype, const RouteArgs& r, cons
     launch_timed(route_tile_kernel<float, false, 1>, dim3(1), dim3(kTileThreads), lds, s, ev, r, st, t, a);
     return hipGetLastError();
   }
-  const bool one_row = a.E <= waves;
-  if (dtype == MOE_DTYPE_FP32) {
-    if (one_row) launch_timed(route_cache_kernel<float, 1>, grid, block, lds, s, ev, r, st, t, a);
-    else launch_timed(route_cache_kernel<float, 4>, grid, block, lds, s, ev, r, st, t, a);
-  } else {
-    if (one_row) launch_timed(route_cache_kernel<uint16_t, 1>, grid, block, lds, s, ev, r, st, t, a);
-    else launch_timed(route_cache_kernel<uint16_t, 4>, grid, block, lds, s, ev, r, st, t, a);
-  }
+  const auto launch = [&](auto type) {
+    using T = decltype(type);
+    if (a.E <= waves) launch_timed(route_cache_kernel<T, 1, 1>, grid, block, lds, s, ev, r, st, t, a);
+    else if (a.E <= 64) launch_timed(route_cache_kernel<T, 4, 1>, grid, block, lds, s, ev, r, st, t, a);
+    else if (a.E <= 256) launch_timed(route_cache_kernel<T, 4, 4>, grid, block, lds, s, ev, r, st, t, a);
+    else launch_timed(route_cache_kernel<T, 4, 16>, grid, block, lds, s, ev, r, st, t, a);
+  };
+  if (dtype == MOE_DTYPE_FP32) launch(float{});
+  else launch(uint16_t{});
   return hipGetLastError();
 }
 
