@@ -50,8 +50,9 @@ __host__ __device__ inline bool fast_table(int policy, int C, int P, int n_share
 // cycles each: 1.2 us of a one-token call at K = 8 against 0.3 us.  Beyond 64 values a bit costs as many compares as there
 // are registers, and up to kFewRounds rounds are the faster way (one-token call, rounds / bits: 1000 experts, K = 1 67.1 / 70.4
 // us, K = 4 71.4 / 72.8, K = 8 76.5 / 75.9; 200 experts, K = 1 27.1 / 28.2, K = 4 28.3 / 29.2, K = 8 31.6 / 31.3).
+// kRounds: the kernel has these rounds as well (code that a launch only jumps over costs it 0.2-0.5 us).
 constexpr int kFewRounds = 4;
-template <int EPL>
+template <int EPL, bool kRounds = false>
 __device__ __forceinline__ void top_select(const float (&z)[EPL], int E, int K, uint64_t (&mask)[EPL]) {
   const int lane = threadIdx.x & 63;
   uint32_t key[EPL];
@@ -62,7 +63,7 @@ __device__ __forceinline__ void top_select(const float (&z)[EPL], int E, int K, 
     key[i] = z[i] != z[i] ? 0u : u ^ ((u >> 31) ? 0xffffffffu : 0x80000000u);
     valid[i] = __ballot(lane + i * kWave < E);
   }
-  if constexpr (EPL > 1) {
+  if constexpr (kRounds) {
     if (K <= kFewRounds) {       // K rounds of arg-max
 #pragma unroll
       for (int i = 0; i < EPL; ++i) {
@@ -118,7 +119,7 @@ __device__ __forceinline__ void top_select(const float (&z)[EPL], int E, int K, 
 // One wave gates one token from the logits in LDS (zs[E]).  kWeights = false: only the selected set (idx_g) is
 // formed - same selection, no softmax - for callers that need to know which experts run, not their weights.
 // kPublish: idx_g is written at device scope, for another workgroup of the same launch to read.
-template <int EPL, bool kWeights = true, bool kPublish = false>
+template <int EPL, bool kWeights = true, bool kPublish = false, bool kRounds = false>
 __device__ __forceinline__ void gate_token(const float* zs, int b, int E, int K, int KS, int norm_topk,
                                            int32_t* idx_g, float* wpair_g, int32_t* user_idx, float* user_w,
                                            int32_t* idx_stage) {
@@ -135,7 +136,7 @@ __device__ __forceinline__ void gate_token(const float* zs, int b, int E, int K,
   }
   zmax = wave_max(zmax);
   uint64_t top[EPL];
-  top_select<EPL>(z, E, K, top);
+  top_select<EPL, kRounds>(z, E, K, top);
 #pragma unroll
   for (int i = 0; i < EPL; ++i) sel[i] = (top[i] >> lane) & 1;
   if constexpr (!kWeights) {

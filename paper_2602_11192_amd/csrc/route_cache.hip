@@ -759,7 +759,7 @@ __global__ void __launch_bounds__(1024) route_cache_kernel(RouteArgs r, LayerSta
 
   // ---- phase 2: gating of token b by wave 0 ----
   if (wave != 0) return;
-  gate_token<EPL>(zs, b, E, K, KS, r.norm_topk, t.idx, t.wpair, r.user_idx, r.user_w, idx_stage);
+  gate_token<EPL, true, false, (EPL > 1)>(zs, b, E, K, KS, r.norm_topk, t.idx, t.wpair, r.user_idx, r.user_w, idx_stage);
 
   if (!single) {
     // ---- the last workgroup to arrive carries on (no waiting anywhere) ----
