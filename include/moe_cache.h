@@ -241,10 +241,12 @@ int moe_cache_prefill_pins(moe_cache_t* cache, int32_t layer, const int32_t* exp
  * is executed as consecutive waves of tokens (the batch is halved until every wave
  * fits; one token always fits); routing, hits, misses, evictions and outputs are the
  * same as for the unsplit call, only slower.
- * Host waits: none on a layer all of whose experts are known to be resident (C >= E and loaded by earlier calls); none
- * for batch 1, or for a cache that holds every expert (C >= E), on bf16 experts in the tiled
- * layout with in-kernel fetch (router, gating, lookups and the expert FFN are then one launch, the combine a
- * second one); every other call waits for the device to report the miss list (copy-engine fetch) or whether
+ * Host waits: none for batch 1, or for up to four tokens on a cache that can hold every expert (C >= E), on bf16 experts in
+ * the tiled layout or INT4 experts, with in-kernel fetch (router, gating, lookups and the expert FFN are then one launch, the
+ * combine a second one); none on a layer all of whose experts are known to be resident: C >= E, and a preload, a prompt or
+ * a decode call that did wait has found them all there since the last reset (calls that do not wait tell the host
+ * nothing).  Such a layer may take other kernels than before, whose fp32 sums are added in another order.  Every other call
+ * waits for the device to report the miss list (copy-engine fetch) or whether
  * it has to be split (batched calls on a constrained cache).
  * Errors: INVALID_ARG (null x/y, batch < 1 or > max_batch, layer out of range), HIP, TIMEOUT.
  */
@@ -354,9 +356,10 @@ int moe_cache_sim_loss(const int32_t* idx_dev, int32_t n_traces, int32_t T, int3
  *   other arguments as for moe_layer_decode; the device is the calling thread's current device.
  * topk_idx and topk_w equal those of moe_layer_decode on a cache of capacity E preloaded with experts 0..E-1 in
  * that order; y equals it up to the order in which the fp32 partial sums of an expert are added: bit for bit when
- * both entry points run the same expert kernel, within the last bf16 digit otherwise (one-token calls on shapes that
- * moe_layer_decode hands to its tile kernel; batches that this entry point runs through the grouped GEMM so that its
- * partial sums fit the array).
+ * both entry points run the same expert kernel, within the last bf16 digit otherwise (with in-kernel fetch, calls of one to four
+ * tokens, which moe_layer_decode may run in its single launch; batches whose partial sums fit the array in the grouped
+ * GEMM's form, or in the one-launch kernel's, only).  The gate weights are equal bit for bit except beside that single
+ * launch, whose logits are summed in another order.
  * Nothing is counted or traced.  A batch whose tables and partial sums exceed the array is rejected with
  * MOE_ERR_UNSUPPORTED (the message names the bytes needed).  All calls on one GPU share the array: calls that
  * overlap in time on one GPU (different streams without ordering, different threads) race.

@@ -16,9 +16,10 @@
 //
 // What bounds it: HBM while an expert sees few tokens (64 DeepSeekMoE-like tokens, 66 experts: gate/up 122 us for 761 MB
 // and down 64 us for 381 MB, i.e. 6.2 and 6.0 TB/s, against 153 and 84 us with a loop that drained its loads at the end of
-// every step).  With hundreds of tokens per expert it is what a compute unit can pull in, ~36 GB/s of weights and
-// tokens together under load - with the weights served from cache the same loop takes 2/3 of the time, with an
-// eighth of the matrix work as good as the same time - so the large tile is chosen for the bytes it saves.
+// every step).  With hundreds of tokens per expert neither HBM (1024 OLMoE-like tokens: 618 MB in 153 us) nor the matrix
+// cores: with the weights served from cache the gate/up loop takes 2/3 of the time, with an eighth of the matrix work
+// nearly all of it.  What the code leaves there: one workgroup of the large tile per compute unit at a time, so that its ~530
+// workgroups make 2.07 rounds, and every tile requests and stages all of its 256 token rows however few it has.
 #include <algorithm>
 #include <type_traits>
 

@@ -152,7 +152,9 @@ struct moe_cache {
 
   std::vector<moe_cache_stats_t> stats;
   std::vector<uint8_t> full;      // [L] 1: the host knows that all E experts of the layer are resident (C >= E; nothing is
-                                  // ever evicted then), so its calls cannot miss and need no answer from the device
+                                  // ever evicted then), so its calls cannot miss and need no answer from the device.  Learnt
+                                  // from the records of calls that wait (preloads, prompts, calls beyond the single launch):
+                                  // a record read without waiting would let timing choose the kernels, and the last bits
 
   bool profiling = false;
   std::vector<ProfSlot> prof;

@@ -8,21 +8,26 @@
 // discounted-count family of Definition C.1; contents change lazily, only by
 // inserting the requested expert (Remark after Definition C.1).
 //
-// Shape of the launch: one workgroup per token.
-//   phase 1: the waves of the workgroup split the E router rows; each wave forms
-//     whole dot products W_r[e,:].x for up to four rows at a time with every
-//     16-byte load issued up front, then DPP reductions.  Logits stay in LDS.
-//   phase 2: wave 0 owns the token: Top-K by K rounds of wave arg-max on the
-//     logits (ties to the lower id; the same set as Top-K of p), softmax with
-//     wave reductions, gate weights, outputs in ascending expert id.
-//   phase 3 (the only workgroup, or for a batch the one that arrives last at a
-//     device-scope counter - nobody waits): ONE wave runs the B*K lookups in
-//     order, since each one changes the state the next one sees.  For the
-//     usual sizes (LRU, at most 64 slots/buffers/pairs) the whole table lives
-//     in registers, one slot per lane, and a lookup is a ballot plus a DPP
-//     arg-min; otherwise the table is staged in LDS.  The wave also groups the
-//     (token, expert) pairs by expert buffer for the FFN kernels and leaves the
-//     miss list in pinned host memory for the copy scheduler.
+// Two shapes of the launch, chosen by launch_route_cache:
+//   route_cache_kernel: one workgroup per token.  The waves split the E router
+//     rows; each forms whole dot products W_r[e,:].x for up to four rows at a time
+//     with every 16-byte load issued up front, then DPP reductions; wave 0 gates
+//     the token.  Of a batch the workgroup that arrives last at a device-scope
+//     counter goes on to the lookups (nobody waits).
+//   route_tile_kernel: sixteen tokens per workgroup (fp32: all of a small call),
+//     logits on the matrix cores, a wave gates a token.
+// Gating (gate_token, gating.hpp): Top-K of the logits by bisection of their
+//   integer keys, ties to the lower id - the same set as Top-K of p - softmax
+//   with wave reductions, gate weights, outputs in ascending expert id.
+// Lookups, in three forms: all of a call's lookups at once on every wave of the
+//   workgroup when every one hits (group_hits, tile kernel); one wave in order on
+//   the table in registers, one slot per lane, a lookup being a ballot plus a
+//   DPP arg-min (cache_phase_fast: LRU, at most 64 slots and buffers); one wave in
+//   order on the table in LDS otherwise (cache_phase_general).  In order, because
+//   each lookup that misses changes the state the next one sees.  The pairs
+//   (token, expert) are grouped by expert buffer for the FFN kernels, the work list
+//   of the grouped GEMM is written, and the miss list goes to pinned host memory
+//   for the copy scheduler.
 // Nothing is committed when the call runs out of spare buffers, so a failed call
 // leaves the cache unchanged.
 #include <algorithm>
@@ -972,10 +977,11 @@ __device__ __forceinline__ void group_hits(unsigned char* smem, const LdsLayout&
 // wave gates a token.  A call of at most 16 tokens is one workgroup, which goes straight on to the lookups; of a larger
 // call the workgroup that arrives last does (nobody waits).  What the others must see of a workgroup are its selected
 // experts only, written past the caches with device-scope stores, so the arrival needs no cache write-back: a
-// write-back in every wave, logits by half of the waves and the grouping through memory made this launch take 53 us at
-// 1024 tokens, 23 us at 64 and 13 us at 16 (64 experts, d = 2048); now 21, 12 and 11.5 us.
-// PACKED: W_r comes from the library's copy in operand order (pack_router_kernel), where a cache has one: a wave-wide load
-// is then one contiguous KiB instead of 16 pieces of 64 bytes (64 x 2048 experts: 11.5 against 17.8 us per launch).
+// write-back in every wave, logits by half of the waves and the grouping through memory made this launch take 53.5 us at
+// 1024 tokens and 23 us at 64 (64 experts, d = 2048, kernel trace); now 31 and 21 us.
+// PACKED: W_r comes from the library's copy in operand order (pack_router_kernel), for the calls of 2 to 4 tokens that may
+// read it: a wave-wide load is then one contiguous KiB instead of 16 pieces of 64 bytes (64 x 2048, 16 tokens: 11.5 against
+// 17.8 us per launch).
 // T = float: the router rows as dot products, one wave per (token, expert); for calls so small that one workgroup does it
 // sooner than several meet (kSmallRouterBytes).
 template <typename T, bool PACKED, int NT>

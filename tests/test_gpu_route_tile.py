@@ -1,7 +1,7 @@
 """Routing of several tokens per launch (tiles of 16 tokens, the grouping in the workgroup that arrives last) at the edges
 of its tiles: token and expert counts around 16 and 64, more lookups than the grouping phase keeps in registers,
-shared experts; through a cache (router matrix in operand order) and through the entry point that allocates nothing
-(row-major), against the layer in 64 bits."""
+shared experts; through a cache and through the entry point that allocates nothing, against the layer in 64 bits.  (The router
+matrix in operand order is read by calls of 2 to 4 tokens only: test_gpu_resident_interleaved.py.)"""
 import numpy as np
 import pytest
 
@@ -79,7 +79,7 @@ def test_routing_of_a_batch(torch, B, batch, E, K, ns, d):
         check(lambda yd, i, wd: B.moe_layer_decode_resident_noalloc(
             n_experts=E, n_shared=ns, top_k=K, d_model=d, d_ff=f, dtype=B.MOE_DTYPE_BF16, pool_layout=B.MOE_LAYOUT_ROWMAJOR,
             router_w=rd, experts=blocks.reshape(-1).cuda(), shared_w=sd, x=xd, y=yd, logit_bias=bd, topk_idx=i, topk_w=wd))
-    # (in-kernel fetch goes with the tiled layout and the router matrix in operand order)
+    # (in-kernel fetch goes with the tiled layout)
     packed = d == 256
     pool = blocks.reshape(-1).clone()
     if packed:

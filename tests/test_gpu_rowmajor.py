@@ -1,5 +1,6 @@
-"""Row-major experts: widths that are and are not whole 16-byte pieces of a W_d row, token counts around the four that a
-wave takes at a time, calls that one workgroup routes; fp32 and bf16, against the layer in 64 bits."""
+"""Row-major experts: widths that are and are not whole 16-byte pieces of a W_d row and token counts around the four that a
+wave takes at a time; fp32 and bf16, against the layer in 64 bits.  (Calls that one workgroup routes, at their limits:
+test_gpu_small_fp32.py.)"""
 import pytest
 
 from tests.helpers import TOL
