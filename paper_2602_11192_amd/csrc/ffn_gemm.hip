@@ -240,11 +240,13 @@ constexpr int kUnits = 256;                                     // compute units
 // of 128 on eight waves lie between.  Up to m = 40 the small one (OLMoE-like, small / large: at m = 24 155 / 170 us per layer
 // call, at 40 173 / 179; Phi-3.5-MoE-like at 32 423 / 452).  Beyond, the small one while it needs less than 1.35 workgroups per
 // compute unit, the two passes weighted by their length (8 experts of 1024 x 512, small / middle / large: m = 64 39 / 46 / 53 us,
-// m = 256 52 / 59 / 84; one of 2048 x 2048, m = 256: 55 / 78 / 132); then the large one, given m > 112 and enough workgroups in
-// either pass (OLMoE-like, m = 128 390 / 302 / 230; 24 of 2560 x 2048, m = 171, 444 / 340 / 242), and the middle one where these
-// are not enough (4 of 3072 x 3072, m = 200, 171 / 125 / 179; 8 of 1024 x 4096, m = 256, 179 / 143 / 187).  Of 262 points (25
-// shapes, m = 30 to 1024) none is slower than with the kernels before the ring, 1.22x in the mean against two tiles split at
-// m = 40.  Experts streamed from the host cross the link once per tile: the large one.
+// m = 256 52 / 59 / 84; one of 2048 x 2048, m = 256: 55 / 78 / 132); then the large one where its workgroups, too, fill the units -
+// three quarters of them in the gate/up pass, as many in the down pass, or half that from m = 112 on (OLMoE-like, m = 128 390 /
+// 302 / 230; 24 of 2560 x 2048, m = 171, 444 / 340 / 242; at m = 64 OLMoE-like 258 / 188 / 190, and with a few experts preferred 10 %
+// more with the middle than with the large one) - and the middle one where not (4 of 3072 x 3072, m = 200, 171 / 125 / 179;
+// 8 of 1024 x 4096, m = 256, 179 / 143 / 187).  Of 262 points (25 shapes, m = 30 to 1024) with evenly spread experts none is slower
+// than with the kernels before the ring, with preferred experts three are, by 5 %; 1.22x and 1.25x in the mean against two tiles
+// split at m = 40.  Experts streamed from the host cross the link once per tile: the large one.
 WorkPlan plan_ffn_gemm(int batch, int KS, int g_max, int d, int f, bool streamed) {
   const int64_t load = (int64_t)batch * KS;
   WorkPlan w{};
@@ -257,8 +259,9 @@ WorkPlan plan_ffn_gemm(int batch, int KS, int g_max, int d, int f, bool streamed
   // workgroups of either pass; its length goes with the contraction (gate/up: d, two matrices of half the rows)
   const double small = tiles(kSmallTile) * ((double)d * blocks(f, 64) + (double)f * blocks(d, 128)) / (d + f);
   if (small < 1.35 * kUnits) return w;
-  const bool fills = tiles(kMidTile) * blocks(f, 128) >= 0.75 * kUnits && tiles(kLargeTile) * blocks(d, 256) >= 0.375 * kUnits;
-  w.shift = load > (int64_t)112 * g_max && fills ? kLargeTile : kMidTile;
+  const double gate = tiles(kMidTile) * blocks(f, 128), down = tiles(kLargeTile) * blocks(d, 256);
+  const bool fills = gate >= 0.75 * kUnits && down >= (load > (int64_t)112 * g_max ? 0.375 : 0.75) * kUnits;
+  w.shift = fills ? kLargeTile : kMidTile;
   return w;
 }
 

@@ -16,8 +16,8 @@ def tile(batch, K, ns, E, d, f):
     blocks = lambda rows, per: -(-rows // per)
     if load <= 40 * g or tiles(64) * (d * blocks(f, 64) + f * blocks(d, 128)) / (d + f) < 1.35 * 256:
         return 64
-    fills = tiles(128) * blocks(f, 128) >= 192 and tiles(256) * blocks(d, 256) >= 96
-    return 256 if load > 112 * g and fills else 128
+    fills = tiles(128) * blocks(f, 128) >= 192 and tiles(256) * blocks(d, 256) >= (96 if load > 112 * g else 192)
+    return 256 if fills else 128
 
 
 @pytest.mark.parametrize("want,batch,E,K,ns,d,f", [
