@@ -7,8 +7,9 @@
 // the partial sums of the expert kernels - lives in one file-scope device array.  No hipMalloc, hipFree or
 // allocating library call is made, here or in the launch helpers.
 //
-// Every call on a GPU uses that GPU's copy of the array and rewrites the parts that must start from a known
-// state, so calls on one GPU must not overlap (different streams without ordering race).
+// Every call on a GPU uses that GPU's copy of the array and rewrites the parts that must start from a known state (the
+// arrival counter of the router launch is zero at first and left at zero by every launch), so calls on one GPU must not
+// overlap (different streams without ordering race).
 #include <mutex>
 
 #include "gating.hpp"
