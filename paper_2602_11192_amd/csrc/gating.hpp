@@ -118,8 +118,7 @@ __device__ __forceinline__ void top_select(const float (&z)[EPL], int E, int K, 
 
 // One wave gates one token from the logits in LDS (zs[E]).  kWeights = false: only the selected set (idx_g) is
 // formed - same selection, no softmax - for callers that need to know which experts run, not their weights.
-// kPublish: idx_g is written at device scope, for another workgroup of the same launch to read.
-template <int EPL, bool kWeights = true, bool kPublish = false, bool kRounds = false>
+template <int EPL, bool kWeights = true, bool kRounds = false>
 __device__ __forceinline__ void gate_token(const float* zs, int b, int E, int K, int KS, int norm_topk,
                                            int32_t* idx_g, float* wpair_g, int32_t* user_idx, float* user_w,
                                            int32_t* idx_stage) {
@@ -172,16 +171,88 @@ __device__ __forceinline__ void gate_token(const float* zs, int b, int E, int K,
     if (sel[i]) {
       const int pos = base + __popcll(m & ((1ull << lane) - 1ull));   // ascending expert id
       const float w = norm_topk ? p[i] / selsum : p[i];
-      if constexpr (kPublish)
-        __hip_atomic_store(&idx_g[(size_t)b * K + pos], e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      else
-        idx_g[(size_t)b * K + pos] = e;
+      idx_g[(size_t)b * K + pos] = e;
       wpair_g[(size_t)b * KS + pos] = w;
       if (idx_stage) idx_stage[(size_t)b * K + pos] = e;
       if (user_idx) user_idx[(size_t)b * K + pos] = e;
       if (user_w) user_w[(size_t)b * K + pos] = w;
     }
     base += __popcll(m);
+  }
+  if (lane < KS - K) wpair_g[(size_t)b * KS + K + lane] = 1.0f;  // shared experts: weight 1
+}
+
+// The same in three steps, for a kernel that sets them apart: which experts run
+// (select_experts), their ids in ascending order (write_selected), their weights (write_weights).
+template <int EPL> struct Gate {
+  float z[EPL];
+  uint64_t top[EPL];       // selected set, one mask per 64 experts
+};
+
+template <int EPL, bool kRounds = false>
+__device__ __forceinline__ void select_experts(const float* zs, int E, int K, Gate<EPL>& g) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) {
+    const int e = lane + i * kWave;
+    g.z[i] = e < E ? zs[e] : -INFINITY;
+  }
+  top_select<EPL, kRounds>(g.z, E, K, g.top);
+}
+
+// kPublish: idx_g is written at device scope, for another workgroup of the same launch to read.
+template <int EPL, bool kPublish>
+__device__ __forceinline__ void write_selected(const Gate<EPL>& g, int b, int K, int32_t* idx_g, int32_t* user_idx, int32_t* idx_stage) {
+  const int lane = threadIdx.x & 63;
+  int base = 0;
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) {
+    if ((g.top[i] >> lane) & 1) {
+      const size_t pos = (size_t)b * K + base + __popcll(g.top[i] & ((1ull << lane) - 1ull));
+      const int e = lane + i * kWave;
+      if constexpr (kPublish)
+        __hip_atomic_store(&idx_g[pos], e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      else
+        idx_g[pos] = e;
+      if (idx_stage) idx_stage[pos] = e;
+      if (user_idx) user_idx[pos] = e;
+    }
+    base += __popcll(g.top[i]);
+  }
+}
+
+template <int EPL>
+__device__ __forceinline__ void write_weights(const Gate<EPL>& g, int b, int E, int K, int KS, int norm_topk, float* wpair_g, float* user_w) {
+  const int lane = threadIdx.x & 63;
+  float zmax = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) zmax = fmaxf(zmax, g.z[i]);
+  zmax = wave_max(zmax);
+  float p[EPL];
+  float psum = 0.f;
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) {
+    p[i] = (lane + i * kWave) < E ? expf(g.z[i] - zmax) : 0.f;
+    psum += p[i];
+  }
+  psum = wave_sum(psum);
+  float selsum = 0.f;
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) {
+    p[i] = p[i] / psum;
+    selsum += ((g.top[i] >> lane) & 1) ? p[i] : 0.f;
+  }
+  selsum = wave_sum(selsum);
+  int base = 0;
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) {
+    if ((g.top[i] >> lane) & 1) {
+      const int pos = base + __popcll(g.top[i] & ((1ull << lane) - 1ull));   // ascending expert id
+      const float w = norm_topk ? p[i] / selsum : p[i];
+      wpair_g[(size_t)b * KS + pos] = w;
+      if (user_w) user_w[(size_t)b * K + pos] = w;
+    }
+    base += __popcll(g.top[i]);
   }
   if (lane < KS - K) wpair_g[(size_t)b * KS + K + lane] = 1.0f;  // shared experts: weight 1
 }

@@ -135,6 +135,8 @@ struct moe_cache {
   void* h = nullptr;
   float* o = nullptr;
   int32_t* arrive = nullptr;
+  int n_arrive = 0;
+  size_t o_bytes = 0;
   uint64_t wave_splits = 0;         // calls that had to be run as two waves of tokens
   std::vector<const char*> pool_host;  // [L] each layer's E expert blocks in pinned host memory
   std::vector<const char*> pool_dev;   // [L] the same as the device sees it (in-kernel fetch); empty if not mapped
@@ -563,7 +565,8 @@ int moe_cache_create(const moe_cache_config_t* cfg, const moe_weights_t* weights
   const size_t o_gd = cm; cm += (size_t)c->G * sizeof(GroupDesc);
   const size_t o_work = cm; cm += (1 + work_capacity(c->G, NP)) * sizeof(int4);
   const size_t o_ng = cm; cm += 16;
-  const size_t o_arr = cm; cm += 16;
+  c->n_arrive = 1 + (Bm + 15) / 16;
+  const size_t o_arr = cm; cm += align_up((size_t)c->n_arrive * 4, 16);
   CREATE_CHK(hipMalloc(&c->call_mem, cm), MOE_ERR_HIP);
   CREATE_CHK(hipMemset(c->call_mem, 0, cm), MOE_ERR_HIP);
   c->t.idx = reinterpret_cast<int32_t*>(c->call_mem + o_idx);
@@ -583,6 +586,8 @@ int moe_cache_create(const moe_cache_config_t* cfg, const moe_weights_t* weights
     const size_t pairs = (size_t)std::min(Bm, 16) * KS;
     o_bytes = std::max(o_bytes, pairs * (size_t)(cfg->d_ff / 32) * cfg->d_model * 4);
   }
+  o_bytes = std::max(o_bytes, route_scratch_bytes(Bm, E, cfg->d_model));      // (the routing launch comes before the partial sums)
+  c->o_bytes = o_bytes;
   CREATE_CHK(hipMalloc(reinterpret_cast<void**>(&c->o), o_bytes), MOE_ERR_HIP);
 
   // ---- pinned mailbox ----
@@ -803,11 +808,12 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   a.row0 = row0;
   a.policy = cf.policy; a.gamma = cf.gamma; a.trace_cap = cf.trace_capacity; a.seq = ++c->seq;
   a.pin_ids = nullptr; a.miss_list = c->miss_list; a.max_miss = c->max_miss;
-  a.mailbox = c->full[layer] ? nullptr : c->mailbox;       // (every lookup hits: nobody reads the record)
+  a.full = c->full[layer];
+  a.mailbox = a.full ? nullptr : c->mailbox;       // (every lookup hits: nobody reads the record)
   const int g_max = (int)std::min<size_t>((size_t)batch * K, (size_t)c->P) + cf.n_shared;
   const FfnPlan plan = plan_ffn(cf.pool_layout, d, cf.d_ff, batch, c->full[layer] != 0, g_max, c->expert_bytes);
   a.work = plan_work(plan, batch, KS, g_max, d, cf.d_ff);
-  HIPCHK(launch_route_cache(s, cf.dtype, ra, state_of(c, layer), c->t, a, ps ? ps->route : KernelEvents{}));
+  HIPCHK(launch_route_cache(s, cf.dtype, ra, state_of(c, layer), c->t, a, RouteScratch{c->o, c->o_bytes, c->n_arrive}, ps ? ps->route : KernelEvents{}));
 
   FfnArgs fa{};
   fa.x = x_dev;
@@ -954,7 +960,7 @@ int moe_layer_prefill(moe_cache_t* c, int32_t layer, const void* x_dev, const fl
   // OLMoE-like layer: 142 / 173 / 353 us with them, 50 / 67 / 191 with the tiles of resident calls).
   const bool streamed = !c->full[layer];
   a.work = q4 ? plan_ffn_gemm_q4(n_tokens, KS, g_max, streamed) : plan_ffn_gemm(n_tokens, KS, g_max, d, cf.d_ff, streamed);
-  HIPCHK(launch_route_cache(s, cf.dtype, ra, state_of(c, layer), c->t, a, KernelEvents{}));
+  HIPCHK(launch_route_cache(s, cf.dtype, ra, state_of(c, layer), c->t, a, RouteScratch{c->o, c->o_bytes, c->n_arrive}, KernelEvents{}));
 
   FfnArgs fa{};
   fa.x = x_dev;

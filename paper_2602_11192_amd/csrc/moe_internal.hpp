@@ -88,6 +88,7 @@ struct CacheCallArgs {
   int32_t max_miss;
   WorkPlan work;          // work list to write for the grouped GEMM
   int32_t resident;       // 1: every expert sits in memory in the order of the ids (register-table case); no table is read
+  int32_t full;           // 1: the host knows that every expert of the layer is resident: no lookup can miss
   int32_t row0;           // row of the caller's batch at which this wave of tokens starts (trace records)
 };
 
@@ -120,8 +121,26 @@ struct RouteArgs {
   int32_t d, norm_topk;
   int32_t* user_idx;      // optional copies of the routing result for the caller
   float* user_w;
-  int32_t* arrive;        // [1] workgroup arrival counter, zero between launches
+  int32_t* arrive;        // [RouteScratch::n_arrive] workgroup arrival counters, zero between launches
 };
+
+// Memory for the routing launch itself: logits and selections that its workgroups hand to each other.
+struct RouteScratch {
+  void* ptr;
+  size_t bytes;
+  int32_t n_arrive;
+};
+// ... as the launch lays it out
+struct RouteWork {
+  int32_t slices;         // of the contraction
+  float* logits;          // [tile of 16 tokens][slice][expert tile][256]
+  uint64_t* masks;        // [B] experts that a token selects, up to 64
+};
+
+// How a call of several bf16 tokens is routed: tiles of 16 tokens x tiles of 16 experts x slices of the contraction.
+struct RouteUnits { int tiles, slices, n_arrive; size_t logit_bytes, scratch_bytes; };
+RouteUnits route_units(int B, int E, int d);
+size_t route_scratch_bytes(int max_batch, int E, int d);       // of any call of up to max_batch tokens
 
 // Everything the single-launch decode kernel needs beyond FfnArgs: it routes and looks up itself.  Every
 // workgroup repeats the routing and the lookups from the table `st_in` (read-only during the launch) and reaches
@@ -147,7 +166,7 @@ struct KernelEvents {
 size_t route_cache_lds_bytes(int E, int C, int P, int n_shared, int B, int K, int KS);
 
 hipError_t launch_route_cache(hipStream_t s, int dtype, const RouteArgs& r, const LayerState& st, const CallTables& t,
-                              const CacheCallArgs& a, KernelEvents ev);
+                              const CacheCallArgs& a, const RouteScratch& scratch, KernelEvents ev);
 hipError_t launch_pin(hipStream_t s, const LayerState& st, const CallTables& t, const CacheCallArgs& a);
 // dev_stats: the layer's device-side counters (hits, misses, evictions), zeroed when non-null
 hipError_t launch_reset(hipStream_t s, const LayerState& st, int E, int C, int P, int clear_trace,

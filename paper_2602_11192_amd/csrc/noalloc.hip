@@ -24,9 +24,14 @@ constexpr int kMaxDevices = 64;
 
 // Host code never uses this name as an address: it is resolved per device with hipGetSymbolAddress below.
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+// Arrival counters of the routing launch, beside the array so that they take no space from a batch: zero at first, left at
+// zero by every launch.
+constexpr int kArrive = 16384;
+static __device__ int32_t arrive_counters[kArrive];
 
 std::mutex g_mu;
 unsigned char* g_ptr[kMaxDevices] = {};     // device address of `scratch` on each GPU
+int32_t* g_arrive[kMaxDevices] = {};        // ... and of `arrive_counters`
 uint32_t g_seq[kMaxDevices] = {};
 
 size_t up(size_t v) { return (v + 255) / 256 * 256; }
@@ -99,10 +104,10 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
 
   // ---- carve the array ----
   size_t o_tick, o_score, o_scal, o_ein, o_bos, o_free, o_zom, o_used, o_idx, o_wp, o_pb, o_sp, o_po, o_gd, o_work, o_ng,
-      o_arr, o_miss, o_h, o_o;
+      o_miss, o_h, o_o;
   auto carve = [&]() {
     size_t o = 0;
-    o_arr = o; o += 256;        // the same place whatever the shape: zero before the first launch and after every one
+    o += 256;                   // (arrival counters sat here: what fits stays what it was)
     o_tick = o; o += up((size_t)E * 8);
     o_score = o; o += up((size_t)E * 8);
     o_scal = o; o += up((size_t)SC_COUNT * 8);
@@ -155,16 +160,20 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
   HIPCHK(hipGetDevice(&dev));
   if (dev < 0 || dev >= kMaxDevices) return fail(MOE_ERR_UNSUPPORTED, "device ordinal %d not supported", dev);
   unsigned char* base = nullptr;
+  int32_t* arrive = nullptr;
   uint32_t seq = 0;
   {
     std::lock_guard<std::mutex> lock(g_mu);
     if (!g_ptr[dev]) {
-      void* p = nullptr;
+      void *p = nullptr, *q = nullptr;
       HIPCHK(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)));
-      if (!p) return fail(MOE_ERR_HIP, "hipGetSymbolAddress returned a null address");
+      HIPCHK(hipGetSymbolAddress(&q, HIP_SYMBOL(arrive_counters)));
+      if (!p || !q) return fail(MOE_ERR_HIP, "hipGetSymbolAddress returned a null address");
+      g_arrive[dev] = static_cast<int32_t*>(q);
       g_ptr[dev] = static_cast<unsigned char*>(p);
     }
     base = g_ptr[dev];
+    arrive = g_arrive[dev];
     seq = ++g_seq[dev];
   }
 
@@ -187,7 +196,6 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
   t.grp = reinterpret_cast<GroupDesc*>(base + o_gd);
   t.work = reinterpret_cast<int4*>(base + o_work);
   t.n_groups = reinterpret_cast<int32_t*>(base + o_ng);
-  int32_t* arrive = reinterpret_cast<int32_t*>(base + o_arr);
 
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   const bool resident = fast_table(MOE_POLICY_LRU, E, E, ns);     // the router kernel knows this table by itself
@@ -204,12 +212,13 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
   CacheCallArgs a{};
   a.mode = 0; a.B = batch; a.K = K; a.KS = KS; a.E = E; a.C = E; a.P = E; a.n_shared = ns;
   a.policy = MOE_POLICY_LRU; a.gamma = 0.0; a.trace_cap = 0; a.seq = seq;
-  a.resident = resident ? 1 : 0;
+  a.resident = a.full = resident ? 1 : 0;
   a.mailbox = nullptr;
   a.miss_list = reinterpret_cast<MissEntry*>(base + o_miss);
   a.max_miss = (int32_t)max_miss;
   a.work = plan_work(plan, batch, KS, G, d, f);
-  HIPCHK(launch_route_cache(s, L->dtype, ra, st, t, a, KernelEvents{}));
+  // (everything behind the tables is free until the expert kernels run; the work list sits in front of o_o)
+  HIPCHK(launch_route_cache(s, L->dtype, ra, st, t, a, RouteScratch{base + o_o, kScratchBytes - o_o, kArrive}, KernelEvents{}));
 
   FfnArgs fa{};
   fa.x = x_dev;

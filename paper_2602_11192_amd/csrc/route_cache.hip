@@ -14,13 +14,15 @@
 //     with every 16-byte load issued up front, then DPP reductions; wave 0 gates
 //     the token.  Of a batch the workgroup that arrives last at a device-scope
 //     counter goes on to the lookups (nobody waits).
-//   route_tile_kernel: sixteen tokens per workgroup (fp32: all of a small call),
-//     logits on the matrix cores, a wave gates a token.
+//   route_units_kernel: 16 tokens x 16 experts x a slice of the contraction per
+//     workgroup, logits on the matrix cores; the last unit of a tile of 16 tokens
+//     gates them, a wave per token (route_small_fp32_kernel: a small fp32 call in
+//     one workgroup).
 // Gating (gate_token, gating.hpp): Top-K of the logits by bisection of their
 //   integer keys, ties to the lower id - the same set as Top-K of p - softmax
 //   with wave reductions, gate weights, outputs in ascending expert id.
 // Lookups, in three forms: all of a call's lookups at once on every wave of the
-//   workgroup when every one hits (group_hits, tile kernel); one wave in order on
+//   workgroup when every one hits (group_hits, up to 64 experts); one wave in order on
 //   the table in registers, one slot per lane, a lookup being a ballot plus a
 //   DPP arg-min (cache_phase_fast: LRU, at most 64 slots and buffers); one wave in
 //   order on the table in LDS otherwise (cache_phase_general).  In order, because
@@ -68,7 +70,9 @@ template <> struct Vec<uint16_t> {
   }
 };
 
-constexpr int kTileMaxE = 256;   // most experts the 16-token tile kernel keeps logits for
+constexpr int kTileMaxE = 256;   // most experts the 16-token tile kernels keep logits for
+constexpr int kRouteSliceKb = 32; // fewest k-blocks of the contraction worth a slice of their own: a pair for each of sixteen waves
+constexpr int kRouteMaxUnits = 256;   // ... and most workgroups that slicing may make: one per compute unit
 
 // ---------------------------------------------------------------- LDS layout
 struct LdsLayout {
@@ -764,7 +768,7 @@ __global__ void __launch_bounds__(1024) route_cache_kernel(RouteArgs r, LayerSta
 
   // ---- phase 2: gating of token b by wave 0 ----
   if (wave != 0) return;
-  gate_token<EPL, true, false, (EPL > 1)>(zs, b, E, K, KS, r.norm_topk, t.idx, t.wpair, r.user_idx, r.user_w, idx_stage);
+  gate_token<EPL, true, (EPL > 1)>(zs, b, E, K, KS, r.norm_topk, t.idx, t.wpair, r.user_idx, r.user_w, idx_stage);
 
   if (!single) {
     // ---- the last workgroup to arrive carries on (no waiting anywhere) ----
@@ -801,152 +805,250 @@ constexpr int kTileWaves = 16, kTileThreads = 64 * kTileWaves, kTileTokens = 16;
 // 20.4 -> 19.8; 16 tokens x 8 experts 25.2 -> 26.7, 8 tokens x 64 experts of 512 columns 24.8 -> 28.0: not taken).
 constexpr int kSmallRouterItems = 128;
 constexpr size_t kSmallRouterBytes = 128 << 10;
-constexpr int kMaxKeys = 2 * kWave; // buffer ids of the register-table case, shared experts included
+constexpr int kChunk = kTileThreads;  // tokens whose pairs are placed at a time, one per thread
 
-// What the grouping phase of the tile kernel keeps in LDS.
+// What the phases behind the logits keep in LDS.
 struct TileLds {
-  int map[kTileMaxE];          // expert -> buffer << 8 | slot, -1 when it is not resident
-  int count[kMaxKeys], start[kMaxKeys], group[kMaxKeys], first[kMaxKeys];
-  int last[kWave], touched[kWave];
-  int any_miss, n_groups, last_arrived;
+  float zs[kTileTokens][kTileMaxE + 4];           // logits (+ 4: the 16 tokens of a column fall on different banks)
+  uint64_t sel[kTileTokens];                      // experts each token of the tile selects (up to 64 experts)
+  int map[kTileMaxE];                             // expert -> buffer << 8 | slot, -1 when it is not resident
+  // per wave of 64 tokens and expert: the tokens that select it, how many, and the position of the first of them
+  uint64_t col[kTileWaves][kWave];
+  int cnt[kTileWaves][kWave], base[kTileWaves][kWave];
+  int first_pair[kWave], last_lookup[kWave];      // ... expert: its first pair, its last lookup + 1
+  int first[kWave], touched[kWave];
+  int last_arrived, any_miss;
 };
 
-// Phase 3 of the tile kernel on the register table (LRU), run by ALL waves of the last workgroup.  The common case -
-// every lookup hits - is embarrassingly parallel: residency does not change, a slot's new tick is the position of its
-// last lookup (LDS atomic max), and the pairs are grouped by a counting sort whose counters sit in LDS; the rank a pair
-// draws from its counter is kept in a register until the group's first position is known, so that nothing goes through
-// memory.  A call with at least one miss hands over to the in-order routine in wave 0.
-// H: lookups a thread keeps in registers (the code of this phase runs once per launch and is fetched cold, so a small
-// call takes the variant that holds one).  idx_at(l): expert of lookup l; copy_to: where the lookups are copied on the
-// way (or null); in_order: where the in-order routine finds them.
-template <int H, typename IdxAt>
-__device__ __forceinline__ void group_hits(unsigned char* smem, const LdsLayout& L, TileLds& tl, const RawTable& raw,
-                                           IdxAt idx_at, int32_t* copy_to, const int32_t* in_order, int32_t* pair_buf,
-                                           const LayerState& st, const CallTables& t, const CacheCallArgs& a) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int C = a.C, P = a.P, K = a.K, KS = a.KS, ns = a.n_shared;
-  const int n_lookups = a.B * K, NB = P + ns;
-  const auto pair_of = [&](int l) { return ns == 0 ? l : l + (l / K) * ns; };
-  int m[H], rank[H];
-  bool miss = false;
-#pragma unroll
-  for (int i = 0; i < H; ++i) {
-    const int l = tid + i * kTileThreads;
-    const int e = l < n_lookups ? idx_at(l) : -1;
-    if (e >= 0 && copy_to) copy_to[l] = e;
-    m[i] = e;
-  }
-#pragma unroll
-  for (int i = 0; i < H; ++i) {
-    if (m[i] < 0) continue;
-    m[i] = tl.map[m[i]];
-    miss |= m[i] < 0;
-  }
-  if constexpr (H > 1)
-    for (int l = tid + H * kTileThreads; l < n_lookups; l += kTileThreads) miss |= tl.map[idx_at(l)] < 0;
-  if (miss) tl.any_miss = 1;
+__device__ __forceinline__ void clear_tile_lds(TileLds& tl, int E) {
+  const int tid = threadIdx.x;
+  for (int e = tid; e < E; e += kTileThreads) tl.map[e] = -1;
+  if (tid == 0) tl.any_miss = 0;
+  if (tid < kWave) { tl.first[tid] = tl.last_lookup[tid] = tl.touched[tid] = 0; tl.first_pair[tid] = 1 << 30; }
+}
+
+__device__ __forceinline__ uint32_t load_published(const void* p) {
+  return __hip_atomic_load(static_cast<const uint32_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Announce this workgroup at a counter once every wave's device-scope stores have arrived; true in the workgroup that
+// comes last (nobody waits), which leaves the counter at zero for the next launch.
+__device__ __forceinline__ bool arrive_last(int32_t* counter, int n, int& flag) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (tl.any_miss) {                          // in-order routine, one wave
-    if (wave != 0) return;
-    if (in_order == t.idx) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");     // reads the other workgroups' results directly
-    cache_phase_fast(table_of(raw), smem, L, in_order, pair_buf, st, t, a);
-    return;
+  if (threadIdx.x == 0) {
+    const int last = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
+    if (last) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    flag = last;
   }
-  // the last lookup of a slot and the position of a pair in its group
-  const auto look_up = [&](int l, int v) {
-    atomicMax(&tl.last[v & 255], l + 1);
-    return atomicAdd(&tl.count[v >> 8], 1);
-  };
+  __syncthreads();
+  return flag != 0;
+}
+
+// Inclusive sum over the lanes of a wave, on the vector unit's own lane shifts (a scan through LDS takes ten times as long).
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+#define MOE_SCAN_STEP(CTRL, ROWS) v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false)
+  MOE_SCAN_STEP(0x111, 0xf);      // row_shr 1, 2, 4, 8: sums inside a row of 16 lanes
+  MOE_SCAN_STEP(0x112, 0xf);
+  MOE_SCAN_STEP(0x114, 0xf);
+  MOE_SCAN_STEP(0x118, 0xf);
+  MOE_SCAN_STEP(0x142, 0xa);      // lane 15 of a row into the next, rows 1 and 3
+  MOE_SCAN_STEP(0x143, 0xc);      // lane 31 into rows 2 and 3
+#undef MOE_SCAN_STEP
+  return v;
+}
+
+// Pairs of a call that are put in order in LDS before they are written out.
+constexpr int kStagedLeast = 1024, kStagedMost = 8192;
+__host__ __device__ inline bool stage_pairs(int B, int KS) { return B * KS >= kStagedLeast && B * KS <= kStagedMost; }
+
+// The 64 x 64 bit matrix whose row r lane r holds, transposed: lane c gets column c.
+__device__ __forceinline__ uint64_t transpose_bits(uint64_t x) {
+  const int lane = threadIdx.x & 63;
+  constexpr uint64_t kLow[6] = {0x5555555555555555ull, 0x3333333333333333ull, 0x0f0f0f0f0f0f0f0full, 0x00ff00ff00ff00ffull,
+                                0x0000ffff0000ffffull, 0x00000000ffffffffull};
 #pragma unroll
-  for (int i = 0; i < H; ++i) {
-    const int l = tid + i * kTileThreads;
-    rank[i] = l < n_lookups ? look_up(l, m[i]) : 0;
+  for (int i = 5; i >= 0; --i) {
+    const int j = 1 << i;
+    const uint64_t y = __shfl_xor((unsigned long long)x, j);
+    x = (lane & j) ? (x & ~kLow[i]) | ((y >> j) & kLow[i]) : (x & kLow[i]) | ((y & kLow[i]) << j);
   }
-  if constexpr (H > 1)
-    for (int l = tid + H * kTileThreads; l < n_lookups; l += kTileThreads)      // beyond the registers: parked in pos_of
-      t.pos_of[pair_of(l)] = look_up(l, tl.map[idx_at(l)]);
+  return x;
+}
+
+// Phase 3 on the register table (LRU) of a layer of up to 64 experts, run by ALL waves of the last workgroup.  The common case -
+// every lookup hits - is embarrassingly parallel: residency does not change, and the place of a pair in its group is the number
+// of earlier tokens that select the same expert.  A wave holds the selections of 64 tokens as one mask per lane; transposed, lane
+// e has the tokens of expert e, and counts, prefix sums and the order of the groups are a few instructions in every wave alike.
+// Nothing is drawn from a shared counter: with 8192 ranks from LDS atomics this phase took 12 us of a launch.
+// False, with nothing changed, when a lookup misses (FULL: the host knows that none can).
+// masks: the published selections, null: tl.sel.  behind: work of the caller that the first loads leave time for.
+template <bool FULL, typename Behind>
+__device__ __forceinline__ bool group_hits(unsigned char* smem, TileLds& tl, const RawTable& raw, const uint64_t* masks,
+                                           const LayerState& st, const CallTables& t, const CacheCallArgs& a, Behind behind) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int E = a.E, C = a.C, P = a.P, K = a.K, KS = a.KS, ns = a.n_shared, B = a.B;
+  const auto mask_of = [&](int b) -> uint64_t {
+    if (b >= B) return 0;
+    return masks ? __hip_atomic_load(masks + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : tl.sel[b];
+  };
+  uint64_t mine = mask_of(tid);
+  behind();
+  if constexpr (!FULL) {
+    const uint64_t resident = __ballot(lane < E && tl.map[lane] >= 0);
+    uint64_t wanted = mine;
+    for (int b = kChunk + tid; b < B; b += kChunk) wanted |= mask_of(b);
+    if ((wanted & ~resident) != 0) tl.any_miss = 1;
+    __syncthreads();
+    if (tl.any_miss) return false;
+  }
+  // lane e of every wave: the tokens of expert e in a chunk of 1024, in all of its waves and in those before this one
+  const bool ends = !a.resident || a.work.cap == 0;
+  int in_chunk, before;
+  const auto count_chunk = [&](int c0) {
+    if (c0 + wave * kWave < B) {
+      const uint64_t col = transpose_bits(mine);
+      tl.col[wave][lane] = col;
+      tl.cnt[wave][lane] = __popcll(col);
+      // the expert's first pair (for the kernels that go by groups) and last lookup (recency)
+      const uint64_t lower = (1ull << lane) - 1ull;
+      if (ends) {
+        const int b0 = __ffsll((unsigned long long)col) - 1, b1 = 63 - __clzll(col | 1);
+        const int k0 = __popcll(__shfl((unsigned long long)mine, b0 & 63) & lower), k1 = __popcll(__shfl((unsigned long long)mine, b1) & lower);
+        if (col != 0) {
+          atomicMin(&tl.first_pair[lane], (c0 + wave * kWave + b0) * KS + k0);
+          atomicMax(&tl.last_lookup[lane], (c0 + wave * kWave + b1) * K + k1 + 1);
+        }
+      }
+    }
+    __syncthreads();
+    in_chunk = before = 0;
+    const int n = min(kTileWaves, (B - c0 + kWave - 1) / kWave);
+    for (int w = 0; w < n; ++w) {
+      const int c = tl.cnt[w][lane];
+      in_chunk += c;
+      before += w < wave ? c : 0;
+    }
+  };
+  count_chunk(0);
+  int total = in_chunk;
+  for (int c0 = kChunk; c0 < B; c0 += kChunk) {
+    mine = mask_of(c0 + tid);
+    __syncthreads();
+    count_chunk(c0);
+    total += in_chunk;
+  }
+  const int v = lane < E ? tl.map[lane] : -1;
+  const int begin = (int)wave_scan((uint32_t)total) - total;
+  const uint64_t used = __ballot(total > 0);
+  const int group = __popcll(used & ((1ull << lane) - 1ull)), n_routed = __popcll(used);
+  const int tiles = a.work.cap > 0 ? tiles_of(total, a.work) : 0;
+  const int shared_tiles = a.work.cap > 0 ? tiles_of(B, a.work) : 0;
+  if (a.work.cap > 0) {
+    // work list, groups with the most tokens first (the shared experts': every token), ties by id: a wave compares with four experts
+    int larger = 0;
+#pragma unroll
+    for (int i = 0; i < kWave / kTileWaves; ++i) {
+      const int j = wave * (kWave / kTileWaves) + i, cj = readlane_i(total, j);
+      larger += cj > total || (cj == total && j < lane) ? tiles_of(cj, a.work) : 0;
+    }
+    atomicAdd(&tl.first[lane], larger);
+  }
+  __syncthreads();
+  if (wave == kTileWaves - 1) {
+    if (total > 0) {
+      GroupDesc* gd = &t.grp[group];
+      *reinterpret_cast<int4*>(gd) = int4{v >> 8, begin, total, 0};
+      *reinterpret_cast<int2*>(&gd->pair0) = int2{tl.first_pair[lane], -1};
+      int4* items = t.work + 1 + ns * shared_tiles + tl.first[lane];
+      for (int i = 0; i < tiles; ++i) items[i] = work_item(i << a.work.shift, v >> 8, begin, total, 0);
+    }
+    if (lane < ns) {
+      const int first = B * K + lane * B;
+      t.grp[n_routed + lane] = GroupDesc{P + lane, first, B, 0, K + lane, -1, {0, 0}};
+      for (int i = 0; i < shared_tiles; ++i) t.work[1 + lane * shared_tiles + i] = work_item(i << a.work.shift, P + lane, first, B, 0);
+    }
+    const int n_items = readlane_i((int)wave_scan((uint32_t)tiles), kWave - 1) + ns * shared_tiles;
+    if (lane == 0) {
+      *t.n_groups = n_routed + ns;
+      if (a.work.cap > 0) t.work[0] = int4{n_items, 0, 0, 0};
+    }
+  }
+  const auto place = [&](int32_t* sorted, int32_t* pos_of) {
+    int run = 0;               // the expert's pairs in the chunks before
+    for (int c0 = 0; c0 < B; c0 += kChunk) {
+      if (B > kChunk) {        // more than 1024 tokens: chunk by chunk once more
+        __syncthreads();
+        mine = mask_of(c0 + tid);
+        count_chunk(c0);
+      }
+      if (c0 + wave * kWave < B) {
+        tl.base[wave][lane] = begin + before + run;
+        wave_sync();
+        const int b = c0 + tid;
+        const uint64_t lt_mask = (1ull << lane) - 1ull;
+        uint64_t m = mine;                             // (K bits; none beyond the call's tokens)
+        int p = b * KS;
+        constexpr int U = 4;                           // pairs whose reads are in flight together
+        for (int k0 = 0; k0 < K; k0 += U) {
+          int e[U], pos[U];
+          uint64_t col[U];
+          bool there[U];
+  #pragma unroll
+          for (int u = 0; u < U; ++u) {
+            there[u] = m != 0;
+            e[u] = (__ffsll((unsigned long long)m) - 1) & 63;
+            m &= m - 1;
+            col[u] = tl.col[wave][e[u]];
+            pos[u] = tl.base[wave][e[u]];
+          }
+  #pragma unroll
+          for (int u = 0; u < U; ++u) {
+            if (there[u]) {
+              pos[u] += __popcll(col[u] & lt_mask);
+              sorted[pos[u]] = p + u;
+              pos_of[p + u] = pos[u];
+            }
+          }
+          p += U;
+        }
+      }
+      run += in_chunk;
+    }
+    for (int i = tid; i < B * ns; i += kTileThreads) {
+      const int b = i / ns, sidx = i - b * ns, p = b * KS + K + sidx, pos = B * K + sidx * B + b;
+      sorted[pos] = p;
+      pos_of[p] = pos;
+    }
+  };
   if (a.trace_cap > 0) {
     const int64_t trace_n = st.scalars[SC_TRACE_N];
-    for (int l = tid; l < n_lookups && trace_n + l < a.trace_cap; l += kTileThreads)
-      st.trace[trace_n + l] = moe_trace_rec_t{a.row0 + l / K, idx_at(l), 1, -1};
-  }
-  __syncthreads();
-  if (a.work.cap > 0) {
-    // work list, groups with the most tokens first: a group's items come behind those of all larger ones (ties by id)
-    constexpr int kParts = kTileThreads / kMaxKeys;
-    const int key = tid % kMaxKeys, part = tid / kMaxKeys;
-    const int c = key < P ? tl.count[key] : key < NB ? a.B : 0;
-    int before = 0;
-    for (int j = part; j < NB; j += kParts) {
-      const int cj = j < P ? tl.count[j] : a.B;
-      before += cj > c || (cj == c && j < key) ? tiles_of(cj, a.work) : 0;
+    for (int b = tid; b < B; b += kTileThreads) {
+      uint64_t m = mask_of(b);
+      for (int l = b * K; m != 0; ++l, m &= m - 1)
+        if (trace_n + l < a.trace_cap) st.trace[trace_n + l] = moe_trace_rec_t{a.row0 + b, __ffsll((unsigned long long)m) - 1, 1, -1};
     }
-    atomicAdd(&tl.first[key], before);
   }
-  if (wave == 0) {
-    // group descriptors in ascending buffer id (every token is in the group of every shared expert)
-    const uint64_t lt_mask = (1ull << lane) - 1ull;
-    int n_groups = 0, offset = 0;
-    float n_tiles = 0.f;
-#pragma unroll 1
-    for (int base = 0; base < NB; base += kWave) {
-      const int id = base + lane;
-      const int c = id < P ? tl.count[id] : id < NB ? a.B : 0;
-      n_tiles += (float)tiles_of(c, a.work);
-      int incl = c;
-#pragma unroll
-      for (int dlt = 1; dlt < kWave; dlt <<= 1) {
-        const int v = __shfl_up(incl, dlt);
-        if (lane >= dlt) incl += v;
-      }
-      const int begin = offset + incl - c;
-      const uint64_t gm = __ballot(c > 0);
-      const int gi = n_groups + __popcll(gm & lt_mask);
-      if (c > 0) {
-        GroupDesc* gd = &t.grp[gi];
-        *reinterpret_cast<int4*>(gd) = int4{id, begin, c, 0};       // pair0: whoever drew rank 0, below
-        gd->expert = -1;
-      }
-      if (id < NB) { tl.start[id] = begin; tl.group[id] = gi; }
-      n_groups += __popcll(gm);
-      offset += __shfl(incl, kWave - 1);
+  // a scattered store takes the address unit a cycle per lane: many pairs are put in order in LDS
+  const bool staged = stage_pairs(B, KS);
+  if (!staged) {
+    place(t.sorted_pair, t.pos_of);
+    if (a.resident) return true;
+    __syncthreads();
+  } else {
+    const int n = B * KS;
+    int32_t *sorted = reinterpret_cast<int32_t*>(smem), *pos_of = sorted + (n + 3) / 4 * 4;
+    place(sorted, pos_of);
+    __syncthreads();
+    for (int i = tid * 4; i < n; i += kTileThreads * 4) {        // (the tables are whole multiples of 16 bytes long)
+      *reinterpret_cast<int4*>(t.sorted_pair + i) = *reinterpret_cast<const int4*>(sorted + i);
+      *reinterpret_cast<int4*>(t.pos_of + i) = *reinterpret_cast<const int4*>(pos_of + i);
     }
-    if (a.work.cap > 0) {       // (whole numbers below 2^24: the float sum is exact)
-      n_tiles = wave_sum(n_tiles);
-      if (lane == 0) t.work[0] = int4{(int)n_tiles, 0, 0, 0};
-    }
-    if (lane == 0) { *t.n_groups = n_groups; tl.n_groups = n_groups; }
   }
-  __syncthreads();
-  if (a.work.cap > 0 && tid < NB) {
-    const int c = tid < P ? tl.count[tid] : a.B;
-    int4* items = t.work + 1 + tl.first[tid];
-    for (int i = 0; i < tiles_of(c, a.work); ++i) items[i] = work_item(i << a.work.shift, tid, tl.start[tid], c, 0);
-  }
-  const auto place = [&](int p, int key, int r) {
-    const int pos = tl.start[key] + r;
-    t.sorted_pair[pos] = p;
-    t.pos_of[p] = pos;
-    if (r == 0) t.grp[tl.group[key]].pair0 = p;
-  };
-#pragma unroll
-  for (int i = 0; i < H; ++i) {
-    const int l = tid + i * kTileThreads;
-    if (l < n_lookups) place(pair_of(l), m[i] >> 8, rank[i]);
-  }
-  if constexpr (H > 1)
-    for (int l = tid + H * kTileThreads; l < n_lookups; l += kTileThreads) {
-      const int p = pair_of(l);
-      place(p, tl.map[idx_at(l)] >> 8, t.pos_of[p]);
-    }
-  for (int p = tid; p < a.B * ns; p += kTileThreads) {
-    const int b = p / ns, sidx = p - b * ns;
-    place(b * KS + K + sidx, P + sidx, b);
-  }
-  if (a.resident || wave != 0) return;
+  if (a.resident || wave != 0) return true;
   // ---- the table after the call: recency of the slots, buffers in use, released buffers free again ----
   FastTable f = table_of(raw);
-  const int last = lane < C ? tl.last[lane] : 0;
+  const int last = lane < C && f.exp >= 0 ? tl.last_lookup[f.exp] : 0;
   if (last > 0) {
     f.tick = (uint64_t)(f.clock + last);
     tl.touched[f.buf] = 1;
@@ -959,201 +1061,226 @@ __device__ __forceinline__ void group_hits(unsigned char* smem, const LdsLayout&
   if (lane < C) { st.tick[lane] = f.tick; st.expert_in[lane] = f.exp; st.buf_of_slot[lane] = f.buf; }
   if (lane < P) { st.used_stamp[lane] = f.used; st.free_buf[lane] = f.free_b; st.zombie[lane] = f.zomb; }
   if (lane == 0) {
-    st.scalars[SC_CLOCK] = f.clock + n_lookups;
+    st.scalars[SC_CLOCK] = f.clock + B * K;
     st.scalars[SC_NRES] = f.n_res;
     st.scalars[SC_NFREE] = f.n_free + f.n_zombie;
     st.scalars[SC_NZOMBIE] = 0;
     st.scalars[SC_CALLSEQ] = a.seq;
-    st.scalars[SC_TRACE_N] = f.trace_n + n_lookups;
-    publish_record(a.mailbox, MOE_OK, 0, 0, tl.n_groups, n_lookups, f.n_res, a.seq);
+    st.scalars[SC_TRACE_N] = f.trace_n + B * K;
+    publish_record(a.mailbox, MOE_OK, 0, 0, n_routed + ns, B * K, f.n_res, a.seq);
+  }
+  return true;
+}
+
+// Phases 2 and 3 from the logits of a tile of 16 tokens (tl.zs), by the sixteen waves of one workgroup per tile: a wave selects a
+// token's experts, and the last workgroup of the launch goes on to the lookups.  What the others must see of a workgroup - its
+// selections - goes past the caches with device-scope stores, so the arrival needs no cache write-back; the gate weights, which
+// no one in this launch reads, are formed behind it.
+// One kernel per kind of call: code that a launch only jumps over is fetched cold with the rest, and its registers spill the others'.
+//   kFull    mode 0 on the register table, every expert known to be resident (then there are at most 64): no lookup can miss
+//   kTable   mode 0 on the register table, up to 64 experts
+//   kOther   other tables, more experts, prompt streaming: one wave looks up in order
+enum RouteKind { kFull, kTable, kOther };
+
+template <RouteKind KIND>
+__device__ __forceinline__ void gate_and_group(unsigned char* smem, TileLds& tl, const RawTable& raw, int tile, int n_tiles,
+                                               const RouteArgs& r, uint64_t* masks, const LayerState& st, const CallTables& t, const CacheCallArgs& a) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int E = a.E, K = a.K, KS = a.KS, b = tile * kTileTokens + wave;
+  const bool single = n_tiles == 1, mine = b < a.B;
+  if (KIND != kOther && wave == 0 && lane < a.C && raw.exp >= 0) tl.map[raw.exp] = raw.buf << 8 | lane;
+  const LdsLayout L = lds_layout(E, a.C, a.P, a.n_shared, a.B, K, KS);
+  int32_t* idx_stage = KIND != kFull && stage_in_lds(a.B, KS) ? reinterpret_cast<int32_t*>(smem + L.idx_stage) : nullptr;
+  constexpr int EPL = KIND == kOther ? kTileMaxE / kWave : 1;
+  Gate<1> g1;
+  Gate<EPL> g4;
+  const bool few = KIND != kOther || E <= kWave;
+  if (mine) {
+    if (few) {
+      select_experts<1>(tl.zs[wave], E, K, g1);
+      if (KIND != kOther && lane == 0) {
+        if (single) tl.sel[wave] = g1.top[0];
+        else __hip_atomic_store(masks + b, g1.top[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      if constexpr (KIND != kFull) write_selected<1, true>(g1, b, K, t.idx, nullptr, single ? idx_stage : nullptr);
+    } else {
+      select_experts<EPL>(tl.zs[wave], E, K, g4);
+      write_selected<EPL, true>(g4, b, K, t.idx, nullptr, single ? idx_stage : nullptr);
+    }
+  }
+  const auto weights = [&] {
+    if (!mine) return;
+    if (few) {
+      if (r.user_idx) write_selected<1, false>(g1, b, K, r.user_idx, nullptr, nullptr);
+      write_weights<1>(g1, b, E, K, KS, r.norm_topk, t.wpair, r.user_w);
+    } else {
+      if (r.user_idx) write_selected<EPL, false>(g4, b, K, r.user_idx, nullptr, nullptr);
+      write_weights<EPL>(g4, b, E, K, KS, r.norm_topk, t.wpair, r.user_w);
+    }
+  };
+  if (single) {
+    __syncthreads();
+  } else if (!arrive_last(r.arrive, n_tiles, tl.last_arrived)) {
+    weights();
+    return;
+  }
+  if constexpr (KIND != kOther) {
+    // the weights fill the time that the others' selections take to arrive; with nothing to wait for they come last
+    const bool hits = group_hits<KIND == kFull>(smem, tl, raw, single ? nullptr : masks, st, t, a, [&] { if (!single) weights(); });
+    if (hits) {
+      if (single) weights();
+      return;
+    }
+  }
+  if constexpr (KIND != kFull) {
+    // in order, one wave; the others have the weights of their tokens to form where that is not done
+    if (!single && idx_stage)
+      for (int i = tid; i < a.B * K; i += kTileThreads) idx_stage[i] = (int)load_published(t.idx + i);
+    __syncthreads();
+    if (single || KIND == kOther) weights();
+    if (wave != 0) return;
+    if (!idx_stage) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");     // reads the other workgroups' results directly
+    const int32_t* in_order = idx_stage ? idx_stage : t.idx;
+    int32_t* pair_stage = idx_stage ? reinterpret_cast<int32_t*>(smem + L.pair_stage) : t.pair_buf;
+    if constexpr (KIND == kTable) {
+      cache_phase_fast(table_of(raw), smem, L, in_order, pair_stage, st, t, a);
+    } else {
+      if (a.mode == 2) prefill_phase(smem, L, in_order, pair_stage, st, t, a);
+      else if (fast_table(a.policy, a.C, a.P, a.n_shared)) cache_phase_fast(table_of(raw_load(st, a)), smem, L, in_order, pair_stage, st, t, a);
+      else cache_phase_general(smem, L, in_order, pair_stage, st, t, a);
+    }
   }
 }
 
-// Phases 1 to 3 for calls of two and more bf16 tokens: a workgroup of sixteen waves routes a tile of 16 tokens.  The
-// router logits of the tile are one small matrix product (experts x tokens) on the matrix cores: rows of W_r are the
-// A operand, the tokens the B operand of v_mfma_f32_16x16x32_bf16.  The waves split the contraction - a wave takes pairs
-// of adjacent k-blocks and multiplies them with NT expert tiles, so that every byte of x and of W_r reaches the
-// workgroup once and all loads of a wave are in flight together - and their partial tiles meet in LDS.  Then a
-// wave gates a token.  A call of at most 16 tokens is one workgroup, which goes straight on to the lookups; of a larger
-// call the workgroup that arrives last does (nobody waits).  What the others must see of a workgroup are its selected
-// experts only, written past the caches with device-scope stores, so the arrival needs no cache write-back: a
-// write-back in every wave, logits by half of the waves and the grouping through memory made this launch take 53.5 us at
-// 1024 tokens and 23 us at 64 (64 experts, d = 2048, kernel trace); now 31 and 21 us.
+// Calls of two and more bf16 tokens.  The router logits are a matrix product (experts x tokens) on the matrix cores: rows of W_r
+// are the A operand, the tokens the B operand of v_mfma_f32_16x16x32_bf16.  A workgroup of sixteen waves forms 16 experts x 16
+// tokens over one slice of the contraction (a unit): its waves take pairs of adjacent k-blocks, every load of a wave is in
+// flight at once, and their partial tiles meet in LDS.  Units publish their logits past the caches, and the one that arrives
+// last of its token tile gates (gate_and_group).
+// What bounds it is the chain of round trips - first touch after the launch, publication, arrival, gating, arrival, grouping -
+// and, with whole tiles of 64 experts in one workgroup, the 320 KB that one compute unit had to pull in: row-major
+// fragments are 16 pieces of 64 bytes each, and the address unit sets the pace.
 // PACKED: W_r comes from the library's copy in operand order (pack_router_kernel), for the calls of 2 to 4 tokens that may
-// read it: a wave-wide load is then one contiguous KiB instead of 16 pieces of 64 bytes (64 x 2048, 16 tokens: 11.5 against
-// 17.8 us per launch).
-// T = float: the router rows as dot products, one wave per (token, expert); for calls so small that one workgroup does it
-// sooner than several meet (kSmallRouterBytes).
-template <typename T, bool PACKED, int NT>
-__global__ void __launch_bounds__(kTileThreads) route_tile_kernel(RouteArgs r, LayerState st, CallTables t, CacheCallArgs a) {
+// read it.  PAIRS: pairs of k-blocks a wave requests at a time.
+template <int PAIRS, bool PACKED, RouteKind KIND>
+__global__ void __launch_bounds__(kTileThreads) route_units_kernel(RouteArgs r, RouteWork rw, LayerState st, CallTables t, CacheCallArgs a) {
   typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
   typedef float f32x4 __attribute__((ext_vector_type(4)));
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   extern __shared__ __align__(16) unsigned char smem[];     // partial tiles of the logits, then phase 3's scratch
-  __shared__ float zs_tile[kTileTokens][kTileMaxE + 4];     // (+ 4: the 16 tokens of a column fall on different banks)
   __shared__ TileLds tl;
-  float* pz = reinterpret_cast<float*>(smem);               // [8 waves][NT][256]
+  float* pz = reinterpret_cast<float*>(smem);               // [16 waves][256]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 15, q = lane >> 4;
-  const int E = a.E, K = a.K, KS = a.KS, d = r.d;
-  const int t0 = blockIdx.x * kTileTokens;
+  const int E = a.E, d = r.d;
+  const int n_et = (E + 15) >> 4, units = n_et * rw.slices, n_tiles = (a.B + kTileTokens - 1) / kTileTokens;
+  const int tile = blockIdx.x / units, u = blockIdx.x - tile * units;
+  const int sl = u / n_et, et = u - sl * n_et;
+  const int t0 = tile * kTileTokens;
   const int nkb = d >> 5;
-  const bool single = gridDim.x == 1;
-  const bool fast = a.mode == 0 && fast_table(a.policy, a.C, a.P, a.n_shared);
+  const int tok = t0 + n < a.B ? t0 + n : a.B - 1;          // clamped: in bounds, the column is dropped below
+  const u32x4* xrow = reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(r.x) + (size_t)tok * d) + q;
+  constexpr int w_step = PACKED ? 64 : 4;                   // (16-byte pieces between k-blocks)
+  const u32x4* wrow = PACKED ? static_cast<const u32x4*>(r.router_packed) + (size_t)et * nkb * 64 + lane
+                             : reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(r.router_w) + (size_t)min(et * 16 + n, E - 1) * d) + q;
+  const int per = ((nkb + rw.slices - 1) / rw.slices + 1) & ~1;
+  const int hi = min(nkb, (sl + 1) * per);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int kb0 = sl * per + 2 * wave; kb0 < hi; kb0 += 2 * PAIRS * kTileWaves) {
+    u32x4 xb[2 * PAIRS], wa[2 * PAIRS];
+#pragma unroll
+    for (int i = 0; i < 2 * PAIRS; ++i) {
+      const int kb = min(kb0 + (i >> 1) * 2 * kTileWaves + (i & 1), hi - 1);
+      xb[i] = xrow[(size_t)kb * 4];
+      wa[i] = wrow[(size_t)kb * w_step];
+    }
+#pragma unroll
+    for (int i = 0; i < 2 * PAIRS; ++i)
+      if (kb0 + (i >> 1) * 2 * kTileWaves + (i & 1) < hi)      // uniform
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wa[i]), __builtin_bit_cast(bf16x8, xb[i]), acc, 0, 0, 0);
+  }
   // nobody changes the table before the last workgroup of this launch does: every workgroup may fetch it now
   RawTable raw{};
-  if (fast && wave == 0) raw = raw_load(st, a);
-  for (int e = tid; e < E; e += kTileThreads) tl.map[e] = -1;
-  if (tid < kMaxKeys) tl.count[tid] = tl.first[tid] = 0;
-  if (tid < kWave) { tl.last[tid] = 0; tl.touched[tid] = 0; }
-  if (tid == 0) tl.any_miss = 0;
-
-  if constexpr (std::is_same<T, float>::value) {
-    const int n_vec = d / 4, n_items = min(kTileTokens, a.B - t0) * E;
-    constexpr int U = 4;                                    // products of a wave in flight together
-    for (int it0 = wave; it0 < n_items; it0 += U * kTileWaves) {
-      float acc[U], bias[U];
-      const float4 *xv[U], *wv[U];
+  if (KIND != kOther && wave == 0) raw = raw_load(st, a);
+  // element el = tid % 256 of expert tile tid / 256 + 4 j: the MFMA leaves rows 4 (ln / 16) + el % 4, token ln % 16 with ln = el / 4
+  const int el = tid & 255, el_tok = (el >> 2) & 15, el_row = (el >> 6) * 4 + (el & 3);
+  constexpr int NJ = KIND != kOther ? 1 : kTileMaxE / 16 / (kTileThreads / 256);
+  float bias[NJ];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int it = min(it0 + u * kTileWaves, n_items - 1);       // clamped: in bounds, formed again
-        const int b = it / E, e = it - b * E;
-        xv[u] = reinterpret_cast<const float4*>(static_cast<const float*>(r.x) + (size_t)(t0 + b) * d);
-        wv[u] = reinterpret_cast<const float4*>(static_cast<const float*>(r.router_w) + (size_t)e * d);
-        bias[u] = r.bias ? r.bias[(size_t)(t0 + b) * E + e] : 0.f;
-        acc[u] = 0.f;
-      }
-      for (int c = lane; c < n_vec; c += kWave) {
-        float4 xc[U], wc[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) { xc[u] = xv[u][c]; wc[u] = wv[u][c]; }
-#pragma unroll
-        for (int u = 0; u < U; ++u) acc[u] = Vec<float>::dot(wc[u], xc[u], acc[u]);
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int it = min(it0 + u * kTileWaves, n_items - 1);
-        const float sum = wave_sum(acc[u]);
-        if (lane == 0) zs_tile[it / E][it % E] = sum + bias[u];
-      }
-    }
-    __syncthreads();
-  } else {
-  const int tok = t0 + n < a.B ? t0 + n : a.B - 1;          // clamped: in bounds, the column is dropped below
-  const uint16_t* xrow = static_cast<const uint16_t*>(r.x) + (size_t)tok * d + q * 8;
-  for (int eg = 0; eg < E; eg += 16 * NT) {
-    float bias[(NT * 256 + kTileThreads - 1) / kTileThreads];
-#pragma unroll
-    for (int i = 0; i < (NT * 256 + kTileThreads - 1) / kTileThreads; ++i) {
-      const int el = tid + i * kTileThreads, ln = (el & 255) >> 2;
-      const int e = eg + (el >> 8) * 16 + (ln >> 4) * 4 + (el & 3), tb = t0 + (ln & 15);
-      bias[i] = (r.bias && el < NT * 256 && e < E && tb < a.B) ? r.bias[(size_t)tb * E + e] : 0.f;
-    }
-    const u32x4* wt[NT];                                    // this lane's piece of k-block 0 of every tile
-    constexpr int w_step = PACKED ? 64 : 4;
-#pragma unroll
-    for (int i = 0; i < NT; ++i) {
-      if constexpr (PACKED) {
-        const int tile = min((eg >> 4) + i, (E - 1) >> 4);
-        wt[i] = static_cast<const u32x4*>(r.router_packed) + (size_t)tile * nkb * 64 + lane;
-      } else {
-        const int er = min(eg + i * 16 + n, E - 1);
-        wt[i] = reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(r.router_w) + (size_t)er * d + q * 8);
-      }
-    }
-    f32x4 acc[NT];
-#pragma unroll
-    for (int i = 0; i < NT; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    constexpr int U = NT == 1 ? 8 : 4;                      // k-blocks in flight (two adjacent ones at a time)
-    for (int kb0 = 2 * wave; kb0 < nkb; kb0 += U * kTileWaves) {
-      u32x4 xb[U], wa[U][NT];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int kb = min(kb0 + (u >> 1) * 2 * kTileWaves + (u & 1), nkb - 1);
-        xb[u] = *reinterpret_cast<const u32x4*>(xrow + (size_t)kb * 32);
-#pragma unroll
-        for (int i = 0; i < NT; ++i) wa[u][i] = wt[i][(size_t)kb * w_step];
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (kb0 + (u >> 1) * 2 * kTileWaves + (u & 1) < nkb) {      // uniform
-#pragma unroll
-          for (int i = 0; i < NT; ++i)
-            acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wa[u][i]),
-                                                             __builtin_bit_cast(bf16x8, xb[u]), acc[i], 0, 0, 0);
-        }
-    }
-    // the upper eight waves hand their partial tiles to the lower eight, whose sums are then added up per element
-    if (wave >= kTileWaves / 2) {
-#pragma unroll
-      for (int i = 0; i < NT; ++i)
-        *reinterpret_cast<f32x4*>(pz + ((wave - kTileWaves / 2) * NT + i) * 256 + lane * 4) = acc[i];
-    }
-    __syncthreads();
-    if (wave < kTileWaves / 2) {
-#pragma unroll
-      for (int i = 0; i < NT; ++i) {
-        f32x4* slot = reinterpret_cast<f32x4*>(pz + (wave * NT + i) * 256 + lane * 4);
-        *slot = acc[i] + *slot;
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < (NT * 256 + kTileThreads - 1) / kTileThreads; ++i) {
-      const int el = tid + i * kTileThreads;
-      if (el < NT * 256) {
-        float v = 0.f;
-#pragma unroll
-        for (int w = 0; w < kTileWaves / 2; ++w) v += pz[w * NT * 256 + el];
-        const int ln = (el & 255) >> 2;                     // the MFMA left rows 4 (ln / 16) + el % 4, token ln % 16
-        const int e = eg + (el >> 8) * 16 + (ln >> 4) * 4 + (el & 3);
-        if (e < E) zs_tile[ln & 15][e] = v + bias[i];
-      }
-    }
-    __syncthreads();
+  for (int j = 0; j < NJ; ++j) {
+    const int e = ((tid >> 8) + j * (kTileThreads / 256)) * 16 + el_row;
+    bias[j] = (r.bias && e < E && t0 + el_tok < a.B) ? r.bias[(size_t)(t0 + el_tok) * E + e] : 0.f;
   }
-  }
-  if (fast && wave == 0 && lane < a.C && raw.exp >= 0) tl.map[raw.exp] = raw.buf << 8 | lane;
-
-  const LdsLayout L = lds_layout(E, a.C, a.P, a.n_shared, a.B, K, KS);
-  const bool stage = stage_in_lds(a.B, KS);
-  int32_t* idx_stage = stage ? reinterpret_cast<int32_t*>(smem + L.idx_stage) : nullptr;
-  int32_t* pair_stage = stage ? reinterpret_cast<int32_t*>(smem + L.pair_stage) : t.pair_buf;
-  if (t0 + wave < a.B) {
-    int32_t* lds_idx = single ? idx_stage : nullptr;
-    if (E <= 64) gate_token<1, true, true>(zs_tile[wave], t0 + wave, E, K, KS, r.norm_topk, t.idx, t.wpair, r.user_idx, r.user_w, lds_idx);
-    else gate_token<kTileMaxE / 64, true, true>(zs_tile[wave], t0 + wave, E, K, KS, r.norm_topk, t.idx, t.wpair, r.user_idx,
-                                                r.user_w, lds_idx);
-  }
-  if (!single) {
-    // the selected experts went past the caches; once every wave's stores have arrived the workgroup is announced
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (tid == 0)
-      tl.last_arrived = __hip_atomic_fetch_add(r.arrive, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
-    __syncthreads();
-    if (!tl.last_arrived) return;
-    if (tid == 0) __hip_atomic_store(r.arrive, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch on this stream
-  } else {
-    __syncthreads();
-  }
-  // (a single workgroup's lookups always fit the LDS copy: 16 tokens of at most 128 pairs)
-  const auto published = [&](int l) { return __hip_atomic_load(&t.idx[l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-  const int32_t* in_order = stage ? idx_stage : t.idx;
-  if (fast) {
-    if (single) group_hits<1>(smem, L, tl, raw, [&](int l) { return idx_stage[l]; }, nullptr, in_order, pair_stage, st, t, a);
-    else if (a.B * K <= kTileThreads) group_hits<1>(smem, L, tl, raw, published, idx_stage, in_order, pair_stage, st, t, a);
-    else group_hits<8>(smem, L, tl, raw, published, idx_stage, in_order, pair_stage, st, t, a);
-    return;
-  }
-  if (!single && stage)
-    for (int i = tid; i < a.B * K; i += kTileThreads) idx_stage[i] = published(i);
+  clear_tile_lds(tl, E);
+  *reinterpret_cast<f32x4*>(pz + wave * 256 + lane * 4) = acc;
   __syncthreads();
-  if (wave != 0) return;
-  if (!stage) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  if (a.mode == 2) prefill_phase(smem, L, in_order, pair_stage, st, t, a);
-  else cache_phase_general(smem, L, in_order, pair_stage, st, t, a);
+  float z = 0.f;
+  if (tid < 256) {
+#pragma unroll
+    for (int w = 0; w < kTileWaves; ++w) z += pz[w * 256 + tid];
+  }
+  if (units == 1) {
+    if (tid < 256 && el_row < E) tl.zs[el_tok][el_row] = z + bias[0];
+  } else {
+    if (tid < 256) __hip_atomic_store(rw.logits + (size_t)blockIdx.x * 256 + tid, z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!arrive_last(r.arrive + 1 + tile, units, tl.last_arrived)) return;
+    const float* zp = rw.logits + (size_t)tile * units * 256 + el;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int t16 = (tid >> 8) + j * (kTileThreads / 256), e = t16 * 16 + el_row;
+      if (t16 < n_et) {
+        float v = 0.f;
+        for (int s = 0; s < rw.slices; ++s) v += __builtin_bit_cast(float, load_published(zp + (size_t)(s * n_et + t16) * 256));
+        if (e < E) tl.zs[el_tok][e] = v + bias[j];
+      }
+    }
+  }
+  __syncthreads();
+  gate_and_group<KIND>(smem, tl, raw, tile, n_tiles, r, rw.masks, st, t, a);
+}
+
+// A small fp32 call (kSmallRouterBytes): one workgroup forms the router rows as dot products, one wave per (token, expert),
+// sooner than several meet.
+template <RouteKind KIND>
+__global__ void __launch_bounds__(kTileThreads) route_small_fp32_kernel(RouteArgs r, LayerState st, CallTables t, CacheCallArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ TileLds tl;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int E = a.E, d = r.d;
+  RawTable raw{};
+  if (KIND != kOther && wave == 0) raw = raw_load(st, a);
+  clear_tile_lds(tl, E);
+  const int n_vec = d / 4, n_items = a.B * E;
+  constexpr int U = 4;                                    // products of a wave in flight together
+  for (int it0 = wave; it0 < n_items; it0 += U * kTileWaves) {
+    float acc[U], bias[U];
+    const float4 *xv[U], *wv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int it = min(it0 + u * kTileWaves, n_items - 1);       // clamped: in bounds, formed again
+      const int b = it / E, e = it - b * E;
+      xv[u] = reinterpret_cast<const float4*>(static_cast<const float*>(r.x) + (size_t)b * d);
+      wv[u] = reinterpret_cast<const float4*>(static_cast<const float*>(r.router_w) + (size_t)e * d);
+      bias[u] = r.bias ? r.bias[(size_t)b * E + e] : 0.f;
+      acc[u] = 0.f;
+    }
+    for (int c = lane; c < n_vec; c += kWave) {
+      float4 xc[U], wc[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) { xc[u] = xv[u][c]; wc[u] = wv[u][c]; }
+#pragma unroll
+      for (int u = 0; u < U; ++u) acc[u] = Vec<float>::dot(wc[u], xc[u], acc[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int it = min(it0 + u * kTileWaves, n_items - 1);
+      const float sum = wave_sum(acc[u]);
+      if (lane == 0) tl.zs[it / E][it % E] = sum + bias[u];
+    }
+  }
+  __syncthreads();
+  gate_and_group<KIND>(smem, tl, raw, 0, 1, r, nullptr, st, t, a);
 }
 
 __global__ void __launch_bounds__(64) pin_kernel(LayerState st, CallTables t, CacheCallArgs a) {
@@ -1184,45 +1311,67 @@ __global__ void reset_kernel(LayerState st, int E, int C, int P, int clear_trace
 
 }  // namespace
 
+// Slices pay although they make units meet where one would do: 16 experts of 4096 columns, 8 / 64 tokens, one slice 12.7 / 15.3 us per
+// launch, four 9.0 / 11.0; of 2048 columns, 16 tokens, 10.9 / 9.2 with two.
+RouteUnits route_units(int B, int E, int d) {
+  RouteUnits u{};
+  u.tiles = (B + kTileTokens - 1) / kTileTokens;
+  const int n_et = (E + 15) / 16, nkb = d / 32;
+  u.slices = 1;
+  while (u.slices < 4 && nkb / (2 * u.slices) >= kRouteSliceKb && u.tiles * n_et * u.slices * 2 <= kRouteMaxUnits) u.slices *= 2;
+  const size_t units = (size_t)u.tiles * n_et * u.slices;
+  u.n_arrive = 1 + u.tiles;
+  u.logit_bytes = units * 256 * sizeof(float);
+  u.scratch_bytes = u.logit_bytes + (size_t)u.tiles * kTileTokens * sizeof(uint64_t);
+  return u;
+}
+
+size_t route_scratch_bytes(int max_batch, int E, int d) {
+  const RouteUnits u = route_units(max_batch, E, d);     // (a smaller call may be sliced further)
+  return std::max(u.scratch_bytes, (size_t)kRouteMaxUnits * 256 * sizeof(float) + (size_t)u.tiles * kTileTokens * sizeof(uint64_t));
+}
+
 size_t route_cache_lds_bytes(int E, int C, int P, int n_shared, int B, int K, int KS) {
   return lds_layout(E, C, P, n_shared, B, K, KS).total;
 }
 
 hipError_t launch_route_cache(hipStream_t s, int dtype, const RouteArgs& r, const LayerState& st, const CallTables& t,
-                              const CacheCallArgs& a, KernelEvents ev) {
+                              const CacheCallArgs& a, const RouteScratch& scratch, KernelEvents ev) {
   // Few tokens: 16 waves per token so that the router rows stream with many loads
   // in flight.  Many tokens: the grid supplies the parallelism.
   int waves = a.B <= 16 ? 16 : 4;
   if (waves > a.E) waves = a.E;
   dim3 grid(a.B), block(64 * waves);
   const size_t lds = route_cache_lds_bytes(a.E, a.C, a.P, a.n_shared, a.B, a.K, a.KS);
-  // Tiles of 16 tokens: from two tokens on with the packed router matrix (calls of up to four tokens have one).  Reading it
-  // row-major the tile kernel needs 6 us more on 64 x 2048 (a layer call of 16 tokens 82.5 against 79.1 us, of 24 86.3
-  // against 86.5, of 48 89.5 against 92.2, of 64 90.6 against 111.4); with few experts a workgroup per token keeps up for
-  // longer (16 x 4096, 64 tokens: 96.0 against 93.7 us), and so it does where the tile's logits take several passes (200
-  // experts of 1024 columns, launch of 33 tokens 104 against 79 us, of 64 155 against 125) or one wave looks up in order
-  // whatever routes (64 experts under discounted counts, layer call of 64 tokens 149 against 144 us).
-  const bool in_order = a.mode == 0 && !fast_table(a.policy, a.C, a.P, a.n_shared);
-  const int tile_min = r.router_packed ? 2 : a.E > 32 && a.E <= 64 && !in_order ? 32 : 112;
-  if (dtype == MOE_DTYPE_BF16 && a.B >= tile_min && a.E <= kTileMaxE && r.d % 32 == 0) {
-    const int nt = a.E <= 16 ? 1 : a.E <= 32 ? 2 : 4;
-    const size_t bytes = std::max(lds, (size_t)(kTileWaves / 2) * nt * 256 * sizeof(float));
-    const dim3 tiles((a.B + kTileTokens - 1) / kTileTokens), threads(kTileThreads);
-    const auto launch = [&](auto kernel) { launch_timed(kernel, tiles, threads, bytes, s, ev, r, st, t, a); };
-    if (r.router_packed) {
-      if (nt == 1) launch(route_tile_kernel<uint16_t, true, 1>);
-      else if (nt == 2) launch(route_tile_kernel<uint16_t, true, 2>);
-      else launch(route_tile_kernel<uint16_t, true, 4>);
-    } else {
-      if (nt == 1) launch(route_tile_kernel<uint16_t, false, 1>);
-      else if (nt == 2) launch(route_tile_kernel<uint16_t, false, 2>);
-      else launch(route_tile_kernel<uint16_t, false, 4>);
+  const RouteKind kind = a.mode != 0 || a.E > kWave || !fast_table(a.policy, a.C, a.P, a.n_shared) ? kOther : a.full ? kFull : kTable;
+  // Units where every lookup is known to hit (392 points of 8-256 experts, 1024-4096 columns, 2-1024 tokens: none slower than the
+  // kernels before, 1.50x in the mean; 64 x 2048, 16 / 64 / 1024 tokens 10.8 / 12.6 / 19.4 against 13.2 / 21.1 / 28.9 us in layer
+  // calls) and on the register table (16 tokens on 64 experts, half of them resident, 144 against 153 us) from 17 experts on: with
+  // fewer, and a wave that looks up in order, a workgroup per token keeps up to 112 tokens (16 tokens, 8 experts, misses 21.7
+  // against 22.7 us).  Where one wave looks up in order whatever routes, from 112 tokens too (64 tokens on 16 experts under
+  // discounted counts 115.8 against 121.1 us), prompts on more than 32 experts from 32.
+  const int least = kind == kFull ? 2 : kind == kTable ? (a.E > 16 ? 2 : 112) : a.mode == 2 && a.E > 32 ? 32 : 112;
+  if (dtype == MOE_DTYPE_BF16 && a.B >= least && a.E <= kTileMaxE && r.d % 32 == 0) {
+    const RouteUnits ru = route_units(a.B, a.E, r.d);
+    if (ru.n_arrive <= scratch.n_arrive && ru.scratch_bytes <= scratch.bytes) {
+      const RouteWork w{ru.slices, static_cast<float*>(scratch.ptr),
+                        reinterpret_cast<uint64_t*>(static_cast<char*>(scratch.ptr) + ru.logit_bytes)};
+      const size_t bytes = std::max({kind == kFull ? 0 : lds, (size_t)kTileWaves * 256 * sizeof(float), stage_pairs(a.B, a.KS) ? (size_t)(a.B * a.KS + 3) / 4 * 32 : 0});
+      const dim3 units(ru.tiles * ((a.E + 15) / 16) * ru.slices), threads(kTileThreads);
+      const auto launch = [&](auto kernel) { launch_timed(kernel, units, threads, bytes, s, ev, r, w, st, t, a); };
+      // pairs of k-blocks a wave has of its unit's slice
+      const bool two = (r.d / 32 + ru.slices * 2 * kTileWaves - 1) / (ru.slices * 2 * kTileWaves) > 1;
+      if (kind == kFull && r.router_packed) launch(two ? route_units_kernel<2, true, kFull> : route_units_kernel<1, true, kFull>);
+      else if (kind == kFull) launch(two ? route_units_kernel<2, false, kFull> : route_units_kernel<1, false, kFull>);
+      else if (kind == kTable) launch(two ? route_units_kernel<2, false, kTable> : route_units_kernel<1, false, kTable>);
+      else launch(two ? route_units_kernel<2, false, kOther> : route_units_kernel<1, false, kOther>);
+      return hipGetLastError();
     }
-    return hipGetLastError();
   }
   if (dtype == MOE_DTYPE_FP32 && a.B >= 2 && a.B <= 8 && a.B * a.E <= kSmallRouterItems &&
       (size_t)a.B * a.E * r.d * sizeof(float) <= kSmallRouterBytes) {
-    launch_timed(route_tile_kernel<float, false, 1>, dim3(1), dim3(kTileThreads), lds, s, ev, r, st, t, a);
+    const auto small = kind == kFull ? route_small_fp32_kernel<kFull> : kind == kTable ? route_small_fp32_kernel<kTable> : route_small_fp32_kernel<kOther>;
+    launch_timed(small, dim3(1), dim3(kTileThreads), kind == kFull ? 0 : lds, s, ev, r, st, t, a);
     return hipGetLastError();
   }
   const auto launch = [&](auto type) {
