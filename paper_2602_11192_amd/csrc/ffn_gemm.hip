@@ -229,6 +229,109 @@ __global__ void __launch_bounds__(64 * WAVES, MINW) ffn_gemm_kernel(FfnArgs a) {
   }
 }
 
+// Calls of up to 16 tokens: a group has one column block, so nothing is staged and nobody waits for anyone.  Every wave streams
+// its own RT row tiles and takes the token fragment of a k-block straight from memory (a few rows that stay in the first cache
+// level), all of it R - 1 k-blocks ahead.  Waves of their own can also walk apart: the row tiles of a workgroup lie a multiple
+// of d x 64 bytes apart, and waves in lockstep meet in the same memory channels (a bare stream of runs of 128 KiB reads 5.7 TB/s with
+// four waves in step, 6.7 with each two k-blocks = 4 KiB ahead of the last; 256 KiB 6.2 and 6.6).
+// What bounds it: HBM, and with one round of workgroups the units that hold one more than the others.  4 Phi-3.5-MoE-like tokens:
+// gate/up 81.5 -> 77 us, down 51 -> 42 (6.6 TB/s), 16 OLMoE-like gate/up 76 -> 72 us; 176 points (11 shapes, 4 to 16 tokens) 1.05x in
+// the mean against the staged kernel, the slowest .974.  With more than one column block its L1 traffic overtakes the
+// staging: 64 tokens on 24 experts of 2560 x 2048 135 -> 162 us.
+constexpr int kFewTokens = 16;
+constexpr int kFewApart = 2;      // k-blocks between neighbouring waves
+template <int NMAT, int RT, int R, int MINW>
+__global__ void __launch_bounds__(256, MINW) ffn_few_kernel(FfnArgs a) {
+  constexpr int WAVES = 4;
+  const int n_rb = ((NMAT == 2 ? a.f : a.d) / 16 + RT * WAVES - 1) / (RT * WAVES);
+  const int item_id = blockIdx.x / n_rb, rb = blockIdx.x % n_rb;
+  const int n_items = a.t.work[0].x;
+  const int4 item = a.t.work[1 + min(item_id, a.work.cap - 1)];
+  if (item_id >= n_items) return;
+  const int begin = item.z, n_tok = item.w & 0x3fffffff, miss = (item.w >> 30) & 1;
+  if (a.pass != 2 && miss != a.pass) return;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = lane & 15, q = lane >> 4;
+  const int nkb = (NMAT == 2 ? a.d : a.f) >> 5, n_rt = (NMAT == 2 ? a.f : a.d) >> 4;
+  const int rt0 = (rb * WAVES + wave) * RT;
+  if (rt0 >= n_rt) return;
+  const char* wsrc = (a.fetch != 0 && miss != 0) ? a.pool + (size_t)item.y * a.expert_bytes : group_weights(a, item.y);
+  const char* wp[RT];
+#pragma unroll
+  for (int i = 0; i < RT; ++i) {
+    const int rt = min(rt0 + i, n_rt - 1);        // clamped: loads stay in bounds, results are dropped
+    wp[i] = NMAT == 2 ? wsrc + (size_t)rt * nkb * 2048 : wsrc + (size_t)4 * a.f * a.d + (size_t)rt * 1024;
+  }
+  const size_t kb_bytes = NMAT == 2 ? 2048 : (size_t)(a.d >> 4) * 1024;
+  int next = NMAT == 2 ? kFewApart * wave % nkb : 0;       // k-block of the next request
+  const int pos = begin + min(n, n_tok - 1);      // columns beyond the group repeat its last token and are dropped
+  const uint16_t* src = NMAT == 2 ? reinterpret_cast<const uint16_t*>(a.x) + (size_t)(a.t.sorted_pair[pos] / a.KS) * a.d + q * 8
+                                  : reinterpret_cast<const uint16_t*>(a.h) + (size_t)pos * a.f + q * 8;
+  u32x4 wr[R][RT][NMAT], xr[R];
+  auto req = [&](int slot) {
+    xr[slot] = *reinterpret_cast<const u32x4*>(src + (size_t)next * 32);
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int m = 0; m < NMAT; ++m)
+        wr[slot][i][m] = __builtin_nontemporal_load(
+            reinterpret_cast<const u32x4*>(wp[i] + (size_t)next * kb_bytes + (uint32_t)(lane * 16 + m * 1024)));
+    next = next + 1 == nkb ? 0 : next + 1;
+  };
+  f32x4 acc[RT][NMAT];
+#pragma unroll
+  for (int i = 0; i < RT; ++i)
+#pragma unroll
+    for (int m = 0; m < NMAT; ++m) acc[i][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto multiply = [&](int u) {
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int m = 0; m < NMAT; ++m)
+        acc[i][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wr[u][i][m]), __builtin_bit_cast(bf16x8, xr[u]),
+                                                            acc[i][m], 0, 0, 0);
+  };
+#pragma unroll
+  for (int u = 0; u < R - 1; ++u) req(u);         // (of a contraction that is shorter some k-blocks once more, not used)
+  int s0 = 0;
+#pragma unroll 1
+  for (; s0 + 2 * R - 1 <= nkb; s0 += R) {
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+      req((u + R - 1) % R);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(u);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < 2 * R - 2; ++u) {
+    if (s0 + u < nkb) {
+      if (s0 + u + R - 1 < nkb) req((u + R - 1) % R);
+      multiply(u % R);
+    }
+  }
+  if (n >= n_tok) return;
+  const size_t row = (size_t)(begin + n);
+#pragma unroll
+  for (int i = 0; i < RT; ++i) {
+    const int rt = rt0 + i;
+    if (rt >= n_rt) break;
+    if (NMAT == 2) {
+      uint16_t hv[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) hv[k] = f32_to_bf16(silu(acc[i][0][k]) * acc[i][NMAT - 1][k]);
+      uint2 pk;
+      pk.x = (uint32_t)hv[0] | ((uint32_t)hv[1] << 16);
+      pk.y = (uint32_t)hv[2] | ((uint32_t)hv[3] << 16);
+      *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.h) + row * a.f + rt * 16 + q * 4) = pk;
+    } else {
+      *reinterpret_cast<f32x4*>(a.o + row * a.d + rt * 16 + q * 4) = acc[i][0];
+    }
+  }
+}
+
 constexpr int kSmallTile = 6, kMidTile = 7, kLargeTile = 8;     // log2 of the tokens per tile
 constexpr int kUnits = 256;                                     // compute units
 
@@ -271,7 +374,14 @@ hipError_t launch_ffn_gemm(hipStream_t s, const FfnArgs& args, KernelEvents e1, 
   const int64_t load = (int64_t)a.max_count * a.KS;     // (token, expert) pairs of the call, all groups together
   const int items = a.g_max + (int)(load >> a.work.shift);
   const auto blocks = [&](int rows, int tiles_per_wg) { return dim3((items + 7) / 8 * 8 * ((rows / 16 + tiles_per_wg - 1) / tiles_per_wg)); };
-  if (a.work.shift == kSmallTile) {
+  if (a.work.shift == kSmallTile && a.max_count <= kFewTokens) {
+    // (a group is one item of the list.)  One row tile of W_d per wave where two leave units idle: 8 to 16 tokens on 8 + 1 experts of
+    // 2048 x 8192, 144 workgroups of eight tiles, 53 / 39 us; on 16 of 1536 x 4096, 192 of them, 26.5 / 31, on 8 of 3072 x 3072 23.5 / 25.5.
+    const auto grid = [&](int rows, int tiles_per_wg) { return dim3(a.g_max * ((rows / 16 + tiles_per_wg - 1) / tiles_per_wg)); };
+    launch_timed(ffn_few_kernel<2, 1, 8, 3>, grid(a.f, 4), dim3(256), 0, s, e1, a);
+    if ((int64_t)a.g_max * ((a.d + 127) / 128) < 160) launch_timed(ffn_few_kernel<1, 1, 8, 5>, grid(a.d, 4), dim3(256), 0, s, e2, a);
+    else launch_timed(ffn_few_kernel<1, 2, 8, 3>, grid(a.d, 8), dim3(256), 0, s, e2, a);
+  } else if (a.work.shift == kSmallTile) {
     // Row blocks of a tile on one die pay where many experts see few tokens each (OLMoE-like, 16 / 64 / 192 tokens: 126 / 139
     // / 158 against 130 / 145 / 163 us); with fewer than four items per die, or busier experts, they leave dies unevenly
     // loaded (Mixtral-like, 12 / 128 tokens: 388 / 525 against 350 / 472 us; OLMoE-like, 256 tokens: 175 against 172).
