@@ -2,6 +2,7 @@
 // expert blocks kept in the plain row-major layout W_g | W_u | W_d, fp32 or
 // bf16.  This is the layout-agnostic path (one wavefront per output row, four tokens at a time, DPP
 // reduction over the contraction); the bf16 production path is ffn_tiled.hip.
+#include <algorithm>
 #include <type_traits>
 
 #include "device_utils.hpp"
@@ -148,6 +149,124 @@ __global__ void __launch_bounds__(64 * kRowsPerBlock) down_rowmajor(FfnArgs a) {
   });
 }
 
+// Small experts, all of them resident: one workgroup takes a token through its KS experts - both projections of every pair, W_d,
+// the weighted sum - with what lies between in LDS.  What bounds such a call is its launches and the memory round trips of
+// each, not bytes.  A row of d or f elements belongs to 16, 32 or 64 lanes, as many as it has 16-byte pieces, and a group of lanes has four rows in
+// flight: at d = 64 a wave holds four rows at a time where the kernels above keep three quarters of it idle.
+constexpr int kTokenThreads = 1024, kTokenRows = 4;
+constexpr size_t kTokenLds = 60 << 10;
+constexpr int64_t kTokenAlways = 200 << 10, kTokenMost = 1 << 20, kTokenBase = 100 << 10, kTokenPerPair = 32 << 10;
+inline size_t token_lds(int KS, int d, int f) { return ((size_t)d + (size_t)KS * (f + d) + 2 * KS) * 4; }
+
+// the sum over each group of 16, 32 or 64 lanes
+__device__ __forceinline__ float lanes_sum(float v, int lanes) {
+  v += dpp_mov<0xB1>(v);
+  v += dpp_mov<0x4E>(v);
+  v += dpp_mov<0x141>(v);
+  v += dpp_mov<0x140>(v);
+  if (lanes > 16) v += __shfl_xor(v, 16);
+  if (lanes > 32) v += __shfl_xor(v, 32);
+  return v;
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kTokenThreads) ffn_token_rowmajor(FfnArgs a, T* __restrict__ y, int lanes_d, int lanes_f) {
+  constexpr int V = kVec<T>;
+  extern __shared__ __align__(16) float token_mem[];
+  const int KS = a.KS, d = a.d, f = a.f, b = blockIdx.x;
+  float* xs = token_mem;                          // [d]; d, f: multiples of V
+  float* h = xs + d;                              // [KS][f]
+  float* o = h + KS * f;                          // [KS][d]
+  float* ws = o + KS * d;                         // [KS] gate weights
+  int* ids = reinterpret_cast<int*>(ws + KS);     // [KS] expert buffers
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if ((int)threadIdx.x < KS) ws[threadIdx.x] = a.t.wpair[(size_t)b * KS + threadIdx.x];
+  for (int i = threadIdx.x * V; i < d; i += kTokenThreads * V) {
+    float v[V];
+    load_vec(reinterpret_cast<const T*>(a.x) + (size_t)b * d + i, v);
+#pragma unroll
+    for (int e = 0; e < V; ++e) xs[i + e] = v[e];
+  }
+  const int ng = *a.t.n_groups;
+  for (int j = wave; j < KS; j += kTokenThreads / 64) {       // the group that holds the pair
+    const int pos = a.t.pos_of[(size_t)b * KS + j];
+    for (int g = lane; g < a.g_max; g += 64) {                // (g_max descriptors exist: requested beside the count)
+      const GroupDesc gd = a.t.grp[g];
+      if (g < ng && pos >= gd.begin && pos < gd.begin + gd.count) ids[j] = gd.buf;
+    }
+  }
+  __syncthreads();
+  // rows: per group of lanes, four at a time; pair and row of a flat index
+  const auto each = [&](int lanes, int per_pair, auto&& rows4) {
+    const int n = KS * per_pair, groups = kTokenThreads / lanes, grp = threadIdx.x / lanes, at = threadIdx.x % lanes;
+    for (int r0 = grp; r0 < n; r0 += kTokenRows * groups) {
+      int r[kTokenRows], j[kTokenRows];
+#pragma unroll
+      for (int u = 0; u < kTokenRows; ++u) {
+        r[u] = min(r0 + u * groups, n - 1);       // clamped: formed again by its owner, with the same result
+        j[u] = r[u] / per_pair;
+      }
+      rows4(r, j, at);
+    }
+  };
+  each(lanes_d, f, [&](const int (&r)[kTokenRows], const int (&j)[kTokenRows], int at) {
+    const T* w[kTokenRows];
+    float sg[kTokenRows], su[kTokenRows];
+#pragma unroll
+    for (int u = 0; u < kTokenRows; ++u) {
+      w[u] = reinterpret_cast<const T*>(group_weights(a, ids[j[u]])) + (size_t)(r[u] - j[u] * f) * d;
+      sg[u] = su[u] = 0.f;
+    }
+    for (int i = at * V; i < d; i += lanes_d * V) {
+      float vg[kTokenRows][V], vu[kTokenRows][V];
+#pragma unroll
+      for (int u = 0; u < kTokenRows; ++u) {
+        load_vec(w[u] + i, vg[u]);
+        load_vec(w[u] + (size_t)f * d + i, vu[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < kTokenRows; ++u)
+#pragma unroll
+        for (int e = 0; e < V; ++e) { sg[u] = fmaf(vg[u][e], xs[i + e], sg[u]); su[u] = fmaf(vu[u][e], xs[i + e], su[u]); }
+    }
+#pragma unroll
+    for (int u = 0; u < kTokenRows; ++u) {
+      const float vg = lanes_sum(sg[u], lanes_d), vu = lanes_sum(su[u], lanes_d);
+      if (at == 0) h[r[u]] = silu(vg) * vu;
+    }
+  });
+  __syncthreads();
+  each(lanes_f, d, [&](const int (&r)[kTokenRows], const int (&j)[kTokenRows], int at) {
+    const T* w[kTokenRows];
+    float s[kTokenRows];
+#pragma unroll
+    for (int u = 0; u < kTokenRows; ++u) {
+      w[u] = reinterpret_cast<const T*>(group_weights(a, ids[j[u]])) + (size_t)2 * f * d + (size_t)(r[u] - j[u] * d) * f;
+      s[u] = 0.f;
+    }
+    for (int i = at * V; i < f; i += lanes_f * V) {
+      float v[kTokenRows][V];
+#pragma unroll
+      for (int u = 0; u < kTokenRows; ++u) load_vec(w[u] + i, v[u]);
+#pragma unroll
+      for (int u = 0; u < kTokenRows; ++u)
+#pragma unroll
+        for (int e = 0; e < V; ++e) s[u] = fmaf(v[u][e], h[j[u] * f + i + e], s[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < kTokenRows; ++u) {
+      const float v = lanes_sum(s[u], lanes_f);
+      if (at == 0) o[r[u]] = v;
+    }
+  });
+  __syncthreads();
+  for (int i = threadIdx.x; i < d; i += kTokenThreads) {
+    float acc = 0.f;
+    for (int j = 0; j < KS; ++j) acc = fmaf(ws[j], o[j * d + i], acc);
+    Elem<T>::store(y + (size_t)b * d + i, acc);
+  }
+}
+
 // y[b][i] = sum_j wpair[b][j] * o[pos_of[b][j]][i], j over the K selected then the shared experts.
 // A thread owns four consecutive columns (16-byte loads); the rows of a batch of pairs are all requested before
 // the first is used; the pairs are added in index order, so the result does not depend on the batch size.
@@ -200,6 +319,30 @@ hipError_t launch_ffn_rowmajor(hipStream_t s, int dtype, const FfnArgs& a, Kerne
   };
   if (dtype == MOE_DTYPE_FP32) run(float{}, 4);
   else run(uint16_t{}, 8);
+  return hipGetLastError();
+}
+
+// A compute unit pulls its token's weights in at ~30 us per MB, however few the tokens; the kernels per expert pay ~1.2 us for each
+// token of a group on top of their three launches.  So: up to 200 KB per token always, then as long as the experts see pairs enough.
+// us per call, per expert / per token, fp32: 64 x 128, 2 of 8 experts (192 KB) 1 token 15.2 / 12.9, 4 15.8 / 15.5, 16 20.7 / 17.8, 64
+// 35.8 / 19.4, 256 99 / 28.3; 128 x 128, 2 of 8 (384 KB) 16 tokens (4 per expert) 20.7 / 24.0, 64 35.6 / 25.7; 128 x 256, 2 of 8 (768 KB)
+// 64 tokens (16 per expert) 36.5 / 37.9, 256 102 / 47; 64 x 128, 8 of 16 (768 KB) 16 tokens (8) 24.2 / 33.9, 64 (32) 53 / 40.
+bool ffn_token_supported(int pool_layout, int dtype, int batch, int KS, int groups, int d, int f) {
+  if (pool_layout != MOE_LAYOUT_ROWMAJOR) return false;
+  const int elem = dtype == MOE_DTYPE_FP32 ? 4 : 2;
+  if (f % (16 / elem) != 0 || KS > kTokenThreads || token_lds(KS, d, f) > kTokenLds) return false;
+  const int64_t bytes = (int64_t)KS * 3 * d * f * elem, rounds = ((int64_t)batch + 255) / 256;       // a workgroup per compute unit
+  const int64_t pairs = (int64_t)batch * KS / groups;                                               // of an expert, in the mean
+  return bytes <= kTokenMost && bytes * rounds <= std::max(kTokenAlways, kTokenBase + kTokenPerPair * pairs);
+}
+
+hipError_t launch_ffn_token(hipStream_t s, int dtype, const FfnArgs& a, int batch, void* y, KernelEvents ev) {
+  const auto lanes = [&](int n) { return n > 32 ? 64 : n > 16 ? 32 : 16; };       // 16-byte pieces of a row
+  const size_t lds = token_lds(a.KS, a.d, a.f);
+  if (dtype == MOE_DTYPE_FP32)
+    launch_timed(ffn_token_rowmajor<float>, dim3(batch), dim3(kTokenThreads), lds, s, ev, a, (float*)y, lanes(a.d / 4), lanes(a.f / 4));
+  else
+    launch_timed(ffn_token_rowmajor<uint16_t>, dim3(batch), dim3(kTokenThreads), lds, s, ev, a, (uint16_t*)y, lanes(a.d / 8), lanes(a.f / 8));
   return hipGetLastError();
 }
 

@@ -826,6 +826,7 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   fa.max_count = batch;
   fa.work = a.work;
   fa.t = c->t; fa.h = c->h; fa.o = c->o;
+  const bool token = c->full[layer] && ffn_token_supported(cf.pool_layout, cf.dtype, batch, KS, g_max, d, cf.d_ff);
   const bool fused = plan.fused;
   fa.fused = fused ? 1 : 0;
   const KernelEvents ke1 = ps ? ps->gate_up : KernelEvents{}, ke2 = ps ? ps->down : KernelEvents{};
@@ -837,7 +838,8 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   fa.pool = in_kernel ? c->pool_dev[layer] : nullptr;
   fa.fetch = in_kernel ? 1 : 0;
   fa.pass = in_kernel ? 2 : 0;
-  HIPCHK(launch_ffn(s, cf.dtype, plan, fa, ke1, ke2));
+  if (token) HIPCHK(launch_ffn_token(s, cf.dtype, fa, batch, y_dev, ke1));
+  else HIPCHK(launch_ffn(s, cf.dtype, plan, fa, ke1, ke2));
 
   Mailbox mb{};
   if (c->full[layer]) {
@@ -859,11 +861,12 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
     HIPCHK(launch_ffn(s, cf.dtype, plan, fa, KernelEvents{}, KernelEvents{}));
   }
   if (ps) {
-    ps->used = true; ps->single = false; ps->mixed = mb.n_miss > 0; ps->fused = fused;
+    ps->used = true; ps->single = false; ps->mixed = mb.n_miss > 0; ps->fused = fused || token;
     ps->fetched = in_kernel ? (uint64_t)mb.n_miss * c->expert_bytes : 0;
   }
-  HIPCHK(fused ? launch_combine_chunks(s, c->o, c->t.wpair, c->t.pos_of, batch, KS, d, cf.d_ff / 32, y_dev)
-               : launch_combine(s, cf.dtype, c->o, c->t.wpair, c->t.pos_of, batch, KS, d, y_dev));
+  if (!token)
+    HIPCHK(fused ? launch_combine_chunks(s, c->o, c->t.wpair, c->t.pos_of, batch, KS, d, cf.d_ff / 32, y_dev)
+                 : launch_combine(s, cf.dtype, c->o, c->t.wpair, c->t.pos_of, batch, KS, d, y_dev));
 
   moe_cache_stats_t& st = c->stats[layer];
   st.lookups += (uint64_t)batch * K;

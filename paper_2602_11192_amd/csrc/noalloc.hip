@@ -234,6 +234,10 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
   fa.o = reinterpret_cast<float*>(base + o_o);
   fa.fused = plan.fused ? 1 : 0;
   fa.pass = 2;
+  if (ffn_token_supported(L->pool_layout, L->dtype, batch, KS, G, d, f)) {
+    HIPCHK(launch_ffn_token(s, L->dtype, fa, batch, y_dev, KernelEvents{}));
+    return MOE_OK;
+  }
   HIPCHK(launch_ffn(s, L->dtype, plan, fa, KernelEvents{}, KernelEvents{}));
   HIPCHK(plan.fused ? launch_combine_chunks(s, fa.o, t.wpair, t.pos_of, batch, KS, d, f / 32, y_dev)
                     : launch_combine(s, L->dtype, fa.o, t.wpair, t.pos_of, batch, KS, d, y_dev));
