@@ -11,13 +11,8 @@ constexpr int kWave = 64;
 __device__ __forceinline__ float bf16_to_f32(uint16_t v) {
   return __builtin_bit_cast(float, (uint32_t)v << 16);
 }
-// round-to-nearest-even; NaN kept quiet
-__device__ __forceinline__ uint16_t f32_to_bf16(float f) {
-  uint32_t u = __builtin_bit_cast(uint32_t, f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
+// round-to-nearest-even; NaN kept quiet.  One v_cvt_pk_bf16_f32, equal to the integer form on all 2^32 values.
+__device__ __forceinline__ uint16_t f32_to_bf16(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 
 template <typename T> struct Elem;
 template <> struct Elem<float> {
