@@ -190,6 +190,7 @@ __global__ void __launch_bounds__(kTokenThreads) ffn_token_rowmajor(FfnArgs a, T
   const int ng = *a.t.n_groups;
   for (int j = wave; j < KS; j += kTokenThreads / 64) {       // the group that holds the pair
     const int pos = a.t.pos_of[(size_t)b * KS + j];
+    if (lane == 0) ids[j] = 0;                                // (a call without groups has no expert to name: stay in bounds)
     for (int g = lane; g < a.g_max; g += 64) {                // (g_max descriptors exist: requested beside the count)
       const GroupDesc gd = a.t.grp[g];
       if (g < ng && pos >= gd.begin && pos < gd.begin + gd.count) ids[j] = gd.buf;
