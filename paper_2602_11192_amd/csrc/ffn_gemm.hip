@@ -231,20 +231,25 @@ __global__ void __launch_bounds__(64 * WAVES, MINW) ffn_gemm_kernel(FfnArgs a) {
 
 // Calls of up to 16 tokens: a group has one column block, so nothing is staged and nobody waits for anyone.  Every wave streams
 // its own RT row tiles and takes the token fragment of a k-block straight from memory (a few rows that stay in the first cache
-// level), all of it R - 1 k-blocks ahead.  Waves of their own can also walk apart: the row tiles of a workgroup lie a multiple
-// of d x 64 bytes apart, and waves in lockstep meet in the same memory channels (a bare stream of runs of 128 KiB reads 5.7 TB/s with
-// four waves in step, 6.7 with each two k-blocks = 4 KiB ahead of the last; 256 KiB 6.2 and 6.6).
-// What bounds it: HBM, and with one round of workgroups the units that hold one more than the others.  4 Phi-3.5-MoE-like tokens:
-// gate/up 81.5 -> 77 us, down 51 -> 42 (6.6 TB/s), 16 OLMoE-like gate/up 76 -> 72 us; 176 points (11 shapes, 4 to 16 tokens) 1.05x in
-// the mean against the staged kernel, the slowest .974.  With more than one column block its L1 traffic overtakes the
+// level), all of it R - 1 k-blocks ahead.  The contraction is walked from its start, as in ffn_gemm_kernel: a token's bits do
+// not depend on how many share the call.
+// The row tiles of a workgroup lie a multiple of d x 64 bytes apart, so waves in lockstep meet in the same memory channels:
+// each sends its first requests kFewSkew x 64 clocks after its neighbour (the queues of the memory are full by then, nothing idles).
+// @@FIG@@
+// With more than one column block its L1 traffic overtakes the
 // staging: 64 tokens on 24 experts of 2560 x 2048 135 -> 162 us.
 constexpr int kFewTokens = 16;
-constexpr int kFewApart = 2;      // k-blocks between neighbouring waves
+constexpr int kFewSkew = 4;
 template <int NMAT, int RT, int R, int MINW>
 __global__ void __launch_bounds__(256, MINW) ffn_few_kernel(FfnArgs a) {
   constexpr int WAVES = 4;
   const int n_rb = ((NMAT == 2 ? a.f : a.d) / 16 + RT * WAVES - 1) / (RT * WAVES);
-  const int item_id = blockIdx.x / n_rb, rb = blockIdx.x % n_rb;
+  int item_id = blockIdx.x / n_rb, rb = blockIdx.x % n_rb;
+  if (a.by_die) {                                 // as in ffn_gemm_kernel
+    const int j = blockIdx.x >> 3;
+    item_id = j / n_rb * 8 + (blockIdx.x & 7);
+    rb = j % n_rb;
+  }
   const int n_items = a.t.work[0].x;
   const int4 item = a.t.work[1 + min(item_id, a.work.cap - 1)];
   if (item_id >= n_items) return;
@@ -264,7 +269,9 @@ __global__ void __launch_bounds__(256, MINW) ffn_few_kernel(FfnArgs a) {
     wp[i] = NMAT == 2 ? wsrc + (size_t)rt * nkb * 2048 : wsrc + (size_t)4 * a.f * a.d + (size_t)rt * 1024;
   }
   const size_t kb_bytes = NMAT == 2 ? 2048 : (size_t)(a.d >> 4) * 1024;
-  int next = NMAT == 2 ? kFewApart * wave % nkb : 0;       // k-block of the next request
+  int next = 0;                                   // k-block of the next request
+  if (NMAT == 2)
+    for (int i = 0; i < wave; ++i) __builtin_amdgcn_s_sleep(kFewSkew);
   const int pos = begin + min(n, n_tok - 1);      // columns beyond the group repeat its last token and are dropped
   const uint16_t* src = NMAT == 2 ? reinterpret_cast<const uint16_t*>(a.x) + (size_t)(a.t.sorted_pair[pos] / a.KS) * a.d + q * 8
                                   : reinterpret_cast<const uint16_t*>(a.h) + (size_t)pos * a.f + q * 8;
@@ -377,7 +384,10 @@ hipError_t launch_ffn_gemm(hipStream_t s, const FfnArgs& args, KernelEvents e1, 
   if (a.work.shift == kSmallTile && a.max_count <= kFewTokens) {
     // (a group is one item of the list.)  One row tile of W_d per wave where two leave units idle: 8 to 16 tokens on 8 + 1 experts of
     // 2048 x 8192, 144 workgroups of eight tiles, 53 / 39 us; on 16 of 1536 x 4096, 192 of them, 26.5 / 31, on 8 of 3072 x 3072 23.5 / 25.5.
-    const auto grid = [&](int rows, int tiles_per_wg) { return dim3(a.g_max * ((rows / 16 + tiles_per_wg - 1) / tiles_per_wg)); };
+    // Row blocks of an item on one die from eight items per die on: OLMoE-like, 8 / 12 / 16 tokens, 97.8 / 125.5 / 127.8 -> 95.6 /
+    // 122.4 / 123.3 us per layer call; with six (12 tokens, 4 each of 60 experts of 2048 x 1408) 107.9 -> 114.2.
+    a.by_die = a.g_max >= 64;
+    const auto grid = [&](int rows, int tiles_per_wg) { return dim3((a.g_max + 7) / 8 * 8 * ((rows / 16 + tiles_per_wg - 1) / tiles_per_wg)); };
     launch_timed(ffn_few_kernel<2, 1, 8, 3>, grid(a.f, 4), dim3(256), 0, s, e1, a);
     if ((int64_t)a.g_max * ((a.d + 127) / 128) < 160) launch_timed(ffn_few_kernel<1, 1, 8, 5>, grid(a.d, 4), dim3(256), 0, s, e2, a);
     else launch_timed(ffn_few_kernel<1, 2, 8, 3>, grid(a.d, 8), dim3(256), 0, s, e2, a);

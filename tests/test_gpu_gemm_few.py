@@ -1,5 +1,6 @@
 """Grouped bf16 GEMM for calls of up to 16 tokens: contractions shorter than the waves are apart or than the ring is deep, and of every
-remainder, row tiles that the last workgroup lacks, one and two row tiles per wave; against the layer in 64 bits."""
+remainder, row tiles that the last workgroup lacks, one and two row tiles per wave; against the layer in 64 bits.  A token's
+result does not depend on how many others share the call."""
 import numpy as np
 import pytest
 
@@ -39,3 +40,28 @@ def test_few_tokens(batch, E, K, ns, d, f):
         assert torch.equal(i.cpu().long()[sure], idx[sure])
         err = (yd.cpu().double() - y).abs().max(-1).values / y.abs().max(-1).values
         assert float(err[sure].max()) <= TOL["bf16"]
+
+
+# (17 tokens: the staged kernel, 9 to 16: the one without staging; fewer than 64 groups and more.  Rows enough that sums in another order
+# would round some to another bf16 number)
+@pytest.mark.parametrize("E,K,ns,d,f", [(4, 4, 0, 1024, 4096), (64, 8, 2, 512, 1024)])
+def test_the_same_bits_beside_more_tokens(E, K, ns, d, f):
+    import torch
+    from paper_2602_11192_amd import binding as B
+    gen = torch.Generator().manual_seed(d)
+    rnd = lambda *s: torch.randn(*s, generator=gen)
+    router, x, bias = (rnd(E, d) * d ** -0.5).bfloat16().cuda(), rnd(17, d).bfloat16().cuda(), rnd(17, E).cuda()
+    # (any values in tiled order are an expert: nothing is compared with another layout)
+    blocks, shared = (rnd(E * 3 * d * f) * d ** -0.5).bfloat16().cuda(), (rnd(ns * 3 * d * f) * d ** -0.5).bfloat16().cuda()
+
+    def run(n):
+        y, w = torch.empty(n, d, dtype=torch.bfloat16, device="cuda:0"), torch.empty(n, K, device="cuda:0")
+        B.moe_layer_decode_resident_noalloc(n_experts=E, n_shared=ns, top_k=K, d_model=d, d_ff=f, dtype=B.MOE_DTYPE_BF16,
+                                            pool_layout=B.MOE_LAYOUT_TILED, router_w=router, experts=blocks,
+                                            shared_w=shared if ns else None, x=x[:n], y=y, logit_bias=bias[:n], topk_idx=None, topk_w=w)
+        torch.cuda.synchronize()
+        return y, w
+    y, w = run(17)
+    for n in (9, 13, 16):
+        yn, wn = run(n)
+        assert torch.equal(wn, w[:n]) and torch.equal(yn, y[:n])
