@@ -240,7 +240,10 @@ int moe_cache_prefill_pins(moe_cache_t* cache, int32_t layer, const int32_t* exp
  * A call whose evictions would need more spare buffers than `staging_buffers` provides
  * is executed as consecutive waves of tokens (the batch is halved until every wave
  * fits; one token always fits); routing, hits, misses, evictions and outputs are the
- * same as for the unsplit call, only slower.
+ * same as for the unsplit call, only slower - up to the order of fp32 sums where a wave is so
+ * small that other kernels run it than the call (one token always; the router of fewer than 112 tokens with at most 16
+ * experts, more than 64, or MOE_POLICY_GAMMA; the experts of up to 8 tokens, INT4 16): gate weights and outputs may
+ * then differ in their last bits, and two logits closer than that may change places.
  * Host waits: none for batch 1, or for up to four tokens on a cache that can hold every expert (C >= E), on bf16 experts in
  * the tiled layout or INT4 experts, with in-kernel fetch (router, gating, lookups and the expert FFN are then one launch, the
  * combine a second one); none on a layer all of whose experts are known to be resident: C >= E, and a preload, a prompt or

@@ -879,7 +879,8 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
 
 // A call whose evictions need more spare buffers than exist changes nothing on the device; it is then run as two
 // consecutive waves of tokens (recursively).  Tokens are looked up in row order either way, so hits, misses,
-// evictions and outputs are those of the unsplit call.  A single token always fits (K <= C).
+// evictions and outputs are those of the unsplit call, as long as waves take the call's kernels: a token's sums are then the
+// same whatever the batch (moe_cache.h says where they do not).  A single token always fits (K <= C).
 int decode_rows(moe_cache_t* c, int32_t layer, const char* x, const float* bias, int32_t batch, char* y,
                 int32_t* idx, float* w, hipStream_t s, int32_t row0) {
   const int rc = decode_wave(c, layer, x, bias, batch, y, idx, w, s, row0);

@@ -133,7 +133,7 @@ struct RouteScratch {
 // ... as the launch lays it out
 struct RouteWork {
   int32_t slices;         // of the contraction
-  float* logits;          // [tile of 16 tokens][slice][expert tile][256]
+  float* logits;          // [tile of 16 tokens][expert tile][256], with several slices [8 partial sums] of each ahead of the 256
   uint64_t* masks;        // [B] experts that a token selects, up to 64
 };
 

@@ -71,7 +71,7 @@ template <> struct Vec<uint16_t> {
 };
 
 constexpr int kTileMaxE = 256;   // most experts the 16-token tile kernels keep logits for
-constexpr int kRouteSliceKb = 32; // fewest k-blocks of the contraction worth a slice of their own: a pair for each of sixteen waves
+constexpr int kRouteSliceKb = 16; // fewest k-blocks of the contraction worth a slice of their own
 constexpr int kRouteMaxUnits = 256;   // ... and most workgroups that slicing may make: one per compute unit
 
 // ---------------------------------------------------------------- LDS layout
@@ -805,6 +805,7 @@ constexpr int kTileWaves = 16, kTileThreads = 64 * kTileWaves, kTileTokens = 16;
 // 20.4 -> 19.8; 16 tokens x 8 experts 25.2 -> 26.7, 8 tokens x 64 experts of 512 columns 24.8 -> 28.0: not taken).
 constexpr int kSmallRouterItems = 128;
 constexpr size_t kSmallRouterBytes = 128 << 10;
+constexpr int kRouteChains = 16;      // partial sums of a logit (route_units_kernel)
 constexpr int kChunk = kTileThreads;  // tokens whose pairs are placed at a time, one per thread
 
 // What the phases behind the logits keep in LDS.
@@ -1153,10 +1154,12 @@ __device__ __forceinline__ void gate_and_group(unsigned char* smem, TileLds& tl,
 }
 
 // Calls of two and more bf16 tokens.  The router logits are a matrix product (experts x tokens) on the matrix cores: rows of W_r
-// are the A operand, the tokens the B operand of v_mfma_f32_16x16x32_bf16.  A workgroup of sixteen waves forms 16 experts x 16
-// tokens over one slice of the contraction (a unit): its waves take pairs of adjacent k-blocks, every load of a wave is in
-// flight at once, and their partial tiles meet in LDS.  Units publish their logits past the caches, and the one that arrives
-// last of its token tile gates (gate_and_group).
+// are the A operand, the tokens the B operand of v_mfma_f32_16x16x32_bf16.  A workgroup forms 16 experts x 16 tokens over one
+// slice of the contraction (a unit), every load of a wave in flight at once; its waves' partial tiles meet in LDS, units publish
+// theirs past the caches, and the one that arrives last of its token tile gates (gate_and_group).
+// A logit is the sum of sixteen chains: chain c takes the pairs of k-blocks c, c + 16, c + 32 ..., and the sums of chains c and c + 8
+// are added up from c = 0.  One wave forms a chain, in whichever slice it lies, so neither the batch nor the number of slices
+// that it calls for changes a bit of a token's logits.
 // What bounds it is the chain of round trips - first touch after the launch, publication, arrival, gating, arrival, grouping -
 // and, with whole tiles of 64 experts in one workgroup, the 320 KB that one compute unit had to pull in: row-major
 // fragments are 16 pieces of 64 bytes each, and the address unit sets the pace.
@@ -1169,7 +1172,7 @@ __global__ void __launch_bounds__(kTileThreads) route_units_kernel(RouteArgs r, 
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   extern __shared__ __align__(16) unsigned char smem[];     // partial tiles of the logits, then phase 3's scratch
   __shared__ TileLds tl;
-  float* pz = reinterpret_cast<float*>(smem);               // [16 waves][256]
+  float* pz = reinterpret_cast<float*>(smem);               // [2 half][256]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 15, q = lane >> 4;
@@ -1184,21 +1187,25 @@ __global__ void __launch_bounds__(kTileThreads) route_units_kernel(RouteArgs r, 
   constexpr int w_step = PACKED ? 64 : 4;                   // (16-byte pieces between k-blocks)
   const u32x4* wrow = PACKED ? static_cast<const u32x4*>(r.router_packed) + (size_t)et * nkb * 64 + lane
                              : reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(r.router_w) + (size_t)min(et * 16 + n, E - 1) * d) + q;
-  const int per = ((nkb + rw.slices - 1) / rw.slices + 1) & ~1;
-  const int hi = min(nkb, (sl + 1) * per);
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int kb0 = sl * per + 2 * wave; kb0 < hi; kb0 += 2 * PAIRS * kTileWaves) {
-    u32x4 xb[2 * PAIRS], wa[2 * PAIRS];
+  // the slice's chains: sl * half ... and the same + 8
+  const int half = kRouteChains / 2 / rw.slices;
+  if (wave < 2 * half) {
+    const int chain = sl * half + (wave < half ? wave : wave - half + kRouteChains / 2);
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int kb0 = 2 * chain; kb0 < nkb; kb0 += 2 * PAIRS * kRouteChains) {
+      u32x4 xb[2 * PAIRS], wa[2 * PAIRS];
 #pragma unroll
-    for (int i = 0; i < 2 * PAIRS; ++i) {
-      const int kb = min(kb0 + (i >> 1) * 2 * kTileWaves + (i & 1), hi - 1);
-      xb[i] = xrow[(size_t)kb * 4];
-      wa[i] = wrow[(size_t)kb * w_step];
+      for (int i = 0; i < 2 * PAIRS; ++i) {
+        const int kb = min(kb0 + (i >> 1) * 2 * kRouteChains + (i & 1), nkb - 1);
+        xb[i] = xrow[(size_t)kb * 4];
+        wa[i] = wrow[(size_t)kb * w_step];
+      }
+#pragma unroll
+      for (int i = 0; i < 2 * PAIRS; ++i)
+        if (kb0 + (i >> 1) * 2 * kRouteChains + (i & 1) < nkb)      // uniform
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wa[i]), __builtin_bit_cast(bf16x8, xb[i]), acc, 0, 0, 0);
     }
-#pragma unroll
-    for (int i = 0; i < 2 * PAIRS; ++i)
-      if (kb0 + (i >> 1) * 2 * kTileWaves + (i & 1) < hi)      // uniform
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wa[i]), __builtin_bit_cast(bf16x8, xb[i]), acc, 0, 0, 0);
+    *reinterpret_cast<f32x4*>(pz + wave * 256 + lane * 4) = acc;
   }
   // nobody changes the table before the last workgroup of this launch does: every workgroup may fetch it now
   RawTable raw{};
@@ -1213,25 +1220,38 @@ __global__ void __launch_bounds__(kTileThreads) route_units_kernel(RouteArgs r, 
     bias[j] = (r.bias && e < E && t0 + el_tok < a.B) ? r.bias[(size_t)(t0 + el_tok) * E + e] : 0.f;
   }
   clear_tile_lds(tl, E);
-  *reinterpret_cast<f32x4*>(pz + wave * 256 + lane * 4) = acc;
   __syncthreads();
+  const auto pair_sum = [&](int c) { return pz[c * 256 + el] + pz[(c + half) * 256 + el]; };
   float z = 0.f;
-  if (tid < 256) {
+  if (rw.slices > 1) {
+    if (tid < half * 256) z = pair_sum(tid >> 8);
+  } else if (tid < 256) {
+    z = pair_sum(0);
 #pragma unroll
-    for (int w = 0; w < kTileWaves; ++w) z += pz[w * 256 + tid];
+    for (int c = 1; c < kRouteChains / 2; ++c) z += pair_sum(c);
   }
   if (units == 1) {
     if (tid < 256 && el_row < E) tl.zs[el_tok][el_row] = z + bias[0];
   } else {
-    if (tid < 256) __hip_atomic_store(rw.logits + (size_t)blockIdx.x * 256 + tid, z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // published: a unit's logits, or its pair sums [expert tile][8][256] where other units have the others
+    const int parts = rw.slices > 1 ? kRouteChains / 2 : 1;
+    float* zt = rw.logits + (size_t)tile * n_et * parts * 256;
+    if (tid < (rw.slices > 1 ? half : 1) * 256)
+      __hip_atomic_store(zt + (size_t)(et * parts + sl * half) * 256 + tid, z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (!arrive_last(r.arrive + 1 + tile, units, tl.last_arrived)) return;
-    const float* zp = rw.logits + (size_t)tile * units * 256 + el;
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
       const int t16 = (tid >> 8) + j * (kTileThreads / 256), e = t16 * 16 + el_row;
       if (t16 < n_et) {
-        float v = 0.f;
-        for (int s = 0; s < rw.slices; ++s) v += __builtin_bit_cast(float, load_published(zp + (size_t)(s * n_et + t16) * 256));
+        const float* zp = zt + (size_t)t16 * parts * 256 + el;
+        float v = __builtin_bit_cast(float, load_published(zp));
+        if (parts > 1) {
+          float more[kRouteChains / 2 - 1];
+#pragma unroll
+          for (int c = 1; c < kRouteChains / 2; ++c) more[c - 1] = __builtin_bit_cast(float, load_published(zp + c * 256));
+#pragma unroll
+          for (int c = 1; c < kRouteChains / 2; ++c) v += more[c - 1];
+        }
         if (e < E) tl.zs[el_tok][e] = v + bias[j];
       }
     }
@@ -1312,7 +1332,8 @@ __global__ void reset_kernel(LayerState st, int E, int C, int P, int clear_trace
 }  // namespace
 
 // Slices pay although they make units meet where one would do: 16 experts of 4096 columns, 8 / 64 tokens, one slice 12.7 / 15.3 us per
-// launch, four 9.0 / 11.0; of 2048 columns, 16 tokens, 10.9 / 9.2 with two.
+// launch, four 9.0 / 11.0; 64 of 2048 columns, 16 / 64 tokens, two 11.0 / 12.2, four 10.2 / 11.8; layer calls on 32 of 1024 columns, 16 /
+// 64 tokens, one 21.1 / 25.7, two 20.8 / 25.0.
 RouteUnits route_units(int B, int E, int d) {
   RouteUnits u{};
   u.tiles = (B + kTileTokens - 1) / kTileTokens;
@@ -1321,14 +1342,16 @@ RouteUnits route_units(int B, int E, int d) {
   while (u.slices < 4 && nkb / (2 * u.slices) >= kRouteSliceKb && u.tiles * n_et * u.slices * 2 <= kRouteMaxUnits) u.slices *= 2;
   const size_t units = (size_t)u.tiles * n_et * u.slices;
   u.n_arrive = 1 + u.tiles;
-  u.logit_bytes = units * 256 * sizeof(float);
+  // (one slice: the logits; several: the eight pair sums of every logit)
+  u.logit_bytes = (u.slices > 1 ? (size_t)u.tiles * n_et * kRouteChains / 2 : units) * 256 * sizeof(float);
   u.scratch_bytes = u.logit_bytes + (size_t)u.tiles * kTileTokens * sizeof(uint64_t);
   return u;
 }
 
 size_t route_scratch_bytes(int max_batch, int E, int d) {
-  const RouteUnits u = route_units(max_batch, E, d);     // (a smaller call may be sliced further)
-  return std::max(u.scratch_bytes, (size_t)kRouteMaxUnits * 256 * sizeof(float) + (size_t)u.tiles * kTileTokens * sizeof(uint64_t));
+  const RouteUnits u = route_units(max_batch, E, d);     // (a smaller call may be sliced further, while its units are few enough)
+  const size_t sliced = (size_t)std::min(u.tiles * ((E + 15) / 16), kRouteMaxUnits / 2) * (kRouteChains / 2) * 256 * sizeof(float);
+  return std::max(u.logit_bytes, sliced) + (size_t)u.tiles * kTileTokens * sizeof(uint64_t);
 }
 
 size_t route_cache_lds_bytes(int E, int C, int P, int n_shared, int B, int K, int KS) {
@@ -1359,12 +1382,16 @@ hipError_t launch_route_cache(hipStream_t s, int dtype, const RouteArgs& r, cons
       const size_t bytes = std::max({kind == kFull ? 0 : lds, (size_t)kTileWaves * 256 * sizeof(float), stage_pairs(a.B, a.KS) ? (size_t)(a.B * a.KS + 3) / 4 * 32 : 0});
       const dim3 units(ru.tiles * ((a.E + 15) / 16) * ru.slices), threads(kTileThreads);
       const auto launch = [&](auto kernel) { launch_timed(kernel, units, threads, bytes, s, ev, r, w, st, t, a); };
-      // pairs of k-blocks a wave has of its unit's slice
-      const bool two = (r.d / 32 + ru.slices * 2 * kTileWaves - 1) / (ru.slices * 2 * kTileWaves) > 1;
-      if (kind == kFull && r.router_packed) launch(two ? route_units_kernel<2, true, kFull> : route_units_kernel<1, true, kFull>);
-      else if (kind == kFull) launch(two ? route_units_kernel<2, false, kFull> : route_units_kernel<1, false, kFull>);
-      else if (kind == kTable) launch(two ? route_units_kernel<2, false, kTable> : route_units_kernel<1, false, kTable>);
-      else launch(two ? route_units_kernel<2, false, kOther> : route_units_kernel<1, false, kOther>);
+      const int pairs = (r.d / 32 + 2 * kRouteChains - 1) / (2 * kRouteChains);      // of k-blocks in a chain
+      const auto with = [&](auto packed, auto k) {
+        constexpr bool P = decltype(packed)::value;
+        constexpr RouteKind Q = decltype(k)::value;
+        launch(pairs > 2 ? route_units_kernel<4, P, Q> : pairs > 1 ? route_units_kernel<2, P, Q> : route_units_kernel<1, P, Q>);
+      };
+      if (kind == kFull && r.router_packed) with(std::true_type{}, std::integral_constant<RouteKind, kFull>{});
+      else if (kind == kFull) with(std::false_type{}, std::integral_constant<RouteKind, kFull>{});
+      else if (kind == kTable) with(std::false_type{}, std::integral_constant<RouteKind, kTable>{});
+      else with(std::false_type{}, std::integral_constant<RouteKind, kOther>{});
       return hipGetLastError();
     }
   }

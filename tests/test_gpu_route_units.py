@@ -80,3 +80,35 @@ def test_batch_that_hits(torch, B, batch, E, K, ns, d, held):
         cache.moe_layer_decode(0, xd[:1], torch.empty(1, d, dtype=torch.bfloat16, device="cuda:0"), b2.cuda(), None, None)
         assert sorted(cache.moe_cache_resident(0)) == sorted(set(order) - set(want[:n_new]) | set(lost[:n_new].tolist()))
     cache.close()
+
+
+# (slices by batch: 64 x 2048 and 64 x 4128 one at 960 tokens, two at 512, four below; 32 x 4128 and 17 x 2080 two and four; 16 x 1056 two.
+# 4128, 2080 and 1056 columns are not divided by them)
+@pytest.mark.parametrize("E,d", [(64, 2048), (64, 4128), (32, 4128), (17, 2080), (16, 1056)])
+def test_logits_do_not_depend_on_the_batch(torch, B, E, d):
+    K, f = 2, 32
+    gen = torch.Generator().manual_seed(E + d)
+    rnd = lambda *s: torch.randn(*s, generator=gen)
+    router, x, bias = (rnd(E, d) * 2 / d ** 0.5).bfloat16(), rnd(960, d).bfloat16(), rnd(960, E)
+    z = x.double() @ router.double().t() + bias.double()
+    top = torch.topk(z, K + 1, dim=-1)
+    sure = top.values[:, K - 1] - top.values[:, K] > 1e-5        # fp32 logits of a few units are off by under 1e-5
+    want = top.indices[:, :K].sort(-1).values
+    rd, xd, bd = router.cuda(), x.cuda(), bias.cuda()
+    blocks = (rnd(E * 3 * d * f) * 0.1).bfloat16().cuda()
+
+    def run(rows):
+        n = rows.stop - rows.start
+        i, w = torch.empty(n, K, dtype=torch.int32, device="cuda:0"), torch.empty(n, K, device="cuda:0")
+        # (weights that are not normalised over the two show every bit of the logits)
+        B.moe_layer_decode_resident_noalloc(n_experts=E, top_k=K, d_model=d, d_ff=f, dtype=B.MOE_DTYPE_BF16, norm_topk=0,
+                                            pool_layout=B.MOE_LAYOUT_ROWMAJOR, router_w=rd, experts=blocks, x=xd[rows],
+                                            y=torch.empty(n, d, dtype=torch.bfloat16, device="cuda:0"), logit_bias=bd[rows], topk_idx=i, topk_w=w)
+        torch.cuda.synchronize()
+        return i.cpu(), w.cpu()
+    i, w = run(slice(0, 960))
+    assert torch.equal(i.long()[sure], want[sure])
+    assert float((w.double() - torch.softmax(z, -1).gather(1, i.long())).abs().max()) < 1e-5
+    for rows in (slice(0, 512), slice(100, 356), slice(500, 533), slice(900, 916), slice(7, 9)):
+        ri, rw = run(rows)
+        assert torch.equal(ri, i[rows]) and torch.equal(rw, w[rows])
