@@ -813,11 +813,13 @@ struct TileLds {
   float zs[kTileTokens][kTileMaxE + 4];           // logits (+ 4: the 16 tokens of a column fall on different banks)
   uint64_t sel[kTileTokens];                      // experts each token of the tile selects (up to 64 experts)
   int map[kTileMaxE];                             // expert -> buffer << 8 | slot, -1 when it is not resident
-  // per wave of 64 tokens and expert: the tokens that select it, how many, and the position of the first of them
+  // A column of the grouping is an expert; of more than 64 experts the resident ones in ascending order have them (kWide)
+  int col_expert[kWave], col_map[kWave];          // kWide: the column's expert and its entry of `map`
+  // per wave of 64 tokens and column: the tokens that select it, how many, and the position of the first of them
   uint64_t col[kTileWaves][kWave];
   int cnt[kTileWaves][kWave], base[kTileWaves][kWave];
-  int first_pair[kWave], last_lookup[kWave];      // ... expert: its first pair, its last lookup + 1
-  int first[kWave], touched[kWave];
+  int first_pair[kWave], last_lookup[kWave];      // ... column: its first pair, its last lookup + 1
+  int first[kWave], touched[kWave], slot_last[kWave];
   int last_arrived, any_miss;
 };
 
@@ -877,14 +879,24 @@ __device__ __forceinline__ uint64_t transpose_bits(uint64_t x) {
   return x;
 }
 
-// Phase 3 on the register table (LRU) of a layer of up to 64 experts, run by ALL waves of the last workgroup.  The common case -
+// One kernel per kind of call: code that a launch only jumps over is fetched cold with the rest, and its registers spill the others'.
+//   kFull    mode 0 on the register table, every expert known to be resident (then there are at most 64): no lookup can miss
+//   kTable   mode 0 on the register table, up to 64 experts
+//   kWide    mode 0 on the register table, 65 to 256 experts
+//   kOther   other tables, more experts, prompt streaming: one wave looks up in order
+enum RouteKind { kFull, kTable, kWide, kOther };
+template <RouteKind KIND> constexpr bool kMany = KIND == kWide || KIND == kOther;      // more than 64 logits of a token
+
+// Phase 3 on the register table (LRU), run by ALL waves of the last workgroup.  The common case -
 // every lookup hits - is embarrassingly parallel: residency does not change, and the place of a pair in its group is the number
 // of earlier tokens that select the same expert.  A wave holds the selections of 64 tokens as one mask per lane; transposed, lane
-// e has the tokens of expert e, and counts, prefix sums and the order of the groups are a few instructions in every wave alike.
+// e has the tokens of column e, and counts, prefix sums and the order of the groups are a few instructions in every wave alike.
 // Nothing is drawn from a shared counter: with 8192 ranks from LDS atomics this phase took 12 us of a launch.
-// False, with nothing changed, when a lookup misses (FULL: the host knows that none can).
+// False, with nothing changed, when a lookup misses.  kWide: there are at most 64 slots, so the resident experts have a column each,
+// and a token whose mask holds fewer than K of them misses.  (Calls that hit, 112 /
+// 1024 tokens with 6 each of 128 experts on 60 slots, grouped by one wave 94.7 / 657 us, here 89.0 / 550.)
 // masks: the published selections, null: tl.sel.  behind: work of the caller that the first loads leave time for.
-template <bool FULL, typename Behind>
+template <RouteKind KIND, typename Behind>
 __device__ __forceinline__ bool group_hits(unsigned char* smem, TileLds& tl, const RawTable& raw, const uint64_t* masks,
                                            const LayerState& st, const CallTables& t, const CacheCallArgs& a, Behind behind) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -895,15 +907,21 @@ __device__ __forceinline__ bool group_hits(unsigned char* smem, TileLds& tl, con
   };
   uint64_t mine = mask_of(tid);
   behind();
-  if constexpr (!FULL) {
-    const uint64_t resident = __ballot(lane < E && tl.map[lane] >= 0);
-    uint64_t wanted = mine;
-    for (int b = kChunk + tid; b < B; b += kChunk) wanted |= mask_of(b);
-    if ((wanted & ~resident) != 0) tl.any_miss = 1;
+  if constexpr (KIND != kFull) {
+    if constexpr (KIND == kWide) {
+      bool misses = tid < B && __popcll(mine) != K;
+      for (int b = kChunk + tid; b < B; b += kChunk) misses |= __popcll(mask_of(b)) != K;
+      if (misses) tl.any_miss = 1;
+    } else {
+      const uint64_t resident = __ballot(lane < E && tl.map[lane] >= 0);
+      uint64_t wanted = mine;
+      for (int b = kChunk + tid; b < B; b += kChunk) wanted |= mask_of(b);
+      if ((wanted & ~resident) != 0) tl.any_miss = 1;
+    }
     __syncthreads();
     if (tl.any_miss) return false;
   }
-  // lane e of every wave: the tokens of expert e in a chunk of 1024, in all of its waves and in those before this one
+  // lane e of every wave: the tokens of column e in a chunk of 1024, in all of its waves and in those before this one
   const bool ends = !a.resident || a.work.cap == 0;
   int in_chunk, before;
   const auto count_chunk = [&](int c0) {
@@ -911,7 +929,7 @@ __device__ __forceinline__ bool group_hits(unsigned char* smem, TileLds& tl, con
       const uint64_t col = transpose_bits(mine);
       tl.col[wave][lane] = col;
       tl.cnt[wave][lane] = __popcll(col);
-      // the expert's first pair (for the kernels that go by groups) and last lookup (recency)
+      // the column's first pair (for the kernels that go by groups) and last lookup (recency)
       const uint64_t lower = (1ull << lane) - 1ull;
       if (ends) {
         const int b0 = __ffsll((unsigned long long)col) - 1, b1 = 63 - __clzll(col | 1);
@@ -939,7 +957,7 @@ __device__ __forceinline__ bool group_hits(unsigned char* smem, TileLds& tl, con
     count_chunk(c0);
     total += in_chunk;
   }
-  const int v = lane < E ? tl.map[lane] : -1;
+  const int v = KIND == kWide ? tl.col_map[lane] : lane < E ? tl.map[lane] : -1;
   const int begin = (int)wave_scan((uint32_t)total) - total;
   const uint64_t used = __ballot(total > 0);
   const int group = __popcll(used & ((1ull << lane) - 1ull)), n_routed = __popcll(used);
@@ -976,7 +994,7 @@ __device__ __forceinline__ bool group_hits(unsigned char* smem, TileLds& tl, con
     }
   }
   const auto place = [&](int32_t* sorted, int32_t* pos_of) {
-    int run = 0;               // the expert's pairs in the chunks before
+    int run = 0;               // the column's pairs in the chunks before
     for (int c0 = 0; c0 < B; c0 += kChunk) {
       if (B > kChunk) {        // more than 1024 tokens: chunk by chunk once more
         __syncthreads();
@@ -1026,8 +1044,10 @@ __device__ __forceinline__ bool group_hits(unsigned char* smem, TileLds& tl, con
     const int64_t trace_n = st.scalars[SC_TRACE_N];
     for (int b = tid; b < B; b += kTileThreads) {
       uint64_t m = mask_of(b);
-      for (int l = b * K; m != 0; ++l, m &= m - 1)
-        if (trace_n + l < a.trace_cap) st.trace[trace_n + l] = moe_trace_rec_t{a.row0 + b, __ffsll((unsigned long long)m) - 1, 1, -1};
+      for (int l = b * K; m != 0; ++l, m &= m - 1) {
+        const int c = __ffsll((unsigned long long)m) - 1;
+        if (trace_n + l < a.trace_cap) st.trace[trace_n + l] = moe_trace_rec_t{a.row0 + b, KIND == kWide ? tl.col_expert[c] : c, 1, -1};
+      }
     }
   }
   // a scattered store takes the address unit a cycle per lane: many pairs are put in order in LDS
@@ -1049,7 +1069,11 @@ __device__ __forceinline__ bool group_hits(unsigned char* smem, TileLds& tl, con
   if (a.resident || wave != 0) return true;
   // ---- the table after the call: recency of the slots, buffers in use, released buffers free again ----
   FastTable f = table_of(raw);
-  const int last = lane < C && f.exp >= 0 ? tl.last_lookup[f.exp] : 0;
+  if constexpr (KIND == kWide) {
+    if (v >= 0) tl.slot_last[v & 255] = tl.last_lookup[lane];
+    wave_sync();
+  }
+  const int last = lane < C && f.exp >= 0 ? (KIND == kWide ? tl.slot_last[lane] : tl.last_lookup[f.exp]) : 0;
   if (last > 0) {
     f.tick = (uint64_t)(f.clock + last);
     tl.touched[f.buf] = 1;
@@ -1077,35 +1101,55 @@ __device__ __forceinline__ bool group_hits(unsigned char* smem, TileLds& tl, con
 // token's experts, and the last workgroup of the launch goes on to the lookups.  What the others must see of a workgroup - its
 // selections - goes past the caches with device-scope stores, so the arrival needs no cache write-back; the gate weights, which
 // no one in this launch reads, are formed behind it.
-// One kernel per kind of call: code that a launch only jumps over is fetched cold with the rest, and its registers spill the others'.
-//   kFull    mode 0 on the register table, every expert known to be resident (then there are at most 64): no lookup can miss
-//   kTable   mode 0 on the register table, up to 64 experts
-//   kOther   other tables, more experts, prompt streaming: one wave looks up in order
-enum RouteKind { kFull, kTable, kOther };
-
 template <RouteKind KIND>
 __device__ __forceinline__ void gate_and_group(unsigned char* smem, TileLds& tl, const RawTable& raw, int tile, int n_tiles,
                                                const RouteArgs& r, uint64_t* masks, const LayerState& st, const CallTables& t, const CacheCallArgs& a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int E = a.E, K = a.K, KS = a.KS, b = tile * kTileTokens + wave;
   const bool single = n_tiles == 1, mine = b < a.B;
-  if (KIND != kOther && wave == 0 && lane < a.C && raw.exp >= 0) tl.map[raw.exp] = raw.buf << 8 | lane;
+  constexpr bool kColumns = KIND != kOther;        // selections travel as masks of columns
+  if (kColumns && wave == 0 && lane < a.C && raw.exp >= 0) tl.map[raw.exp] = raw.buf << 8 | lane;
+  if constexpr (KIND == kWide) {
+    if (wave == 0) {
+      wave_sync();
+      int n_cols = 0;
+#pragma unroll
+      for (int i = 0; i < kTileMaxE / kWave; ++i) {
+        const int e = lane + i * kWave, m = e < E ? tl.map[e] : -1;
+        const uint64_t there = __ballot(m >= 0);
+        const int c = n_cols + __popcll(there & ((1ull << lane) - 1ull));
+        if (m >= 0) { tl.col_expert[c] = e; tl.col_map[c] = m; }      // (no more than there are slots)
+        n_cols += __popcll(there);
+      }
+      if (lane >= n_cols) { tl.col_expert[lane] = 0; tl.col_map[lane] = -1; }
+    }
+    __syncthreads();
+  }
   const LdsLayout L = lds_layout(E, a.C, a.P, a.n_shared, a.B, K, KS);
   int32_t* idx_stage = KIND != kFull && stage_in_lds(a.B, KS) ? reinterpret_cast<int32_t*>(smem + L.idx_stage) : nullptr;
-  constexpr int EPL = KIND == kOther ? kTileMaxE / kWave : 1;
+  constexpr int EPL = kMany<KIND> ? kTileMaxE / kWave : 1;
   Gate<1> g1;
   Gate<EPL> g4;
-  const bool few = KIND != kOther || E <= kWave;
+  const bool few = !kMany<KIND> || (KIND == kOther && E <= kWave);
+  const auto publish = [&](uint64_t columns) {
+    if (lane != 0) return;
+    if (single) tl.sel[wave] = columns;
+    else __hip_atomic_store(masks + b, columns, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
   if (mine) {
     if (few) {
       select_experts<1>(tl.zs[wave], E, K, g1);
-      if (KIND != kOther && lane == 0) {
-        if (single) tl.sel[wave] = g1.top[0];
-        else __hip_atomic_store(masks + b, g1.top[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
+      if constexpr (kColumns) publish(g1.top[0]);
       if constexpr (KIND != kFull) write_selected<1, true>(g1, b, K, t.idx, nullptr, single ? idx_stage : nullptr);
     } else {
       select_experts<EPL>(tl.zs[wave], E, K, g4);
+      if constexpr (KIND == kWide) {
+        const int e = tl.col_expert[lane];
+        uint64_t word = g4.top[0];
+#pragma unroll
+        for (int i = 1; i < EPL; ++i) word = e >> 6 == i ? g4.top[i] : word;
+        publish(__ballot(tl.col_map[lane] >= 0 && ((word >> (e & 63)) & 1) != 0));
+      }
       write_selected<EPL, true>(g4, b, K, t.idx, nullptr, single ? idx_stage : nullptr);
     }
   }
@@ -1125,9 +1169,9 @@ __device__ __forceinline__ void gate_and_group(unsigned char* smem, TileLds& tl,
     weights();
     return;
   }
-  if constexpr (KIND != kOther) {
+  if constexpr (kColumns) {
     // the weights fill the time that the others' selections take to arrive; with nothing to wait for they come last
-    const bool hits = group_hits<KIND == kFull>(smem, tl, raw, single ? nullptr : masks, st, t, a, [&] { if (!single) weights(); });
+    const bool hits = group_hits<KIND>(smem, tl, raw, single ? nullptr : masks, st, t, a, [&] { if (!single) weights(); });
     if (hits) {
       if (single) weights();
       return;
@@ -1143,7 +1187,7 @@ __device__ __forceinline__ void gate_and_group(unsigned char* smem, TileLds& tl,
     if (!idx_stage) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");     // reads the other workgroups' results directly
     const int32_t* in_order = idx_stage ? idx_stage : t.idx;
     int32_t* pair_stage = idx_stage ? reinterpret_cast<int32_t*>(smem + L.pair_stage) : t.pair_buf;
-    if constexpr (KIND == kTable) {
+    if constexpr (kColumns) {
       cache_phase_fast(table_of(raw), smem, L, in_order, pair_stage, st, t, a);
     } else {
       if (a.mode == 2) prefill_phase(smem, L, in_order, pair_stage, st, t, a);
@@ -1212,7 +1256,7 @@ __global__ void __launch_bounds__(kTileThreads) route_units_kernel(RouteArgs r, 
   if (KIND != kOther && wave == 0) raw = raw_load(st, a);
   // element el = tid % 256 of expert tile tid / 256 + 4 j: the MFMA leaves rows 4 (ln / 16) + el % 4, token ln % 16 with ln = el / 4
   const int el = tid & 255, el_tok = (el >> 2) & 15, el_row = (el >> 6) * 4 + (el & 3);
-  constexpr int NJ = KIND != kOther ? 1 : kTileMaxE / 16 / (kTileThreads / 256);
+  constexpr int NJ = kMany<KIND> ? kTileMaxE / 16 / (kTileThreads / 256) : 1;
   float bias[NJ];
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
@@ -1366,7 +1410,8 @@ hipError_t launch_route_cache(hipStream_t s, int dtype, const RouteArgs& r, cons
   if (waves > a.E) waves = a.E;
   dim3 grid(a.B), block(64 * waves);
   const size_t lds = route_cache_lds_bytes(a.E, a.C, a.P, a.n_shared, a.B, a.K, a.KS);
-  const RouteKind kind = a.mode != 0 || a.E > kWave || !fast_table(a.policy, a.C, a.P, a.n_shared) ? kOther : a.full ? kFull : kTable;
+  const RouteKind kind = a.mode != 0 || a.E > kTileMaxE || !fast_table(a.policy, a.C, a.P, a.n_shared) ? kOther
+                         : a.E > kWave ? kWide : a.full ? kFull : kTable;
   // Units where every lookup is known to hit (392 points of 8-256 experts, 1024-4096 columns, 2-1024 tokens: none slower than the
   // kernels before, 1.50x in the mean; 64 x 2048, 16 / 64 / 1024 tokens 10.8 / 12.6 / 19.4 against 13.2 / 21.1 / 28.9 us in layer
   // calls) and on the register table (16 tokens on 64 experts, half of them resident, 144 against 153 us) from 17 experts on: with
@@ -1391,6 +1436,7 @@ hipError_t launch_route_cache(hipStream_t s, int dtype, const RouteArgs& r, cons
       if (kind == kFull && r.router_packed) with(std::true_type{}, std::integral_constant<RouteKind, kFull>{});
       else if (kind == kFull) with(std::false_type{}, std::integral_constant<RouteKind, kFull>{});
       else if (kind == kTable) with(std::false_type{}, std::integral_constant<RouteKind, kTable>{});
+      else if (kind == kWide) with(std::false_type{}, std::integral_constant<RouteKind, kWide>{});
       else with(std::false_type{}, std::integral_constant<RouteKind, kOther>{});
       return hipGetLastError();
     }

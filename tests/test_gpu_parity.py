@@ -367,6 +367,7 @@ def test_odd_widths_take_the_generic_kernels(torch, P, d_model, d_ff):
     (16, 4, 6, 0, 128, "lru"),       # constrained: misses inside the call, in-order routine, waves of tokens
     (8, 2, 8, 0, 300, "lru"),        # fewer experts than one tile of 16
     (100, 6, 100, 0, 200, "lru"),    # 64 < E <= 256, table larger than a wave (LDS table)
+    (100, 6, 40, 1, 130, "lru"),     # 64 < E <= 256 on at most 64 slots, misses inside the call
     (64, 8, 64, 2, 144, "lru"),      # 64 slots, 64 buffers, shared experts
     (16, 4, 8, 0, 140, "gamma"),     # discounted-count policy
     (32, 4, 32, 0, 113, "lru"),      # just above the size from which the tile kernel is used, ragged last tile

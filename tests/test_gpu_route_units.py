@@ -26,7 +26,9 @@ def B():
 # (1024 / 8192 pairs are the limits of the ordering in LDS, 1024 tokens a pass of the grouping)
 @pytest.mark.parametrize("batch,E,K,ns,d,held", [(2, 24, 3, 0, 2080, 24), (17, 64, 8, 1, 64, 40), (127, 60, 8, 0, 64, 60),
                                                  (128, 64, 8, 0, 64, 30), (120, 8, 2, 1, 96, 6), (1024, 64, 8, 0, 32, 50),
-                                                 (1025, 32, 7, 1, 32, 32), (2100, 24, 3, 0, 32, 20), (16, 33, 4, 64, 1056, 30)])
+                                                 (1025, 32, 7, 1, 32, 32), (2100, 24, 3, 0, 32, 20), (16, 33, 4, 64, 1056, 30),
+                                                 # more experts than slots of the register table
+                                                 (112, 65, 2, 0, 64, 64), (130, 100, 5, 1, 2080, 60), (1030, 256, 3, 0, 32, 40)])
 def test_batch_that_hits(torch, B, batch, E, K, ns, d, held):
     f = 32
     gen = torch.Generator().manual_seed(batch * 1000 + E)
