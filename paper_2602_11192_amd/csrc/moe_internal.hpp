@@ -133,12 +133,13 @@ struct RouteScratch {
 // ... as the launch lays it out
 struct RouteWork {
   int32_t slices;         // of the contraction
+  int32_t et_per;         // expert tiles of a unit
   float* logits;          // [tile of 16 tokens][expert tile][256], with several slices [8 partial sums] of each ahead of the 256
   uint64_t* masks;        // [B] experts that a token selects, up to 64
 };
 
 // How a call of several bf16 tokens is routed: tiles of 16 tokens x tiles of 16 experts x slices of the contraction.
-struct RouteUnits { int tiles, slices, n_arrive; size_t logit_bytes, scratch_bytes; };
+struct RouteUnits { int tiles, slices, et_per, units, n_arrive; size_t logit_bytes, scratch_bytes; };
 RouteUnits route_units(int B, int E, int d);
 size_t route_scratch_bytes(int max_batch, int E, int d);       // of any call of up to max_batch tokens
 

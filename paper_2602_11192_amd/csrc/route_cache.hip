@@ -72,7 +72,8 @@ template <> struct Vec<uint16_t> {
 
 constexpr int kTileMaxE = 256;   // most experts the 16-token tile kernels keep logits for
 constexpr int kRouteSliceKb = 16; // fewest k-blocks of the contraction worth a slice of their own
-constexpr int kRouteMaxUnits = 256;   // ... and most workgroups that slicing may make: one per compute unit
+constexpr int kRouteMaxUnits = 256;   // ... and most workgroups that slicing may make: one per compute unit.  (From twice as many
+                                      // expert tiles on a unit takes several of them.)
 
 // ---------------------------------------------------------------- LDS layout
 struct LdsLayout {
@@ -905,7 +906,8 @@ __device__ __forceinline__ bool group_hits(unsigned char* smem, TileLds& tl, con
     if (b >= B) return 0;
     return masks ? __hip_atomic_load(masks + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : tl.sel[b];
   };
-  uint64_t mine = mask_of(tid);
+  uint64_t mine = mask_of(tid), ahead = mask_of(kChunk + tid);       // (of the next chunk: requested a chunk before its use)
+  const uint64_t mine0 = mine;
   behind();
   if constexpr (KIND != kFull) {
     if constexpr (KIND == kWide) {
@@ -952,7 +954,8 @@ __device__ __forceinline__ bool group_hits(unsigned char* smem, TileLds& tl, con
   count_chunk(0);
   int total = in_chunk;
   for (int c0 = kChunk; c0 < B; c0 += kChunk) {
-    mine = mask_of(c0 + tid);
+    mine = ahead;
+    ahead = mask_of(c0 + kChunk + tid);
     __syncthreads();
     count_chunk(c0);
     total += in_chunk;
@@ -998,7 +1001,8 @@ __device__ __forceinline__ bool group_hits(unsigned char* smem, TileLds& tl, con
     for (int c0 = 0; c0 < B; c0 += kChunk) {
       if (B > kChunk) {        // more than 1024 tokens: chunk by chunk once more
         __syncthreads();
-        mine = mask_of(c0 + tid);
+        mine = c0 == 0 ? mine0 : ahead;
+        ahead = mask_of(c0 + kChunk + tid);
         count_chunk(c0);
       }
       if (c0 + wave * kWave < B) {
@@ -1208,8 +1212,9 @@ __device__ __forceinline__ void gate_and_group(unsigned char* smem, TileLds& tl,
 // and, with whole tiles of 64 experts in one workgroup, the 320 KB that one compute unit had to pull in: row-major
 // fragments are 16 pieces of 64 bytes each, and the address unit sets the pace.
 // PACKED: W_r comes from the library's copy in operand order (pack_router_kernel), for the calls of 2 to 4 tokens that may
-// read it.  PAIRS: pairs of k-blocks a wave requests at a time.
-template <int PAIRS, bool PACKED, RouteKind KIND>
+// read it.  PAIRS: pairs of k-blocks a wave requests at a time.  SLICED: several slices, one expert tile per unit; else the whole
+// contraction and one tile or several (a kernel for each: with both in one a call of one unit takes 0.5 us more).
+template <int PAIRS, bool PACKED, RouteKind KIND, bool SLICED>
 __global__ void __launch_bounds__(kTileThreads) route_units_kernel(RouteArgs r, RouteWork rw, LayerState st, CallTables t, CacheCallArgs a) {
   typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
   typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -1221,20 +1226,24 @@ __global__ void __launch_bounds__(kTileThreads) route_units_kernel(RouteArgs r, 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 15, q = lane >> 4;
   const int E = a.E, d = r.d;
-  const int n_et = (E + 15) >> 4, units = n_et * rw.slices, n_tiles = (a.B + kTileTokens - 1) / kTileTokens;
+  const int n_et = (E + 15) >> 4, n_eu = SLICED ? n_et : (n_et + rw.et_per - 1) / rw.et_per;
+  const int slices = SLICED ? rw.slices : 1, units = n_eu * slices;
+  const int n_tiles = (a.B + kTileTokens - 1) / kTileTokens;
   const int tile = blockIdx.x / units, u = blockIdx.x - tile * units;
-  const int sl = u / n_et, et = u - sl * n_et;
+  const int sl = SLICED ? u / n_eu : 0;
+  const int et0 = SLICED ? u - sl * n_eu : u * rw.et_per, et1 = SLICED ? et0 + 1 : min(et0 + rw.et_per, n_et);      // expert tiles et0 to et1 - 1
   const int t0 = tile * kTileTokens;
   const int nkb = d >> 5;
   const int tok = t0 + n < a.B ? t0 + n : a.B - 1;          // clamped: in bounds, the column is dropped below
   const u32x4* xrow = reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(r.x) + (size_t)tok * d) + q;
   constexpr int w_step = PACKED ? 64 : 4;                   // (16-byte pieces between k-blocks)
-  const u32x4* wrow = PACKED ? static_cast<const u32x4*>(r.router_packed) + (size_t)et * nkb * 64 + lane
-                             : reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(r.router_w) + (size_t)min(et * 16 + n, E - 1) * d) + q;
   // the slice's chains: sl * half ... and the same + 8
-  const int half = kRouteChains / 2 / rw.slices;
-  if (wave < 2 * half) {
-    const int chain = sl * half + (wave < half ? wave : wave - half + kRouteChains / 2);
+  const int half = kRouteChains / 2 / slices;
+  const int chain = sl * half + (wave < half ? wave : wave - half + kRouteChains / 2);
+  const auto form_chain = [&](int et) {
+    if (SLICED && wave >= 2 * half) return;
+    const u32x4* wrow = PACKED ? static_cast<const u32x4*>(r.router_packed) + (size_t)et * nkb * 64 + lane
+                               : reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(r.router_w) + (size_t)min(et * 16 + n, E - 1) * d) + q;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     for (int kb0 = 2 * chain; kb0 < nkb; kb0 += 2 * PAIRS * kRouteChains) {
       u32x4 xb[2 * PAIRS], wa[2 * PAIRS];
@@ -1250,7 +1259,8 @@ __global__ void __launch_bounds__(kTileThreads) route_units_kernel(RouteArgs r, 
           acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wa[i]), __builtin_bit_cast(bf16x8, xb[i]), acc, 0, 0, 0);
     }
     *reinterpret_cast<f32x4*>(pz + wave * 256 + lane * 4) = acc;
-  }
+  };
+  form_chain(et0);
   // nobody changes the table before the last workgroup of this launch does: every workgroup may fetch it now
   RawTable raw{};
   if (KIND != kOther && wave == 0) raw = raw_load(st, a);
@@ -1266,37 +1276,53 @@ __global__ void __launch_bounds__(kTileThreads) route_units_kernel(RouteArgs r, 
   clear_tile_lds(tl, E);
   __syncthreads();
   const auto pair_sum = [&](int c) { return pz[c * 256 + el] + pz[(c + half) * 256 + el]; };
-  float z = 0.f;
-  if (rw.slices > 1) {
-    if (tid < half * 256) z = pair_sum(tid >> 8);
-  } else if (tid < 256) {
-    z = pair_sum(0);
-#pragma unroll
-    for (int c = 1; c < kRouteChains / 2; ++c) z += pair_sum(c);
-  }
-  if (units == 1) {
-    if (tid < 256 && el_row < E) tl.zs[el_tok][el_row] = z + bias[0];
+  // published: a unit's logits, or its pair sums [expert tile][8][256] where other units have the others
+  constexpr int parts = SLICED ? kRouteChains / 2 : 1;
+  float* zt = rw.logits + (size_t)tile * n_et * parts * 256;
+  const auto store = [&](int row, float z) {
+    __hip_atomic_store(zt + (size_t)row * 256 + tid, z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  if constexpr (SLICED) {
+    if (tid < half * 256) store(et0 * parts + sl * half, pair_sum(tid >> 8));
   } else {
-    // published: a unit's logits, or its pair sums [expert tile][8][256] where other units have the others
-    const int parts = rw.slices > 1 ? kRouteChains / 2 : 1;
-    float* zt = rw.logits + (size_t)tile * n_et * parts * 256;
-    if (tid < (rw.slices > 1 ? half : 1) * 256)
-      __hip_atomic_store(zt + (size_t)(et * parts + sl * half) * 256 + tid, z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int et = et0;; ++et) {
+      if (tid < 256) {
+        float z = pair_sum(0);
+#pragma unroll
+        for (int c = 1; c < kRouteChains / 2; ++c) z += pair_sum(c);
+        const int e = et * 16 + el_row;
+        if (units > 1) store(et, z);
+        else if (e < E) tl.zs[el_tok][e] = n_et == 1 ? z + bias[0] : z;
+      }
+      if (et + 1 == et1) break;
+      __syncthreads();
+      form_chain(et + 1);
+      __syncthreads();
+    }
+  }
+  if (!SLICED && units == 1) {
+    if (n_et > 1) {
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int e = ((tid >> 8) + j * (kTileThreads / 256)) * 16 + el_row;
+        if (e < E) tl.zs[el_tok][e] += bias[j];
+      }
+    }
+  } else {
     if (!arrive_last(r.arrive + 1 + tile, units, tl.last_arrived)) return;
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
       const int t16 = (tid >> 8) + j * (kTileThreads / 256), e = t16 * 16 + el_row;
       if (t16 < n_et) {
         const float* zp = zt + (size_t)t16 * parts * 256 + el;
-        float v = __builtin_bit_cast(float, load_published(zp));
-        if (parts > 1) {
-          float more[kRouteChains / 2 - 1];
+        float v[parts];
 #pragma unroll
-          for (int c = 1; c < kRouteChains / 2; ++c) more[c - 1] = __builtin_bit_cast(float, load_published(zp + c * 256));
+        for (int c = 0; c < parts; ++c) v[c] = __builtin_bit_cast(float, load_published(zp + c * 256));
+        float z = v[0];
 #pragma unroll
-          for (int c = 1; c < kRouteChains / 2; ++c) v += more[c - 1];
-        }
-        if (e < E) tl.zs[el_tok][e] = v + bias[j];
+        for (int c = 1; c < parts; ++c) z += v[c];
+        if (e < E) tl.zs[el_tok][e] = z + bias[j];
       }
     }
   }
@@ -1377,17 +1403,21 @@ __global__ void reset_kernel(LayerState st, int E, int C, int P, int clear_trace
 
 // Slices pay although they make units meet where one would do: 16 experts of 4096 columns, 8 / 64 tokens, one slice 12.7 / 15.3 us per
 // launch, four 9.0 / 11.0; 64 of 2048 columns, 16 / 64 tokens, two 11.0 / 12.2, four 10.2 / 11.8; layer calls on 32 of 1024 columns, 16 /
-// 64 tokens, one 21.1 / 25.7, two 20.8 / 25.0.
+// 64 tokens, one 21.1 / 25.7, two 20.8 / 25.0.  A unit that is alone in its tile publishes nothing: it is sliced from 2048 columns on
+// (4 / 64 tokens on 16 experts of 1024 columns 17.0 / 22.2 us per layer call, in two 18.6 / 22.5).
+// Several expert tiles per unit where the tiles alone make 512 units: 1024 tokens on 256 experts of 512 columns 111 us per
+// prompt call with a tile each, 94 with two, 83 with four; 2048 on 64 of 2048 144 and 139 with two.
 RouteUnits route_units(int B, int E, int d) {
   RouteUnits u{};
   u.tiles = (B + kTileTokens - 1) / kTileTokens;
   const int n_et = (E + 15) / 16, nkb = d / 32;
+  u.et_per = (int)std::max<int64_t>(1, std::min<int64_t>(n_et, (int64_t)u.tiles * n_et / kRouteMaxUnits));
   u.slices = 1;
-  while (u.slices < 4 && nkb / (2 * u.slices) >= kRouteSliceKb && u.tiles * n_et * u.slices * 2 <= kRouteMaxUnits) u.slices *= 2;
-  const size_t units = (size_t)u.tiles * n_et * u.slices;
+  while (u.slices < 4 && nkb / (2 * u.slices) >= (n_et * u.slices == 1 ? 2 : 1) * kRouteSliceKb && u.tiles * n_et * u.slices * 2 <= kRouteMaxUnits) u.slices *= 2;
+  u.units = u.tiles * ((n_et + u.et_per - 1) / u.et_per) * u.slices;
   u.n_arrive = 1 + u.tiles;
   // (one slice: the logits; several: the eight pair sums of every logit)
-  u.logit_bytes = (u.slices > 1 ? (size_t)u.tiles * n_et * kRouteChains / 2 : units) * 256 * sizeof(float);
+  u.logit_bytes = (size_t)u.tiles * n_et * (u.slices > 1 ? kRouteChains / 2 : 1) * 256 * sizeof(float);
   u.scratch_bytes = u.logit_bytes + (size_t)u.tiles * kTileTokens * sizeof(uint64_t);
   return u;
 }
@@ -1422,16 +1452,20 @@ hipError_t launch_route_cache(hipStream_t s, int dtype, const RouteArgs& r, cons
   if (dtype == MOE_DTYPE_BF16 && a.B >= least && a.E <= kTileMaxE && r.d % 32 == 0) {
     const RouteUnits ru = route_units(a.B, a.E, r.d);
     if (ru.n_arrive <= scratch.n_arrive && ru.scratch_bytes <= scratch.bytes) {
-      const RouteWork w{ru.slices, static_cast<float*>(scratch.ptr),
+      const RouteWork w{ru.slices, ru.et_per, static_cast<float*>(scratch.ptr),
                         reinterpret_cast<uint64_t*>(static_cast<char*>(scratch.ptr) + ru.logit_bytes)};
       const size_t bytes = std::max({kind == kFull ? 0 : lds, (size_t)kTileWaves * 256 * sizeof(float), stage_pairs(a.B, a.KS) ? (size_t)(a.B * a.KS + 3) / 4 * 32 : 0});
-      const dim3 units(ru.tiles * ((a.E + 15) / 16) * ru.slices), threads(kTileThreads);
+      const dim3 units(ru.units), threads(kTileThreads);
       const auto launch = [&](auto kernel) { launch_timed(kernel, units, threads, bytes, s, ev, r, w, st, t, a); };
       const int pairs = (r.d / 32 + 2 * kRouteChains - 1) / (2 * kRouteChains);      // of k-blocks in a chain
-      const auto with = [&](auto packed, auto k) {
-        constexpr bool P = decltype(packed)::value;
+      const auto of = [&](auto packed, auto k, auto sliced) {
+        constexpr bool P = decltype(packed)::value, S = decltype(sliced)::value;
         constexpr RouteKind Q = decltype(k)::value;
-        launch(pairs > 2 ? route_units_kernel<4, P, Q> : pairs > 1 ? route_units_kernel<2, P, Q> : route_units_kernel<1, P, Q>);
+        launch(pairs > 2 ? route_units_kernel<4, P, Q, S> : pairs > 1 ? route_units_kernel<2, P, Q, S> : route_units_kernel<1, P, Q, S>);
+      };
+      const auto with = [&](auto packed, auto k) {
+        if (ru.slices > 1) of(packed, k, std::true_type{});
+        else of(packed, k, std::false_type{});
       };
       if (kind == kFull && r.router_packed) with(std::true_type{}, std::integral_constant<RouteKind, kFull>{});
       else if (kind == kFull) with(std::false_type{}, std::integral_constant<RouteKind, kFull>{});

@@ -1,6 +1,6 @@
 """Routing of a batch in units of 16 tokens x 16 experts x a slice of the contraction: every lookup hits on a cache that does not hold
 every expert, pairs put in order in LDS at the limits of that, calls of more than 1024 tokens, contractions that the slices do
-not divide; against a stable sort of the selected experts and the layer in 64 bits."""
+not divide, more experts than slots; against a stable sort of the selected experts and the layer in 64 bits."""
 import numpy as np
 import pytest
 
@@ -28,7 +28,10 @@ def B():
                                                  (128, 64, 8, 0, 64, 30), (120, 8, 2, 1, 96, 6), (1024, 64, 8, 0, 32, 50),
                                                  (1025, 32, 7, 1, 32, 32), (2100, 24, 3, 0, 32, 20), (16, 33, 4, 64, 1056, 30),
                                                  # more experts than slots of the register table
-                                                 (112, 65, 2, 0, 64, 64), (130, 100, 5, 1, 2080, 60), (1030, 256, 3, 0, 32, 40)])
+                                                 (112, 65, 2, 0, 64, 64), (130, 100, 5, 1, 2080, 60), (1030, 256, 3, 0, 32, 40),
+                                                 # pairs in LDS that are no multiple of four; a wave's second round over its chain;
+                                                 # units of several expert tiles (above, too), of all of them
+                                                 (147, 64, 7, 0, 64, 64), (1024, 64, 4, 0, 4128, 64), (4100, 20, 2, 0, 32, 20)])
 def test_batch_that_hits(torch, B, batch, E, K, ns, d, held):
     f = 32
     gen = torch.Generator().manual_seed(batch * 1000 + E)
