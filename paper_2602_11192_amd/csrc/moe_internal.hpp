@@ -140,7 +140,7 @@ struct RouteWork {
 
 // How a call of several bf16 tokens is routed: tiles of 16 tokens x tiles of 16 experts x slices of the contraction.
 struct RouteUnits { int tiles, slices, et_per, units, n_arrive; size_t logit_bytes, scratch_bytes; };
-RouteUnits route_units(int B, int E, int d);
+RouteUnits route_units(int B, int E, int d, bool sliced);
 size_t route_scratch_bytes(int max_batch, int E, int d);       // of any call of up to max_batch tokens
 
 // Everything the single-launch decode kernel needs beyond FfnArgs: it routes and looks up itself.  Every

@@ -881,14 +881,19 @@ __device__ __forceinline__ uint64_t transpose_bits(uint64_t x) {
 }
 
 // One kernel per kind of call: code that a launch only jumps over is fetched cold with the rest, and its registers spill the others'.
-//   kFull    mode 0 on the register table, every expert known to be resident (then there are at most 64): no lookup can miss
+//   kFull    mode 0, at most 64 experts and slots, every expert known to be resident: no lookup can miss, so no buffer is taken or
+//            released and the size of the buffer tables (spare ones) does not matter
+//   kScored  the same under the discounted-count policy
 //   kTable   mode 0 on the register table, up to 64 experts
 //   kWide    mode 0 on the register table, 65 to 256 experts
-//   kOther   other tables, more experts, prompt streaming: one wave looks up in order
-enum RouteKind { kFull, kTable, kWide, kOther };
-template <RouteKind KIND> constexpr bool kMany = KIND == kWide || KIND == kOther;      // more than 64 logits of a token
+//   kOther   mode 0 on other tables: one wave looks up in order
+//   kPrompt  mode 2: prompt streaming
+enum RouteKind { kFull, kScored, kTable, kWide, kOther, kPrompt };
+template <RouteKind KIND> constexpr bool kHits = KIND == kFull || KIND == kScored;      // no lookup can miss
+template <RouteKind KIND> constexpr bool kColumns = KIND < kOther;       // selections travel as masks of columns
+template <RouteKind KIND> constexpr bool kMany = KIND >= kWide;          // more than 64 logits of a token
 
-// Phase 3 on the register table (LRU), run by ALL waves of the last workgroup.  The common case -
+// Phase 3 of kFull to kWide, run by ALL waves of the last workgroup.  The common case -
 // every lookup hits - is embarrassingly parallel: residency does not change, and the place of a pair in its group is the number
 // of earlier tokens that select the same expert.  A wave holds the selections of 64 tokens as one mask per lane; transposed, lane
 // e has the tokens of column e, and counts, prefix sums and the order of the groups are a few instructions in every wave alike.
@@ -909,7 +914,7 @@ __device__ __forceinline__ bool group_hits(unsigned char* smem, TileLds& tl, con
   uint64_t mine = mask_of(tid), ahead = mask_of(kChunk + tid);       // (of the next chunk: requested a chunk before its use)
   const uint64_t mine0 = mine;
   behind();
-  if constexpr (KIND != kFull) {
+  if constexpr (!kHits<KIND>) {
     if constexpr (KIND == kWide) {
       bool misses = tid < B && __popcll(mine) != K;
       for (int b = kChunk + tid; b < B; b += kChunk) misses |= __popcll(mask_of(b)) != K;
@@ -1080,20 +1085,37 @@ __device__ __forceinline__ bool group_hits(unsigned char* smem, TileLds& tl, con
   const int last = lane < C && f.exp >= 0 ? (KIND == kWide ? tl.slot_last[lane] : tl.last_lookup[f.exp]) : 0;
   if (last > 0) {
     f.tick = (uint64_t)(f.clock + last);
-    tl.touched[f.buf] = 1;
+    if constexpr (!kHits<KIND>) tl.touched[f.buf] = 1;
   }
-  wave_sync();
-  if (lane < P && tl.touched[lane]) f.used = a.seq;
-  const int src = lane - f.n_free;
-  const int z = __shfl(f.zomb, src < 0 ? 0 : src);
-  if (src >= 0 && src < f.n_zombie) f.free_b = z;
   if (lane < C) { st.tick[lane] = f.tick; st.expert_in[lane] = f.exp; st.buf_of_slot[lane] = f.buf; }
-  if (lane < P) { st.used_stamp[lane] = f.used; st.free_buf[lane] = f.free_b; st.zombie[lane] = f.zomb; }
+  if constexpr (!kHits<KIND>) {     // (where no lookup can miss, no buffer was ever released and nobody asks for the use stamps)
+    wave_sync();
+    if (lane < P && tl.touched[lane]) f.used = a.seq;
+    const int src = lane - f.n_free;
+    const int z = __shfl(f.zomb, src < 0 ? 0 : src);
+    if (src >= 0 && src < f.n_zombie) f.free_b = z;
+    if (lane < P) { st.used_stamp[lane] = f.used; st.free_buf[lane] = f.free_b; st.zombie[lane] = f.zomb; }
+    if (lane == 0) {
+      st.scalars[SC_NFREE] = f.n_free + f.n_zombie;
+      st.scalars[SC_NZOMBIE] = 0;
+    }
+  }
+  if constexpr (KIND == kScored) {       // Definition C.1: the discounted counts advance once per token
+    double score = lane < E ? st.score[lane] : 0.0;
+    for (int b0 = 0; b0 < B; b0 += kWave) {
+      const uint64_t m = mask_of(b0 + lane);
+      const int n = min(kWave, B - b0);
+      for (int j = 0; j < n; ++j) {
+        const uint32_t lo = (uint32_t)readlane_i((int)(uint32_t)m, j), hi = (uint32_t)readlane_i((int)(uint32_t)(m >> 32), j);
+        const uint32_t wanted = (lane < 32 ? lo >> lane : hi >> (lane - 32)) & 1u;
+        score = __dadd_rn(__dmul_rn(a.gamma, score), (double)wanted);
+      }
+    }
+    if (lane < E) st.score[lane] = score;
+  }
   if (lane == 0) {
     st.scalars[SC_CLOCK] = f.clock + B * K;
     st.scalars[SC_NRES] = f.n_res;
-    st.scalars[SC_NFREE] = f.n_free + f.n_zombie;
-    st.scalars[SC_NZOMBIE] = 0;
     st.scalars[SC_CALLSEQ] = a.seq;
     st.scalars[SC_TRACE_N] = f.trace_n + B * K;
     publish_record(a.mailbox, MOE_OK, 0, 0, n_routed + ns, B * K, f.n_res, a.seq);
@@ -1111,8 +1133,7 @@ __device__ __forceinline__ void gate_and_group(unsigned char* smem, TileLds& tl,
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int E = a.E, K = a.K, KS = a.KS, b = tile * kTileTokens + wave;
   const bool single = n_tiles == 1, mine = b < a.B;
-  constexpr bool kColumns = KIND != kOther;        // selections travel as masks of columns
-  if (kColumns && wave == 0 && lane < a.C && raw.exp >= 0) tl.map[raw.exp] = raw.buf << 8 | lane;
+  if (kColumns<KIND> && wave == 0 && lane < a.C && raw.exp >= 0) tl.map[raw.exp] = raw.buf << 8 | lane;
   if constexpr (KIND == kWide) {
     if (wave == 0) {
       wave_sync();
@@ -1130,11 +1151,11 @@ __device__ __forceinline__ void gate_and_group(unsigned char* smem, TileLds& tl,
     __syncthreads();
   }
   const LdsLayout L = lds_layout(E, a.C, a.P, a.n_shared, a.B, K, KS);
-  int32_t* idx_stage = KIND != kFull && stage_in_lds(a.B, KS) ? reinterpret_cast<int32_t*>(smem + L.idx_stage) : nullptr;
+  int32_t* idx_stage = !kHits<KIND> && stage_in_lds(a.B, KS) ? reinterpret_cast<int32_t*>(smem + L.idx_stage) : nullptr;
   constexpr int EPL = kMany<KIND> ? kTileMaxE / kWave : 1;
   Gate<1> g1;
   Gate<EPL> g4;
-  const bool few = !kMany<KIND> || (KIND == kOther && E <= kWave);
+  const bool few = !kMany<KIND> || (!kColumns<KIND> && E <= kWave);
   const auto publish = [&](uint64_t columns) {
     if (lane != 0) return;
     if (single) tl.sel[wave] = columns;
@@ -1143,8 +1164,8 @@ __device__ __forceinline__ void gate_and_group(unsigned char* smem, TileLds& tl,
   if (mine) {
     if (few) {
       select_experts<1>(tl.zs[wave], E, K, g1);
-      if constexpr (kColumns) publish(g1.top[0]);
-      if constexpr (KIND != kFull) write_selected<1, true>(g1, b, K, t.idx, nullptr, single ? idx_stage : nullptr);
+      if constexpr (kColumns<KIND>) publish(g1.top[0]);
+      if constexpr (!kHits<KIND>) write_selected<1, true>(g1, b, K, t.idx, nullptr, single ? idx_stage : nullptr);
     } else {
       select_experts<EPL>(tl.zs[wave], E, K, g4);
       if constexpr (KIND == kWide) {
@@ -1173,7 +1194,7 @@ __device__ __forceinline__ void gate_and_group(unsigned char* smem, TileLds& tl,
     weights();
     return;
   }
-  if constexpr (kColumns) {
+  if constexpr (kColumns<KIND>) {
     // the weights fill the time that the others' selections take to arrive; with nothing to wait for they come last
     const bool hits = group_hits<KIND>(smem, tl, raw, single ? nullptr : masks, st, t, a, [&] { if (!single) weights(); });
     if (hits) {
@@ -1181,23 +1202,19 @@ __device__ __forceinline__ void gate_and_group(unsigned char* smem, TileLds& tl,
       return;
     }
   }
-  if constexpr (KIND != kFull) {
+  if constexpr (!kHits<KIND>) {
     // in order, one wave; the others have the weights of their tokens to form where that is not done
     if (!single && idx_stage)
       for (int i = tid; i < a.B * K; i += kTileThreads) idx_stage[i] = (int)load_published(t.idx + i);
     __syncthreads();
-    if (single || KIND == kOther) weights();
+    if (single || !kColumns<KIND>) weights();
     if (wave != 0) return;
     if (!idx_stage) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");     // reads the other workgroups' results directly
     const int32_t* in_order = idx_stage ? idx_stage : t.idx;
     int32_t* pair_stage = idx_stage ? reinterpret_cast<int32_t*>(smem + L.pair_stage) : t.pair_buf;
-    if constexpr (kColumns) {
-      cache_phase_fast(table_of(raw), smem, L, in_order, pair_stage, st, t, a);
-    } else {
-      if (a.mode == 2) prefill_phase(smem, L, in_order, pair_stage, st, t, a);
-      else if (fast_table(a.policy, a.C, a.P, a.n_shared)) cache_phase_fast(table_of(raw_load(st, a)), smem, L, in_order, pair_stage, st, t, a);
-      else cache_phase_general(smem, L, in_order, pair_stage, st, t, a);
-    }
+    if constexpr (kColumns<KIND>) cache_phase_fast(table_of(raw), smem, L, in_order, pair_stage, st, t, a);
+    else if constexpr (KIND == kPrompt) prefill_phase(smem, L, in_order, pair_stage, st, t, a);
+    else cache_phase_general(smem, L, in_order, pair_stage, st, t, a);
   }
 }
 
@@ -1263,7 +1280,7 @@ __global__ void __launch_bounds__(kTileThreads) route_units_kernel(RouteArgs r, 
   form_chain(et0);
   // nobody changes the table before the last workgroup of this launch does: every workgroup may fetch it now
   RawTable raw{};
-  if (KIND != kOther && wave == 0) raw = raw_load(st, a);
+  if (kColumns<KIND> && wave == 0) raw = raw_load(st, a);
   // element el = tid % 256 of expert tile tid / 256 + 4 j: the MFMA leaves rows 4 (ln / 16) + el % 4, token ln % 16 with ln = el / 4
   const int el = tid & 255, el_tok = (el >> 2) & 15, el_row = (el >> 6) * 4 + (el & 3);
   constexpr int NJ = kMany<KIND> ? kTileMaxE / 16 / (kTileThreads / 256) : 1;
@@ -1339,7 +1356,7 @@ __global__ void __launch_bounds__(kTileThreads) route_small_fp32_kernel(RouteArg
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int E = a.E, d = r.d;
   RawTable raw{};
-  if (KIND != kOther && wave == 0) raw = raw_load(st, a);
+  if (kColumns<KIND> && wave == 0) raw = raw_load(st, a);
   clear_tile_lds(tl, E);
   const int n_vec = d / 4, n_items = a.B * E;
   constexpr int U = 4;                                    // products of a wave in flight together
@@ -1407,13 +1424,13 @@ __global__ void reset_kernel(LayerState st, int E, int C, int P, int clear_trace
 // (4 / 64 tokens on 16 experts of 1024 columns 17.0 / 22.2 us per layer call, in two 18.6 / 22.5).
 // Several expert tiles per unit where the tiles alone make 512 units: 1024 tokens on 256 experts of 512 columns 111 us per
 // prompt call with a tile each, 94 with two, 83 with four; 2048 on 64 of 2048 144 and 139 with two.
-RouteUnits route_units(int B, int E, int d) {
+RouteUnits route_units(int B, int E, int d, bool sliced) {
   RouteUnits u{};
   u.tiles = (B + kTileTokens - 1) / kTileTokens;
   const int n_et = (E + 15) / 16, nkb = d / 32;
   u.et_per = (int)std::max<int64_t>(1, std::min<int64_t>(n_et, (int64_t)u.tiles * n_et / kRouteMaxUnits));
   u.slices = 1;
-  while (u.slices < 4 && nkb / (2 * u.slices) >= (n_et * u.slices == 1 ? 2 : 1) * kRouteSliceKb && u.tiles * n_et * u.slices * 2 <= kRouteMaxUnits) u.slices *= 2;
+  while (sliced && u.slices < 4 && nkb / (2 * u.slices) >= (n_et * u.slices == 1 ? 2 : 1) * kRouteSliceKb && u.tiles * n_et * u.slices * 2 <= kRouteMaxUnits) u.slices *= 2;
   u.units = u.tiles * ((n_et + u.et_per - 1) / u.et_per) * u.slices;
   u.n_arrive = 1 + u.tiles;
   // (one slice: the logits; several: the eight pair sums of every logit)
@@ -1423,7 +1440,7 @@ RouteUnits route_units(int B, int E, int d) {
 }
 
 size_t route_scratch_bytes(int max_batch, int E, int d) {
-  const RouteUnits u = route_units(max_batch, E, d);     // (a smaller call may be sliced further, while its units are few enough)
+  const RouteUnits u = route_units(max_batch, E, d, true);     // (a smaller call may be sliced further, while its units are few enough)
   const size_t sliced = (size_t)std::min(u.tiles * ((E + 15) / 16), kRouteMaxUnits / 2) * (kRouteChains / 2) * 256 * sizeof(float);
   return std::max(u.logit_bytes, sliced) + (size_t)u.tiles * kTileTokens * sizeof(uint64_t);
 }
@@ -1440,21 +1457,26 @@ hipError_t launch_route_cache(hipStream_t s, int dtype, const RouteArgs& r, cons
   if (waves > a.E) waves = a.E;
   dim3 grid(a.B), block(64 * waves);
   const size_t lds = route_cache_lds_bytes(a.E, a.C, a.P, a.n_shared, a.B, a.K, a.KS);
-  const RouteKind kind = a.mode != 0 || a.E > kTileMaxE || !fast_table(a.policy, a.C, a.P, a.n_shared) ? kOther
-                         : a.E > kWave ? kWide : a.full ? kFull : kTable;
-  // Units where every lookup is known to hit (392 points of 8-256 experts, 1024-4096 columns, 2-1024 tokens: none slower than the
-  // kernels before, 1.50x in the mean; 64 x 2048, 16 / 64 / 1024 tokens 10.8 / 12.6 / 19.4 against 13.2 / 21.1 / 28.9 us in layer
-  // calls) and on the register table (16 tokens on 64 experts, half of them resident, 144 against 153 us) from 17 experts on: with
-  // fewer, and a wave that looks up in order, a workgroup per token keeps up to 112 tokens (16 tokens, 8 experts, misses 21.7
-  // against 22.7 us).  Where one wave looks up in order whatever routes, from 112 tokens too (64 tokens on 16 experts under
-  // discounted counts 115.8 against 121.1 us), prompts on more than 32 experts from 32.
-  const int least = kind == kFull ? 2 : kind == kTable ? (a.E > 16 ? 2 : 112) : a.mode == 2 && a.E > 32 ? 32 : 112;
+  const RouteKind kind = a.mode == 0 && a.full && a.E <= kWave && a.C <= kWave ? (a.policy == MOE_POLICY_LRU ? kFull : kScored)
+                         : a.mode == 2 ? kPrompt
+                         : a.E > kTileMaxE || !fast_table(a.policy, a.C, a.P, a.n_shared) ? kOther
+                         : a.E > kWave ? kWide : kTable;
+  const bool hits = kind == kFull || kind == kScored;
+  // Units from two tokens on where every lookup is known to hit, whatever the policy and the spare buffers, so that a full cache routes a
+  // batch bit for bit as the allocation-free entry point does (30 points of 8 to 64 experts of 1024 to 4096 columns, 4 to 1024 tokens: 1.19x
+  // in the mean against the kernels before, none slower; discounted counts, 64 tokens on 64 / 16 experts, looked up in order by one wave
+  // 338 / 94.5 us per layer call, here 118 / 37) and on the register table (16 tokens on 64 experts, half of them resident, 144
+  // against 153 us) from 17 experts on: with fewer, and a wave that looks up in order, a workgroup per token keeps up to 112 tokens
+  // (16 tokens, 8 experts, misses 21.7 against 22.7 us).  From 112 tokens, too, where one wave looks up in order whatever routes (64
+  // tokens on 16 experts under discounted counts 115.8 against 121.1 us), and with more than 64 experts (112 tokens that hit on 128
+  // 89 against 108 us); prompts on more than 32 experts from 32.
+  const int least = hits ? 2 : kind == kTable ? (a.E > 16 ? 2 : 112) : kind == kPrompt && a.E > 32 ? 32 : 112;
   if (dtype == MOE_DTYPE_BF16 && a.B >= least && a.E <= kTileMaxE && r.d % 32 == 0) {
-    const RouteUnits ru = route_units(a.B, a.E, r.d);
+    const RouteUnits ru = route_units(a.B, a.E, r.d, kind != kOther);      // (lookups in order take far longer than a slice saves)
     if (ru.n_arrive <= scratch.n_arrive && ru.scratch_bytes <= scratch.bytes) {
       const RouteWork w{ru.slices, ru.et_per, static_cast<float*>(scratch.ptr),
                         reinterpret_cast<uint64_t*>(static_cast<char*>(scratch.ptr) + ru.logit_bytes)};
-      const size_t bytes = std::max({kind == kFull ? 0 : lds, (size_t)kTileWaves * 256 * sizeof(float), stage_pairs(a.B, a.KS) ? (size_t)(a.B * a.KS + 3) / 4 * 32 : 0});
+      const size_t bytes = std::max({hits ? 0 : lds, (size_t)kTileWaves * 256 * sizeof(float), stage_pairs(a.B, a.KS) ? (size_t)(a.B * a.KS + 3) / 4 * 32 : 0});
       const dim3 units(ru.units), threads(kTileThreads);
       const auto launch = [&](auto kernel) { launch_timed(kernel, units, threads, bytes, s, ev, r, w, st, t, a); };
       const int pairs = (r.d / 32 + 2 * kRouteChains - 1) / (2 * kRouteChains);      // of k-blocks in a chain
@@ -1464,21 +1486,26 @@ hipError_t launch_route_cache(hipStream_t s, int dtype, const RouteArgs& r, cons
         launch(pairs > 2 ? route_units_kernel<4, P, Q, S> : pairs > 1 ? route_units_kernel<2, P, Q, S> : route_units_kernel<1, P, Q, S>);
       };
       const auto with = [&](auto packed, auto k) {
-        if (ru.slices > 1) of(packed, k, std::true_type{});
-        else of(packed, k, std::false_type{});
+        if constexpr (decltype(k)::value != kOther)
+          if (ru.slices > 1) return of(packed, k, std::true_type{});
+        of(packed, k, std::false_type{});
       };
-      if (kind == kFull && r.router_packed) with(std::true_type{}, std::integral_constant<RouteKind, kFull>{});
-      else if (kind == kFull) with(std::false_type{}, std::integral_constant<RouteKind, kFull>{});
-      else if (kind == kTable) with(std::false_type{}, std::integral_constant<RouteKind, kTable>{});
-      else if (kind == kWide) with(std::false_type{}, std::integral_constant<RouteKind, kWide>{});
-      else with(std::false_type{}, std::integral_constant<RouteKind, kOther>{});
+#define MOE_KIND(K) std::integral_constant<RouteKind, K>{}
+      if (kind == kFull && r.router_packed) with(std::true_type{}, MOE_KIND(kFull));
+      else if (kind == kFull) with(std::false_type{}, MOE_KIND(kFull));
+      else if (kind == kScored) with(std::false_type{}, MOE_KIND(kScored));
+      else if (kind == kTable) with(std::false_type{}, MOE_KIND(kTable));
+      else if (kind == kWide) with(std::false_type{}, MOE_KIND(kWide));
+      else if (kind == kPrompt) with(std::false_type{}, MOE_KIND(kPrompt));
+      else with(std::false_type{}, MOE_KIND(kOther));
+#undef MOE_KIND
       return hipGetLastError();
     }
   }
   if (dtype == MOE_DTYPE_FP32 && a.B >= 2 && a.B <= 8 && a.B * a.E <= kSmallRouterItems &&
       (size_t)a.B * a.E * r.d * sizeof(float) <= kSmallRouterBytes) {
-    const auto small = kind == kFull ? route_small_fp32_kernel<kFull> : kind == kTable ? route_small_fp32_kernel<kTable> : route_small_fp32_kernel<kOther>;
-    launch_timed(small, dim3(1), dim3(kTileThreads), kind == kFull ? 0 : lds, s, ev, r, st, t, a);
+    const auto small = kind == kFull ? route_small_fp32_kernel<kFull> : kind == kScored ? route_small_fp32_kernel<kScored> : kind == kTable ? route_small_fp32_kernel<kTable> : route_small_fp32_kernel<kOther>;
+    launch_timed(small, dim3(1), dim3(kTileThreads), hits ? 0 : lds, s, ev, r, st, t, a);
     return hipGetLastError();
   }
   const auto launch = [&](auto type) {

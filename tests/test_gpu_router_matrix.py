@@ -30,10 +30,10 @@ def inputs(torch, B, batch):
     return router, x, bias, blocks, pool
 
 
-def make(B, router, pool, capacity, batch):
+def make(B, router, pool, capacity, batch, **kw):
     return B.MoECache(n_layers=1, n_experts=E, top_k=K, d_model=D, d_ff=F, capacity=capacity, dtype=B.MOE_DTYPE_BF16,
                       router_w=router, expert_pool=pool.pin_memory(), max_batch=batch, pool_layout=B.MOE_LAYOUT_TILED,
-                      fetch_mode=B.MOE_FETCH_IN_KERNEL)
+                      fetch_mode=B.MOE_FETCH_IN_KERNEL, **kw)
 
 
 @pytest.mark.parametrize("call,capacity,batch", [("decode", 64, 5), ("decode", 64, 16), ("decode", 64, 40), ("decode", 16, 2),
@@ -63,10 +63,22 @@ def test_a_router_changed_in_place_is_followed(torch, call, capacity, batch):
 
 @pytest.mark.parametrize("batch", [5, 16, 31, 40, 130])
 def test_batched_calls_route_as_the_allocation_free_entry_point(torch, batch):
+    same_as_allocation_free(torch, batch)
+
+
+# caches whose tables are not the register table (neither takes the single launch, so two tokens are a batched call, too)
+@pytest.mark.parametrize("policy,staging", [("gamma", 0), ("lru", 16)])
+@pytest.mark.parametrize("batch", [2, 16, 40, 111, 130])
+def test_full_caches_of_any_policy_and_spare_buffers_do(torch, policy, staging, batch):
+    from paper_2602_11192_amd import binding as B
+    same_as_allocation_free(torch, batch, staging_buffers=staging, **(dict(policy=B.MOE_POLICY_GAMMA, gamma=0.9) if policy == "gamma" else {}))
+
+
+def same_as_allocation_free(torch, batch, **kw):
     from paper_2602_11192_amd import binding as B
     router, x, bias, blocks, pool = inputs(torch, B, batch)
     rd, xd, bd = router.cuda(), x.cuda(), bias.cuda()
-    cache = make(B, rd, pool, E, batch)
+    cache = make(B, rd, pool, E, batch, **kw)
     cache.moe_cache_prefill_pins(0, list(range(E)))
     print("same routing, batch", batch, flush=True)
     out = []
