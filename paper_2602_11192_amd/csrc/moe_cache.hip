@@ -810,7 +810,8 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   a.pin_ids = nullptr; a.miss_list = c->miss_list; a.max_miss = c->max_miss;
   a.full = c->full[layer];
   a.mailbox = a.full ? nullptr : c->mailbox;       // (every lookup hits: nobody reads the record)
-  const int g_max = (int)std::min<size_t>((size_t)batch * K, (size_t)c->P) + cf.n_shared;
+  // (a buffer per expert where all are resident: spare buffers choose no other kernels than the allocation-free entry point takes)
+  const int g_max = (int)std::min<size_t>((size_t)batch * K, (size_t)(a.full ? E : c->P)) + cf.n_shared;
   const FfnPlan plan = plan_ffn(cf.pool_layout, d, cf.d_ff, batch, c->full[layer] != 0, g_max, c->expert_bytes);
   a.work = plan_work(plan, batch, KS, g_max, d, cf.d_ff);
   HIPCHK(launch_route_cache(s, cf.dtype, ra, state_of(c, layer), c->t, a, RouteScratch{c->o, c->o_bytes, c->n_arrive}, ps ? ps->route : KernelEvents{}));

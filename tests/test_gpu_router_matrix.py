@@ -95,3 +95,23 @@ def same_as_allocation_free(torch, batch, **kw):
     for a, b in zip(*out):
         assert torch.equal(a, b)
     cache.close()
+
+
+def test_spare_buffers_choose_no_other_expert_kernel(torch):
+    # 6 tokens x 2 of 8 experts of 29 MB: the one-launch FFN; were every pair to have a buffer of its own, the grouped GEMM
+    from paper_2602_11192_amd import binding as B
+    n, k, d, f, batch = 8, 2, 2048, 2400, 6
+    gen = torch.Generator(device="cuda:0").manual_seed(1)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda:0")
+    router, x, bias = (rnd(n, d) * d ** -0.5).bfloat16(), rnd(batch, d).bfloat16(), rnd(batch, n)
+    blocks = (rnd(n * 3 * d * f) * d ** -0.5).bfloat16()         # (any values in tiled order are an expert)
+    y = [torch.full((batch, d), 7.0, dtype=torch.bfloat16, device="cuda:0") for _ in range(2)]
+    shape = dict(n_experts=n, top_k=k, d_model=d, d_ff=f, dtype=B.MOE_DTYPE_BF16, pool_layout=B.MOE_LAYOUT_TILED, router_w=router)
+    B.moe_layer_decode_resident_noalloc(experts=blocks, x=x, y=y[0], logit_bias=bias, **shape)
+    cache = B.MoECache(n_layers=1, n_shared=0, capacity=n, expert_pool=blocks.cpu().pin_memory(), max_batch=batch, staging_buffers=8,
+                       fetch_mode=B.MOE_FETCH_IN_KERNEL, **shape)
+    cache.moe_cache_prefill_pins(0, list(range(n)))
+    cache.moe_layer_decode(0, x, y[1], bias)
+    torch.cuda.synchronize()
+    assert torch.equal(y[0], y[1])
+    cache.close()
