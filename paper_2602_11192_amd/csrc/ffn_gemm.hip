@@ -261,7 +261,7 @@ __global__ void __launch_bounds__(256, MINW) ffn_few_kernel(FfnArgs a) {
   const int nkb = (NMAT == 2 ? a.d : a.f) >> 5, n_rt = (NMAT == 2 ? a.f : a.d) >> 4;
   const int rt0 = (rb * WAVES + wave) * RT;
   if (rt0 >= n_rt) return;
-  const char* wsrc = (a.fetch != 0 && miss != 0) ? a.pool + (size_t)item.y * a.expert_bytes : group_weights(a, item.y);
+  const char* wsrc = group_weights(a, item.y);    // (experts streamed from the host take the large tile)
   const char* wp[RT];
 #pragma unroll
   for (int i = 0; i < RT; ++i) {

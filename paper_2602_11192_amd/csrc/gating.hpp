@@ -182,8 +182,9 @@ __device__ __forceinline__ void gate_token(const float* zs, int b, int E, int K,
   if (lane < KS - K) wpair_g[(size_t)b * KS + K + lane] = 1.0f;  // shared experts: weight 1
 }
 
-// The same in three steps, for a kernel that sets them apart: which experts run
-// (select_experts), their ids in ascending order (write_selected), their weights (write_weights).
+// The same in steps, for a kernel that sets them apart: which experts run (select_experts), their ids in ascending order
+// (write_selected), their weights (write_weights).  (gate_token made of these gives the kernels around it other code: 64 tokens on
+// 200 experts, looked up in order, 172 -> 175 to 178 us per layer call, one token on 16 18.2 -> 18.4 to 19.4.)
 template <int EPL> struct Gate {
   float z[EPL];
   uint64_t top[EPL];       // selected set, one mask per 64 experts
@@ -200,9 +201,9 @@ __device__ __forceinline__ void select_experts(const float* zs, int E, int K, Ga
   top_select<EPL, kRounds>(g.z, E, K, g.top);
 }
 
-// kPublish: idx_g is written at device scope, for another workgroup of the same launch to read.
-template <int EPL, bool kPublish>
-__device__ __forceinline__ void write_selected(const Gate<EPL>& g, int b, int K, int32_t* idx_g, int32_t* user_idx, int32_t* idx_stage) {
+// (idx_g is written at device scope, for another workgroup of the same launch to read)
+template <int EPL>
+__device__ __forceinline__ void write_selected(const Gate<EPL>& g, int b, int K, int32_t* idx_g, int32_t* idx_stage) {
   const int lane = threadIdx.x & 63;
   int base = 0;
 #pragma unroll
@@ -210,19 +211,16 @@ __device__ __forceinline__ void write_selected(const Gate<EPL>& g, int b, int K,
     if ((g.top[i] >> lane) & 1) {
       const size_t pos = (size_t)b * K + base + __popcll(g.top[i] & ((1ull << lane) - 1ull));
       const int e = lane + i * kWave;
-      if constexpr (kPublish)
-        __hip_atomic_store(&idx_g[pos], e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      else
-        idx_g[pos] = e;
+      __hip_atomic_store(&idx_g[pos], e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (idx_stage) idx_stage[pos] = e;
-      if (user_idx) user_idx[pos] = e;
     }
     base += __popcll(g.top[i]);
   }
 }
 
-template <int EPL>
-__device__ __forceinline__ void write_weights(const Gate<EPL>& g, int b, int E, int K, int KS, int norm_topk, float* wpair_g, float* user_w) {
+// ids(pos, e): expert e is at `pos` of idx; what a caller has to write of that beside the weight
+template <int EPL, typename Ids>
+__device__ __forceinline__ void write_weights(const Gate<EPL>& g, int b, int E, int K, int KS, int norm_topk, float* wpair_g, float* user_w, Ids ids) {
   const int lane = threadIdx.x & 63;
   float zmax = -INFINITY;
 #pragma unroll
@@ -249,6 +247,7 @@ __device__ __forceinline__ void write_weights(const Gate<EPL>& g, int b, int E, 
     if ((g.top[i] >> lane) & 1) {
       const int pos = base + __popcll(g.top[i] & ((1ull << lane) - 1ull));   // ascending expert id
       const float w = norm_topk ? p[i] / selsum : p[i];
+      ids((size_t)b * K + pos, lane + i * kWave);
       wpair_g[(size_t)b * KS + pos] = w;
       if (user_w) user_w[(size_t)b * K + pos] = w;
     }

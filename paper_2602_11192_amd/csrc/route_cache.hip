@@ -1170,7 +1170,7 @@ __device__ __forceinline__ void gate_and_group(unsigned char* smem, TileLds& tl,
     if (few) {
       select_experts<1>(tl.zs[wave], E, K, g1);
       if constexpr (kColumns<KIND>) publish(g1.top[0]);
-      if constexpr (!kHits<KIND>) write_selected<1, true>(g1, b, K, t.idx, nullptr, single ? idx_stage : nullptr);
+      if constexpr (!kHits<KIND>) write_selected<1>(g1, b, K, t.idx, single ? idx_stage : nullptr);
     } else {
       select_experts<EPL>(tl.zs[wave], E, K, g4);
       if constexpr (KIND == kWide) {
@@ -1180,18 +1180,14 @@ __device__ __forceinline__ void gate_and_group(unsigned char* smem, TileLds& tl,
         for (int i = 1; i < EPL; ++i) word = e >> 6 == i ? g4.top[i] : word;
         publish(__ballot(tl.col_map[lane] >= 0 && ((word >> (e & 63)) & 1) != 0));
       }
-      write_selected<EPL, true>(g4, b, K, t.idx, nullptr, single ? idx_stage : nullptr);
+      write_selected<EPL>(g4, b, K, t.idx, single ? idx_stage : nullptr);
     }
   }
   const auto weights = [&] {
     if (!mine) return;
-    if (few) {
-      if (r.user_idx) write_selected<1, false>(g1, b, K, r.user_idx, nullptr, nullptr);
-      write_weights<1>(g1, b, E, K, KS, r.norm_topk, t.wpair, r.user_w);
-    } else {
-      if (r.user_idx) write_selected<EPL, false>(g4, b, K, r.user_idx, nullptr, nullptr);
-      write_weights<EPL>(g4, b, E, K, KS, r.norm_topk, t.wpair, r.user_w);
-    }
+    const auto ids = [&](size_t pos, int e) { if (r.user_idx) r.user_idx[pos] = e; };
+    if (few) write_weights<1>(g1, b, E, K, KS, r.norm_topk, t.wpair, r.user_w, ids);
+    else write_weights<EPL>(g4, b, E, K, KS, r.norm_topk, t.wpair, r.user_w, ids);
   };
   if (single) {
     __syncthreads();
