@@ -155,7 +155,13 @@ __global__ void __launch_bounds__(64 * kRowsPerBlock) down_rowmajor(FfnArgs a) {
 // flight: at d = 64 a wave holds four rows at a time where the kernels above keep three quarters of it idle.
 constexpr int kTokenThreads = 1024, kTokenRows = 4;
 constexpr size_t kTokenLds = 60 << 10;
-constexpr int64_t kTokenAlways = 200 << 10, kTokenMost = 1 << 20, kTokenBase = 100 << 10, kTokenPerPair = 32 << 10;
+constexpr int64_t kTokenMost = 1 << 20;
+inline int token_lanes(int pieces) { return pieces > 32 ? 64 : pieces > 16 ? 32 : 16; }       // ... of a row of so many
+// steps of a workgroup over `rows` rows: as many rows at a time as its groups of lanes have in flight, 16 bytes a lane at a time
+inline int64_t token_steps(int64_t rows, int pieces) {
+  const int lanes = token_lanes(pieces), at_once = kTokenRows * kTokenThreads / lanes;
+  return (rows + at_once - 1) / at_once * ((pieces + lanes - 1) / lanes);
+}
 inline size_t token_lds(int KS, int d, int f) { return ((size_t)d + (size_t)KS * (f + d) + 2 * KS) * 4; }
 
 // the sum over each group of 16, 32 or 64 lanes
@@ -323,27 +329,33 @@ hipError_t launch_ffn_rowmajor(hipStream_t s, int dtype, const FfnArgs& a, Kerne
   return hipGetLastError();
 }
 
-// A compute unit pulls its token's weights in at ~30 us per MB, however few the tokens; the kernels per expert pay ~1.2 us for each
-// token of a group on top of their three launches.  So: up to 200 KB per token always, then as long as the experts see pairs enough.
-// us per call, per expert / per token, fp32: 64 x 128, 2 of 8 experts (192 KB) 1 token 15.2 / 12.9, 4 15.8 / 15.5, 16 20.7 / 17.8, 64
-// 35.8 / 19.4, 256 99 / 28.3; 128 x 128, 2 of 8 (384 KB) 16 tokens (4 per expert) 20.7 / 24.0, 64 35.6 / 25.7; 128 x 256, 2 of 8 (768 KB)
-// 64 tokens (16 per expert) 36.5 / 37.9, 256 102 / 47; 64 x 128, 8 of 16 (768 KB) 16 tokens (8) 24.2 / 33.9, 64 (32) 53 / 40.
-bool ffn_token_supported(int pool_layout, int dtype, int batch, int KS, int groups, int d, int f) {
+// A workgroup's time follows its steps, ~3 us each in fp32 and ~4 in bf16 beside 7 fixed, not its bytes: fp32, 2 of 8 experts, 1 token, 64 x 128
+// (192 KB, 1 + 1 steps) 12.9 us per call, 64 x 144 (216 KB, 2 + 2) 16.4, 96 x 128 (288 KB, 2 + 2) 19.2, 128 x 128 (384 KB, 2 + 2) 19.1; bf16, 2 of 8 of
+// 64 x 256 (192 KB, 2 + 1) 19.3.  The kernels per expert take 16.4 us, the rate at which four launches are issued, until the
+// tokens of their largest group and all pairs together cost more.  Counted in thirds of an fp32 step (a
+// bf16 step has four), against the kernels per expert, us per call, here / there:
+//   two steps in all, the least there is, in fp32; in bf16 only for one token:        fp32 64 x 128, 2 of 8, 1 / 16 tokens 12.9 / 16.3, 17.6 /
+//     19.7, bf16 128 x 256, 1 of 8, 1 / 8 tokens 15.7 / 16.2, 17.3 / 16.2
+//   a third more for every 32 pairs, and for every 4 tokens of the largest group that have 64 pieces of a row of W_g or W_d to add
+//     up: fp32 128 x 128, 2 of 8, 16 / 64 tokens 24.1 / 19.6, 25.1 / 26.0; 64 x 80, 4 of 16, 25.6 / 22.7, 25.9 / 32.6
+// 1430 points (130 shapes of 4 to 64 experts, up to 1024 tokens): 1.36x in the mean against the kernels per expert, 24 of
+// them more than 2 % slower (the worst 1.14x); the better of the two at every point would be 1.37x.
+bool ffn_token_supported(int pool_layout, int dtype, int batch, int K, int n_shared, int E, int d, int f) {
   if (pool_layout != MOE_LAYOUT_ROWMAJOR) return false;
-  const int elem = dtype == MOE_DTYPE_FP32 ? 4 : 2;
-  if (f % (16 / elem) != 0 || KS > kTokenThreads || token_lds(KS, d, f) > kTokenLds) return false;
-  const int64_t bytes = (int64_t)KS * 3 * d * f * elem, rounds = ((int64_t)batch + 255) / 256;       // a workgroup per compute unit
-  const int64_t pairs = (int64_t)batch * KS / groups;                                               // of an expert, in the mean
-  return bytes <= kTokenMost && bytes * rounds <= std::max(kTokenAlways, kTokenBase + kTokenPerPair * pairs);
+  const int KS = K + n_shared, elem = dtype == MOE_DTYPE_FP32 ? 4 : 2, V = 16 / elem;
+  if (f % V != 0 || KS > kTokenThreads || token_lds(KS, d, f) > kTokenLds || (int64_t)KS * 3 * d * f * elem > kTokenMost) return false;
+  const int64_t steps = token_steps((int64_t)KS * f, d / V) + token_steps((int64_t)KS * d, f / V), rounds = ((int64_t)batch + 255) / 256;
+  const int64_t pairs = (int64_t)batch * K, largest8 = n_shared > 0 ? 8 * (int64_t)batch : 8 * pairs / std::min<int64_t>(pairs, E);     // (in the mean)
+  const int64_t pieces64 = (d / V + 63) / 64 + (f / V + 63) / 64;
+  return 32 * steps * rounds * (dtype == MOE_DTYPE_FP32 ? 3 : 4) <= 32 * (batch == 1 ? 8 : 6) + (int64_t)batch * KS + largest8 * pieces64;
 }
 
 hipError_t launch_ffn_token(hipStream_t s, int dtype, const FfnArgs& a, int batch, void* y, KernelEvents ev) {
-  const auto lanes = [&](int n) { return n > 32 ? 64 : n > 16 ? 32 : 16; };       // 16-byte pieces of a row
   const size_t lds = token_lds(a.KS, a.d, a.f);
   if (dtype == MOE_DTYPE_FP32)
-    launch_timed(ffn_token_rowmajor<float>, dim3(batch), dim3(kTokenThreads), lds, s, ev, a, (float*)y, lanes(a.d / 4), lanes(a.f / 4));
+    launch_timed(ffn_token_rowmajor<float>, dim3(batch), dim3(kTokenThreads), lds, s, ev, a, (float*)y, token_lanes(a.d / 4), token_lanes(a.f / 4));
   else
-    launch_timed(ffn_token_rowmajor<uint16_t>, dim3(batch), dim3(kTokenThreads), lds, s, ev, a, (uint16_t*)y, lanes(a.d / 8), lanes(a.f / 8));
+    launch_timed(ffn_token_rowmajor<uint16_t>, dim3(batch), dim3(kTokenThreads), lds, s, ev, a, (uint16_t*)y, token_lanes(a.d / 8), token_lanes(a.f / 8));
   return hipGetLastError();
 }
 

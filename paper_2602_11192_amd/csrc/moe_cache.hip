@@ -827,7 +827,7 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   fa.max_count = batch;
   fa.work = a.work;
   fa.t = c->t; fa.h = c->h; fa.o = c->o;
-  const bool token = c->full[layer] && ffn_token_supported(cf.pool_layout, cf.dtype, batch, KS, g_max, d, cf.d_ff);
+  const bool token = c->full[layer] && ffn_token_supported(cf.pool_layout, cf.dtype, batch, K, cf.n_shared, E, d, cf.d_ff);
   const bool fused = plan.fused;
   fa.fused = fused ? 1 : 0;
   const KernelEvents ke1 = ps ? ps->gate_up : KernelEvents{}, ke2 = ps ? ps->down : KernelEvents{};

@@ -173,8 +173,8 @@ hipError_t launch_pin(hipStream_t s, const LayerState& st, const CallTables& t, 
 hipError_t launch_reset(hipStream_t s, const LayerState& st, int E, int C, int P, int clear_trace,
                         unsigned long long* dev_stats);
 hipError_t launch_ffn_rowmajor(hipStream_t s, int dtype, const FfnArgs& a, KernelEvents gate_up, KernelEvents down);
-// Row-major experts that are all in memory, few enough bytes per token: FFN and combine in one launch, a workgroup per token.
-bool ffn_token_supported(int pool_layout, int dtype, int batch, int KS, int groups, int d, int f);
+// Row-major experts that are all in memory, where that is the faster way: FFN and combine in one launch, a workgroup per token.
+bool ffn_token_supported(int pool_layout, int dtype, int batch, int K, int n_shared, int E, int d, int f);
 hipError_t launch_ffn_token(hipStream_t s, int dtype, const FfnArgs& a, int batch, void* y, KernelEvents ev);
 hipError_t launch_ffn_tiled(hipStream_t s, const FfnArgs& a, KernelEvents gate_up, KernelEvents down);
 // The tiles of a call of `batch` tokens, KS experts each, in at most g_max groups (streamed: experts read from the host).

@@ -234,7 +234,7 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
   fa.o = reinterpret_cast<float*>(base + o_o);
   fa.fused = plan.fused ? 1 : 0;
   fa.pass = 2;
-  if (ffn_token_supported(L->pool_layout, L->dtype, batch, KS, G, d, f)) {
+  if (ffn_token_supported(L->pool_layout, L->dtype, batch, K, ns, E, d, f)) {
     HIPCHK(launch_ffn_token(s, L->dtype, fa, batch, y_dev, KernelEvents{}));
     return MOE_OK;
   }
