@@ -867,8 +867,11 @@ __device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
   return v;
 }
 
-// Pairs of a call that are put in order in LDS before they are written out.
-constexpr int kStagedLeast = 1024, kStagedMost = 8192;
+// Pairs of a call that are put in order in LDS before they are written out.  At the least of them that is neither here nor there, with few
+// pairs per token it never pays; the most are what a unit's 160 KB hold beside the kernel's own.  Layer calls, in LDS / scattered:
+// 8 each of 64 experts, 256 / 1024 / 2048 / 8192 pairs 20.6 / 23.2 / 25.6 / 39.3 and 20.3 / 23.1 / 26.1 / 42.6 us, with a shared expert, 9216 /
+// 12285 pairs, 41.8 / 53.5 and 43.7 / 55.7; 4 each 1024 / 4096 pairs 23.2 / 32.6 and 23.1 / 33.2; 2 each of 16 2048 pairs 25.9 and 25.7.
+constexpr int kStagedLeast = 1024, kStagedMost = 12288;
 __host__ __device__ inline bool stage_pairs(int B, int KS) { return B * KS >= kStagedLeast && B * KS <= kStagedMost; }
 
 // The 64 x 64 bit matrix whose row r lane r holds, transposed: lane c gets column c.
@@ -1462,7 +1465,7 @@ hipError_t launch_route_cache(hipStream_t s, int dtype, const RouteArgs& r, cons
                          : a.mode == 2 ? kPrompt
                          : a.E > kTileMaxE || !fast_table(a.policy, a.C, a.P, a.n_shared) ? kOther
                          : a.E > kWave ? kWide : kTable;
-  const bool hits = kind == kFull || kind == kScored;
+  const bool hits = kind == kFull || kind == kScored, columns = kind < kOther;
   // Units from two tokens on where every lookup is known to hit, whatever the policy and the spare buffers, so that a full cache routes a
   // batch bit for bit as the allocation-free entry point does (30 points of 8 to 64 experts of 1024 to 4096 columns, 4 to 1024 tokens: 1.19x
   // in the mean against the kernels before, none slower; discounted counts, 64 tokens on 64 / 16 experts, looked up in order by one wave
@@ -1477,7 +1480,8 @@ hipError_t launch_route_cache(hipStream_t s, int dtype, const RouteArgs& r, cons
     if (ru.n_arrive <= scratch.n_arrive && ru.scratch_bytes <= scratch.bytes) {
       const RouteWork w{ru.slices, ru.et_per, static_cast<float*>(scratch.ptr),
                         reinterpret_cast<uint64_t*>(static_cast<char*>(scratch.ptr) + ru.logit_bytes)};
-      const size_t bytes = std::max({hits ? 0 : lds, (size_t)kTileWaves * 256 * sizeof(float), stage_pairs(a.B, a.KS) ? (size_t)(a.B * a.KS + 3) / 4 * 32 : 0});
+      const size_t bytes = std::max({hits ? 0 : lds, (size_t)kTileWaves * 256 * sizeof(float), columns && stage_pairs(a.B, a.KS) ? (size_t)(a.B * a.KS + 3) / 4 * 32 : 0});
+      static_assert(sizeof(TileLds) + kStagedMost * 2 * sizeof(int32_t) <= 160 << 10, "a unit's LDS");
       const dim3 units(ru.units), threads(kTileThreads);
       const auto launch = [&](auto kernel) { launch_timed(kernel, units, threads, bytes, s, ev, r, w, st, t, a); };
       const int pairs = (r.d / 32 + 2 * kRouteChains - 1) / (2 * kRouteChains);      // of k-blocks in a chain

@@ -23,7 +23,7 @@ def B():
     return binding
 
 
-# (1024 / 8192 pairs are the limits of the ordering in LDS, 1024 tokens a pass of the grouping)
+# (1024 / 12288 pairs are the limits of the ordering in LDS, 1024 tokens a pass of the grouping)
 @pytest.mark.parametrize("batch,E,K,ns,d,held", [(2, 24, 3, 0, 2080, 24), (17, 64, 8, 1, 64, 40), (127, 60, 8, 0, 64, 60),
                                                  (128, 64, 8, 0, 64, 30), (120, 8, 2, 1, 96, 6), (1024, 64, 8, 0, 32, 50),
                                                  (1025, 32, 7, 1, 32, 32), (2100, 24, 3, 0, 32, 20), (16, 33, 4, 64, 1056, 30),
@@ -31,7 +31,8 @@ def B():
                                                  (112, 65, 2, 0, 64, 64), (130, 100, 5, 1, 2080, 60), (1030, 256, 3, 0, 32, 40),
                                                  # pairs in LDS that are no multiple of four; a wave's second round over its chain;
                                                  # units of several expert tiles (above, too), of all of them
-                                                 (147, 64, 7, 0, 64, 64), (1024, 64, 4, 0, 4128, 64), (4100, 20, 2, 0, 32, 20)])
+                                                 (147, 64, 7, 0, 64, 64), (1024, 64, 4, 0, 4128, 64), (4100, 20, 2, 0, 32, 20),
+                                                 (1365, 64, 8, 1, 64, 50), (1366, 64, 8, 1, 64, 64)])
 def test_batch_that_hits(torch, B, batch, E, K, ns, d, held):
     f = 32
     gen = torch.Generator().manual_seed(batch * 1000 + E)
