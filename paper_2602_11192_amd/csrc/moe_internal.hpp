@@ -57,7 +57,7 @@ struct CallTables {
   int32_t* idx;          // [B][K]  selected experts, ascending id
   float* wpair;          // [B][KS] gate weight per (token, expert) pair; 1 for shared experts
   int32_t* pair_buf;     // [B*KS]  buffer id the pair reads (>= P: shared expert P + s)
-  int32_t* sorted_pair;  // [B*KS]  pairs ordered by buffer id, in any order inside a group
+  int32_t* sorted_pair;  // [B*KS]  pairs ordered by group, a group's in any order
   int32_t* pos_of;       // [B*KS]  inverse of sorted_pair
   GroupDesc* grp;        // [G]     one record per distinct expert buffer of the call
   int32_t* n_groups;     // [1]     number of groups of the call (0 if the call failed)

@@ -14,15 +14,15 @@
 //     with every 16-byte load issued up front, then DPP reductions; wave 0 gates
 //     the token.  Of a batch the workgroup that arrives last at a device-scope
 //     counter goes on to the lookups (nobody waits).
-//   route_units_kernel: 16 tokens x 16 experts x a slice of the contraction per
-//     workgroup, logits on the matrix cores; the last unit of a tile of 16 tokens
-//     gates them, a wave per token (route_small_fp32_kernel: a small fp32 call in
-//     one workgroup).
+//   route_units_kernel: 16 tokens x 16 experts (or several times that) x a slice of
+//     the contraction per workgroup, logits on the matrix cores; the last unit of a
+//     tile of 16 tokens gates them, a wave per token (route_small_fp32_kernel: a
+//     small fp32 call in one workgroup).
 // Gating (gate_token, gating.hpp): Top-K of the logits by bisection of their
 //   integer keys, ties to the lower id - the same set as Top-K of p - softmax
 //   with wave reductions, gate weights, outputs in ascending expert id.
 // Lookups, in three forms: all of a call's lookups at once on every wave of the
-//   workgroup when every one hits (group_hits, up to 64 experts); one wave in order on
+//   workgroup when every one hits (group_hits: at most 64 slots); one wave in order on
 //   the table in registers, one slot per lane, a lookup being a ballot plus a
 //   DPP arg-min (cache_phase_fast: LRU, at most 64 slots and buffers); one wave in
 //   order on the table in LDS otherwise (cache_phase_general).  In order, because
@@ -1476,7 +1476,10 @@ hipError_t launch_route_cache(hipStream_t s, int dtype, const RouteArgs& r, cons
   // 89 against 108 us); prompts on more than 32 experts from 32.
   const int least = hits ? 2 : kind == kTable ? (a.E > 16 ? 2 : 112) : kind == kPrompt && a.E > 32 ? 32 : 112;
   if (dtype == MOE_DTYPE_BF16 && a.B >= least && a.E <= kTileMaxE && r.d % 32 == 0) {
-    const RouteUnits ru = route_units(a.B, a.E, r.d, kind != kOther);      // (lookups in order take far longer than a slice saves)
+    // (Lookups in order take far longer than a slice saves.  Prompts whose pairs do not fit the LDS run the code that the kernel without
+    // slices has for them faster: 400 / 512 tokens on 64 experts of 2048 columns 95 / 115 us per layer call in slices, 86 / 102 without, 200 / 256
+    // tokens, which fit, 57 / 63 and 58 / 64.)
+    const RouteUnits ru = route_units(a.B, a.E, r.d, kind == kPrompt ? stage_in_lds(a.B, a.KS) : kind != kOther);
     if (ru.n_arrive <= scratch.n_arrive && ru.scratch_bytes <= scratch.bytes) {
       const RouteWork w{ru.slices, ru.et_per, static_cast<float*>(scratch.ptr),
                         reinterpret_cast<uint64_t*>(static_cast<char*>(scratch.ptr) + ru.logit_bytes)};

@@ -1,6 +1,5 @@
-"""Grouped bf16 GEMM for calls of up to 16 tokens: contractions shorter than the waves are apart or than the ring is deep, and of every
-remainder, row tiles that the last workgroup lacks, one and two row tiles per wave; against the layer in 64 bits.  A token's
-result does not depend on how many others share the call."""
+"""Grouped bf16 GEMM for calls of up to 16 tokens: contractions shorter than the ring is deep, and of every remainder, row tiles that
+the last workgroup lacks, one and two row tiles per wave; against the layer in 64 bits.  A token's result does not depend on how many others share the call."""
 import numpy as np
 import pytest
 

@@ -371,7 +371,7 @@ def test_odd_widths_take_the_generic_kernels(torch, P, d_model, d_ff):
     (64, 8, 64, 2, 144, "lru"),      # 64 slots, 64 buffers, shared experts
     (16, 4, 8, 0, 140, "gamma"),     # discounted-count policy
     (16, 4, 16, 1, 140, "gamma"),    # ... with everything resident
-    (32, 4, 32, 0, 113, "lru"),      # just above the size from which the tile kernel is used, ragged last tile
+    (32, 4, 32, 0, 113, "lru"),      # everything resident, ragged last tile of 16 tokens
 ])
 def test_large_calls_route_in_tiles_of_16_tokens(torch, P, E, K, C, n_shared, batch, policy):
     # calls of 112 tokens and more: router logits of 16 tokens per workgroup on the matrix cores, cache phase on
