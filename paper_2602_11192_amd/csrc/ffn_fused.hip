@@ -73,8 +73,8 @@ __global__ void pack_router_kernel(const uint16_t* __restrict__ w, uint16_t* __r
 // launch was built and measured: the workgroups have to meet at a device-scope counter, and on this GPU that
 // meeting alone - 8 us for 256 workgroups, far more with release/acquire fences, which write back and invalidate
 // whole L2 caches - costs more than the separate combine launch.)
-template <int WAVES, int SLOT0, bool ROUTED>
-__device__ __forceinline__ void fused_body(const FfnArgs& a, const RoutedArgs* rap) {
+template <int WAVES, int SLOT0, bool ROUTED, bool SHARED = false>
+__device__ __forceinline__ void fused_body(const FfnArgs& a, const RoutedArgs* rap, const ShareArgs* sh = nullptr) {
   __shared__ float red[WAVES][2][256];            // partial gate / up tiles of the waves
   __shared__ __align__(16) uint16_t hs[16][32];   // h of the chunk, bf16, [token][row in chunk]
   __shared__ typename std::conditional<ROUTED, RoutedLds, int>::type rl_store;
@@ -88,7 +88,7 @@ __device__ __forceinline__ void fused_body(const FfnArgs& a, const RoutedArgs* r
   int gd_buf, gd_begin, gd_count, gd_miss, gd_expert, gd_pair0;
   if constexpr (ROUTED) {
     GroupView gv;
-    if (!routed_prologue<WAVES>(a, *rap, rl_store, &red[0][0][0], gv)) return;
+    if (!routed_prologue<WAVES, SHARED, false>(a, *rap, sh, rl_store, &red[0][0][0], gv)) return;
     gd_buf = gv.buf; gd_begin = gv.begin; gd_count = gv.count; gd_miss = gv.miss; gd_expert = gv.expert;
     gd_pair0 = 0;
   } else {
@@ -130,7 +130,7 @@ __device__ __forceinline__ void fused_body(const FfnArgs& a, const RoutedArgs* r
   const uint16_t* xrow = nullptr;
   if (n < cnt) {
     int p;
-    if constexpr (ROUTED) p = a.max_count == 1 ? begin : rl_store.sorted_pair[begin + n];   // one token: pairs in order
+    if constexpr (ROUTED) p = SHARED || a.max_count == 1 ? begin : rl_store.sorted_pair[begin + n];   // one token: pairs in order
     else p = n == 0 ? gd_pair0 : a.t.sorted_pair[begin + n];   // a single-token group needs no second look-up
     xrow = reinterpret_cast<const uint16_t*>(a.x) + (size_t)(p / a.KS) * d + (size_t)kb0 * 32 + q * 8;
   }
@@ -221,6 +221,10 @@ template <int WAVES, int SLOT0>
 __global__ void __launch_bounds__(64 * WAVES, 4) decode_single_kernel(FfnArgs a, RoutedArgs ra) {
   fused_body<WAVES, SLOT0, true>(a, &ra);
 }
+template <int WAVES, int SLOT0>
+__global__ void __launch_bounds__(64 * WAVES, 4) decode_shared_kernel(FfnArgs a, RoutedArgs ra, ShareArgs sh) {
+  fused_body<WAVES, SLOT0, true, true>(a, &ra, &sh);
+}
 
 // y[b][i] = sum_j wpair[b][j] * sum_c o_part[pos_of[b][j]][c][i].
 // A workgroup owns 32 columns (128 bytes of every partial row) of one token: 8 lanes x 4 columns, 128 slices.
@@ -232,9 +236,8 @@ constexpr int kCombLanes = 8, kCombSlices = 128, kCombBatch = 8;
 // IDENT: pair (b, j) sits at partial row b * KS + j (a call of one token through the single-launch decode keeps its
 // pairs in order), so the addresses of the partial rows do not wait for pos_of: one memory round trip instead of two.
 template <typename T, bool IDENT>
-__global__ void __launch_bounds__(kCombLanes * kCombSlices)
-combine_chunks_kernel(const float* __restrict__ o_part, const float* __restrict__ wpair,
-                      const int32_t* __restrict__ pos_of, int KS, int d, int n_chunks, T* __restrict__ y) {
+__device__ __forceinline__ void combine_body(const float* __restrict__ o_part, const float* __restrict__ wpair,
+                                             const int32_t* __restrict__ pos_of, int KS, int d, int n_chunks, T* __restrict__ y) {
   __shared__ f32x4 part[kCombSlices / 8][kCombLanes];
   const int b = blockIdx.x;
   const int cl = threadIdx.x % kCombLanes, sl = threadIdx.x / kCombLanes;
@@ -276,6 +279,26 @@ combine_chunks_kernel(const float* __restrict__ o_part, const float* __restrict_
   }
 }
 
+template <typename T, bool IDENT>
+__global__ void __launch_bounds__(kCombLanes * kCombSlices)
+combine_chunks_kernel(const float* __restrict__ o_part, const float* __restrict__ wpair,
+                      const int32_t* __restrict__ pos_of, int KS, int d, int n_chunks, T* __restrict__ y) {
+  combine_body<T, IDENT>(o_part, wpair, pos_of, KS, d, n_chunks, y);
+}
+
+// The same behind a launch whose workgroups shared the logits of a token.  The last workgroup clears their words (stores in front of the others'
+// loads cost every one of them 0.5 us).
+template <typename T>
+__global__ void __launch_bounds__(kCombLanes * kCombSlices)
+combine_clear_kernel(const float* __restrict__ o_part, const float* __restrict__ wpair, int KS, int d, int n_chunks, T* __restrict__ y,
+                     unsigned long long* __restrict__ share) {
+  if (blockIdx.y + 1 == gridDim.y) {
+    for (int i = threadIdx.x; i < 8 * kShareWords; i += kCombLanes * kCombSlices) share[i] = 0;
+    return;
+  }
+  combine_body<T, true>(o_part, wpair, nullptr, KS, d, n_chunks, y);
+}
+
 }  // namespace
 
 namespace {
@@ -310,14 +333,20 @@ void launch_fused_waves(hipStream_t s, const FfnArgs& a, KernelEvents ev) {
 }
 
 template <int WAVES>
-void launch_single_waves(hipStream_t s, const FfnArgs& a, const RoutedArgs& ra, KernelEvents ev) {
+void launch_single_waves(hipStream_t s, const FfnArgs& a, const RoutedArgs& ra, ShareArgs& sh, KernelEvents ev) {
   dim3 grid(a.f / 32, a.g_max + 1), block(64 * WAVES);     // + the bookkeeping row
+  const bool shared = plan_share(sh, ra, WAVES, a.f / 32 * a.g_max);
+  const auto launch = [&](auto slot0) {
+    constexpr int SLOT0 = decltype(slot0)::value;
+    if (shared) launch_timed(decode_shared_kernel<WAVES, SLOT0>, grid, block, 0, s, ev, a, ra, sh);
+    else launch_timed(decode_single_kernel<WAVES, SLOT0>, grid, block, 0, s, ev, a, ra);
+  };
   const int na = (a.d / 32) / (WAVES / 2);
   switch (na % kDepth) {
-    case 0: launch_timed(decode_single_kernel<WAVES, 0>, grid, block, 0, s, ev, a, ra); break;
-    case 1: launch_timed(decode_single_kernel<WAVES, 1>, grid, block, 0, s, ev, a, ra); break;
-    case 2: launch_timed(decode_single_kernel<WAVES, 2>, grid, block, 0, s, ev, a, ra); break;
-    default: launch_timed(decode_single_kernel<WAVES, 4>, grid, block, 0, s, ev, a, ra); break;
+    case 0: launch(std::integral_constant<int, 0>{}); break;
+    case 1: launch(std::integral_constant<int, 1>{}); break;
+    case 2: launch(std::integral_constant<int, 2>{}); break;
+    default: launch(std::integral_constant<int, 4>{}); break;
   }
 }
 
@@ -348,12 +377,12 @@ bool decode_single_supported(int pool_layout, int policy, int E, int C, int P, i
   return waves != 0 && (E + 15) / 16 <= 2 * waves;      // the logit tiles of the waves fit their LDS scratch
 }
 
-hipError_t launch_decode_single(hipStream_t s, int pool_layout, const FfnArgs& a, const RoutedArgs& ra, KernelEvents ev) {
-  if (pool_layout == MOE_LAYOUT_TILED_INT4) return launch_decode_single_q4(s, a, ra, ev);
+hipError_t launch_decode_single(hipStream_t s, int pool_layout, const FfnArgs& a, const RoutedArgs& ra, ShareArgs& sh, KernelEvents ev) {
+  if (pool_layout == MOE_LAYOUT_TILED_INT4) return launch_decode_single_q4(s, a, ra, sh, ev);
   switch (pick_waves(a.d, (a.f / 32) * a.g_max)) {
-    case 4: launch_single_waves<4>(s, a, ra, ev); break;
-    case 8: launch_single_waves<8>(s, a, ra, ev); break;
-    case 16: launch_single_waves<16>(s, a, ra, ev); break;
+    case 4: launch_single_waves<4>(s, a, ra, sh, ev); break;
+    case 8: launch_single_waves<8>(s, a, ra, sh, ev); break;
+    case 16: launch_single_waves<16>(s, a, ra, sh, ev); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -376,9 +405,11 @@ hipError_t launch_ffn_fused(hipStream_t s, const FfnArgs& a, KernelEvents ev) {
 }
 
 hipError_t launch_combine_chunks(hipStream_t s, const float* o_part, const float* wpair, const int32_t* pos_of,
-                                 int B, int KS, int d, int n_chunks, void* y, bool identity) {
-  dim3 grid(B, d / (kCombLanes * 4)), block(kCombLanes * kCombSlices);
-  if (identity)
+                                 int B, int KS, int d, int n_chunks, void* y, bool identity, unsigned long long* share) {
+  dim3 grid(B, d / (kCombLanes * 4) + (share ? 1 : 0)), block(kCombLanes * kCombSlices);
+  if (share)
+    hipLaunchKernelGGL(combine_clear_kernel<uint16_t>, grid, block, 0, s, o_part, wpair, KS, d, n_chunks, (uint16_t*)y, share);
+  else if (identity)
     hipLaunchKernelGGL((combine_chunks_kernel<uint16_t, true>), grid, block, 0, s, o_part, wpair, pos_of, KS, d,
                        n_chunks, (uint16_t*)y);
   else

@@ -76,15 +76,15 @@ __device__ __forceinline__ const char* group_weights(const FfnArgs& a, int id) {
 // then scaled and accumulated, which removes a quarter of the vector arithmetic that bounds this kernel.
 // ROUTED: the launch is the decode call up to the combine; every workgroup first derives the routing, the cache
 // lookups and the groups for itself (routed_prologue.hpp).
-template <int WAVES, bool ONE, bool ROUTED>
-__device__ __forceinline__ void fused_q4_body(const FfnArgs& a, const RoutedArgs* rap) {
+template <int WAVES, bool ONE, bool ROUTED, bool SHARED = false>
+__device__ __forceinline__ void fused_q4_body(const FfnArgs& a, const RoutedArgs* rap, const ShareArgs* sh = nullptr) {
   __shared__ float red[WAVES][2][256];            // partial gate / up tiles of the waves
   __shared__ __align__(16) uint16_t hs[16][32];   // h of the chunk, bf16, [token][row in chunk]
   __shared__ typename std::conditional<ROUTED, RoutedLds, int>::type rl_store;
   GroupView gd;
   int pair0 = 0;
   if constexpr (ROUTED) {
-    if (!routed_prologue<WAVES>(a, *rap, rl_store, &red[0][0][0], gd)) return;
+    if (!routed_prologue<WAVES, SHARED, false>(a, *rap, sh, rl_store, &red[0][0][0], gd)) return;
   } else {
     const int g = blockIdx.y;
     const int ng = *a.t.n_groups;
@@ -123,7 +123,8 @@ __device__ __forceinline__ void fused_q4_body(const FfnArgs& a, const RoutedArgs
   const uint16_t* xrow = nullptr;
   if (n < cnt) {
     int p;
-    if constexpr (ROUTED) p = a.max_count == 1 ? begin : rl_store.sorted_pair[begin + n];   // one token: pairs in order
+    if constexpr (ROUTED && ONE) p = begin;  // pairs in order
+    else if constexpr (ROUTED) p = rl_store.sorted_pair[begin + n];
     else p = n == 0 ? pair0 : a.t.sorted_pair[begin + n];
     xrow = reinterpret_cast<const uint16_t*>(a.x) + (size_t)(p / a.KS) * d + (size_t)ks * 128 + q * 8;
   }
@@ -249,6 +250,10 @@ template <int WAVES, bool ONE>
 __global__ void __launch_bounds__(64 * WAVES, 4) decode_single_q4_kernel(FfnArgs a, RoutedArgs ra) {
   fused_q4_body<WAVES, ONE, true>(a, &ra);
 }
+template <int WAVES>
+__global__ void __launch_bounds__(64 * WAVES, 4) decode_shared_q4_kernel(FfnArgs a, RoutedArgs ra, ShareArgs sh) {
+  fused_q4_body<WAVES, true, true, true>(a, &ra, &sh);
+}
 
 int pick_waves_q4(int d) { return d % 512 == 0 ? 8 : d % 256 == 0 ? 4 : 0; }
 
@@ -260,15 +265,18 @@ bool ffn_fused_q4_supported(int d, int f, int max_count) {
 
 int fused_q4_waves(int d) { return pick_waves_q4(d); }
 
-hipError_t launch_decode_single_q4(hipStream_t s, const FfnArgs& a, const RoutedArgs& ra, KernelEvents ev) {
+hipError_t launch_decode_single_q4(hipStream_t s, const FfnArgs& a, const RoutedArgs& ra, ShareArgs& sh, KernelEvents ev) {
   dim3 grid(a.f / 32, a.g_max + 1);     // + the bookkeeping row
+  const bool shared = plan_share(sh, ra, pick_waves_q4(a.d), a.f / 32 * a.g_max);
   switch (pick_waves_q4(a.d)) {
     case 8:
-      if (a.max_count == 1) launch_timed(decode_single_q4_kernel<8, true>, grid, dim3(512), 0, s, ev, a, ra);
+      if (shared) launch_timed(decode_shared_q4_kernel<8>, grid, dim3(512), 0, s, ev, a, ra, sh);
+      else if (a.max_count == 1) launch_timed(decode_single_q4_kernel<8, true>, grid, dim3(512), 0, s, ev, a, ra);
       else launch_timed(decode_single_q4_kernel<8, false>, grid, dim3(512), 0, s, ev, a, ra);
       break;
     case 4:
-      if (a.max_count == 1) launch_timed(decode_single_q4_kernel<4, true>, grid, dim3(256), 0, s, ev, a, ra);
+      if (shared) launch_timed(decode_shared_q4_kernel<4>, grid, dim3(256), 0, s, ev, a, ra, sh);
+      else if (a.max_count == 1) launch_timed(decode_single_q4_kernel<4, true>, grid, dim3(256), 0, s, ev, a, ra);
       else launch_timed(decode_single_q4_kernel<4, false>, grid, dim3(256), 0, s, ev, a, ra);
       break;
     default: return hipErrorInvalidValue;

@@ -41,8 +41,8 @@ constexpr int kXv = (kRoutedMaxX / 8 + 64 * kTilesWaves - 1) / (64 * kTilesWaves
 __device__ __forceinline__ u32x4 ldw(const u32x4* p) { return __builtin_nontemporal_load(p); }
 
 // NPW = d / 256: k-blocks of the model dimension per wave and tile.
-template <int NPW>
-__global__ void __launch_bounds__(64 * kTilesWaves, 4) decode_tiles_kernel(FfnArgs a, RoutedArgs ra) {
+template <int NPW, bool SHARED>
+__device__ __forceinline__ void tiles_body(const FfnArgs& a, const RoutedArgs& ra, const ShareArgs* sh) {
   constexpr int WAVES = kTilesWaves;
   constexpr int D = NPW < 8 ? NPW : 8;     // ring depth: divides the per-tile and per-k-block item counts
   __shared__ float red[WAVES * 2 * 256];   // prologue scratch, then [tile][gate|up][wave][16 rows]
@@ -64,7 +64,7 @@ __global__ void __launch_bounds__(64 * kTilesWaves, 4) decode_tiles_kernel(FfnAr
       const int v = threadIdx.x + i * 64 * WAVES;
       xv[i] = v < a.d / 8 ? static_cast<const u32x4*>(a.x)[v] : u32x4{0, 0, 0, 0};
     }
-  } else if (!routed_prologue<WAVES>(a, ra, rl, red, gv)) {
+  } else if (!routed_prologue<WAVES, SHARED, true>(a, ra, sh, rl, red, gv)) {
     return;
   }
 
@@ -267,6 +267,11 @@ __global__ void __launch_bounds__(64 * kTilesWaves, 4) decode_tiles_kernel(FfnAr
     reinterpret_cast<f32x4*>(orow)[i] = reinterpret_cast<const f32x4*>(red)[i];
 }
 
+template <int NPW>
+__global__ void __launch_bounds__(64 * kTilesWaves, 4) decode_tiles_kernel(FfnArgs a, RoutedArgs ra) { tiles_body<NPW, false>(a, ra, nullptr); }
+template <int NPW>
+__global__ void __launch_bounds__(64 * kTilesWaves, 4) decode_tiles_shared_kernel(FfnArgs a, RoutedArgs ra, ShareArgs sh) { tiles_body<NPW, true>(a, ra, &sh); }
+
 int npw_of(int d) {
   switch (d) {
     case 256: return 1;
@@ -305,14 +310,20 @@ int decode_tiles_parts(int pool_layout, int d, int f, int batch, int groups, int
   return n_parts;
 }
 
-hipError_t launch_decode_tiles(hipStream_t s, const FfnArgs& a, const RoutedArgs& ra, KernelEvents ev) {
+hipError_t launch_decode_tiles(hipStream_t s, const FfnArgs& a, const RoutedArgs& ra, ShareArgs& sh, KernelEvents ev) {
+  const bool shared = plan_share(sh, ra, kTilesWaves, a.n_parts * ra.a.K);      // (the workgroups of shared experts do not route)
   dim3 grid(a.n_parts, a.g_max + 1), block(64 * kTilesWaves);     // + the bookkeeping row
+  const auto launch = [&](auto npw) {
+    constexpr int NPW = decltype(npw)::value;
+    if (shared) launch_timed(decode_tiles_shared_kernel<NPW>, grid, block, 0, s, ev, a, ra, sh);
+    else launch_timed(decode_tiles_kernel<NPW>, grid, block, 0, s, ev, a, ra);
+  };
   switch (npw_of(a.d)) {
-    case 1: launch_timed(decode_tiles_kernel<1>, grid, block, 0, s, ev, a, ra); break;
-    case 2: launch_timed(decode_tiles_kernel<2>, grid, block, 0, s, ev, a, ra); break;
-    case 4: launch_timed(decode_tiles_kernel<4>, grid, block, 0, s, ev, a, ra); break;
-    case 8: launch_timed(decode_tiles_kernel<8>, grid, block, 0, s, ev, a, ra); break;
-    case 16: launch_timed(decode_tiles_kernel<16>, grid, block, 0, s, ev, a, ra); break;
+    case 1: launch(std::integral_constant<int, 1>{}); break;
+    case 2: launch(std::integral_constant<int, 2>{}); break;
+    case 4: launch(std::integral_constant<int, 4>{}); break;
+    case 8: launch(std::integral_constant<int, 8>{}); break;
+    case 16: launch(std::integral_constant<int, 16>{}); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

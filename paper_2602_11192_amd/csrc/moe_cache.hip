@@ -126,6 +126,7 @@ struct moe_cache {
   bool dev_stats_used = false;
   size_t layer_stride = 0;             // bytes between the tables (and device counters) of consecutive layers
   char* router_packed = nullptr;       // [L] router matrices in operand order, for the calls that the single-launch decode covers
+  unsigned long long* share = nullptr; // words through which the workgroups of a one-token call hand each other the logits
   bool single_ok = false;              // the single-launch decode kernel covers this cache's shape and policy
   int single_max_batch = 0;
   int n_cu = 0;                        // compute units of the device
@@ -260,6 +261,7 @@ void free_all(moe_cache* c) {
   if (c->table_mem) (void)hipFree(c->table_mem);
   if (c->call_mem) (void)hipFree(c->call_mem);
   if (c->router_packed) (void)hipFree(c->router_packed);
+  if (c->share) (void)hipFree(c->share);
   if (c->h) (void)hipFree(c->h);
   if (c->o) (void)hipFree(c->o);
   if (c->host_mem) (void)hipHostFree(c->host_mem);
@@ -645,6 +647,8 @@ int moe_cache_create(const moe_cache_config_t* cfg, const moe_weights_t* weights
   CREATE_CHK(hipDeviceGetAttribute(&c->n_cu, hipDeviceAttributeMultiprocessorCount, c->device), MOE_ERR_HIP);
   if (c->single_ok) {
     CREATE_CHK(hipMalloc(&c->router_packed, router_packed_bytes(E, cfg->d_model) * L), MOE_ERR_HIP);
+    CREATE_CHK(hipMalloc(reinterpret_cast<void**>(&c->share), kShareBytes), MOE_ERR_HIP);
+    CREATE_CHK(hipMemset(c->share, 0, kShareBytes), MOE_ERR_HIP);
     CREATE_CHK(launch_pack_router(nullptr, weights->router_w, c->router_packed, E, cfg->d_model, L), MOE_ERR_HIP);
   }
   CREATE_CHK(hipStreamCreateWithFlags(&c->copy_stream, hipStreamNonBlocking), MOE_ERR_HIP);
@@ -791,11 +795,12 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
     fa.fused = 1; fa.pass = 2;
     fa.pool = c->pool_dev[layer];
     fa.fetch = 1;
+    ShareArgs sh{c->share, 0, 0, 0};
     fa.n_parts = decode_tiles_parts(cf.pool_layout, d, cf.d_ff, batch, fa.g_max, c->n_cu, E);
-    if (fa.n_parts > 0) HIPCHK(launch_decode_tiles(s, fa, q, ps ? ps->gate_up : KernelEvents{}));
-    else HIPCHK(launch_decode_single(s, cf.pool_layout, fa, q, ps ? ps->gate_up : KernelEvents{}));
+    if (fa.n_parts > 0) HIPCHK(launch_decode_tiles(s, fa, q, sh, ps ? ps->gate_up : KernelEvents{}));
+    else HIPCHK(launch_decode_single(s, cf.pool_layout, fa, q, sh, ps ? ps->gate_up : KernelEvents{}));
     HIPCHK(launch_combine_chunks(s, c->o, c->t.wpair, c->t.pos_of, batch, KS, d,
-                                 fa.n_parts > 0 ? fa.n_parts : cf.d_ff / 32, y_dev, batch == 1));
+                                 fa.n_parts > 0 ? fa.n_parts : cf.d_ff / 32, y_dev, batch == 1, sh.words));
     c->cur[layer] ^= 1;
     c->dev_stats_used = true;
     c->stats[layer].lookups += (uint64_t)batch * K;

@@ -156,6 +156,16 @@ struct RoutedArgs {
   Mailbox* log;              // optional second copy of the call record (host-mapped), for the profiler
 };
 
+// The logits of one token formed by the workgroups together (share_logits, routed_prologue.hpp): units of 16 experts x one of `slices`
+// slices of the contraction, per_wave k-blocks of it per wave, dealt to the first `sharers` workgroups of every die.  (An argument of its own: a launch
+// that does not share pays 0.2 us for a longer list.)
+struct ShareArgs {
+  unsigned long long* words;      // [8][kShareWords], zero between calls; null: not shared
+  int32_t sharers, per_wave, slices;
+};
+constexpr int kShareWords = 256;                // per die: 16 units, the tiles of 256 experts
+constexpr size_t kShareBytes = 8 * kShareWords * sizeof(unsigned long long);
+
 // Pairs (token, expert) of a call are staged in LDS up to this many; larger calls use global scratch.
 constexpr size_t kStageMaxPairs = 2048;
 
@@ -192,12 +202,13 @@ size_t router_packed_bytes(int E, int d);      // per layer
 hipError_t launch_pack_router(hipStream_t s, const void* router_w, void* out, int E, int d, int n_layers);
 bool decode_single_supported(int pool_layout, int policy, int E, int C, int P, int n_shared, int K, int d, int f,
                              int batch);
-hipError_t launch_decode_single(hipStream_t s, int pool_layout, const FfnArgs& a, const RoutedArgs& ra, KernelEvents ev);
-hipError_t launch_decode_single_q4(hipStream_t s, const FfnArgs& a, const RoutedArgs& ra, KernelEvents ev);
+// sh.words: memory for sharing the logits; null afterwards if the launch did not use it.
+hipError_t launch_decode_single(hipStream_t s, int pool_layout, const FfnArgs& a, const RoutedArgs& ra, ShareArgs& sh, KernelEvents ev);
+hipError_t launch_decode_single_q4(hipStream_t s, const FfnArgs& a, const RoutedArgs& ra, ShareArgs& sh, KernelEvents ev);
 // Tile variant of the single-launch decode (one workgroup per compute unit, bf16 experts, one token): workgroups per
 // group it would use on a GPU of n_cu compute units, 0 when the chunk kernel is the one to launch.
 int decode_tiles_parts(int pool_layout, int d, int f, int batch, int groups, int n_cu, int E);
-hipError_t launch_decode_tiles(hipStream_t s, const FfnArgs& a, const RoutedArgs& ra, KernelEvents ev);
+hipError_t launch_decode_tiles(hipStream_t s, const FfnArgs& a, const RoutedArgs& ra, ShareArgs& sh, KernelEvents ev);
 int fused_q4_waves(int d);
 bool ffn_fused_q4_supported(int d, int f, int max_count);
 hipError_t launch_ffn_fused_q4(hipStream_t s, const FfnArgs& a, KernelEvents ev);
@@ -208,9 +219,9 @@ struct FfnPlan { bool fused, gemm, tiled, q4; };      // gemm: a grouped GEMM, w
 FfnPlan plan_ffn(int pool_layout, int d, int f, int batch, bool resident, int groups, uint64_t expert_bytes);
 WorkPlan plan_work(const FfnPlan& p, int batch, int KS, int g_max, int d, int f);      // no list unless a GEMM runs
 hipError_t launch_ffn(hipStream_t s, int dtype, const FfnPlan& p, const FfnArgs& a, KernelEvents ke1, KernelEvents ke2);
-// identity: pair (b, j) has partial row b * KS + j (pos_of is not read)
+// identity: pair (b, j) has partial row b * KS + j (pos_of is not read).  share: words that the launch before left (ShareArgs), cleared here unless null
 hipError_t launch_combine_chunks(hipStream_t s, const float* o_part, const float* wpair, const int32_t* pos_of,
-                                 int B, int KS, int d, int n_chunks, void* y, bool identity = false);
+                                 int B, int KS, int d, int n_chunks, void* y, bool identity = false, unsigned long long* share = nullptr);
 hipError_t launch_combine(hipStream_t s, int dtype, const float* o, const float* wpair, const int32_t* pos_of,
                           int B, int KS, int d, void* y);
 

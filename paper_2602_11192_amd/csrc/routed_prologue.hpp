@@ -2,6 +2,7 @@
 // logits (paper Eq. 1), the selected experts, the cache lookups and the groups of the call for itself, so that the
 // expert FFN can start in the same launch without a round trip through memory or the host.
 #pragma once
+#include <algorithm>
 #include <type_traits>
 
 #include "device_utils.hpp"
@@ -15,6 +16,22 @@ typedef float rp_f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t rp_u32x4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------- single-launch decode: prologue pieces
+// Whether the `wgs` workgroups (of `waves` waves) of a call share the logits, and how; sh.words becomes null where not.
+// The hand-over costs what 130 KB of W_r cost every workgroup.  us per layer call, W_r whole / shared: bf16, 64 experts x 4096 (512 fragments) 32.3 /
+// 27.5, 64 x 2048 (256) 20.5 / 18.5, 48 x 1536 (144) 21.3 / 19.0, but 64 x 1024, 32 x 2048, 16 x 4096 (128) 18.2 / 18.1, 26.2 / 26.0, 40.8 / 40.5; INT4,
+// 64 x 4096 24.8 / 20.8, 48 x 1536 14.4 / 13.7, 64 x 1024 14.3 / 14.4, 32 x 2048 15.3 / 15.8.  Eight units at most, fewer to wait for: 64 x 2048 in 4 / 6
+// / 8 / 16 / 32 of them 26.7 / 26.7 / 26.8 / 26.9 / 27.2 us.  With two workgroups per die it is still no slower (64 x 2048, 16 workgroups, 18.9 / 18.6).
+constexpr int kShareMost = 8, kShareLeast = 2, kShareFrags = 136;
+inline bool plan_share(ShareArgs& sh, const RoutedArgs& ra, int waves, int wgs) {
+  const int tiles = (ra.a.E + 15) / 16, nkb = ra.r.d / 32;
+  sh.sharers = wgs / 8;
+  const int slices = std::max(1, std::min(kShareMost, sh.sharers) / tiles);
+  sh.per_wave = (nkb + waves * slices - 1) / (waves * slices);
+  sh.slices = (nkb + waves * sh.per_wave - 1) / (waves * sh.per_wave);
+  if (ra.a.B != 1 || sh.sharers < kShareLeast || tiles * nkb < kShareFrags) sh.words = nullptr;
+  return sh.words != nullptr;
+}
+
 // Limits of the routed variant: tokens per call, experts whose logits a workgroup keeps, token elements staged.
 constexpr int kRoutedMaxB = 4, kRoutedMaxE = 256, kRoutedMaxX = 8192;
 
@@ -29,6 +46,7 @@ struct RoutedLds {
   int32_t sorted_pair[64], pos_of[64];  // pairs ordered by group, and the inverse
   int32_t g_buf[64], g_begin[64], g_count[64], g_miss[64], g_expert[64];   // groups
   int32_t n_groups, status;
+  int32_t late;                         // a part of the logits that another workgroup forms did not arrive in time
 };
 
 // Cache lookups and grouping of a call of at most 64 (token, expert) pairs on the register-resident LRU table
@@ -295,6 +313,106 @@ __device__ __forceinline__ void route_logits(const RoutedArgs& ra, float* pz, Ro
 }
 
 
+// The same for ONE token, the work shared by the workgroups of a die: a unit is 16 experts x a slice of the contraction, each workgroup forms its own, hands the 16 sums to the others through the die's L2 - a word holds a sum and the
+// number of the call, so that one store publishes both - and takes theirs.  What bounds it is a first touch and that hand-over, where the
+// whole matrix in every workgroup took 3.3 us at 64 x 2048 beside the first touch (the rate at which one compute unit pulls in 262 KB).
+// The wait is bounded: a unit that has not arrived after kShareTries looks is formed here, by the same instructions on the same inputs,
+// so all workgroups have the same logits whoever formed them.  The combine launch clears the words (launch_combine_chunks).
+// id: the workgroup's place in the launch, consecutive ones go to the dies in turn; -1: it forms nothing by itself.  STAGE: the token
+// is left in LDS as well.
+constexpr int kShareTries = 64;
+template <int WAVES, bool STAGE>
+__device__ __forceinline__ void share_logits(const RoutedArgs& ra, const ShareArgs& sh, float* pz, RoutedLds& rl, int id, int tb_exp, int tb_buf) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 15, q = lane >> 4;
+  const int E = ra.a.E, d = ra.r.d, nkb = d >> 5, tiles = (E + 15) >> 4;
+  const int per_wave = sh.per_wave, units = tiles * sh.slices, sharers = sh.sharers;
+  const int mine = id >= 0 && (id >> 3) < sharers ? id >> 3 : units;
+  float* part = rl.zs[0] + kRoutedMaxE;                   // [units][16]; the rows of tokens that do not exist
+  const rp_u32x4* x = static_cast<const rp_u32x4*>(ra.r.x);
+  const rp_u32x4* w = static_cast<const rp_u32x4*>(ra.r.router_packed);
+  // (hardware register 20: the number of the die)
+  unsigned long long* words = sh.words + (size_t)(__builtin_amdgcn_s_getreg(20 | (3 << 11)) & 7) * kShareWords;
+  const unsigned long long tag = (unsigned long long)(ra.a.seq | 0x80000000u) << 32;
+  constexpr int U = 8;                                    // fragments a wave keeps in flight
+  const auto form = [&](int u, auto first) {
+    const int slice = u / tiles, tile = u - slice * tiles;
+    const int kb0 = slice * per_wave * WAVES + wave;
+    rp_f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int i0 = 0; i0 < per_wave; i0 += U) {
+      rp_u32x4 wa[U], xb[U];
+#pragma unroll
+      for (int i = 0; i < U; ++i) {
+        const int kb = min(kb0 + (i0 + i) * WAVES, nkb - 1);          // clamped: in bounds, not used below
+        wa[i] = w[((size_t)tile * nkb + kb) * 64 + lane];
+        xb[i] = x[(size_t)kb * 4 + q];                    // (every column is the token; column 0 is looked at)
+      }
+      if (i0 == 0) first();
+#pragma unroll
+      for (int i = 0; i < U; ++i)
+        if (i0 + i < per_wave && kb0 + (i0 + i) * WAVES < nkb)        // uniform
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(rp_bf16x8, wa[i]), __builtin_bit_cast(rp_bf16x8, xb[i]), acc, 0, 0, 0);
+    }
+    if (n == 0) *reinterpret_cast<rp_f32x4*>(pz + wave * 16 + q * 4) = acc;
+    __syncthreads();
+    if (tid < 16) {
+      float v = pz[tid];
+#pragma unroll
+      for (int k = 1; k < WAVES; ++k) v += pz[k * 16 + tid];
+      part[u * 16 + tid] = v;
+      return v;
+    }
+    return 0.f;
+  };
+  float bias[kRoutedMaxE / (64 * WAVES) + 1];
+  const auto init = [&] {
+#pragma unroll
+    for (int i = 0; i < kRoutedMaxE / (64 * WAVES) + 1; ++i) {
+      const int e = tid + i * 64 * WAVES;
+      bias[i] = ra.r.bias && e < E ? ra.r.bias[e] : 0.f;
+    }
+    if constexpr (STAGE)
+      for (int v = tid; v < d / 8; v += 64 * WAVES) rl.xs[v] = x[v];
+    for (int e = tid; e < E; e += 64 * WAVES) rl.buf_of[e] = -1;
+    if (tid == 0) rl.late = 0;
+  };
+  if (mine >= units) {
+    init();
+    __syncthreads();
+  }
+  for (int u = mine; u < units; u += sharers) {
+    const float v = form(u, [&] { if (u == mine) init(); });
+    if (tid < 16)
+      __hip_atomic_store(words + u * 16 + tid, tag | __builtin_bit_cast(uint32_t, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (u + sharers < units) __syncthreads();
+  }
+  if (tb_exp >= 0) rl.buf_of[tb_exp] = tb_buf;            // (behind the first barrier, which follows the clearing)
+  for (int i = tid; i < units * 16; i += 64 * WAVES) {
+    if ((i >> 4) % sharers == mine) continue;
+    unsigned long long got = 0;
+    for (int t = 0; t < kShareTries; ++t) {
+      got = __hip_atomic_load(words + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if ((got >> 32) == (tag >> 32)) break;
+      __builtin_amdgcn_s_sleep(1);
+    }
+    if ((got >> 32) == (tag >> 32)) part[i] = __builtin_bit_cast(float, (uint32_t)got);
+    else rl.late = 1;
+  }
+  __syncthreads();
+  if (rl.late)          // (the same in every lane)
+    for (int u = 0; u < units; ++u) {
+      form(u, [] {});
+      __syncthreads();
+    }
+  for (int e = tid, i = 0; e < E; e += 64 * WAVES, ++i) {
+    const float* p = part + (e >> 4) * 16 + (e & 15);
+    float v = p[0];
+    for (int sl = 1; sl < sh.slices; ++sl) v += p[sl * tiles * 16];
+    rl.zs[0][e] = v + bias[i];
+  }
+  __syncthreads();
+}
+
 // The group a workgroup of the expert phase works on.
 struct GroupView { int buf, begin, count, miss, expert; };
 
@@ -335,8 +453,9 @@ __device__ __forceinline__ bool resident_group(const RoutedLds& rl, int g, const
 // others do, plus the gate weights, the table after the call, the trace, the counters and the call record; it
 // runs no expert, so none of that delays the streaming).  Returns false when the workgroup has nothing to
 // stream: the bookkeeping row, rows beyond the call's groups, a call that failed.
-template <int WAVES>
-__device__ __forceinline__ bool routed_prologue(const FfnArgs& a, const RoutedArgs& ra, RoutedLds& rl, float* pz,
+// SHARED: a call of one token whose logits the workgroups form together.  STAGE: its caller reads the token from LDS.
+template <int WAVES, bool SHARED, bool STAGE>
+__device__ __forceinline__ bool routed_prologue(const FfnArgs& a, const RoutedArgs& ra, const ShareArgs* sh, RoutedLds& rl, float* pz,
                                                 GroupView& gd) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = blockIdx.y;
@@ -346,12 +465,13 @@ __device__ __forceinline__ bool routed_prologue(const FfnArgs& a, const RoutedAr
   if (wave == 0) ft = fast_load(ra.st_in, ra.a.C, ra.a.P);     // in flight while the logits are formed
   int tb_exp = -1, tb_buf = -1;     // the last wave inverts the table: expert -> buffer
   if (wave == WAVES - 1 && lane < ra.a.C) { tb_exp = ra.st_in.expert_in[lane]; tb_buf = ra.st_in.buf_of_slot[lane]; }
-  route_logits<WAVES>(ra, pz, rl, tb_exp, tb_buf);
-  if (ra.a.B == 1 && !keeper) {
+  if constexpr (SHARED) share_logits<WAVES, STAGE>(ra, *sh, pz, rl, keeper ? -1 : (int)(blockIdx.y * gridDim.x + blockIdx.x), tb_exp, tb_buf);
+  else route_logits<WAVES>(ra, pz, rl, tb_exp, tb_buf);
+  if ((SHARED || ra.a.B == 1) && !keeper) {
     if (g >= ra.a.KS) return false;
     if (ra.a.E <= 64 ? resident_group<1>(rl, g, ra.a, gd) : resident_group<kRoutedMaxE / 64>(rl, g, ra.a, gd)) return true;
   }
-  for (int b = wave; b < ra.a.B; b += WAVES) {
+  for (int b = wave; b < (SHARED ? 1 : ra.a.B); b += WAVES) {
     if (keeper) {
       if (ra.a.E <= 64) gate_token<1>(rl.zs[b], b, ra.a.E, ra.a.K, ra.a.KS, ra.r.norm_topk, rl.idx, rl.wpair, ra.r.user_idx, ra.r.user_w, nullptr);
       else gate_token<kRoutedMaxE / 64>(rl.zs[b], b, ra.a.E, ra.a.K, ra.a.KS, ra.r.norm_topk, rl.idx, rl.wpair, ra.r.user_idx, ra.r.user_w, nullptr);
