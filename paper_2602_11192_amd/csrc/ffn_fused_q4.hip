@@ -38,7 +38,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-// Items a wave keeps in flight.  Shallow on purpose: the unpacked operands and the MFMA chains of four k-blocks
+// Items a wave keeps in flight (but see kDeepA).  Shallow on purpose: the unpacked operands and the MFMA chains of four k-blocks
 // already take ~100 registers, and staying under 128 lets two workgroups share a compute unit, which hides the
 // start-up and the LDS reduction of one behind the streaming of the other (measured: 64 -> 47 us on the
 // Mixtral-like shape against rings of 4 and 8).
@@ -72,11 +72,17 @@ __device__ __forceinline__ const char* group_weights(const FfnArgs& a, int id) {
                   : a.shared + (size_t)(id - a.P) * a.expert_bytes;
 }
 
+// The single launch has its tokens in LDS (2 to 4 tokens, 4 of 8 experts of 2048 x 2048, 24.3 -> 23.0 us, 2 of 16 of 2048 x 512 17.1 -> 16.6).  With one
+// token that leaves room for twice the gate/up items, and while every workgroup has a compute unit to itself nobody else fills its pauses (kDeepWgs).  us per layer call, token from memory / from LDS / with two items and six of W_d: 256
+// workgroups, 8 of 64 experts of 2048 x 1024, 18.2 / 17.6 / 16.8, 2 of 8 of 4096 x 1024 (64 of them) 20.9 / 19.9 / 18.8; beyond, 2 of 8 of 4096 x 14336
+// (896) 60.6 / 55.2 / 58.0, 2 of 16 of 4096 x 6400 (400) 31.2 / 28.9 / 30.2.  Four items at a time lose what two gain (the registers).
+constexpr int kDeepA = 2, kDeepB = 6, kDeepWgs = 256;
+
 // ONE: every group holds a single token (batch 1).  Only component 0 of the MFMA results (token 0 of the tile) is
 // then scaled and accumulated, which removes a quarter of the vector arithmetic that bounds this kernel.
 // ROUTED: the launch is the decode call up to the combine; every workgroup first derives the routing, the cache
 // lookups and the groups for itself (routed_prologue.hpp).
-template <int WAVES, bool ONE, bool ROUTED, bool SHARED = false>
+template <int WAVES, bool ONE, bool ROUTED, bool SHARED = false, bool DEEP = false>
 __device__ __forceinline__ void fused_q4_body(const FfnArgs& a, const RoutedArgs* rap, const ShareArgs* sh = nullptr) {
   __shared__ float red[WAVES][2][256];            // partial gate / up tiles of the waves
   __shared__ __align__(16) uint16_t hs[16][32];   // h of the chunk, bf16, [token][row in chunk]
@@ -84,7 +90,7 @@ __device__ __forceinline__ void fused_q4_body(const FfnArgs& a, const RoutedArgs
   GroupView gd;
   int pair0 = 0;
   if constexpr (ROUTED) {
-    if (!routed_prologue<WAVES, SHARED, false>(a, *rap, sh, rl_store, &red[0][0][0], gd)) return;
+    if (!routed_prologue<WAVES, SHARED, ONE>(a, *rap, sh, rl_store, &red[0][0][0], gd)) return;
   } else {
     const int g = blockIdx.y;
     const int ng = *a.t.n_groups;
@@ -120,23 +126,25 @@ __device__ __forceinline__ void fused_q4_body(const FfnArgs& a, const RoutedArgs
   constexpr size_t a_step = (size_t)KS * q4::kGateUpRecord, b_step = (size_t)WAVES * q4::kDownRecord;
 
   const int begin = gd.begin, cnt = gd.count;
+  constexpr bool XLDS = ROUTED;       // the tokens are in LDS (rows of the operand beyond the group's repeat its first one and are not looked at)
+  constexpr int DA = DEEP ? kDeepA : kDepthA, DB = DEEP ? kDeepB : kDepthB;
   const uint16_t* xrow = nullptr;
-  if (n < cnt) {
-    int p;
-    if constexpr (ROUTED && ONE) p = begin;  // pairs in order
-    else if constexpr (ROUTED) p = rl_store.sorted_pair[begin + n];
-    else p = n == 0 ? pair0 : a.t.sorted_pair[begin + n];
+  if constexpr (XLDS) {
+    const int p = ONE ? begin : rl_store.sorted_pair[n < cnt ? begin + n : begin];      // one token: pairs in order
+    xrow = reinterpret_cast<const uint16_t*>(rl_store.xs) + (ONE ? 0 : (size_t)(p / a.KS) * d) + ks * 128 + q * 8;
+  } else if (n < cnt) {
+    const int p = n == 0 ? pair0 : a.t.sorted_pair[begin + n];
     xrow = reinterpret_cast<const uint16_t*>(a.x) + (size_t)(p / a.KS) * d + (size_t)ks * 128 + q * 8;
   }
 
-  u32x4 awg[kDepthA], awu[kDepthA], asc[kDepthA], ax[kDepthA][4];
-  u32x4 bwd[kDepthB];
-  u32x2 bsd[kDepthB];
+  u32x4 awg[DA], awu[DA], asc[DA], ax[XLDS ? 1 : DA][4];
+  u32x4 bwd[DB];
+  u32x2 bsd[DB];
   auto issue_a = [&](int slot, int item) {
     if (item < na) {
       const char* rec = pa + (size_t)item * a_step;
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < (XLDS ? 0 : 4); ++j)
         ax[slot][j] = xrow ? *reinterpret_cast<const u32x4*>(xrow + (size_t)item * (KS * 128) + j * 32)
                            : u32x4{0, 0, 0, 0};
       awg[slot] = ldnt<u32x4>(rec + lane * 16);
@@ -152,20 +160,20 @@ __device__ __forceinline__ void fused_q4_body(const FfnArgs& a, const RoutedArgs
     }
   };
 #pragma unroll
-  for (int u = 0; u < kDepthA; ++u) issue_a(u, u);
+  for (int u = 0; u < DA; ++u) issue_a(u, u);
 #pragma unroll
-  for (int u = 0; u < kDepthB; ++u) issue_b(u, u);
+  for (int u = 0; u < DB; ++u) issue_b(u, u);
 
   const bf16x8 minus136 = __builtin_bit_cast(bf16x8, u32x4{0xC308C308u, 0xC308C308u, 0xC308C308u, 0xC308C308u});
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
   f32x4 accg = zero, accu = zero;
-  for (int base = 0; base < na; base += kDepthA) {
+  for (int base = 0; base < na; base += DA) {
 #pragma unroll
-    for (int u = 0; u < kDepthA; ++u) {
+    for (int u = 0; u < DA; ++u) {
       if (base + u < na) {      // uniform
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const bf16x8 xa = __builtin_bit_cast(bf16x8, ax[u][j]);
+          const bf16x8 xa = __builtin_bit_cast(bf16x8, XLDS ? *reinterpret_cast<const u32x4*>(xrow + (size_t)(base + u) * (KS * 128) + j * 32) : ax[XLDS ? 0 : u][j]);
           const f32x4 off = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, minus136, zero, 0, 0, 0);
           const f32x4 dg = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, codes_to_bf16(awg[u][j]), off, 0, 0, 0);
           const f32x4 du = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, codes_to_bf16(awu[u][j]), off, 0, 0, 0);
@@ -183,7 +191,7 @@ __device__ __forceinline__ void fused_q4_body(const FfnArgs& a, const RoutedArgs
           fill(rec + 1024 + lane * 16, awu[u]);
           if (q == 0) fill(rec + 2048 + n * 16, asc[u]);
         }
-        issue_a(u, base + u + kDepthA);
+        issue_a(u, base + u + DA);
       }
     }
   }
@@ -212,9 +220,9 @@ __device__ __forceinline__ void fused_q4_body(const FfnArgs& a, const RoutedArgs
   const size_t n_chunks = (size_t)(a.f >> 5);
   // lane: rows 64 dq + 4n .. +3 of W_d (one per register of the load) for tokens 4q .. 4q+3
   float* obase = a.o + ((size_t)(begin + q * 4) * n_chunks + c) * d + n * 4;
-  for (int base = 0; base < nb; base += kDepthB) {
+  for (int base = 0; base < nb; base += DB) {
 #pragma unroll
-    for (int u = 0; u < kDepthB; ++u) {
+    for (int u = 0; u < DB; ++u) {
       const int j = base + u;
       if (j < nb) {             // uniform
         f32x4 r[4] = {zero, zero, zero, zero};
@@ -229,7 +237,7 @@ __device__ __forceinline__ void fused_q4_body(const FfnArgs& a, const RoutedArgs
           fill(rec + lane * 16, bwd[u]);
           if (q == 0) fill(rec + 1024 + n * 8, bsd[u]);
         }
-        issue_b(u, j + kDepthB);
+        issue_b(u, j + DB);
         const int dq = wave + WAVES * j;
 #pragma unroll
         for (int i = 0; i < (ONE ? 1 : 4); ++i)
@@ -246,13 +254,13 @@ __global__ void __launch_bounds__(64 * WAVES) ffn_fused_q4_kernel(FfnArgs a) {
   fused_q4_body<WAVES, ONE, false>(a, nullptr);
 }
 
-template <int WAVES, bool ONE>
+template <int WAVES, bool ONE, bool DEEP>
 __global__ void __launch_bounds__(64 * WAVES, 4) decode_single_q4_kernel(FfnArgs a, RoutedArgs ra) {
-  fused_q4_body<WAVES, ONE, true>(a, &ra);
+  fused_q4_body<WAVES, ONE, true, false, DEEP>(a, &ra);
 }
-template <int WAVES>
+template <int WAVES, bool DEEP>
 __global__ void __launch_bounds__(64 * WAVES, 4) decode_shared_q4_kernel(FfnArgs a, RoutedArgs ra, ShareArgs sh) {
-  fused_q4_body<WAVES, true, true, true>(a, &ra, &sh);
+  fused_q4_body<WAVES, true, true, true, DEEP>(a, &ra, &sh);
 }
 
 int pick_waves_q4(int d) { return d % 512 == 0 ? 8 : d % 256 == 0 ? 4 : 0; }
@@ -268,17 +276,23 @@ int fused_q4_waves(int d) { return pick_waves_q4(d); }
 hipError_t launch_decode_single_q4(hipStream_t s, const FfnArgs& a, const RoutedArgs& ra, ShareArgs& sh, KernelEvents ev) {
   dim3 grid(a.f / 32, a.g_max + 1);     // + the bookkeeping row
   const bool shared = plan_share(sh, ra, pick_waves_q4(a.d), a.f / 32 * a.g_max);
+  const bool deep = (int64_t)a.f / 32 * a.g_max <= kDeepWgs;
+  const auto launch = [&](auto waves) {
+    constexpr int W = decltype(waves)::value;
+    const dim3 block(64 * W);
+    if (shared) {
+      if (deep) launch_timed(decode_shared_q4_kernel<W, true>, grid, block, 0, s, ev, a, ra, sh);
+      else launch_timed(decode_shared_q4_kernel<W, false>, grid, block, 0, s, ev, a, ra, sh);
+    } else if (a.max_count == 1) {
+      if (deep) launch_timed(decode_single_q4_kernel<W, true, true>, grid, block, 0, s, ev, a, ra);
+      else launch_timed(decode_single_q4_kernel<W, true, false>, grid, block, 0, s, ev, a, ra);
+    } else {
+      launch_timed(decode_single_q4_kernel<W, false, false>, grid, block, 0, s, ev, a, ra);
+    }
+  };
   switch (pick_waves_q4(a.d)) {
-    case 8:
-      if (shared) launch_timed(decode_shared_q4_kernel<8>, grid, dim3(512), 0, s, ev, a, ra, sh);
-      else if (a.max_count == 1) launch_timed(decode_single_q4_kernel<8, true>, grid, dim3(512), 0, s, ev, a, ra);
-      else launch_timed(decode_single_q4_kernel<8, false>, grid, dim3(512), 0, s, ev, a, ra);
-      break;
-    case 4:
-      if (shared) launch_timed(decode_shared_q4_kernel<4>, grid, dim3(256), 0, s, ev, a, ra, sh);
-      else if (a.max_count == 1) launch_timed(decode_single_q4_kernel<4, true>, grid, dim3(256), 0, s, ev, a, ra);
-      else launch_timed(decode_single_q4_kernel<4, false>, grid, dim3(256), 0, s, ev, a, ra);
-      break;
+    case 8: launch(std::integral_constant<int, 8>{}); break;
+    case 4: launch(std::integral_constant<int, 4>{}); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
