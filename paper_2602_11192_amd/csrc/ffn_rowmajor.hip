@@ -6,6 +6,7 @@
 #include <type_traits>
 
 #include "device_utils.hpp"
+#include "gating.hpp"
 #include "moe_internal.hpp"
 
 namespace moe {
@@ -162,7 +163,7 @@ inline int64_t token_steps(int64_t rows, int pieces) {
   const int lanes = token_lanes(pieces), at_once = kTokenRows * kTokenThreads / lanes;
   return (rows + at_once - 1) / at_once * ((pieces + lanes - 1) / lanes);
 }
-inline size_t token_lds(int KS, int d, int f) { return ((size_t)d + (size_t)KS * (f + d) + 2 * KS) * 4; }
+inline size_t token_lds(int KS, int d, int f) { return ((size_t)d + (size_t)KS * (f + d) + 4 * KS) * 4; }
 
 // the sum over each group of 16, 32 or 64 lanes
 __device__ __forceinline__ float lanes_sum(float v, int lanes) {
@@ -175,43 +176,48 @@ __device__ __forceinline__ float lanes_sum(float v, int lanes) {
   return v;
 }
 
+// What a workgroup keeps of its token in LDS.
+struct TokenLds {
+  float *xs, *h, *o;           // [d] token, [KS][f], [KS][d]
+  const char** wp;             // [KS] expert blocks
+  float* ws;                   // [KS] gate weights
+  int* ids;                    // [KS] expert buffers
+};
+__device__ __forceinline__ TokenLds token_lds_of(float* mem, const FfnArgs& a) {      // (d, f: multiples of V)
+  TokenLds l;
+  l.xs = mem; l.h = l.xs + a.d; l.o = l.h + a.KS * a.f;
+  l.wp = reinterpret_cast<const char**>(l.o + a.KS * a.d); l.ws = reinterpret_cast<float*>(l.wp + a.KS); l.ids = reinterpret_cast<int*>(l.ws + a.KS);
+  return l;
+}
 template <typename T>
-__global__ void __launch_bounds__(kTokenThreads) ffn_token_rowmajor(FfnArgs a, T* __restrict__ y, int lanes_d, int lanes_f) {
+__device__ __forceinline__ void stage_token(const FfnArgs& a, float* xs, int b) {
   constexpr int V = kVec<T>;
-  extern __shared__ __align__(16) float token_mem[];
-  const int KS = a.KS, d = a.d, f = a.f, b = blockIdx.x;
-  float* xs = token_mem;                          // [d]; d, f: multiples of V
-  float* h = xs + d;                              // [KS][f]
-  float* o = h + KS * f;                          // [KS][d]
-  float* ws = o + KS * d;                         // [KS] gate weights
-  int* ids = reinterpret_cast<int*>(ws + KS);     // [KS] expert buffers
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if ((int)threadIdx.x < KS) ws[threadIdx.x] = a.t.wpair[(size_t)b * KS + threadIdx.x];
-  for (int i = threadIdx.x * V; i < d; i += kTokenThreads * V) {
+  for (int i = threadIdx.x * V; i < a.d; i += kTokenThreads * V) {
     float v[V];
-    load_vec(reinterpret_cast<const T*>(a.x) + (size_t)b * d + i, v);
+    load_vec(reinterpret_cast<const T*>(a.x) + (size_t)b * a.d + i, v);
 #pragma unroll
     for (int e = 0; e < V; ++e) xs[i + e] = v[e];
   }
-  const int ng = *a.t.n_groups;
-  for (int j = wave; j < KS; j += kTokenThreads / 64) {       // the group that holds the pair
-    const int pos = a.t.pos_of[(size_t)b * KS + j];
-    if (lane == 0) ids[j] = 0;                                // (a call without groups has no expert to name: stay in bounds)
-    for (int g = lane; g < a.g_max; g += 64) {                // (g_max descriptors exist: requested beside the count)
-      const GroupDesc gd = a.t.grp[g];
-      if (g < ng && pos >= gd.begin && pos < gd.begin + gd.count) ids[j] = gd.buf;
-    }
-  }
-  __syncthreads();
-  // rows: per group of lanes, four at a time; pair and row of a flat index
+}
+
+// From the token and its experts in LDS (behind a barrier) to y.  between(): after the first projections.
+template <typename T, typename Between>
+__device__ __forceinline__ void token_ffn(const FfnArgs& a, const TokenLds& l, int b, T* __restrict__ y, int lanes_d, int lanes_f, Between between) {
+  constexpr int V = kVec<T>;
+  const int KS = a.KS, d = a.d, f = a.f;
+  float *xs = l.xs, *h = l.h, *o = l.o, *ws = l.ws;
+  const char** wp = l.wp;
+  // Rows: per group of lanes, four at a time; pair and row of a flat index.  What bounds a step is the instructions around its
+  // products (16 waves share the unit): the pair by a multiplication, its block from LDS, one silu for the four rows.
   const auto each = [&](int lanes, int per_pair, auto&& rows4) {
     const int n = KS * per_pair, groups = kTokenThreads / lanes, grp = threadIdx.x / lanes, at = threadIdx.x % lanes;
+    const uint32_t inverse = 0xffffffffu / (uint32_t)per_pair + 1;      // (per_pair > 1; n x per_pair < 2^32: exact)
     for (int r0 = grp; r0 < n; r0 += kTokenRows * groups) {
       int r[kTokenRows], j[kTokenRows];
 #pragma unroll
       for (int u = 0; u < kTokenRows; ++u) {
         r[u] = min(r0 + u * groups, n - 1);       // clamped: formed again by its owner, with the same result
-        j[u] = r[u] / per_pair;
+        j[u] = (int)__umulhi((uint32_t)r[u], inverse);
       }
       rows4(r, j, at);
     }
@@ -221,7 +227,7 @@ __global__ void __launch_bounds__(kTokenThreads) ffn_token_rowmajor(FfnArgs a, T
     float sg[kTokenRows], su[kTokenRows];
 #pragma unroll
     for (int u = 0; u < kTokenRows; ++u) {
-      w[u] = reinterpret_cast<const T*>(group_weights(a, ids[j[u]])) + (size_t)(r[u] - j[u] * f) * d;
+      w[u] = reinterpret_cast<const T*>(wp[j[u]]) + (r[u] - j[u] * f) * d;      // (an expert is at most kTokenMost bytes)
       sg[u] = su[u] = 0.f;
     }
     for (int i = at * V; i < d; i += lanes_d * V) {
@@ -229,26 +235,32 @@ __global__ void __launch_bounds__(kTokenThreads) ffn_token_rowmajor(FfnArgs a, T
 #pragma unroll
       for (int u = 0; u < kTokenRows; ++u) {
         load_vec(w[u] + i, vg[u]);
-        load_vec(w[u] + (size_t)f * d + i, vu[u]);
+        load_vec(w[u] + f * d + i, vu[u]);
       }
 #pragma unroll
       for (int u = 0; u < kTokenRows; ++u)
 #pragma unroll
         for (int e = 0; e < V; ++e) { sg[u] = fmaf(vg[u][e], xs[i + e], sg[u]); su[u] = fmaf(vu[u][e], xs[i + e], su[u]); }
     }
+    float vg = 0.f, vu = 0.f;
+    int row = 0;
 #pragma unroll
     for (int u = 0; u < kTokenRows; ++u) {
-      const float vg = lanes_sum(sg[u], lanes_d), vu = lanes_sum(su[u], lanes_d);
-      if (at == 0) h[r[u]] = silu(vg) * vu;
+      const float tg = lanes_sum(sg[u], lanes_d), tu = lanes_sum(su[u], lanes_d);
+      vg = at == u ? tg : vg;
+      vu = at == u ? tu : vu;
+      row = at == u ? r[u] : row;
     }
+    if (at < kTokenRows) h[row] = silu(vg) * vu;
   });
   __syncthreads();
+  between();
   each(lanes_f, d, [&](const int (&r)[kTokenRows], const int (&j)[kTokenRows], int at) {
     const T* w[kTokenRows];
     float s[kTokenRows];
 #pragma unroll
     for (int u = 0; u < kTokenRows; ++u) {
-      w[u] = reinterpret_cast<const T*>(group_weights(a, ids[j[u]])) + (size_t)2 * f * d + (size_t)(r[u] - j[u] * d) * f;
+      w[u] = reinterpret_cast<const T*>(wp[j[u]]) + 2 * f * d + (r[u] - j[u] * d) * f;
       s[u] = 0.f;
     }
     for (int i = at * V; i < f; i += lanes_f * V) {
@@ -271,6 +283,150 @@ __global__ void __launch_bounds__(kTokenThreads) ffn_token_rowmajor(FfnArgs a, T
     float acc = 0.f;
     for (int j = 0; j < KS; ++j) acc = fmaf(ws[j], o[j * d + i], acc);
     Elem<T>::store(y + (size_t)b * d + i, acc);
+  }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kTokenThreads) ffn_token_rowmajor(FfnArgs a, T* __restrict__ y, int lanes_d, int lanes_f) {
+  extern __shared__ __align__(16) float token_mem[];
+  const int KS = a.KS, b = blockIdx.x;
+  const TokenLds l = token_lds_of(token_mem, a);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if ((int)threadIdx.x < KS) l.ws[threadIdx.x] = a.t.wpair[(size_t)b * KS + threadIdx.x];
+  stage_token<T>(a, l.xs, b);
+  const int ng = *a.t.n_groups;
+  for (int j = wave; j < KS; j += kTokenThreads / 64) {       // the group that holds the pair
+    const int pos = a.t.pos_of[(size_t)b * KS + j];
+    if (lane == 0) l.ids[j] = 0;                              // (a call without groups has no expert to name: stay in bounds)
+    for (int g = lane; g < a.g_max; g += 64) {                // (g_max descriptors exist: requested beside the count)
+      const GroupDesc gd = a.t.grp[g];
+      if (g < ng && pos >= gd.begin && pos < gd.begin + gd.count) l.ids[j] = gd.buf;
+    }
+    wave_sync();
+    if (lane == 0) l.wp[j] = group_weights(a, l.ids[j]);
+  }
+  __syncthreads();
+  token_ffn<T>(a, l, b, y, lanes_d, lanes_f, [] {});
+}
+
+// The whole layer call in ONE launch: fp32 experts that are all in memory, up to 64 of them and 64 tokens, a workgroup per token.  Such a call is
+// launches and memory round trips, and the routing launch was half of it: 4 tokens, 2 of 8 experts of 64 x 128, 15.7 -> 10.0 us per layer call, 16 tokens,
+// 4 of 60 of 64 x 64, 22.1 -> 10.8.  A workgroup routes its own token - products with the rows of W_r as route_small_fp32_kernel forms them, a
+// wave per expert - and looks its experts up itself, since residency does not change; it reads no other token, so y may be x.  KEEP: the recency
+// of the slots is brought up to date by the workgroup that arrives last, from the selections that the others sent past the caches; all have
+// read the table before they arrive.
+constexpr int kLayerTokens = 64;
+// Bytes of W_r, which every workgroup reads: 1 of 64 experts of 1024 x 64, 1 / 16 / 64 tokens, 18.2 / 23.2 / 40.6 us with a launch for the routing, 15.4 / 17.8 / 23.8 without.
+constexpr size_t kLayerRouter = 256 << 10;
+constexpr int kLayerSteps = 4;
+template <bool KEEP>
+__global__ void __launch_bounds__(kTokenThreads) token_layer_kernel(FfnArgs a, RouteArgs r, LayerState st, CacheCallArgs c, uint64_t* masks,
+                                                                    float* __restrict__ y, int lanes_d, int lanes_f) {
+  extern __shared__ __align__(16) float token_mem[];
+  __shared__ float zs[kWave];
+  __shared__ int map[kWave], last;
+  const int KS = a.KS, K = c.K, E = c.E, B = c.B, d = a.d, b = blockIdx.x;
+  const TokenLds l = token_lds_of(token_mem, a);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // wave 0: the table of the layer, a slot per lane
+  int slot_expert = -1, slot_buf = 0;
+  int64_t sc = 0;
+  double score = 0.0;
+  if (wave == 0) {
+    if (KEEP) {
+      slot_expert = lane < c.C ? st.expert_in[lane] : -1;
+      slot_buf = lane < c.C ? st.buf_of_slot[lane] : 0;
+      sc = lane < SC_COUNT ? st.scalars[lane] : 0;
+      if (c.policy == MOE_POLICY_GAMMA && lane < E) score = st.score[lane];
+    } else {
+      slot_expert = lane < E ? lane : -1;
+      slot_buf = lane;
+    }
+  }
+  stage_token<float>(a, l.xs, b);
+  {
+    const int n_vec = d / 4;
+    constexpr int U = 4, WAVES = kTokenThreads / 64;      // products of a wave in flight together
+    const float4* xv = reinterpret_cast<const float4*>(static_cast<const float*>(r.x) + (size_t)b * d);
+    for (int e0 = wave; e0 < E; e0 += U * WAVES) {
+      float acc[U], bias[U];
+      const float4* wv[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int e = min(e0 + u * WAVES, E - 1);         // clamped: in bounds, formed again
+        wv[u] = reinterpret_cast<const float4*>(static_cast<const float*>(r.router_w) + (size_t)e * d);
+        bias[u] = r.bias ? r.bias[(size_t)b * E + e] : 0.f;
+        acc[u] = 0.f;
+      }
+      for (int i = lane; i < n_vec; i += kWave) {
+        const float4 x = xv[i];
+        float4 w[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) w[u] = wv[u][i];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          acc[u] = fmaf(w[u].x, x.x, acc[u]); acc[u] = fmaf(w[u].y, x.y, acc[u]);
+          acc[u] = fmaf(w[u].z, x.z, acc[u]); acc[u] = fmaf(w[u].w, x.w, acc[u]);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const float sum = wave_sum(acc[u]);
+        if (lane == 0) zs[min(e0 + u * WAVES, E - 1)] = sum + bias[u];
+      }
+    }
+  }
+  if (wave == 0 && slot_expert >= 0) map[slot_expert] = slot_buf;
+  __syncthreads();
+  uint64_t mine = 0;
+  if (wave == 0) {
+    Gate<1> g;
+    select_experts<1>(zs, E, K, g);
+    mine = g.top[0];
+    if (KEEP && B > 1 && lane == 0) __hip_atomic_store(masks + b, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    write_weights<1>(g, 0, E, K, KS, r.norm_topk, l.ws, r.user_w ? r.user_w + (size_t)b * K : nullptr, [&](size_t pos, int e) {
+      l.wp[pos] = group_weights(a, map[e]);
+      if (r.user_idx) r.user_idx[(size_t)b * K + pos] = e;
+    });
+    if (lane < KS - K) l.wp[K + lane] = group_weights(a, a.P + lane);
+  }
+  __syncthreads();
+  int arrived = 0;
+  token_ffn<float>(a, l, b, y, lanes_d, lanes_f, [&] {
+    if (KEEP && B > 1 && threadIdx.x == 0) {              // (its answer comes while the second projection runs)
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // the selection has arrived: it was sent ahead of the weights' loads
+      arrived = __hip_atomic_fetch_add(r.arrive, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  });
+  if constexpr (KEEP) {
+    if (threadIdx.x == 0) last = arrived == B - 1;
+    if (wave != 0) return;
+    wave_sync();
+    if (!last) return;
+    if (B > 1) {
+      if (lane == 0) __hip_atomic_store(r.arrive, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // ready for the next launch
+      mine = lane < B ? __hip_atomic_load(masks + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    } else if (lane > 0) {
+      mine = 0;
+    }
+    // lane b: the selection of token b; lane s: slot s; lane e: the discounted count of expert e
+    const int64_t clock = (int64_t)uniform64(__shfl(sc, SC_CLOCK)), trace_n = (int64_t)uniform64(__shfl(sc, SC_TRACE_N));
+    int last_use = 0;
+    for (int t = 0; t < B; ++t) {
+      const uint64_t m = ((uint64_t)(uint32_t)readlane_i((int)(uint32_t)(mine >> 32), t) << 32) | (uint32_t)readlane_i((int)(uint32_t)mine, t);
+      if (slot_expert >= 0 && ((m >> slot_expert) & 1)) last_use = t * K + __popcll(m & ((1ull << slot_expert) - 1ull)) + 1;
+      if (c.policy == MOE_POLICY_GAMMA) score = __dadd_rn(__dmul_rn(c.gamma, score), (double)((m >> lane) & 1));      // Definition C.1, once per token
+    }
+    if (last_use > 0) st.tick[lane] = (uint64_t)(clock + last_use);
+    if (c.policy == MOE_POLICY_GAMMA && lane < E) st.score[lane] = score;
+    int q = lane * K;
+    for (uint64_t m = mine; m != 0; m &= m - 1, ++q)
+      if (trace_n + q < c.trace_cap) st.trace[trace_n + q] = moe_trace_rec_t{c.row0 + lane, __ffsll((unsigned long long)m) - 1, 1, -1};
+    if (lane == 0) {
+      st.scalars[SC_CLOCK] = clock + B * K;
+      st.scalars[SC_CALLSEQ] = c.seq;
+      st.scalars[SC_TRACE_N] = trace_n + B * K;
+    }
   }
 }
 
@@ -329,22 +485,21 @@ hipError_t launch_ffn_rowmajor(hipStream_t s, int dtype, const FfnArgs& a, Kerne
   return hipGetLastError();
 }
 
-// A workgroup's time follows its steps, ~3 us each in fp32 and ~4 in bf16 beside 7 fixed, not its bytes: fp32, 2 of 8 experts, 1 token, 64 x 128
-// (192 KB, 1 + 1 steps) 12.9 us per call, 64 x 144 (216 KB, 2 + 2) 16.4, 96 x 128 (288 KB, 2 + 2) 19.2, 128 x 128 (384 KB, 2 + 2) 19.1; bf16, 2 of 8 of
-// 64 x 256 (192 KB, 2 + 1) 19.3.  The kernels per expert take 16.4 us, the rate at which four launches are issued, until the
-// tokens of their largest group and all pairs together cost more.  Counted in thirds of an fp32 step (a
-// bf16 step has four), against the kernels per expert, us per call, here / there:
-//   two steps in all, the least there is, in fp32; in bf16 only for one token:        fp32 64 x 128, 2 of 8, 1 / 16 tokens 12.9 / 16.3, 17.6 /
-//     19.7, bf16 128 x 256, 1 of 8, 1 / 8 tokens 15.7 / 16.2, 17.3 / 16.2
-//   a third more for every 32 pairs, and for every 4 tokens of the largest group that have 64 pieces of a row of W_g or W_d to add
-//     up: fp32 128 x 128, 2 of 8, 16 / 64 tokens 24.1 / 19.6, 25.1 / 26.0; 64 x 80, 4 of 16, 25.6 / 22.7, 25.9 / 32.6
-// 1430 points (130 shapes of 4 to 64 experts, up to 1024 tokens): 1.36x in the mean against the kernels per expert, 24 of
-// them more than 2 % slower (the worst 1.14x); the better of the two at every point would be 1.37x.
-bool ffn_token_supported(int pool_layout, int dtype, int batch, int K, int n_shared, int E, int d, int f) {
+// A workgroup's time follows its steps, not its bytes: ~1.5 us each beside 7 fixed (3 and 4 in bf16 while a step still divided and formed four silu; the rule
+// for calls with a routing launch is from then).  The kernels per expert take 15 to 18 us, the rate at which four launches are issued, until the
+// tokens of their largest group and all pairs together cost more.
+//   In one launch with the routing (`whole`): four steps in all, and beyond as many as the root of 4/3 of the tokens.  us per call, whole / per expert, 220
+// points: 2 steps, 1 / 8 / 64 tokens 9.5 / 10.7 / 14.6 and 15.1 / 19.4 / 25; 4 steps 12.2 / 13.5 / 17.5 and 15.2 / 18.7 / 29; 6 steps 16.8 / 18.0 / 22 and
+// 15.3 / 19.3 / 30; 8 steps 19.8 / 21.0 / 25.2 and 15.2 / 19.9 / 34; 13 steps, 64 tokens, 32.9 and 39: 1.13x in the mean, three points slower by more than 2 %.
+//   Behind a routing launch, counted in thirds of an fp32 step (a bf16 step has four): two steps, in bf16 only for one token, and a third more for
+// every 32 pairs, and for every 4 tokens of the largest group that have 64 pieces of a row of W_g or W_d to add up (1430 points of 130 shapes, 4 to 64
+// experts, up to 1024 tokens: 1.36x in the mean against the kernels per expert, 24 of them more than 2 % slower).
+bool ffn_token_supported(int pool_layout, int dtype, int batch, int K, int n_shared, int E, int d, int f, bool whole) {
   if (pool_layout != MOE_LAYOUT_ROWMAJOR) return false;
   const int KS = K + n_shared, elem = dtype == MOE_DTYPE_FP32 ? 4 : 2, V = 16 / elem;
   if (f % V != 0 || KS > kTokenThreads || token_lds(KS, d, f) > kTokenLds || (int64_t)KS * 3 * d * f * elem > kTokenMost) return false;
   const int64_t steps = token_steps((int64_t)KS * f, d / V) + token_steps((int64_t)KS * d, f / V), rounds = ((int64_t)batch + 255) / 256;
+  if (whole && (steps <= kLayerSteps || (steps - kLayerSteps) * (steps - kLayerSteps) * 3 <= 4 * batch)) return true;
   const int64_t pairs = (int64_t)batch * K, largest8 = n_shared > 0 ? 8 * (int64_t)batch : 8 * pairs / std::min<int64_t>(pairs, E);     // (in the mean)
   const int64_t pieces64 = (d / V + 63) / 64 + (f / V + 63) / 64;
   return 32 * steps * rounds * (dtype == MOE_DTYPE_FP32 ? 3 : 4) <= 32 * (batch == 1 ? 8 : 6) + (int64_t)batch * KS + largest8 * pieces64;
@@ -356,6 +511,21 @@ hipError_t launch_ffn_token(hipStream_t s, int dtype, const FfnArgs& a, int batc
     launch_timed(ffn_token_rowmajor<float>, dim3(batch), dim3(kTokenThreads), lds, s, ev, a, (float*)y, token_lanes(a.d / 4), token_lanes(a.f / 4));
   else
     launch_timed(ffn_token_rowmajor<uint16_t>, dim3(batch), dim3(kTokenThreads), lds, s, ev, a, (uint16_t*)y, token_lanes(a.d / 8), token_lanes(a.f / 8));
+  return hipGetLastError();
+}
+
+bool token_layer_supported(int pool_layout, int dtype, int batch, int E, int C, int d) {
+  return pool_layout == MOE_LAYOUT_ROWMAJOR && dtype == MOE_DTYPE_FP32 && batch <= kLayerTokens && E <= kWave && C <= kWave && (size_t)E * d * sizeof(float) <= kLayerRouter;
+}
+
+hipError_t launch_token_layer(hipStream_t s, const FfnArgs& a, const RouteArgs& r, const LayerState& st, const CacheCallArgs& c, uint64_t* masks,
+                              void* y, KernelEvents ev) {
+  const size_t lds = token_lds(a.KS, a.d, a.f);
+  const auto launch = [&](auto kernel) {
+    launch_timed(kernel, dim3(c.B), dim3(kTokenThreads), lds, s, ev, a, r, st, c, masks, (float*)y, token_lanes(a.d / 4), token_lanes(a.f / 4));
+  };
+  if (c.resident) launch(token_layer_kernel<false>);
+  else launch(token_layer_kernel<true>);
   return hipGetLastError();
 }
 

@@ -819,7 +819,11 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   const int g_max = (int)std::min<size_t>((size_t)batch * K, (size_t)(a.full ? E : c->P)) + cf.n_shared;
   const FfnPlan plan = plan_ffn(cf.pool_layout, d, cf.d_ff, batch, c->full[layer] != 0, g_max, c->expert_bytes);
   a.work = plan_work(plan, batch, KS, g_max, d, cf.d_ff);
-  HIPCHK(launch_route_cache(s, cf.dtype, ra, state_of(c, layer), c->t, a, RouteScratch{c->o, c->o_bytes, c->n_arrive}, ps ? ps->route : KernelEvents{}));
+  const bool could = token_layer_supported(cf.pool_layout, cf.dtype, batch, E, c->C, d);
+  const bool token = c->full[layer] && ffn_token_supported(cf.pool_layout, cf.dtype, batch, K, cf.n_shared, E, d, cf.d_ff, could);
+  const bool whole = token && could;
+  if (!whole)
+    HIPCHK(launch_route_cache(s, cf.dtype, ra, state_of(c, layer), c->t, a, RouteScratch{c->o, c->o_bytes, c->n_arrive}, ps ? ps->route : KernelEvents{}));
 
   FfnArgs fa{};
   fa.x = x_dev;
@@ -832,7 +836,6 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   fa.max_count = batch;
   fa.work = a.work;
   fa.t = c->t; fa.h = c->h; fa.o = c->o;
-  const bool token = c->full[layer] && ffn_token_supported(cf.pool_layout, cf.dtype, batch, K, cf.n_shared, E, d, cf.d_ff);
   const bool fused = plan.fused;
   fa.fused = fused ? 1 : 0;
   const KernelEvents ke1 = ps ? ps->gate_up : KernelEvents{}, ke2 = ps ? ps->down : KernelEvents{};
@@ -844,7 +847,8 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   fa.pool = in_kernel ? c->pool_dev[layer] : nullptr;
   fa.fetch = in_kernel ? 1 : 0;
   fa.pass = in_kernel ? 2 : 0;
-  if (token) HIPCHK(launch_ffn_token(s, cf.dtype, fa, batch, y_dev, ke1));
+  if (whole) HIPCHK(launch_token_layer(s, fa, ra, state_of(c, layer), a, reinterpret_cast<uint64_t*>(c->o), y_dev, ke1));
+  else if (token) HIPCHK(launch_ffn_token(s, cf.dtype, fa, batch, y_dev, ke1));
   else HIPCHK(launch_ffn(s, cf.dtype, plan, fa, ke1, ke2));
 
   Mailbox mb{};
@@ -867,7 +871,8 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
     HIPCHK(launch_ffn(s, cf.dtype, plan, fa, KernelEvents{}, KernelEvents{}));
   }
   if (ps) {
-    ps->used = true; ps->single = false; ps->mixed = mb.n_miss > 0; ps->fused = fused || token;
+    if (whole) c->call_log[ps - c->prof.data()] = Mailbox{};        // (one launch, and no lookup missed)
+    ps->used = true; ps->single = whole; ps->tiles = false; ps->mixed = mb.n_miss > 0; ps->fused = fused || token;
     ps->fetched = in_kernel ? (uint64_t)mb.n_miss * c->expert_bytes : 0;
   }
   if (!token)

@@ -184,8 +184,12 @@ hipError_t launch_reset(hipStream_t s, const LayerState& st, int E, int C, int P
                         unsigned long long* dev_stats);
 hipError_t launch_ffn_rowmajor(hipStream_t s, int dtype, const FfnArgs& a, KernelEvents gate_up, KernelEvents down);
 // Row-major experts that are all in memory, where that is the faster way: FFN and combine in one launch, a workgroup per token.
-bool ffn_token_supported(int pool_layout, int dtype, int batch, int K, int n_shared, int E, int d, int f);
+bool ffn_token_supported(int pool_layout, int dtype, int batch, int K, int n_shared, int E, int d, int f, bool whole);
 hipError_t launch_ffn_token(hipStream_t s, int dtype, const FfnArgs& a, int batch, void* y, KernelEvents ev);
+// ... with the routing and the table's recency in the same launch (`whole`) where token_layer_supported holds as well.  masks: a word per token.
+bool token_layer_supported(int pool_layout, int dtype, int batch, int E, int C, int d);
+hipError_t launch_token_layer(hipStream_t s, const FfnArgs& a, const RouteArgs& r, const LayerState& st, const CacheCallArgs& c, uint64_t* masks,
+                              void* y, KernelEvents ev);
 hipError_t launch_ffn_tiled(hipStream_t s, const FfnArgs& a, KernelEvents gate_up, KernelEvents down);
 // The tiles of a call of `batch` tokens, KS experts each, in at most g_max groups (streamed: experts read from the host).
 WorkPlan plan_ffn_gemm(int batch, int KS, int g_max, int d, int f, bool streamed);

@@ -218,7 +218,11 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
   a.max_miss = (int32_t)max_miss;
   a.work = plan_work(plan, batch, KS, G, d, f);
   // (everything behind the tables is free until the expert kernels run; the work list sits in front of o_o)
-  HIPCHK(launch_route_cache(s, L->dtype, ra, st, t, a, RouteScratch{base + o_o, kScratchBytes - o_o, kArrive}, KernelEvents{}));
+  const bool could = resident && token_layer_supported(L->pool_layout, L->dtype, batch, E, E, d);
+  const bool token = ffn_token_supported(L->pool_layout, L->dtype, batch, K, ns, E, d, f, could);
+  const bool whole = token && could;
+  if (!whole)
+    HIPCHK(launch_route_cache(s, L->dtype, ra, st, t, a, RouteScratch{base + o_o, kScratchBytes - o_o, kArrive}, KernelEvents{}));
 
   FfnArgs fa{};
   fa.x = x_dev;
@@ -234,7 +238,11 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
   fa.o = reinterpret_cast<float*>(base + o_o);
   fa.fused = plan.fused ? 1 : 0;
   fa.pass = 2;
-  if (ffn_token_supported(L->pool_layout, L->dtype, batch, K, ns, E, d, f)) {
+  if (whole) {
+    HIPCHK(launch_token_layer(s, fa, ra, st, a, nullptr, y_dev, KernelEvents{}));
+    return MOE_OK;
+  }
+  if (token) {
     HIPCHK(launch_ffn_token(s, L->dtype, fa, batch, y_dev, KernelEvents{}));
     return MOE_OK;
   }

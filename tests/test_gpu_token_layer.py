@@ -1,0 +1,67 @@
+"""fp32 layers whose experts are all in memory, the whole call in one launch: at both ends of its limits (64 tokens, 64 experts, one expert),
+on odd widths and several steps of a workgroup, under LRU and discounted counts.  Outputs, selections, trace, counters and resident sets
+against the oracle; in place; and replayed from a graph."""
+import numpy as np
+import pytest
+
+import oracle
+from tests.helpers import TOL, OracleStack, compare_traces_and_stats, rel_err
+from workload import MoEConfig, Workload, widen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("E,K,ns,d,f", [(8, 2, 0, 64, 128), (64, 8, 1, 36, 20), (1, 1, 0, 260, 8), (63, 3, 2, 100, 60), (64, 1, 0, 1024, 8)])
+@pytest.mark.parametrize("policy,gamma", [(oracle.POLICY_LRU, 1.0), (oracle.POLICY_GAMMA, 0.9)])
+def test_whole_layer(E, K, ns, d, f, policy, gamma):
+    import torch
+    from paper_2602_11192_amd import pool as P
+    cfg = MoEConfig("token_layer", 61, "fp32", 1, d, f, E, ns, K, E, 66, 5, 0, 1.5, min(K, 3), min(K, 3), 1e-5)
+    wl = Workload(cfg)
+    cache = P.make_cache(wl, max_batch=66, trace_capacity=4096, policy=P.B.MOE_POLICY_LRU if policy == oracle.POLICY_LRU else P.B.MOE_POLICY_GAMMA,
+                         gamma=gamma)
+    ost = OracleStack(wl, policy=policy, gamma=gamma, keep=E)
+    ids = list(range(E))[::-1]
+    cache.moe_cache_prefill_pins(0, ids)
+    ost.caches[0].pin(ids)
+    trace = []
+    for step, batch in enumerate((1, 64, 2, 65, 7)):             # (65: routed by a launch of its own)
+        print("token layer", E, K, policy, batch, flush=True)
+        xs = np.stack([wl.tokens(s)[step] for s in range(batch)])
+        bias = np.stack([wl.bias(0, s) for s in range(batch)])
+        idx = torch.empty((batch, K), dtype=torch.int32, device="cuda:0")
+        w = torch.empty((batch, K), dtype=torch.float32, device="cuda:0")
+        y = P.to_device(xs)                                      # in place
+        cache.moe_layer_decode(0, y, y, torch.from_numpy(bias).cuda(), idx, w)
+        res = ost.decode(0, widen(xs), bias)
+        torch.cuda.synchronize()
+        assert idx.cpu().numpy().tolist() == res.idx.tolist()
+        np.testing.assert_allclose(w.cpu().numpy(), res.w, rtol=0, atol=2e-5)
+        assert rel_err(P.to_numpy(y), res.y).max() <= TOL["fp32"]
+        trace.extend(res.trace)
+    compare_traces_and_stats(cache, ost, [trace], cfg.expert_bytes)
+    cache.close()
+
+
+def test_replays_of_a_captured_call():
+    import torch
+    from paper_2602_11192_amd import pool as P
+    E, K, d, f, batch = 16, 2, 64, 128, 5
+    cfg = MoEConfig("token_layer", 62, "fp32", 1, d, f, E, 0, K, E, 30, 2, 0, 1.5, 2, 2, 1e-5)
+    wl = Workload(cfg)
+    cache = P.make_cache(wl, max_batch=batch)
+    cache.moe_cache_prefill_pins(0, list(range(E)))
+    x = P.to_device(np.stack([wl.tokens(s)[0] for s in range(batch)]))
+    y, eager = torch.empty_like(x), torch.empty_like(x)
+    cache.moe_layer_decode(0, x, y)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        cache.moe_layer_decode(0, x, y)
+    for i in range(5):
+        x.copy_(P.to_device(np.stack([wl.tokens((i * batch + s) % 30)[1] for s in range(batch)])))
+        graph.replay()
+        cache.moe_layer_decode(0, x, eager)
+        torch.cuda.synchronize()
+        assert torch.equal(y, eager), i
+    cache.close()
