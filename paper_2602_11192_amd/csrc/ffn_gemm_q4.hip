@@ -2,7 +2,7 @@
 // (section 3.2) as a grouped GEMM, for calls in which an expert sees many
 // tokens: batched decode and prompt processing.
 //
-// One workgroup = 4 waves x a tile of up to TOK of one expert's tokens.  Tokens
+// One workgroup = 1, 2 or 4 groups of 4 waves x a tile of up to TOK of one expert's tokens.  Tokens
 // are the A operand of v_mfma_f32_16x16x32_bf16, staged through LDS in fragment
 // order, four k-blocks (128 columns) per step of the gate/up pass and two per step of the down pass, double buffered; weights are the
 // B operand, unpacked from 4-bit codes in registers (see ffn_fused_q4.hip for
@@ -14,6 +14,7 @@
 //     the eight scales.  h = silu(g) * u is written as bf16, rows in group order.
 //   down pass: wave w owns the block of 64 rows 4 bx + w of W_d; per k-block one
 //     16-byte load per lane brings the codes of its four row tiles.
+//   The groups share the rows and split the contraction, a step each in turn; their sums meet in LDS.
 // Codes and tokens are requested R - 1 steps ahead of their use into a ring of fixed register slots.
 // Every weight byte is read by exactly one wave of a token tile, so a group whose expert is not
 // resident can stream it from the pinned host pool (prompt streaming).
@@ -62,13 +63,17 @@ __device__ __forceinline__ const char* group_weights(const FfnArgs& a, int id) {
 // TOK: tokens per workgroup.  R: steps in flight.  MINW: waves per SIMD the registers have to leave room for.
 // STREAM: experts may have to be read over the link: nothing is requested beyond the contraction (a branch around the
 // loads; without it the last requests of a wave repeat its last step).
-template <int NMAT, int TOK, int R, int MINW, bool STREAM>
-__global__ void __launch_bounds__(64 * kWaves, MINW) ffn_gemm_q4_kernel(FfnArgs a) {
+// KG: groups of kWaves waves that share the rows and split the contraction; group 0 adds up their sums.
+template <int NMAT, int TOK, int R, int MINW, bool STREAM, int KG>
+__global__ void __launch_bounds__(64 * kWaves * KG, MINW) ffn_gemm_q4_kernel(FfnArgs a) {
   constexpr int CB = TOK / 16;        // column blocks of 16 tokens
-  constexpr int kSkb = NMAT == 2 ? 4 : 2;                   // k-blocks per step
+  constexpr int kSkb = NMAT == 2 ? 4 : 2;                   // k-blocks per step of a group
+  constexpr int NA = NMAT == 2 ? 2 : 4;                     // accumulators per column block
   constexpr int PIECES = TOK * kSkb * 4 / (64 * kWaves);    // 16-byte pieces of the token tile each thread stages per step
-  // [buffer][k-block of the step][column block][lane] x 16 bytes
-  __shared__ u32x4 xs[2][kSkb][CB][64];
+  // [buffer][k-block of the step][column block][lane] x 16 bytes; after the loop the sums of the groups behind the first
+  constexpr int kStage = 2 * kSkb * KG * CB, kSums = (KG - 1) * kWaves * CB * NA;
+  __shared__ u32x4 lds[(kStage > kSums ? kStage : kSums)][64];
+  auto& xs = reinterpret_cast<u32x4(&)[2][kSkb * KG][CB][64]>(lds);
   const int d = a.d, f = a.f;
   const int n_units = NMAT == 2 ? (f >> 4) : (d >> 6);         // row tiles of 16 / row blocks of 64
   const int n_rb = (n_units + kWaves - 1) / kWaves;
@@ -82,10 +87,11 @@ __global__ void __launch_bounds__(64 * kWaves, MINW) ffn_gemm_q4_kernel(FfnArgs 
   const int n_cb = (n_tok + 15) >> 4;
 
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave_id = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave = KG > 1 ? wave_id % kWaves : wave_id, group = KG > 1 ? wave_id / kWaves : 0;
   const int n = lane & 15, q = lane >> 4;
   const int nkb = (NMAT == 2 ? d : f) >> 5;                    // k-blocks of the contraction
-  const int n_steps = (nkb + kSkb - 1) / kSkb;
+  const int n_steps = (nkb + kSkb * KG - 1) / (kSkb * KG);
   const int unit = rb * kWaves + wave;                         // this wave's row tile / row block
   const bool has_rows = unit < n_units;
   const int uc = has_rows ? unit : n_units - 1;                // clamped: loads stay in bounds, results are dropped
@@ -101,14 +107,14 @@ __global__ void __launch_bounds__(64 * kWaves, MINW) ffn_gemm_q4_kernel(FfnArgs 
   u32x4 wr[R][NW];
   auto req_w = [&](int slot, int step) {
     if (NMAT == 2) {
-      const char* rec = wrec + (size_t)step * q4::kGateUpRecord;
+      const char* rec = wrec + (size_t)(KG > 1 ? min(step * KG + group, nsb - 1) : step) * q4::kGateUpRecord;
       wr[slot][0] = ldnt<u32x4>(rec + lane * 16);
       wr[slot][1] = ldnt<u32x4>(rec + 1024 + lane * 16);
       wr[slot][2] = ldnt<u32x4>(rec + 2048 + n * 16);
     } else {
 #pragma unroll
       for (int j = 0; j < kSkb; ++j) {
-        const int kb = min(step * kSkb + j, nkb - 1);          // clamped; the surplus k-blocks are skipped below
+        const int kb = min((step * KG + group) * kSkb + j, nkb - 1);          // clamped; the surplus k-blocks are skipped below
         const char* rec = wrec + (size_t)kb * n_dq * q4::kDownRecord;
         wr[slot][j] = ldnt<u32x4>(rec + lane * 16);
         const u32x2 s2 = ldnt<u32x2>(rec + 1024 + n * 8);
@@ -124,14 +130,14 @@ __global__ void __launch_bounds__(64 * kWaves, MINW) ffn_gemm_q4_kernel(FfnArgs 
   //      tile repeat its last token, their results are dropped at the end ----
   const uint16_t* src[PIECES];
   int dst[PIECES];
-  constexpr int SEGS = 4 * kSkb;                                 // 16-byte segments of a row's step
+  constexpr int SEGS = 4 * kSkb * KG;                                 // 16-byte segments of a row's step
   const int sg = threadIdx.x % SEGS, kbl = sg >> 2, qq = sg & 3;
   // the lanes that write together hold the (k-block, slice) pieces of one or two rows: the XOR spreads them over the
   // banks, and keeps the rows of neighbouring slices of a k-block apart for the reader
-  const auto swz = [](int kb, int slice) { return (slice + 4 * kb) * (kSkb == 4 ? 1 : 2); };
+  const auto swz = [](int kb, int slice) { return (slice + 4 * (kb % kSkb)) * (kSkb == 4 ? 1 : 2); };
 #pragma unroll
   for (int i = 0; i < PIECES; ++i) {
-    const int r = threadIdx.x / SEGS + 64 * kWaves / SEGS * i;   // token row of the tile
+    const int r = threadIdx.x / SEGS + 64 * kWaves * KG / SEGS * i;   // token row of the tile
     dst[i] = (kbl * CB + (r >> 4)) * 64 + qq * 16 + ((r & 15) ^ swz(kbl, qq));
     const int pos = begin + tok0 + min(r, n_tok - 1);
     src[i] = NMAT == 2 ? reinterpret_cast<const uint16_t*>(a.x) + (size_t)(a.t.sorted_pair[pos] / a.KS) * d + qq * 8
@@ -139,7 +145,7 @@ __global__ void __launch_bounds__(64 * kWaves, MINW) ffn_gemm_q4_kernel(FfnArgs 
   }
   u32x4 xq[R][PIECES];
   auto req_x = [&](int slot, int step) {
-    const int kb = min(step * kSkb + kbl, nkb - 1);
+    const int kb = min(step * kSkb * KG + kbl, nkb - 1);
 #pragma unroll
     for (int i = 0; i < PIECES; ++i) xq[slot][i] = *reinterpret_cast<const u32x4*>(src[i] + (size_t)kb * 32);
   };
@@ -151,7 +157,6 @@ __global__ void __launch_bounds__(64 * kWaves, MINW) ffn_gemm_q4_kernel(FfnArgs 
   const bf16x8 minus136 = __builtin_bit_cast(bf16x8, u32x4{0xC308C308u, 0xC308C308u, 0xC308C308u, 0xC308C308u});
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
   // gate/up: acc[cb][0] gate, acc[cb][1] up; down: acc[cb][j] row tile j of the block
-  constexpr int NA = NMAT == 2 ? 2 : 4;
   f32x4 acc[CB][NA];
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb)
@@ -168,12 +173,12 @@ __global__ void __launch_bounds__(64 * kWaves, MINW) ffn_gemm_q4_kernel(FfnArgs 
     auto multiply = [&](int u, int b, int n_kb) {
       u32x4 fr[2][NCB];               // token fragments of a k-block, those of the next one on their way
 #pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) fr[0][cb] = xs[b][0][cb][lane ^ swz(0, q)];
+      for (int cb = 0; cb < NCB; ++cb) fr[0][cb] = xs[b][group * kSkb][cb][lane ^ swz(0, q)];
 #pragma unroll
       for (int j = 0; j < kSkb; ++j) {
         if (j + 1 < kSkb) {
 #pragma unroll
-          for (int cb = 0; cb < NCB; ++cb) fr[(j + 1) & 1][cb] = xs[b][j + 1][cb][lane ^ swz(j + 1, q)];
+          for (int cb = 0; cb < NCB; ++cb) fr[(j + 1) & 1][cb] = xs[b][group * kSkb + j + 1][cb][lane ^ swz(j + 1, q)];
         }
         __builtin_amdgcn_sched_barrier(0);
         if (j < n_kb) {      // uniform
@@ -207,7 +212,7 @@ __global__ void __launch_bounds__(64 * kWaves, MINW) ffn_gemm_q4_kernel(FfnArgs 
           req_w((u + R - 1) % R, min(ahead, n_steps - 1));
         }
         __builtin_amdgcn_sched_barrier(0);
-        if (s0 + u < n_steps) multiply(u, (s0 + u) & 1, nkb - (s0 + u) * kSkb);
+        if (s0 + u < n_steps) multiply(u, (s0 + u) & 1, nkb - ((s0 + u) * KG + group) * kSkb);
         put_x((s0 + u + 1) & 1, (u + 1) % R);
         __syncthreads();
       }
@@ -218,6 +223,25 @@ __global__ void __launch_bounds__(64 * kWaves, MINW) ffn_gemm_q4_kernel(FfnArgs 
   else run(std::integral_constant<int, CB>{});
 
   // ---- epilogue: lane holds weight row n of its tile(s) for tokens 16 cb + 4 q + i ----
+  if constexpr (KG > 1) {        // (the loop ended with a barrier)
+    auto& sums = reinterpret_cast<f32x4(&)[KG - 1][kWaves][CB][NA][64]>(lds);
+    if (group > 0) {
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb)
+        if (cb < n_cb)
+#pragma unroll
+          for (int m = 0; m < NA; ++m) sums[group - 1][wave][cb][m][lane] = acc[cb][m];
+    }
+    __syncthreads();
+    if (group > 0) return;
+#pragma unroll
+    for (int g = 0; g < KG - 1; ++g)
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb)
+        if (cb < n_cb)
+#pragma unroll
+          for (int m = 0; m < NA; ++m) acc[cb][m] += sums[g][wave][cb][m][lane];
+  }
   if (!has_rows) return;
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb) {
@@ -239,6 +263,15 @@ __global__ void __launch_bounds__(64 * kWaves, MINW) ffn_gemm_q4_kernel(FfnArgs 
   }
 }
 
+// A wave takes ~0.5 us per step, however far ahead it asks (three and five steps ahead: -2 .. 0 %), for the chain of LDS, products, scaling and
+// barrier; where the workgroups leave a SIMD fewer than four waves, groups of waves that split the contraction fill it (us per
+// call, one / two / four groups; workgroups of each pass in brackets; at most two pairs of 40 tokens):
+//   tiles of 32: 8 experts of 4096 x 14336 (2016 + 144) 239 / 205 / 189, 16 of 4096 x 1024 (288 + 288) 49 / 42.5 / 41, 24 of 2048 x 768 (348
+//     + 232) 37.4 / 35.9 / 37.5, 32 of 2048 x 512 (456 + 456; 200 tokens) 46.5 / 45.4 / 57, 64 of 2048 x 1024 (1280 + 640; 64 tokens)
+//     59 / 60.5 / 62.
+//   Four need four steps each: 16 of 1024 x 512 (144 + 72) 27.6 / 26.1 / 27.
+//   tiles of 64: 8 of 4096 x 14336, 400 tokens (4480 + 320) 571 / 534, 8 of 2048 x 1024, 300 (272 + 136) 58.3 / 52, 600 (416 + 208) 66.8 / 68.3.
+constexpr int kSplit4 = 320, kSplitSteps = 4, kSplit2 = 512, kSplitLarge = 352;
 constexpr int kSmallTile = 5, kLargeTile = 6, kStreamedTile = 7;     // log2 of the tokens per tile
 
 }  // namespace
@@ -260,17 +293,30 @@ WorkPlan plan_ffn_gemm_q4(int batch, int KS, int g_max, bool streamed) {
 hipError_t launch_ffn_gemm_q4(hipStream_t s, const FfnArgs& a, KernelEvents e1, KernelEvents e2) {
   if (a.g_max <= 0) return hipSuccess;
   const int items = a.g_max + (int)(((int64_t)a.max_count * a.KS) >> a.work.shift);     // upper bound
-  const auto blocks = [&](int units) { return dim3(items * ((units + kWaves - 1) / kWaves)); };
-  const dim3 block(64 * kWaves);
+  const auto run = [&](auto kernel, int units, int groups, KernelEvents e) {
+    launch_timed(kernel, dim3(items * ((units + kWaves - 1) / kWaves)), dim3(64 * kWaves * groups), 0, s, e, a);
+  };
+  const auto split = [&](int units, int kblocks, int step) {
+    const int wgs = items * ((units + kWaves - 1) / kWaves);
+    return wgs <= kSplit4 && kblocks >= 4 * kSplitSteps * step ? 4 : wgs <= kSplit2 ? 2 : 1;
+  };
+  const int s1 = split(a.f / 16, a.d / 32, 4), s2 = split(a.d / 64, a.f / 32, 2);
   if (a.work.shift == kStreamedTile) {
-    launch_timed(ffn_gemm_q4_kernel<2, 128, 2, 1, true>, blocks(a.f / 16), block, 0, s, e1, a);
-    launch_timed(ffn_gemm_q4_kernel<1, 128, 2, 1, true>, blocks(a.d / 64), block, 0, s, e2, a);
+    run(ffn_gemm_q4_kernel<2, 128, 2, 1, true, 1>, a.f / 16, 1, e1);
+    run(ffn_gemm_q4_kernel<1, 128, 2, 1, true, 1>, a.d / 64, 1, e2);
   } else if (a.work.shift == kSmallTile) {
-    launch_timed(ffn_gemm_q4_kernel<2, 32, 2, 4, false>, blocks(a.f / 16), block, 0, s, e1, a);
-    launch_timed(ffn_gemm_q4_kernel<1, 32, 2, 4, false>, blocks(a.d / 64), block, 0, s, e2, a);
+    if (s1 == 4) run(ffn_gemm_q4_kernel<2, 32, 2, 4, false, 4>, a.f / 16, 4, e1);
+    else if (s1 == 2) run(ffn_gemm_q4_kernel<2, 32, 2, 4, false, 2>, a.f / 16, 2, e1);
+    else run(ffn_gemm_q4_kernel<2, 32, 2, 4, false, 1>, a.f / 16, 1, e1);
+    if (s2 == 4) run(ffn_gemm_q4_kernel<1, 32, 2, 4, false, 4>, a.d / 64, 4, e2);
+    else if (s2 == 2) run(ffn_gemm_q4_kernel<1, 32, 2, 4, false, 2>, a.d / 64, 2, e2);
+    else run(ffn_gemm_q4_kernel<1, 32, 2, 4, false, 1>, a.d / 64, 1, e2);
   } else {
-    launch_timed(ffn_gemm_q4_kernel<2, 64, 2, 3, false>, blocks(a.f / 16), block, 0, s, e1, a);
-    launch_timed(ffn_gemm_q4_kernel<1, 64, 2, 2, false>, blocks(a.d / 64), block, 0, s, e2, a);
+    const auto large = [&](int units) { return items * ((units + kWaves - 1) / kWaves) <= kSplitLarge; };
+    if (large(a.f / 16)) run(ffn_gemm_q4_kernel<2, 64, 2, 2, false, 2>, a.f / 16, 2, e1);
+    else run(ffn_gemm_q4_kernel<2, 64, 2, 3, false, 1>, a.f / 16, 1, e1);
+    if (large(a.d / 64)) run(ffn_gemm_q4_kernel<1, 64, 2, 2, false, 2>, a.d / 64, 2, e2);
+    else run(ffn_gemm_q4_kernel<1, 64, 2, 2, false, 1>, a.d / 64, 1, e2);
   }
   return hipGetLastError();
 }
