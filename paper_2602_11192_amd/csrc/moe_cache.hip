@@ -43,24 +43,28 @@ int fail(int code, const char* fmt, ...) {
 
 // The single-launch FFN kernels (one partial row per 32 rows of d_ff) for a few tokens, the grouped GEMM beyond.  On a layer
 // whose experts are all resident the GEMM may take over earlier, from 4 tokens (INT4: 5), where
-//   - the call reads enough weights (every pair on an expert of its own) to outweigh the second launch: 350 MB, INT4 120 MB (4
-//     tokens, the kernel / the GEMM: 8 experts of 1024 x 4096, 201 MB, 32 / 59 us, 32 of 2048 x 512, 100 MB, 27 / 38); and
+//   - bf16: the call reads enough weights (every pair on an expert of its own) to outweigh the second launch: 350 MB (4
+//     tokens, the kernel / the GEMM: 8 experts of 1024 x 4096, 201 MB, 32 / 59 us, 32 of 2048 x 512, 100 MB, 27 / 38);
+//   - INT4, where more pairs cost the kernel more than more bytes: the experts of all pairs, once each, are 95 MB, and 120 f / d.  Kernel /
+//     GEMM: 12 experts of 3072 x 1024, 8 tokens (85) 31.8 / 34.1, 10 (106) 36 / 34.5, 16 of 2048 x 1024, 12 (85) 30.6 / 31.8, 16 (113) 33.2 / 32.3,
+//     32 of 4096 x 512, 8 (113) 40.9 / 36.7, but one of 16 of 2048 x 2048, 16 (113) 35.9 / 38.6; and
 //   - its down pass has workgroups enough - groups x blocks of 128 (INT4: 256) rows - to fill the units, each of them working
-//     through all of d_ff, in proportion to what more tokens cost the other kernel: 160 and 1000 / tokens of them (INT4 192 and
-//     1500 / tokens).  Kernel / GEMM, bf16: 4 Phi-3.5-MoE-like tokens (256 workgroups) 182 / 172, 4 Mixtral-like (256) 275 / 266, 6 on 16
-//     of 1536 x 4096 (192) 112 / 104, but 4 on 16 of 512 x 12288 (64) 81 / 137, 4 on 8 of 1536 x 6144 (96) 71 / 95; INT4: 6
-//     OLMoE-like tokens (384) 57 / 55, 16 (512) 77 / 61, 12 Phi-3.5-MoE-like (256) 156 / 145, but 10 on 16 of 512 x 12288 (32) 72 / 144,
-//     10 on 8 of 2048 x 8192 (64) 76 / 113.
+//     through all of d_ff, in proportion to what more tokens cost the other kernel: 160 (INT4 96) and 1000 / tokens of them.
+//     Kernel / GEMM, bf16: 4 Phi-3.5-MoE-like tokens (256 workgroups) 182 / 172, 4 Mixtral-like (256) 275 / 266, 6 on 16
+//     of 1536 x 4096 (192) 112 / 104, but 4 on 16 of 512 x 12288 (64) 81 / 137, 4 on 8 of 1536 x 6144 (96) 71 / 95; INT4: on 8 of 4096 x
+//     14336 (128) 5 tokens 150 / 153, 8 182 / 162, on 8 of 3072 x 8192 (96) 8 tokens 82 / 83, 11 96 / 92, but on 8 of 2048 x 8192 (64) 16 tokens
+//     79 / 83, on 16 of 512 x 12288 (32) 60 / 95.
 // Smaller layers, and calls that may have to fetch experts, stay with the kernel for longer.  The split-K pair (ffn_tiled.hip)
 // remains for small calls on shapes the kernel does not cover.
-FfnPlan plan_ffn(int pool_layout, int d, int f, int batch, bool resident, int groups, uint64_t expert_bytes) {
+FfnPlan plan_ffn(int pool_layout, int d, int f, int batch, int K, bool resident, int groups, uint64_t expert_bytes) {
   FfnPlan p{};
   p.tiled = pool_layout == MOE_LAYOUT_TILED;
   p.q4 = pool_layout == MOE_LAYOUT_TILED_INT4;
   const bool shape = p.q4 || (p.tiled && ffn_fused_supported(d, f, 1));
   const int64_t down_wgs = (int64_t)groups * (p.q4 ? (d + 255) / 256 : (d + 127) / 128);
-  const bool heavy = resident && groups * expert_bytes >= (p.q4 ? 120ull : 350ull) * 1000000 &&
-                     down_wgs >= (p.q4 ? 192 : 160) && down_wgs * batch >= (p.q4 ? 1500 : 1000);
+  const uint64_t pair_bytes = (uint64_t)batch * K * expert_bytes;
+  const bool weighty = p.q4 ? pair_bytes >= 95000000ull && pair_bytes / f >= 120000000ull / d : groups * expert_bytes >= 350000000ull;
+  const bool heavy = resident && weighty && down_wgs >= (p.q4 ? 96 : 160) && down_wgs * batch >= 1000;
   const int most = heavy ? (p.q4 ? 4 : 3) : p.q4 ? 16 : fused_max_tokens(f);
   p.fused = shape && batch <= most;
   p.gemm = !p.fused && (shape || (p.tiled && batch > fused_max_tokens(f)));
@@ -817,7 +821,7 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   a.mailbox = a.full ? nullptr : c->mailbox;       // (every lookup hits: nobody reads the record)
   // (a buffer per expert where all are resident: spare buffers choose no other kernels than the allocation-free entry point takes)
   const int g_max = (int)std::min<size_t>((size_t)batch * K, (size_t)(a.full ? E : c->P)) + cf.n_shared;
-  const FfnPlan plan = plan_ffn(cf.pool_layout, d, cf.d_ff, batch, c->full[layer] != 0, g_max, c->expert_bytes);
+  const FfnPlan plan = plan_ffn(cf.pool_layout, d, cf.d_ff, batch, K, c->full[layer] != 0, g_max, c->expert_bytes);
   a.work = plan_work(plan, batch, KS, g_max, d, cf.d_ff);
   const bool could = token_layer_supported(cf.pool_layout, cf.dtype, batch, E, c->C, d);
   const bool token = c->full[layer] && ffn_token_supported(cf.pool_layout, cf.dtype, batch, K, cf.n_shared, E, d, cf.d_ff, could);

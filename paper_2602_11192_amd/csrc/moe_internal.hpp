@@ -220,7 +220,7 @@ WorkPlan plan_ffn_gemm_q4(int batch, int KS, int g_max, bool streamed);
 hipError_t launch_ffn_gemm_q4(hipStream_t s, const FfnArgs& a, KernelEvents gate_up, KernelEvents down);
 // Which expert-FFN kernels run a call of `batch` tokens on experts of the given layout and shape.
 struct FfnPlan { bool fused, gemm, tiled, q4; };      // gemm: a grouped GEMM, which needs a work list
-FfnPlan plan_ffn(int pool_layout, int d, int f, int batch, bool resident, int groups, uint64_t expert_bytes);
+FfnPlan plan_ffn(int pool_layout, int d, int f, int batch, int K, bool resident, int groups, uint64_t expert_bytes);
 WorkPlan plan_work(const FfnPlan& p, int batch, int KS, int g_max, int d, int f);      // no list unless a GEMM runs
 hipError_t launch_ffn(hipStream_t s, int dtype, const FfnPlan& p, const FfnArgs& a, KernelEvents ke1, KernelEvents ke2);
 // identity: pair (b, j) has partial row b * KS + j (pos_of is not read).  share: words that the launch before left (ShareArgs), cleared here unless null

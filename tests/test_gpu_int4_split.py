@@ -26,3 +26,20 @@ def test_groups_that_split_the_contraction(d_model, d_ff, n_experts, batch):
     traces[0].extend(batched_step(torch, P, wl, cache, ost, 0, list(range(batch)), 0))
     compare_traces_and_stats(cache, ost, traces, q4_bytes(cfg))
     cache.close()
+
+
+# (either side of the line from which fewer than 17 tokens take the GEMM: 85 and 113 MB of experts over all pairs)
+@pytest.mark.parametrize("batch", [6, 8])
+def test_few_tokens_on_a_large_layer(batch):
+    import torch
+    from paper_2602_11192_amd import pool as P
+    cfg = small_cfg(d_model=4096, d_ff=512, n_experts=8, top_k=4, n_seqs=batch, n_steps=1, n_layers=1, capacity=8, n_shared=0,
+                    beta=1.0, pref_lo=1, pref_hi=1)
+    wl = Workload(cfg)
+    cache = P.make_cache(wl, int4=True, max_batch=batch, trace_capacity=4096)
+    cache.moe_cache_prefill_pins(0, list(range(8)))
+    ost = OracleStack(wl, int4=True, capacity=8, keep=9)
+    ost.caches[0].pin(list(range(8)))
+    traces = [batched_step(torch, P, wl, cache, ost, 0, list(range(batch)), 0)]
+    compare_traces_and_stats(cache, ost, traces, q4_bytes(cfg))
+    cache.close()
