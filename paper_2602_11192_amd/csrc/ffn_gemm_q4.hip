@@ -273,8 +273,21 @@ __global__ void __launch_bounds__(64 * kWaves * KG, MINW) ffn_gemm_q4_kernel(Ffn
 //   tiles of 64: 8 of 4096 x 14336, 400 tokens (4480 + 320) 571 / 534, 8 of 2048 x 1024, 300 (272 + 136) 58.3 / 52, 600 (416 + 208) 66.8 / 68.3.
 constexpr int kSplit4 = 320, kSplitSteps = 4, kSplit2 = 512, kSplitLarge = 352;
 constexpr int kSmallTile = 5, kLargeTile = 6, kStreamedTile = 7;     // log2 of the tokens per tile
+bool small_tile(int64_t load, int groups) { return load <= (int64_t)56 * groups; }
 
 }  // namespace
+
+Q4Split split_ffn_gemm_q4(int batch, int KS, int groups, int d, int f) {
+  const int64_t load = (int64_t)batch * KS;
+  const bool small = small_tile(load, groups);
+  const int64_t items = groups + (load >> (small ? kSmallTile : kLargeTile));     // upper bound
+  const auto pass = [&](int units, int kblocks, int step) {
+    const int64_t wgs = items * ((units + kWaves - 1) / kWaves);
+    if (!small) return wgs <= kSplitLarge ? 2 : 1;
+    return wgs <= kSplit4 && kblocks >= 4 * kSplitSteps * step ? 4 : wgs <= kSplit2 ? 2 : 1;
+  };
+  return {pass(f / 16, d / 32, 4), pass(d / 64, f / 32, 2)};
+}
 
 // What bounds it: the vector arithmetic of unpacking and scaling and the exchange through LDS as much as the codes, so
 // occupancy beats depth: one step ahead at four waves per SIMD takes 61.6 us per layer call of 64 OLMoE-like tokens, two
@@ -282,25 +295,23 @@ constexpr int kSmallTile = 5, kLargeTile = 6, kStreamedTile = 7;     // log2 of 
 // 27 us for 75 MB).  Tiles of 32 tokens win up to a mean of ~64 pairs per expert: 57 / 61.6 / 74 / 95.5 / 145 / 237 us at 17 /
 // 64 / 128 / 256 / 512 / 1024 tokens against 65 / 70 / 79 / 104 / 142 / 229 with tiles of 64.  Experts streamed from the host
 // cross the link once per tile: 128 tokens.
-WorkPlan plan_ffn_gemm_q4(int batch, int KS, int g_max, bool streamed) {
+// (Four groups exist for tiles of 32 only: they go with them where the buffers of a constrained cache, fewer than the experts, would ask for 64.)
+WorkPlan plan_ffn_gemm_q4(int batch, int KS, int g_max, bool streamed, const Q4Split& split) {
   const int64_t load = (int64_t)batch * KS;
+  const bool four = split.gate_up == 4 || split.down == 4;
   WorkPlan w{};
-  w.shift = streamed ? kStreamedTile : load <= (int64_t)56 * g_max ? kSmallTile : kLargeTile;
+  w.shift = streamed ? kStreamedTile : four || small_tile(load, g_max) ? kSmallTile : kLargeTile;
   w.cap = (int)work_capacity(g_max, load);
   return w;
 }
 
-hipError_t launch_ffn_gemm_q4(hipStream_t s, const FfnArgs& a, KernelEvents e1, KernelEvents e2) {
+hipError_t launch_ffn_gemm_q4(hipStream_t s, const FfnArgs& a, const Q4Split& split, KernelEvents e1, KernelEvents e2) {
   if (a.g_max <= 0) return hipSuccess;
   const int items = a.g_max + (int)(((int64_t)a.max_count * a.KS) >> a.work.shift);     // upper bound
   const auto run = [&](auto kernel, int units, int groups, KernelEvents e) {
     launch_timed(kernel, dim3(items * ((units + kWaves - 1) / kWaves)), dim3(64 * kWaves * groups), 0, s, e, a);
   };
-  const auto split = [&](int units, int kblocks, int step) {
-    const int wgs = items * ((units + kWaves - 1) / kWaves);
-    return wgs <= kSplit4 && kblocks >= 4 * kSplitSteps * step ? 4 : wgs <= kSplit2 ? 2 : 1;
-  };
-  const int s1 = split(a.f / 16, a.d / 32, 4), s2 = split(a.d / 64, a.f / 32, 2);
+  const int s1 = split.gate_up, s2 = split.down;
   if (a.work.shift == kStreamedTile) {
     run(ffn_gemm_q4_kernel<2, 128, 2, 1, true, 1>, a.f / 16, 1, e1);
     run(ffn_gemm_q4_kernel<1, 128, 2, 1, true, 1>, a.d / 64, 1, e2);
@@ -312,10 +323,9 @@ hipError_t launch_ffn_gemm_q4(hipStream_t s, const FfnArgs& a, KernelEvents e1, 
     else if (s2 == 2) run(ffn_gemm_q4_kernel<1, 32, 2, 4, false, 2>, a.d / 64, 2, e2);
     else run(ffn_gemm_q4_kernel<1, 32, 2, 4, false, 1>, a.d / 64, 1, e2);
   } else {
-    const auto large = [&](int units) { return items * ((units + kWaves - 1) / kWaves) <= kSplitLarge; };
-    if (large(a.f / 16)) run(ffn_gemm_q4_kernel<2, 64, 2, 2, false, 2>, a.f / 16, 2, e1);
+    if (s1 == 2) run(ffn_gemm_q4_kernel<2, 64, 2, 2, false, 2>, a.f / 16, 2, e1);
     else run(ffn_gemm_q4_kernel<2, 64, 2, 3, false, 1>, a.f / 16, 1, e1);
-    if (large(a.d / 64)) run(ffn_gemm_q4_kernel<1, 64, 2, 2, false, 2>, a.d / 64, 2, e2);
+    if (s2 == 2) run(ffn_gemm_q4_kernel<1, 64, 2, 2, false, 2>, a.d / 64, 2, e2);
     else run(ffn_gemm_q4_kernel<1, 64, 2, 2, false, 1>, a.d / 64, 1, e2);
   }
   return hipGetLastError();

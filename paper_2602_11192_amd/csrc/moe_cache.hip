@@ -56,7 +56,7 @@ int fail(int code, const char* fmt, ...) {
 //     79 / 83, on 16 of 512 x 12288 (32) 60 / 95.
 // Smaller layers, and calls that may have to fetch experts, stay with the kernel for longer.  The split-K pair (ffn_tiled.hip)
 // remains for small calls on shapes the kernel does not cover.
-FfnPlan plan_ffn(int pool_layout, int d, int f, int batch, int K, bool resident, int groups, uint64_t expert_bytes) {
+FfnPlan plan_ffn(int pool_layout, int d, int f, int batch, int K, bool resident, int groups, uint64_t expert_bytes, int call_batch, int E, int n_shared) {
   FfnPlan p{};
   p.tiled = pool_layout == MOE_LAYOUT_TILED;
   p.q4 = pool_layout == MOE_LAYOUT_TILED_INT4;
@@ -68,15 +68,17 @@ FfnPlan plan_ffn(int pool_layout, int d, int f, int batch, int K, bool resident,
   const int most = heavy ? (p.q4 ? 4 : 3) : p.q4 ? 16 : fused_max_tokens(f);
   p.fused = shape && batch <= most;
   p.gemm = !p.fused && (shape || (p.tiled && batch > fused_max_tokens(f)));
+  // (from the whole call and the experts, neither the wave nor the spare buffers: however a call is run, a token's sums are the same)
+  p.split = split_ffn_gemm_q4(call_batch, K + n_shared, (int)std::min<int64_t>((int64_t)call_batch * K, E) + n_shared, d, f);
   return p;
 }
 
 WorkPlan plan_work(const FfnPlan& p, int batch, int KS, int g_max, int d, int f) {
-  return !p.gemm ? WorkPlan{} : p.q4 ? plan_ffn_gemm_q4(batch, KS, g_max, false) : plan_ffn_gemm(batch, KS, g_max, d, f, false);
+  return !p.gemm ? WorkPlan{} : p.q4 ? plan_ffn_gemm_q4(batch, KS, g_max, false, p.split) : plan_ffn_gemm(batch, KS, g_max, d, f, false);
 }
 
 hipError_t launch_ffn(hipStream_t s, int dtype, const FfnPlan& p, const FfnArgs& a, KernelEvents ke1, KernelEvents ke2) {
-  return p.q4 ? (p.fused ? launch_ffn_fused_q4(s, a, ke1) : launch_ffn_gemm_q4(s, a, ke1, ke2))
+  return p.q4 ? (p.fused ? launch_ffn_fused_q4(s, a, ke1) : launch_ffn_gemm_q4(s, a, p.split, ke1, ke2))
          : p.fused ? launch_ffn_fused(s, a, ke1)
          : p.gemm ? launch_ffn_gemm(s, a, ke1, ke2)
          : p.tiled ? launch_ffn_tiled(s, a, ke1, ke2)
@@ -735,9 +737,9 @@ int moe_cache_prefill_pins(moe_cache_t* c, int32_t layer, const int32_t* expert_
 
 namespace {
 
-// One wave of tokens: the whole call when its evictions fit the spare buffers.
+// One wave of tokens: the whole call, of call_batch tokens, when its evictions fit the spare buffers.
 int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* logit_bias_dev, int32_t batch,
-                void* y_dev, int32_t* topk_idx_dev, float* topk_w_dev, hipStream_t s, int32_t row0) {
+                void* y_dev, int32_t* topk_idx_dev, float* topk_w_dev, hipStream_t s, int32_t row0, int32_t call_batch) {
   const moe_cache_config_t& cf = c->cfg;
   const int E = cf.n_experts, K = cf.top_k, KS = c->KS, d = cf.d_model;
 
@@ -821,7 +823,7 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
   a.mailbox = a.full ? nullptr : c->mailbox;       // (every lookup hits: nobody reads the record)
   // (a buffer per expert where all are resident: spare buffers choose no other kernels than the allocation-free entry point takes)
   const int g_max = (int)std::min<size_t>((size_t)batch * K, (size_t)(a.full ? E : c->P)) + cf.n_shared;
-  const FfnPlan plan = plan_ffn(cf.pool_layout, d, cf.d_ff, batch, K, c->full[layer] != 0, g_max, c->expert_bytes);
+  const FfnPlan plan = plan_ffn(cf.pool_layout, d, cf.d_ff, batch, K, c->full[layer] != 0, g_max, c->expert_bytes, call_batch, E, cf.n_shared);
   a.work = plan_work(plan, batch, KS, g_max, d, cf.d_ff);
   const bool could = token_layer_supported(cf.pool_layout, cf.dtype, batch, E, c->C, d);
   const bool token = c->full[layer] && ffn_token_supported(cf.pool_layout, cf.dtype, batch, K, cf.n_shared, E, d, cf.d_ff, could);
@@ -895,19 +897,20 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
 // A call whose evictions need more spare buffers than exist changes nothing on the device; it is then run as two
 // consecutive waves of tokens (recursively).  Tokens are looked up in row order either way, so hits, misses,
 // evictions and outputs are those of the unsplit call, as long as waves take the call's kernels: a token's sums are then the
-// same whatever the batch (moe_cache.h says where they do not).  A single token always fits (K <= C).
+// same whatever the batch, in the INT4 grouped GEMM because a wave splits the contraction as its call does (moe_cache.h says where
+// they do not).  A single token always fits (K <= C).
 int decode_rows(moe_cache_t* c, int32_t layer, const char* x, const float* bias, int32_t batch, char* y,
-                int32_t* idx, float* w, hipStream_t s, int32_t row0) {
-  const int rc = decode_wave(c, layer, x, bias, batch, y, idx, w, s, row0);
+                int32_t* idx, float* w, hipStream_t s, int32_t row0, int32_t call_batch) {
+  const int rc = decode_wave(c, layer, x, bias, batch, y, idx, w, s, row0, call_batch);
   if (rc != MOE_ERR_STAGING_EXHAUSTED || batch == 1) return rc;
   ++c->wave_splits;
   const int n1 = batch / 2;
   const size_t row = (size_t)c->cfg.d_model * c->elem;
   const int E = c->cfg.n_experts, K = c->cfg.top_k;
-  const int rc1 = decode_rows(c, layer, x, bias, n1, y, idx, w, s, row0);
+  const int rc1 = decode_rows(c, layer, x, bias, n1, y, idx, w, s, row0, call_batch);
   if (rc1 != MOE_OK) return rc1;
   return decode_rows(c, layer, x + n1 * row, bias ? bias + (size_t)n1 * E : nullptr, batch - n1, y + n1 * row,
-                     idx ? idx + (size_t)n1 * K : nullptr, w ? w + (size_t)n1 * K : nullptr, s, row0 + n1);
+                     idx ? idx + (size_t)n1 * K : nullptr, w ? w + (size_t)n1 * K : nullptr, s, row0 + n1, call_batch);
 }
 
 }  // namespace
@@ -925,7 +928,7 @@ int moe_layer_decode(moe_cache_t* c, int32_t layer, const void* x_dev, const flo
   DeviceGuard guard;
   HIPCHK(guard.enter(c->device));
   return decode_rows(c, layer, static_cast<const char*>(x_dev), logit_bias_dev, batch, static_cast<char*>(y_dev),
-                     topk_idx_dev, topk_w_dev, static_cast<hipStream_t>(hip_stream), 0);
+                     topk_idx_dev, topk_w_dev, static_cast<hipStream_t>(hip_stream), 0, batch);
 }
 
 int moe_pooled_prefetch_set(const float* scores, int32_t n_seqs, int32_t n_experts, int32_t capacity,
@@ -978,7 +981,8 @@ int moe_layer_prefill(moe_cache_t* c, int32_t layer, const void* x_dev, const fl
   // Tiles for experts that cross the link, unless all are known to be resident (8 / 33 / 512 INT4 tokens through a resident
   // OLMoE-like layer: 142 / 173 / 353 us with them, 50 / 67 / 191 with the tiles of resident calls).
   const bool streamed = !c->full[layer];
-  a.work = q4 ? plan_ffn_gemm_q4(n_tokens, KS, g_max, streamed) : plan_ffn_gemm(n_tokens, KS, g_max, d, cf.d_ff, streamed);
+  const Q4Split split = streamed ? Q4Split{1, 1} : split_ffn_gemm_q4(n_tokens, KS, g_max, d, cf.d_ff);
+  a.work = q4 ? plan_ffn_gemm_q4(n_tokens, KS, g_max, streamed, split) : plan_ffn_gemm(n_tokens, KS, g_max, d, cf.d_ff, streamed);
   HIPCHK(launch_route_cache(s, cf.dtype, ra, state_of(c, layer), c->t, a, RouteScratch{c->o, c->o_bytes, c->n_arrive}, KernelEvents{}));
 
   FfnArgs fa{};
@@ -995,7 +999,7 @@ int moe_layer_prefill(moe_cache_t* c, int32_t layer, const void* x_dev, const fl
   fa.pass = 2; fa.fused = 0;
   fa.pool = c->pool_dev[layer];
   fa.fetch = 1;
-  HIPCHK(q4 ? launch_ffn_gemm_q4(s, fa, KernelEvents{}, KernelEvents{}) : launch_ffn_gemm(s, fa, KernelEvents{}, KernelEvents{}));
+  HIPCHK(q4 ? launch_ffn_gemm_q4(s, fa, split, KernelEvents{}, KernelEvents{}) : launch_ffn_gemm(s, fa, KernelEvents{}, KernelEvents{}));
 
   Mailbox mb{};
   if (!c->full[layer]) {          // with every expert resident nothing is streamed

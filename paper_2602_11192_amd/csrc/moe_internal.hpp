@@ -216,11 +216,15 @@ hipError_t launch_decode_tiles(hipStream_t s, const FfnArgs& a, const RoutedArgs
 int fused_q4_waves(int d);
 bool ffn_fused_q4_supported(int d, int f, int max_count);
 hipError_t launch_ffn_fused_q4(hipStream_t s, const FfnArgs& a, KernelEvents ev);
-WorkPlan plan_ffn_gemm_q4(int batch, int KS, int g_max, bool streamed);
-hipError_t launch_ffn_gemm_q4(hipStream_t s, const FfnArgs& a, KernelEvents gate_up, KernelEvents down);
+// Groups of waves that split the contraction of either pass of the INT4 grouped GEMM (1, 2 or 4); part of the order in which a token's sums are formed.
+struct Q4Split { int gate_up, down; };
+Q4Split split_ffn_gemm_q4(int batch, int KS, int groups, int d, int f);
+WorkPlan plan_ffn_gemm_q4(int batch, int KS, int g_max, bool streamed, const Q4Split& split);
+hipError_t launch_ffn_gemm_q4(hipStream_t s, const FfnArgs& a, const Q4Split& split, KernelEvents gate_up, KernelEvents down);
 // Which expert-FFN kernels run a call of `batch` tokens on experts of the given layout and shape.
-struct FfnPlan { bool fused, gemm, tiled, q4; };      // gemm: a grouped GEMM, which needs a work list
-FfnPlan plan_ffn(int pool_layout, int d, int f, int batch, int K, bool resident, int groups, uint64_t expert_bytes);
+struct FfnPlan { bool fused, gemm, tiled, q4; Q4Split split; };      // gemm: a grouped GEMM, which needs a work list
+// call_batch: tokens of the whole call, of which these may be a part (a wave); E: experts of the layer
+FfnPlan plan_ffn(int pool_layout, int d, int f, int batch, int K, bool resident, int groups, uint64_t expert_bytes, int call_batch, int E, int n_shared);
 WorkPlan plan_work(const FfnPlan& p, int batch, int KS, int g_max, int d, int f);      // no list unless a GEMM runs
 hipError_t launch_ffn(hipStream_t s, int dtype, const FfnPlan& p, const FfnArgs& a, KernelEvents ke1, KernelEvents ke2);
 // identity: pair (b, j) has partial row b * KS + j (pos_of is not read).  share: words that the launch before left (ShareArgs), cleared here unless null

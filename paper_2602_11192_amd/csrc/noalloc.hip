@@ -100,7 +100,7 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
   const size_t NP = (size_t)batch * KS;
   const int G = (int)std::min<size_t>((size_t)batch * K, (size_t)E) + ns;
   const size_t max_miss = std::max<size_t>((size_t)batch * K, (size_t)E);
-  FfnPlan plan = plan_ffn(L->pool_layout, d, f, batch, K, true, G, eb);
+  FfnPlan plan = plan_ffn(L->pool_layout, d, f, batch, K, true, G, eb, batch, E, ns);
 
   // ---- carve the array ----
   size_t o_tick, o_score, o_scal, o_ein, o_bos, o_free, o_zom, o_used, o_idx, o_wp, o_pb, o_sp, o_po, o_gd, o_work, o_ng,
@@ -142,7 +142,7 @@ extern "C" int moe_layer_decode_resident_noalloc(const moe_resident_layer_t* L, 
   } else if (o > kScratchBytes && plan.gemm) {
     // with so few rows of d_ff that a pair's partial rows are smaller than its h and GEMM row together, a few tokens may
     // fit the single-launch kernel alone
-    const FfnPlan few = plan_ffn(L->pool_layout, d, f, batch, K, false, 0, 0);
+    const FfnPlan few = plan_ffn(L->pool_layout, d, f, batch, K, false, 0, 0, batch, E, ns);
     if (few.fused) {
       plan = few;
       o = carve();

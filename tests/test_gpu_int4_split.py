@@ -43,3 +43,42 @@ def test_few_tokens_on_a_large_layer(batch):
     traces = [batched_step(torch, P, wl, cache, ost, 0, list(range(batch)), 0)]
     compare_traces_and_stats(cache, ost, traces, q4_bytes(cfg))
     cache.close()
+
+
+# Every token of part p of the call prefers the experts of set p, so that the parts take turns in the slots.  Where the split of a part by itself would be
+# another than that of the whole call: (4096 x 512, 256) down pass, 1024 and 512 workgroups, and gate/up, 512 and 256; (1024 x 256, 1400) 64-token tiles;
+# (512 x 1024, 1000) one set: 32-token tiles by the experts, 64-token ones by the slots.
+@pytest.mark.parametrize("d,f,E,C,batch,parts", [(4096, 512, 48, 24, 256, 2), (1024, 256, 48, 24, 1400, 2), (512, 1024, 64, 16, 1000, 1)])
+def test_a_call_run_as_waves_has_the_bits_of_the_unsplit_one(d, f, E, C, batch, parts):
+    import torch
+    from paper_2602_11192_amd import binding as B
+    K = 2
+    gen = torch.Generator().manual_seed(3)
+    gate_up = torch.randint(0, 256, (E, f // 16 * (d // 128), 2304), generator=gen, dtype=torch.uint8)       # 2048 bytes of codes, 256 of scales
+    down = torch.randint(0, 256, (E, f // 32 * (d // 64), 1152), generator=gen, dtype=torch.uint8)           # 1024 and 128
+    for records, codes in ((gate_up, 2048), (down, 1024)):
+        scales = torch.rand(*records.shape[:2], (records.shape[2] - codes) // 2, generator=gen) * 0.02 + 0.005
+        records[..., codes:] = scales.bfloat16().view(torch.uint8)
+    pool = torch.cat([gate_up.reshape(E, -1), down.reshape(E, -1)], dim=1).reshape(-1).pin_memory()
+    router = (torch.randn(1, E, d, generator=gen) * d ** -0.5).bfloat16().cuda()
+    x = torch.randn(batch, d, generator=gen).bfloat16().cuda()
+    bias = torch.zeros(batch, E)
+    for p in range(parts):
+        bias[p * batch // parts:(p + 1) * batch // parts, p * C:(p + 1) * C] = 60.0
+    bias = bias.cuda()
+    out = []
+    for staging in (0, E):
+        print("waves", d, f, batch, staging, flush=True)
+        cache = B.MoECache(n_layers=1, n_experts=E, top_k=K, d_model=d, d_ff=f, capacity=C, dtype=B.MOE_DTYPE_BF16, router_w=router, expert_pool=pool,
+                           max_batch=batch, staging_buffers=staging, pool_layout=B.MOE_LAYOUT_TILED_INT4)
+        y = torch.empty(batch, d, dtype=torch.bfloat16, device="cuda:0")
+        idx = torch.empty(batch, K, dtype=torch.int32, device="cuda:0")
+        w = torch.empty(batch, K, device="cuda:0")
+        cache.moe_layer_decode(0, x, y, bias, idx, w)
+        torch.cuda.synchronize()
+        out.append((y.cpu().view(torch.int16), idx.cpu(), w.cpu(), cache.moe_cache_stats(0)))
+        cache.close()
+    assert out[0][3] == out[1][3] and out[0][3]["misses"] >= parts * (C - 1)
+    assert torch.isfinite(out[0][0].view(torch.bfloat16).float()).all()
+    for a, b in zip(out[0][:3], out[1][:3]):
+        assert torch.equal(a, b)
