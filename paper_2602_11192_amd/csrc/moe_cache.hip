@@ -133,6 +133,7 @@ struct moe_cache {
   size_t layer_stride = 0;             // bytes between the tables (and device counters) of consecutive layers
   char* router_packed = nullptr;       // [L] router matrices in operand order, for the calls that the single-launch decode covers
   unsigned long long* share = nullptr; // words through which the workgroups of a one-token call hand each other the logits
+  int32_t share_blind = 0;             // (tests) workgroups that do not look at them
   bool single_ok = false;              // the single-launch decode kernel covers this cache's shape and policy
   int single_max_batch = 0;
   int n_cu = 0;                        // compute units of the device
@@ -801,7 +802,7 @@ int decode_wave(moe_cache_t* c, int32_t layer, const void* x_dev, const float* l
     fa.fused = 1; fa.pass = 2;
     fa.pool = c->pool_dev[layer];
     fa.fetch = 1;
-    ShareArgs sh{c->share, 0, 0, 0};
+    ShareArgs sh{c->share, 0, 0, 0, c->share_blind};
     fa.n_parts = decode_tiles_parts(cf.pool_layout, d, cf.d_ff, batch, fa.g_max, c->n_cu, E);
     if (fa.n_parts > 0) HIPCHK(launch_decode_tiles(s, fa, q, sh, ps ? ps->gate_up : KernelEvents{}));
     else HIPCHK(launch_decode_single(s, cf.pool_layout, fa, q, sh, ps ? ps->gate_up : KernelEvents{}));
@@ -1114,6 +1115,18 @@ int moe_cache_timing(moe_cache_t* c, moe_timing_t* out, int32_t clear) {
   }
   *out = c->timing;
   if (clear) c->timing = moe_timing_t{};
+  return MOE_OK;
+}
+
+}  // extern "C"
+
+// ---------------------------------------------------------------- for the tests: no part of the interface (moe_cache.h)
+extern "C" {
+
+// The even (bit 0) and odd (bit 1) workgroups of a die of a one-token call do not look for the logits that others form: they form all by themselves.
+int moe_test_share_blind(moe_cache_t* c, int32_t which) {
+  if (!c || which < 0 || which > 3) return fail(MOE_ERR_INVALID_ARG, "bad argument");
+  c->share_blind = which;
   return MOE_OK;
 }
 

@@ -162,6 +162,7 @@ struct RoutedArgs {
 struct ShareArgs {
   unsigned long long* words;      // [8][kShareWords], zero between calls; null: not shared
   int32_t sharers, per_wave, slices;
+  int32_t blind;                  // 0; tests: bit 0 / 1, the even / odd workgroups of a die do not look at the words
 };
 constexpr int kShareWords = 256;                // per die: 16 units, the tiles of 256 experts
 constexpr size_t kShareBytes = 8 * kShareWords * sizeof(unsigned long long);

@@ -387,10 +387,11 @@ __device__ __forceinline__ void share_logits(const RoutedArgs& ra, const ShareAr
     if (u + sharers < units) __syncthreads();
   }
   if (tb_exp >= 0) rl.buf_of[tb_exp] = tb_buf;            // (behind the first barrier, which follows the clearing)
+  const bool look = ((sh.blind >> ((id >> 3) & 1)) & 1) == 0;
   for (int i = tid; i < units * 16; i += 64 * WAVES) {
     if ((i >> 4) % sharers == mine) continue;
     unsigned long long got = 0;
-    for (int t = 0; t < kShareTries; ++t) {
+    for (int t = look ? 0 : kShareTries; t < kShareTries; ++t) {
       got = __hip_atomic_load(words + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if ((got >> 32) == (tag >> 32)) break;
       __builtin_amdgcn_s_sleep(1);

@@ -72,3 +72,36 @@ def test_replays_of_a_captured_call(int4):
         if i % 3 == 2:
             assert torch.equal(y.view(torch.int16), eager.view(torch.int16)), i
     cache.close()
+
+
+@pytest.mark.parametrize("int4,shape", [(False, CHUNK[0]), (False, CHUNK[1]), (False, CHUNK[3]), (False, TILES[0]), (True, INT4[0]), (True, INT4[3])])
+def test_logits_that_do_not_arrive_in_time(int4, shape):
+    """A workgroup whose looks for the others' logits were in vain forms all of them by itself.  Here all workgroups do without looking, or every other
+    one of a die while the rest take what arrives (the bookkeeping one is among the odd): selections, weights, outputs, trace and counters keep their bits."""
+    import torch
+    from paper_2602_11192_amd import pool as P
+    E, K, cap, ns, d, f = shape
+    cfg = small_cfg(n_experts=E, top_k=K, capacity=cap, n_shared=ns, d_model=d, d_ff=f, n_layers=1, n_seqs=1, n_steps=5, pref_lo=min(K, 4),
+                    pref_hi=K + 1, beta=2.0, cfg_id=73)
+    wl = Workload(cfg)
+    x = P.to_device(wl.tokens(0))
+    bias = torch.from_numpy(wl.bias(0, 0)[None, :]).cuda()
+    runs = []
+    for blind in (0, 3, 2, 1):
+        print("blind", blind, int4, shape, flush=True)
+        cache = P.make_cache(wl, tiled=not int4, int4=int4, trace_capacity=256, fetch_mode=P.B.MOE_FETCH_IN_KERNEL)
+        assert P.B.lib.moe_test_share_blind(cache._h, blind) == 0
+        out = []
+        for t in range(cfg.n_steps):
+            y = torch.empty((1, d), dtype=torch.bfloat16, device="cuda:0")
+            idx = torch.empty((1, K), dtype=torch.int32, device="cuda:0")
+            w = torch.empty((1, K), dtype=torch.float32, device="cuda:0")
+            cache.moe_layer_decode(0, x[t:t + 1], y, bias, idx, w)
+            out += [y.view(torch.int16), idx, w.view(torch.int32)]
+        torch.cuda.synchronize()
+        trace, total = cache.moe_cache_read_trace(0)
+        runs.append([o.cpu().tolist() for o in out] + [trace.tolist(), total, cache.moe_cache_stats(0)])
+        cache.close()
+    assert runs[0][-1]["misses"] > 0 and runs[0][-2] == cfg.n_steps * K
+    for other in runs[1:]:
+        assert other == runs[0]
