@@ -1130,4 +1130,25 @@ int moe_test_share_blind(moe_cache_t* c, int32_t which) {
   return MOE_OK;
 }
 
+// The recency a layer's table holds, after all enqueued work: per expert the time of its last lookup (0: not resident) and its discounted count
+// (tick, score: host, [n_experts]); the number of lookups so far.
+int moe_test_recency(moe_cache_t* c, int32_t layer, uint64_t* tick, double* score, int64_t* clock) {
+  if (!c || layer < 0 || layer >= c->cfg.n_layers || !tick || !score || !clock) return fail(MOE_ERR_INVALID_ARG, "bad argument");
+  DeviceGuard guard;
+  HIPCHK(guard.enter(c->device));
+  HIPCHK(hipDeviceSynchronize());
+  const LayerState& st = state_of(c, layer);
+  const int E = c->cfg.n_experts;
+  std::vector<uint64_t> slot_tick(c->C);
+  std::vector<int32_t> expert(c->C);
+  HIPCHK(hipMemcpy(slot_tick.data(), st.tick, (size_t)c->C * 8, hipMemcpyDeviceToHost));
+  HIPCHK(hipMemcpy(expert.data(), st.expert_in, (size_t)c->C * 4, hipMemcpyDeviceToHost));
+  HIPCHK(hipMemcpy(score, st.score, (size_t)E * 8, hipMemcpyDeviceToHost));
+  HIPCHK(hipMemcpy(clock, st.scalars + SC_CLOCK, 8, hipMemcpyDeviceToHost));
+  std::fill(tick, tick + E, 0ull);
+  for (int i = 0; i < c->C; ++i)
+    if (expert[i] >= 0 && expert[i] < E) tick[expert[i]] = slot_tick[i];
+  return MOE_OK;
+}
+
 }  // extern "C"

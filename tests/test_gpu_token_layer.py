@@ -1,6 +1,8 @@
 """fp32 layers whose experts are all in memory, the whole call in one launch: at both ends of its limits (64 tokens, 64 experts, one expert),
 on odd widths and several steps of a workgroup, under LRU and discounted counts.  Outputs, selections, trace, counters and resident sets
-against the oracle; in place; and replayed from a graph."""
+against the oracle; recency against the kernels with a routing launch; in place; and replayed from a graph."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -41,6 +43,42 @@ def test_whole_layer(E, K, ns, d, f, policy, gamma):
         trace.extend(res.trace)
     compare_traces_and_stats(cache, ost, [trace], cfg.expert_bytes)
     cache.close()
+
+
+@pytest.mark.parametrize("E,K,ns,d,f", [(8, 2, 0, 64, 128), (64, 8, 1, 36, 20), (1, 1, 0, 260, 8), (63, 3, 2, 100, 60), (64, 1, 0, 1024, 8)])
+@pytest.mark.parametrize("policy,gamma", [(oracle.POLICY_LRU, 1.0), (oracle.POLICY_GAMMA, 0.9)])
+def test_recency_is_that_of_a_launch_for_the_routing(E, K, ns, d, f, policy, gamma):
+    """Last lookups, discounted counts and clock after every call, against a layer of the same router and tokens whose experts are too
+    large for the one launch (nothing is evicted from a full layer, so no trace would tell)."""
+    import torch
+    from paper_2602_11192_amd import binding as B
+    gen = torch.Generator().manual_seed(E * d)
+    router = (torch.randn(1, E, d, generator=gen) * d ** -0.5).cuda()
+    caches = []
+    for width in (f, ((1 << 20) // (12 * (K + ns) * d) // 4 + 1) * 4):
+        pool = torch.zeros(E * 3 * d * width, pin_memory=True)
+        cache = B.MoECache(n_layers=1, n_experts=E, n_shared=ns, top_k=K, d_model=d, d_ff=width, capacity=E, dtype=B.MOE_DTYPE_FP32, router_w=router,
+                           expert_pool=pool, shared_w=torch.zeros(ns * 3 * d * width, device="cuda:0") if ns else None, max_batch=64, trace_capacity=4096,
+                           policy=B.MOE_POLICY_LRU if policy == oracle.POLICY_LRU else B.MOE_POLICY_GAMMA, gamma=gamma)
+        cache.moe_cache_prefill_pins(0, list(range(E))[::-1])
+        cache.moe_cache_set_profiling(True)
+        caches.append(cache)
+    for batch in (1, 64, 2, 7):
+        print("recency", E, K, policy, batch, flush=True)
+        x, bias = torch.randn(batch, d, generator=gen).cuda(), torch.randn(batch, E, generator=gen).cuda()
+        seen = []
+        for cache in caches:
+            idx = torch.empty((batch, K), dtype=torch.int32, device="cuda:0")
+            cache.moe_layer_decode(0, x, torch.empty_like(x), bias, idx)
+            tick, score, clock = np.zeros(E, np.uint64), np.zeros(E, np.float64), np.zeros(1, np.int64)
+            assert B.lib.moe_test_recency(cache._h, 0, *(v.ctypes.data_as(C.c_void_p) for v in (tick, score, clock))) == 0
+            seen.append((idx.cpu().tolist(), tick.tolist(), score.tolist(), clock.tolist(), cache.moe_cache_read_trace(0)[0].tolist()))
+        assert seen[0] == seen[1]
+        assert len(set(seen[0][1])) == E and (policy == oracle.POLICY_LRU or max(seen[0][2]) > 0)
+    launches = [cache.moe_cache_timing() for cache in caches]
+    assert launches[0]["decode_single_launches"] >= 1 and launches[1]["decode_single_launches"] == 0      # (1024 x 8: 64 tokens only)
+    for cache in caches:
+        cache.close()
 
 
 def test_replays_of_a_captured_call():
