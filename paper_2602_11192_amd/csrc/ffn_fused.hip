@@ -73,7 +73,8 @@ __global__ void pack_router_kernel(const uint16_t* __restrict__ w, uint16_t* __r
 // launch was built and measured: the workgroups have to meet at a device-scope counter, and on this GPU that
 // meeting alone - 8 us for 256 workgroups, far more with release/acquire fences, which write back and invalidate
 // whole L2 caches - costs more than the separate combine launch.)
-template <int WAVES, int SLOT0, bool ROUTED, bool SHARED = false>
+// XLDS: the tokens are read from the prologue's LDS.
+template <int WAVES, int SLOT0, bool ROUTED, bool SHARED = false, bool XLDS = ROUTED>
 __device__ __forceinline__ void fused_body(const FfnArgs& a, const RoutedArgs* rap, const ShareArgs* sh = nullptr) {
   __shared__ float red[WAVES][2][256];            // partial gate / up tiles of the waves
   __shared__ __align__(16) uint16_t hs[16][32];   // h of the chunk, bf16, [token][row in chunk]
@@ -128,14 +129,13 @@ __device__ __forceinline__ void fused_body(const FfnArgs& a, const RoutedArgs* r
 
   const int begin = gd_begin, cnt = gd_count;
   const uint16_t* xrow = nullptr;
-  // The single launch has the tokens in LDS: a third of the gate/up requests fewer.  us per layer call, from memory / from LDS: 2 of 8 experts of
-  // 2048 x 512 16.6 / 15.8, of 4096 x 512 26.7 / 25.7, 2 of 48 of 1536 x 1024 18.8 / 17.5, two tokens 2 of 8 of 2048 x 512 20.2 / 19.5; where every unit
-  // streams, 4 of 8 of 2048 x 2048 (256 workgroups), 25.1 / 25.3.
-  if constexpr (ROUTED) {      // (columns beyond the group's repeat its first token and are not looked at)
+  if constexpr (XLDS) {      // (columns beyond the group's repeat its first token and are not looked at)
     const int p = SHARED || a.max_count == 1 ? begin : rl_store.sorted_pair[n < cnt ? begin + n : begin];   // one token: pairs in order
     xrow = reinterpret_cast<const uint16_t*>(rl_store.xs) + (size_t)(p / a.KS) * d + (size_t)kb0 * 32 + q * 8;
   } else if (n < cnt) {
-    const int p = n == 0 ? gd_pair0 : a.t.sorted_pair[begin + n];   // a single-token group needs no second look-up
+    int p;
+    if constexpr (ROUTED) p = begin;                                // (one token)
+    else p = n == 0 ? gd_pair0 : a.t.sorted_pair[begin + n];        // a single-token group needs no second look-up
     xrow = reinterpret_cast<const uint16_t*>(a.x) + (size_t)(p / a.KS) * d + (size_t)kb0 * 32 + q * 8;
   }
 
@@ -145,7 +145,7 @@ __device__ __forceinline__ void fused_body(const FfnArgs& a, const RoutedArgs* r
   const int total = na + nb;
   auto issue = [&](int slot, int item) {
     if (item < na) {
-      if constexpr (!ROUTED) sx[slot] = xrow ? *reinterpret_cast<const u32x4*>(xrow + (size_t)item * x_step) : u32x4{0, 0, 0, 0};
+      if constexpr (!XLDS) sx[slot] = xrow ? *reinterpret_cast<const u32x4*>(xrow + (size_t)item * x_step) : u32x4{0, 0, 0, 0};
       sg[slot] = ldw(wa + (size_t)item * w_step);
       su[slot] = ldw(wa + (size_t)item * w_step + 64);
     } else if (item < total) {
@@ -160,7 +160,7 @@ __device__ __forceinline__ void fused_body(const FfnArgs& a, const RoutedArgs* r
 #pragma unroll
     for (int u = 0; u < kDepth; ++u) {
       if (base + u < na) {      // uniform
-        const bf16x8 xb = __builtin_bit_cast(bf16x8, ROUTED ? *reinterpret_cast<const u32x4*>(xrow + (size_t)(base + u) * x_step) : sx[u]);
+        const bf16x8 xb = __builtin_bit_cast(bf16x8, XLDS ? *reinterpret_cast<const u32x4*>(xrow + (size_t)(base + u) * x_step) : sx[u]);
         accg = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, sg[u]), xb, accg, 0, 0, 0);
         accu = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, su[u]), xb, accu, 0, 0, 0);
         if (from_host) {
@@ -221,9 +221,9 @@ __global__ void __launch_bounds__(64 * WAVES) ffn_fused_kernel(FfnArgs a) {
 
 // (second launch bound: four waves per SIMD, i.e. at most 128 registers, so that as many workgroups are
 // resident at once as with the plain expert kernel)
-template <int WAVES, int SLOT0>
+template <int WAVES, int SLOT0, bool XLDS>
 __global__ void __launch_bounds__(64 * WAVES, 4) decode_single_kernel(FfnArgs a, RoutedArgs ra) {
-  fused_body<WAVES, SLOT0, true>(a, &ra);
+  fused_body<WAVES, SLOT0, true, false, XLDS>(a, &ra);
 }
 template <int WAVES, int SLOT0>
 __global__ void __launch_bounds__(64 * WAVES, 4) decode_shared_kernel(FfnArgs a, RoutedArgs ra, ShareArgs sh) {
@@ -317,8 +317,9 @@ bool waves_ok(int d, int waves) {
 
 // Small grids need many waves per workgroup to have enough loads in flight; large grids stream best with small
 // workgroups (less time lost at the workgroup barriers).  Measured on MI355X.
+constexpr int kOneEach = 256;
 int pick_waves(int d, int n_workgroups) {
-  const int pref = n_workgroups <= 256 ? 8 : 4;     // eight waves only while every workgroup has a compute unit to itself
+  const int pref = n_workgroups <= kOneEach ? 8 : 4;     // eight waves only while every workgroup has a compute unit to itself
   for (int w : {pref, 8, 4, 16})
     if (waves_ok(d, w)) return w;
   return 0;
@@ -336,16 +337,29 @@ void launch_fused_waves(hipStream_t s, const FfnArgs& a, KernelEvents ev) {
   }
 }
 
+// Where the single launch reads its tokens.  From LDS a wave makes a third fewer requests per gate/up item, but waits for LDS in front of the products; a
+// ring that goes round without a break while a workgroup streams on every unit has no pause to hide that.  us per layer call, from memory / from LDS:
+//   eight waves, one token, 225 to 256 workgroups, two and more full turns of the ring: 8 of 16 experts of 2048 x 1024 26.1 / 26.8, 2 of 8 of 2048 x 4096
+//     26.2 / 27.0, 4 of 8 of 2048 x 1920 24.9 / 25.5, of 4096 x 1920 38.9 / 39.2, of 3072 x 2048 32.6 / 32.7
+//   one turn, or a broken one: 8 of 16 of 1024 x 1024 18.1 / 17.9, 4 of 8 of 2560 x 2048 32.2 / 31.1; 208 workgroups: 4 of 8 of 2048 x 1664 23.0 / 23.0,
+//     of 1024 x 1664 16.3 / 16.1, 96: of 2048 x 768 19.6 / 18.9; 2 to 4 tokens (36 points) 1.1 % in the mean, 2 on 4 of 8 of 3072 x 1024 29.0 / 28.3.
+constexpr int kTokenRingWgs = 225, kTokenRingTurns = 2;
+
 template <int WAVES>
 void launch_single_waves(hipStream_t s, const FfnArgs& a, const RoutedArgs& ra, ShareArgs& sh, KernelEvents ev) {
   dim3 grid(a.f / 32, a.g_max + 1), block(64 * WAVES);     // + the bookkeeping row
-  const bool shared = plan_share(sh, ra, WAVES, a.f / 32 * a.g_max);
+  const int wgs = a.f / 32 * a.g_max;
+  const bool shared = plan_share(sh, ra, WAVES, wgs);
+  const int na = (a.d / 32) / (WAVES / 2);
   const auto launch = [&](auto slot0) {
     constexpr int SLOT0 = decltype(slot0)::value;
-    if (shared) launch_timed(decode_shared_kernel<WAVES, SLOT0>, grid, block, 0, s, ev, a, ra, sh);
-    else launch_timed(decode_single_kernel<WAVES, SLOT0>, grid, block, 0, s, ev, a, ra);
+    if (shared) return launch_timed(decode_shared_kernel<WAVES, SLOT0>, grid, block, 0, s, ev, a, ra, sh);
+    if constexpr (WAVES == 8 && SLOT0 == 0) {
+      if (ra.a.B == 1 && na >= kTokenRingTurns * kDepth && wgs >= kTokenRingWgs && wgs <= kOneEach)
+        return launch_timed(decode_single_kernel<WAVES, SLOT0, false>, grid, block, 0, s, ev, a, ra);
+    }
+    launch_timed(decode_single_kernel<WAVES, SLOT0, true>, grid, block, 0, s, ev, a, ra);
   };
-  const int na = (a.d / 32) / (WAVES / 2);
   switch (na % kDepth) {
     case 0: launch(std::integral_constant<int, 0>{}); break;
     case 1: launch(std::integral_constant<int, 1>{}); break;
