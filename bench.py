@@ -362,8 +362,8 @@ def int4_section(torch, P, wl, a):
             "expert_bytes": qb, "tokens_per_s": n_tok / dt,
             "cache_hit_rate": st["hits"] / max(1, st["lookups"]), "misses_per_token": st["misses"] / max(1, n_tok),
             "pcie_GBps": tm["fetch_bytes"] / (tm["fetch_ms"] * 1e-3) / 1e9 if tm["fetch_ms"] > 0 else None,
-            "main_kernel": {"kernel": ("decode_single_q4_kernel (router, gating, lookups and the 4-bit expert FFN in one "
-                                       "launch)" if single else "ffn_fused_q4_kernel"),
+            "main_kernel": {"kernel": (single_launch_kernels(cfg, int4=True)[0] + " (router, gating, lookups and the 4-bit expert "
+                                       "FFN in one launch)" if single else "ffn_fused_q4_kernel"),
                             "bytes_per_launch": k_bytes, "avg_launch_ms": k_ms,
                               "launches_timed": tm["decode_single_launches"] if single else tm["ffn_fused_launches"],
                               "achieved_GBps": k_bytes / (k_ms * 1e-3) / 1e9 if k_ms > 0 else None,
@@ -419,6 +419,17 @@ def cpu_baseline(wl, n_tokens):
                               "sample": "first %d decode tokens, same loops on one thread" % done1}}
 
 
+SHARED_LOGITS_KIB = 136       # kShareFrags in csrc/routed_prologue.hpp
+
+
+def single_launch_kernels(cfg, tiles=False, int4=False):
+    """Names of the two launches of a one-token call: where W_r (in tiles of 16 experts) is this large, the workgroups form
+    the logits together and the combine clears the words they used."""
+    shared = (cfg.n_experts + 15) // 16 * 16 * cfg.d_model * 2 >= SHARED_LOGITS_KIB * 1024
+    stem = "decode_tiles_shared" if tiles and shared else "decode_tiles" if tiles else "decode_shared" if shared else "decode_single"
+    return stem + ("_q4_kernel" if int4 else "_kernel"), "combine_clear_kernel" if shared else "combine_chunks_kernel"
+
+
 def kernel_roofline(cfg, tm, traffic):
     """Roofline entry of the dominant kernel from the HIP-event sums of a profiled pass (calls without a miss)."""
     K, d, f, s_el, E = cfg.top_k, cfg.d_model, cfg.d_ff, cfg.elem_bytes, cfg.n_experts
@@ -430,7 +441,7 @@ def kernel_roofline(cfg, tm, traffic):
         k_bytes = experts + E * d * s_el + d * s_el + E * 4 + KS_ * d * 4
         k_ms = tm["decode_single_ms"] / tm["decode_single_launches"]
         k_n = tm["decode_single_launches"]
-        k_name = (("decode_tiles_kernel" if tm.get("decode_tiles_launches", 0) > 0 else "decode_single_kernel") +
+        k_name = (single_launch_kernels(cfg, tm.get("decode_tiles_launches", 0) > 0)[0] +
                   " (router GEMV, Top-K gating, cache lookups and gate/up + SiLU*mul + down "
                   "projection of the K selected experts in one launch)")
     elif tm["ffn_fused_launches"] > 0:
@@ -600,8 +611,7 @@ def measure(torch, P, wl, pool, a, steps, warmup, full):
                           "us_per_layer_call": 1e6 / res_tok_s / cfg.n_layers,
                           "algorithmic_GBps_whole_call": layer_bytes * cfg.n_layers * res_tok_s / 1e9,
                           "frac_of_hbm_peak_whole_call": layer_bytes * cfg.n_layers * res_tok_s / 1e9 / HBM_PEAK_GBPS,
-                          "launches_per_call": (("decode_tiles_kernel" if rtm.get("decode_tiles_launches", 0) else
-                                                 "decode_single_kernel") + " + combine_chunks_kernel"
+                          "launches_per_call": (" + ".join(single_launch_kernels(cfg, rtm.get("decode_tiles_launches", 0) > 0))
                                                 if rtm["decode_single_launches"] else
                                                 "route_cache_kernel + expert FFN + combine"),
                           "main_kernel_us": (rtm["ffn_gate_up_ms"] + rtm["ffn_down_ms"] + rtm["ffn_fused_ms"] +

@@ -159,8 +159,9 @@ typedef struct {
   uint64_t fetch_launches; /* in-kernel fetch: expert-FFN launches that also fetched experts */
   uint64_t fetch_bytes;  /* bytes those launches brought in over PCIe                        */
   double fetch_ms;       /* their summed duration (fetch and compute overlap inside them)   */
-  uint64_t decode_single_launches; /* calls without a miss that ran as ONE launch (router, gating, lookups,
-                            expert FFN and combine together)                                  */
+  uint64_t decode_single_launches; /* calls without a miss whose router, gating, lookups and expert FFN
+                            ran as ONE launch (tiled bf16 and INT4 layers; the combine is a second one, not
+                            timed), or which ran as one launch altogether (small fp32 layers)  */
   double decode_single_ms; /* summed duration of those launches                              */
   uint64_t copies;       /* expert copies timed                                             */
   uint64_t copy_bytes;   /* bytes moved by them                                             */

@@ -35,3 +35,21 @@ def test_default_run_covers_both_configurations_the_bandwidth_target_names():
         text = json.dumps(want).lower()
         for value in (cfg.n_experts, cfg.top_k, cfg.d_model, cfg.d_ff, cfg.capacity, cfg.n_layers):
             assert str(value) in text, (name, value)
+
+
+def test_launch_names_follow_the_rule_of_the_library():
+    import re
+    sys.path.insert(0, ROOT)
+    import bench
+    from workload import get_config
+    text = open(os.path.join(ROOT, "paper_2602_11192_amd", "csrc", "routed_prologue.hpp")).read()
+    assert int(re.search(r"kShareFrags = (\d+)", text).group(1)) == bench.SHARED_LOGITS_KIB      # (fragments of a KiB)
+    olmoe, mixtral = get_config("olmoe_like"), get_config("mixtral_like")
+    assert bench.single_launch_kernels(olmoe) == ("decode_shared_kernel", "combine_clear_kernel")
+    assert bench.single_launch_kernels(olmoe, int4=True)[0] == "decode_shared_q4_kernel"
+    assert bench.single_launch_kernels(mixtral, tiles=True) == ("decode_tiles_kernel", "combine_chunks_kernel")
+    kernels = "".join(open(os.path.join(ROOT, "paper_2602_11192_amd", "csrc", f)).read() for f in ("ffn_fused.hip", "ffn_tiles.hip", "ffn_fused_q4.hip"))
+    for cfg in (olmoe, mixtral):
+        for kw in (dict(), dict(tiles=True), dict(int4=True)):
+            for name in bench.single_launch_kernels(cfg, **kw):
+                assert re.search(r"\b%s\(" % name, kernels), name

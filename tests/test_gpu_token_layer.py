@@ -81,6 +81,29 @@ def test_recency_is_that_of_a_launch_for_the_routing(E, K, ns, d, f, policy, gam
         cache.close()
 
 
+# (either side of the line between the one launch and the kernels per expert)
+@pytest.mark.parametrize("E,K,ns,d,f,batch,one", [(24, 2, 0, 140, 244, 64, 0), (8, 1, 0, 180, 196, 8, 0), (16, 4, 0, 192, 112, 64, 1),
+                                                  (4, 2, 1, 80, 236, 32, 1), (8, 2, 0, 64, 128, 64, 1), (8, 2, 0, 64, 128, 65, 0)])
+def test_calls_that_take_the_one_launch(E, K, ns, d, f, batch, one):
+    import torch
+    from paper_2602_11192_amd import pool as P
+    print("one launch", E, K, ns, d, f, batch, flush=True)
+    cfg = MoEConfig("token_layer", 63, "fp32", 1, d, f, E, ns, K, E, batch, 1, 0, 1.5, min(K, 3), min(K, 3), 1e-5)
+    wl = Workload(cfg)
+    cache = P.make_cache(wl, max_batch=batch)
+    cache.moe_cache_prefill_pins(0, list(range(E)))
+    ost = OracleStack(wl, keep=E)
+    ost.caches[0].pin(list(range(E)))
+    xs = np.stack([wl.tokens(s)[0] for s in range(batch)])
+    x = P.to_device(xs)
+    y = torch.empty_like(x)
+    cache.moe_cache_set_profiling(True)
+    cache.moe_layer_decode(0, x, y)
+    assert cache.moe_cache_timing()["decode_single_launches"] == one
+    assert rel_err(P.to_numpy(y), ost.decode(0, widen(xs), None).y).max() <= TOL["fp32"]
+    cache.close()
+
+
 def test_replays_of_a_captured_call():
     import torch
     from paper_2602_11192_amd import pool as P
