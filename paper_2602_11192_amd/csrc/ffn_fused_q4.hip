@@ -73,7 +73,8 @@ __device__ __forceinline__ const char* group_weights(const FfnArgs& a, int id) {
 }
 
 // The single launch has its tokens in LDS (2 to 4 tokens, 4 of 8 experts of 2048 x 2048, 24.3 -> 23.0 us, 2 of 16 of 2048 x 512 17.1 -> 16.6).  With one
-// token that leaves room for twice the gate/up items, and while every workgroup has a compute unit to itself nobody else fills its pauses (kDeepWgs).  us per layer call, token from memory / from LDS / with two items and six of W_d: 256
+// token that leaves room for twice the gate/up items, and while every workgroup has one of the 256 compute units to itself
+// nobody else fills its pauses (kDeepWgs).  us per layer call, token from memory / from LDS / with two items and six of W_d: 256
 // workgroups, 8 of 64 experts of 2048 x 1024, 18.2 / 17.6 / 16.8, 2 of 8 of 4096 x 1024 (64 of them) 20.9 / 19.9 / 18.8; beyond, 2 of 8 of 4096 x 14336
 // (896) 60.6 / 55.2 / 58.0, 2 of 16 of 4096 x 6400 (400) 31.2 / 28.9 / 30.2.  Four items at a time lose what two gain (the registers).
 constexpr int kDeepA = 2, kDeepB = 6, kDeepWgs = 256;

@@ -317,7 +317,8 @@ __global__ void __launch_bounds__(kTokenThreads) ffn_token_rowmajor(FfnArgs a, T
 // of the slots is brought up to date by the workgroup that arrives last, from the selections that the others sent past the caches; all have
 // read the table before they arrive.
 constexpr int kLayerTokens = 64;
-// Bytes of W_r, which every workgroup reads: 1 of 64 experts of 1024 x 64, 1 / 16 / 64 tokens, 18.2 / 23.2 / 40.6 us with a launch for the routing, 15.4 / 17.8 / 23.8 without.
+// Bytes of W_r, which every workgroup reads: 1 of 64 experts of 1024 x 64, 1 / 16 / 64 tokens, 18.2 / 23.2 / 40.6 us with a launch for the
+// routing, 15.4 / 17.8 / 23.8 without.
 constexpr size_t kLayerRouter = 256 << 10;
 constexpr int kLayerSteps = 4, kLayerCost = 42;
 template <bool KEEP>
@@ -486,21 +487,24 @@ hipError_t launch_ffn_rowmajor(hipStream_t s, int dtype, const FfnArgs& a, Kerne
   return hipGetLastError();
 }
 
-// A workgroup's time follows its steps, not its bytes.  The kernels per expert take 15 to 18 us, the rate at which four launches are issued, until the tokens of
-// their largest group and all pairs together cost more.
-//   In one launch with the routing (`whole`): four steps in all, and beyond as many as the root of 4/3 of the tokens.  us per call, whole / per expert: 2
-// steps, 1 / 8 / 64 tokens 9.5 / 10.7 / 14.6 and 15.1 / 19.4 / 25; 4 steps 12.2 / 13.5 / 17.5 and 15.2 / 18.7 / 29; 6 steps 16.8 / 18.0 / 22 and 15.3 / 19.3 / 30; 8
-// steps 19.8 / 21.0 / 25.2 and 15.2 / 19.9 / 34; 13 steps, 64 tokens, 32.9 and 39.  Steps are not alike, though: the time is 4.7 us and 0.78 for every load of a
-// step (two in the first projection) and 0.58 for every sum over 32 or 64 lanes, little for one over 16 (737 points to 9 %), and with few pairs per expert the
-// kernels per expert stop growing beyond 32 tokens.  `cost`, in quarter loads behind those of four steps, leaves them what they do faster: 64 tokens, 2 of
-// 24 of 140 x 244, 37.9 / 34.3; 56, 2 of 64 of 180 x 184, 33.6 / 29.8; 8, 1 of 8 of 180 x 196, 18.9 / 17.6 - but not with shared experts, a group of all tokens each:
-// 32 tokens, 2 of 4 + 1 of 80 x 236, 23.6 / 31.6.  2260 points in all, 1.8x in the mean; what is left slower are 3 and 4 tokens (6 steps, 17.2 / 16.5) and two
-// points of 64 by 4 %.
-//   Behind a routing launch, counted in thirds of an fp32 step (a bf16 step has four): two steps, in bf16 only for one token, and a third more for
-// every 32 pairs, and for every 4 tokens of the largest group that have 64 pieces of a row of W_g or W_d to add up.  us per call, a token's workgroup / per
-// expert: bf16, 2 steps, 1 / 8 / 64 / 256 tokens 12.9 / 16.4 / 19.6 / 25.8 and 15.7 / 18.7 / 33 / 74; 3 steps 15.7 / 18.3 / 21.0 / 26.1 and 16.3 / 18.2 / 31 / 64; 5 steps 19.5 / 23.9 /
-// 26.4 / 38.9 and 15.7 / 20.0 / 39 / 104; fp32, 128 / 256 tokens, 2 steps 21.3 / 28.2 and 46 / 75, 5 steps 29.2 / 38.7 and 71 / 124.  919 points: the 591 that the rule
-// takes 2.3x in the mean, the least 1.07x; of the 328 it leaves, all bf16, 203 would be slower and 93 faster by more than 5 % (two steps and 2 to 8 tokens, most of them).
+// A workgroup's time follows its steps, not its bytes.  The kernels per expert take 15 to 18 us, the rate at which four launches are
+// issued, until the tokens of their largest group and all pairs together cost more.
+//   In one launch with the routing (`whole`): four steps in all, and beyond as many as the root of 4/3 of the tokens.  us per call, whole /
+// per expert: 2 steps, 1 / 8 / 64 tokens 9.5 / 10.7 / 14.6 and 15.1 / 19.4 / 25; 4 steps 12.2 / 13.5 / 17.5 and 15.2 / 18.7 / 29; 6 steps
+// 16.8 / 18.0 / 22 and 15.3 / 19.3 / 30; 8 steps 19.8 / 21.0 / 25.2 and 15.2 / 19.9 / 34; 13 steps, 64 tokens, 32.9 and 39.  Steps are not
+// alike, though: the time is 4.7 us and 0.78 for every load of a step (two in the first projection) and 0.58 for every sum over 32 or 64
+// lanes, little for one over 16 (737 points to 9 %), and with few pairs per expert the kernels per expert hardly grow beyond 32 tokens.
+// `cost`, in quarter loads behind those of four steps, leaves them what they do faster: 64 tokens, 2 of 24 of 140 x 244, 37.9 / 34.3; 56, 2
+// of 64 of 180 x 184, 33.6 / 29.8; 8, 1 of 8 of 180 x 196, 18.9 / 17.6 - but not with shared experts, a group of all tokens each: 32
+// tokens, 2 of 4 + 1 of 80 x 236, 23.6 / 31.6.  2260 points in all, 1.8x in the mean; what is left slower are 3 and 4 tokens (6 steps, 17.2
+// / 16.5) and two points of 64 by 4 %.
+//   Behind a routing launch, counted in thirds of an fp32 step (a bf16 step has four): two steps, in bf16 only for one token, and a third
+// more for every 32 pairs, and for every 4 tokens of the largest group that have 64 pieces of a row of W_g or W_d to add up.  us per call,
+// a token's workgroup / per expert: bf16, 2 steps, 1 / 8 / 64 / 256 tokens 12.9 / 16.4 / 19.6 / 25.8 and 15.7 / 18.7 / 33 / 74; 3 steps
+// 15.7 / 18.3 / 21.0 / 26.1 and 16.3 / 18.2 / 31 / 64; 5 steps 19.5 / 23.9 / 26.4 / 38.9 and 15.7 / 20.0 / 39 / 104; fp32, 128 / 256
+// tokens, 2 steps 21.3 / 28.2 and 46 / 75, 5 steps 29.2 / 38.7 and 71 / 124.  919 points: the 591 that the rule takes 2.3x in the mean, the
+// least 1.07x; of the 328 it leaves, all bf16, 203 would be slower and 93 faster by more than 5 % (two steps and 2 to 8 tokens, most of
+// them).
 bool ffn_token_supported(int pool_layout, int dtype, int batch, int K, int n_shared, int E, int d, int f, bool whole) {
   if (pool_layout != MOE_LAYOUT_ROWMAJOR) return false;
   const int KS = K + n_shared, elem = dtype == MOE_DTYPE_FP32 ? 4 : 2, V = 16 / elem;
@@ -530,7 +534,8 @@ hipError_t launch_ffn_token(hipStream_t s, int dtype, const FfnArgs& a, int batc
 }
 
 bool token_layer_supported(int pool_layout, int dtype, int batch, int E, int C, int d) {
-  return pool_layout == MOE_LAYOUT_ROWMAJOR && dtype == MOE_DTYPE_FP32 && batch <= kLayerTokens && E <= kWave && C <= kWave && (size_t)E * d * sizeof(float) <= kLayerRouter;
+  return pool_layout == MOE_LAYOUT_ROWMAJOR && dtype == MOE_DTYPE_FP32 && batch <= kLayerTokens && E <= kWave && C <= kWave &&
+         (size_t)E * d * sizeof(float) <= kLayerRouter;
 }
 
 hipError_t launch_token_layer(hipStream_t s, const FfnArgs& a, const RouteArgs& r, const LayerState& st, const CacheCallArgs& c, uint64_t* masks,

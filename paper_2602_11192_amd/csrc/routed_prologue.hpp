@@ -1,6 +1,7 @@
-// Prologue of the single-launch decode kernels (bf16 and INT4 experts): every workgroup derives the router
-// logits (paper Eq. 1), the selected experts, the cache lookups and the groups of the call for itself, so that the
-// expert FFN can start in the same launch without a round trip through memory or the host.
+// Prologue of the single-launch decode kernels (bf16 and INT4 experts): every workgroup derives the selected
+// experts, the cache lookups and the groups of the call for itself, so that the expert FFN can start in the same
+// launch without a round trip through memory or the host.  The router logits (paper Eq. 1) it forms by itself as well
+// (route_logits), or, for one token and a large W_r, together with the other workgroups of its die (share_logits).
 #pragma once
 #include <algorithm>
 #include <type_traits>
@@ -16,11 +17,12 @@ typedef float rp_f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t rp_u32x4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------- single-launch decode: prologue pieces
-// Whether the `wgs` workgroups (of `waves` waves) of a call share the logits, and how; sh.words becomes null where not.
-// The hand-over costs what 130 KB of W_r cost every workgroup.  us per layer call, W_r whole / shared: bf16, 64 experts x 4096 (512 fragments) 32.3 /
-// 27.5, 64 x 2048 (256) 20.5 / 18.5, 48 x 1536 (144) 21.3 / 19.0, but 64 x 1024, 32 x 2048, 16 x 4096 (128) 18.2 / 18.1, 26.2 / 26.0, 40.8 / 40.5; INT4,
-// 64 x 4096 24.8 / 20.8, 48 x 1536 14.4 / 13.7, 64 x 1024 14.3 / 14.4, 32 x 2048 15.3 / 15.8.  Eight units at most, fewer to wait for: 64 x 2048 in 4 / 6
-// / 8 / 16 / 32 of them 26.7 / 26.7 / 26.8 / 26.9 / 27.2 us.  With two workgroups per die it is still no slower (64 x 2048, 16 workgroups, 18.9 / 18.6).
+// Whether the `wgs` workgroups (of `waves` waves) of a call share the logits, and how; sh.words becomes null where not. The hand-over costs
+// what 130 KB of W_r cost every workgroup.  us per layer call, W_r whole / shared: bf16, 64 experts x 4096 (512 fragments) 32.3 / 27.5, 64
+// x 2048 (256) 20.5 / 18.5, 48 x 1536 (144) 21.3 / 19.0, but 64 x 1024, 32 x 2048, 16 x 4096 (128) 18.2 / 18.1, 26.2 / 26.0, 40.8 / 40.5;
+// INT4, 64 x 4096 24.8 / 20.8, 48 x 1536 14.4 / 13.7, 64 x 1024 14.3 / 14.4, 32 x 2048 15.3 / 15.8.  One unit per 16 experts, and beyond
+// that slices only up to eight units, fewer to wait for: 64 x 2048 in 4 / 6 / 8 / 16 / 32 of them 26.7 / 26.7 / 26.8 / 26.9 / 27.2 us.
+// With two workgroups per die it is still no slower (64 x 2048, 16 workgroups, 18.9 / 18.6).
 constexpr int kShareMost = 8, kShareLeast = 2, kShareFrags = 136;
 inline bool plan_share(ShareArgs& sh, const RoutedArgs& ra, int waves, int wgs) {
   const int tiles = (ra.a.E + 15) / 16, nkb = ra.r.d / 32;
@@ -220,16 +222,14 @@ __device__ inline void lookup_small(FastTable f, RoutedLds& rl, const RoutedArgs
   }
 }
 
-// Router logits of the call's (at most 4) tokens as one small matrix product on the matrix cores, repeated by
-// every workgroup (Eq. 1): rows of W_r are the A operand, the tokens the B operand of v_mfma_f32_16x16x32_bf16.
-// W_r is read from the library's own copy in operand order (pack_router_kernel below): one wave-wide load is one
-// contiguous KiB, as for the expert weights; read row-major, the same fragment is 16 pieces of 64 bytes and the
-// address unit of the compute unit, not the cache, sets the pace (measured: 10 us against 5 us per workgroup).
-// The tokens go through LDS, so that a wave can keep 16 weight fragments in flight.  What remains (5 us for a
-// 64 x 2048 matrix) is the rate at which the caches serve the same 262 KB to all 256 compute units at once, not
-// latency: deeper batches, sixteen waves and touching the later fragments ahead of time all left it unchanged.  The waves split the expert
-// tiles and, when there are more waves than tiles, the contraction; the slices meet in LDS (pz, WAVES x 2 x 256
-// floats).
+// Router logits of the call's (at most 4) tokens as one small matrix product on the matrix cores, repeated by every workgroup (Eq. 1): rows
+// of W_r are the A operand, the tokens the B operand of v_mfma_f32_16x16x32_bf16. W_r is read from the library's own copy in operand order
+// (pack_router_kernel below): one wave-wide load is one contiguous KiB, as for the expert weights; read row-major, the same fragment is 16
+// pieces of 64 bytes and the address unit of the compute unit, not the cache, sets the pace (measured: 10 us against 5 us per workgroup).
+// The tokens go through LDS, so that a wave can keep 16 weight fragments in flight.  What remains (5 us for a 64 x 2048 matrix, 3.3 beside
+// the first touch; share_logits is for such matrices) is the rate at which the caches serve the same 262 KB to all 256 compute units at
+// once, not latency: deeper batches, sixteen waves and touching the later fragments ahead of time all left it unchanged.  The waves split
+// the expert tiles and, when there are more waves than tiles, the contraction; the slices meet in LDS (pz, WAVES x 2 x 256 floats).
 template <int WAVES>
 __device__ __forceinline__ void route_logits(const RoutedArgs& ra, float* pz, RoutedLds& rl, int tb_exp, int tb_buf) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -313,8 +313,10 @@ __device__ __forceinline__ void route_logits(const RoutedArgs& ra, float* pz, Ro
 }
 
 
-// The same for ONE token, the work shared by the workgroups of a die: a unit is 16 experts x a slice of the contraction, each workgroup forms its own, hands the 16 sums to the others through the die's L2 - a word holds a sum and the
-// number of the call, so that one store publishes both - and takes theirs.  What bounds it is a first touch and that hand-over, where the
+// The same for ONE token, the work shared by the workgroups of a die: a unit is 16 experts x a slice of the contraction; each
+// workgroup forms its own, hands the 16 sums to the others through the die's L2 - a word holds a sum and the number of the
+// call, so that one store publishes both - and takes theirs.  (Eight dies; where there are fewer, several workgroups of a
+// die form the same unit.)  What bounds it is a first touch and that hand-over, where the
 // whole matrix in every workgroup took 3.3 us at 64 x 2048 beside the first touch (the rate at which one compute unit pulls in 262 KB).
 // The wait is bounded: a unit that has not arrived after kShareTries looks is formed here, by the same instructions on the same inputs,
 // so all workgroups have the same logits whoever formed them.  The combine launch clears the words (launch_combine_chunks).
