@@ -423,8 +423,10 @@ SHARED_LOGITS_KIB = 136       # kShareFrags in csrc/routed_prologue.hpp
 
 
 def single_launch_kernels(cfg, tiles=False, int4=False):
-    """Names of the two launches of a one-token call: where W_r (in tiles of 16 experts) is this large, the workgroups form
-    the logits together and the combine clears the words they used."""
+    """Names of the launches of a one-token call whose routing and expert FFN are one: where W_r (in tiles of 16 experts) is
+    this large, the workgroups form the logits together and the combine clears the words they used.  fp32: one launch in all."""
+    if cfg.dtype == "fp32":
+        return ("token_layer_kernel",)
     shared = (cfg.n_experts + 15) // 16 * 16 * cfg.d_model * 2 >= SHARED_LOGITS_KIB * 1024
     stem = "decode_tiles_shared" if tiles and shared else "decode_tiles" if tiles else "decode_shared" if shared else "decode_single"
     return stem + ("_q4_kernel" if int4 else "_kernel"), "combine_clear_kernel" if shared else "combine_chunks_kernel"

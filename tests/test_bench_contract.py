@@ -48,8 +48,11 @@ def test_launch_names_follow_the_rule_of_the_library():
     assert bench.single_launch_kernels(olmoe) == ("decode_shared_kernel", "combine_clear_kernel")
     assert bench.single_launch_kernels(olmoe, int4=True)[0] == "decode_shared_q4_kernel"
     assert bench.single_launch_kernels(mixtral, tiles=True) == ("decode_tiles_kernel", "combine_chunks_kernel")
-    kernels = "".join(open(os.path.join(ROOT, "paper_2602_11192_amd", "csrc", f)).read() for f in ("ffn_fused.hip", "ffn_tiles.hip", "ffn_fused_q4.hip"))
-    for cfg in (olmoe, mixtral):
+    fp32 = get_config("tiny_fp32")
+    assert bench.single_launch_kernels(fp32) == ("token_layer_kernel",)
+    files = ("ffn_fused.hip", "ffn_tiles.hip", "ffn_fused_q4.hip", "ffn_rowmajor.hip")
+    kernels = "".join(open(os.path.join(ROOT, "paper_2602_11192_amd", "csrc", f)).read() for f in files)
+    for cfg in (olmoe, mixtral, fp32):
         for kw in (dict(), dict(tiles=True), dict(int4=True)):
             for name in bench.single_launch_kernels(cfg, **kw):
                 assert re.search(r"\b%s\(" % name, kernels), name
