@@ -320,7 +320,7 @@ constexpr int kLayerTokens = 64;
 // Bytes of W_r, which every workgroup reads: 1 of 64 experts of 1024 x 64, 1 / 16 / 64 tokens, 18.2 / 23.2 / 40.6 us with a launch for the
 // routing, 15.4 / 17.8 / 23.8 without.
 constexpr size_t kLayerRouter = 256 << 10;
-constexpr int kLayerSteps = 4, kLayerCost = 42;
+constexpr int kLayerSteps = 5;
 template <bool KEEP>
 __global__ void __launch_bounds__(kTokenThreads) token_layer_kernel(FfnArgs a, RouteArgs r, LayerState st, CacheCallArgs c, uint64_t* masks,
                                                                     float* __restrict__ y, int lanes_d, int lanes_f) {
@@ -489,15 +489,13 @@ hipError_t launch_ffn_rowmajor(hipStream_t s, int dtype, const FfnArgs& a, Kerne
 
 // A workgroup's time follows its steps, not its bytes.  The kernels per expert take 15 to 18 us, the rate at which four launches are
 // issued, until the tokens of their largest group and all pairs together cost more.
-//   In one launch with the routing (`whole`): four steps in all, and beyond as many as the root of 4/3 of the tokens.  us per call, whole /
-// per expert: 2 steps, 1 / 8 / 64 tokens 9.5 / 10.7 / 14.6 and 15.1 / 19.4 / 25; 4 steps 12.2 / 13.5 / 17.5 and 15.2 / 18.7 / 29; 6 steps
-// 16.8 / 18.0 / 22 and 15.3 / 19.3 / 30; 8 steps 19.8 / 21.0 / 25.2 and 15.2 / 19.9 / 34; 13 steps, 64 tokens, 32.9 and 39.  Steps are not
-// alike, though: the time is 4.7 us and 0.78 for every load of a step (two in the first projection) and 0.58 for every sum over 32 or 64
-// lanes, little for one over 16 (737 points to 9 %), and with few pairs per expert the kernels per expert hardly grow beyond 32 tokens.
-// `cost`, in quarter loads behind those of four steps, leaves them what they do faster: 64 tokens, 2 of 24 of 140 x 244, 37.9 / 34.3; 56, 2
-// of 64 of 180 x 184, 33.6 / 29.8; 8, 1 of 8 of 180 x 196, 18.9 / 17.6 - but not with shared experts, a group of all tokens each: 32
-// tokens, 2 of 4 + 1 of 80 x 236, 23.6 / 31.6.  2260 points in all, 1.8x in the mean; what is left slower are 3 and 4 tokens (6 steps, 17.2
-// / 16.5) and two points of 64 by 4 %.
+//   In one launch with the routing (`whole`): always up to five steps in all.  us per call, whole / per expert: 2 steps, 1 / 8 / 64 tokens 9.5 /
+// 10.7 / 14.6 and 15.1 / 19.4 / 25; 4 steps 12.2 / 13.5 / 17.5 and 15.2 / 18.7 / 29; 957 points 1.03x at the least.  Beyond, by what
+// either way costs, in 21sts of a us: every round of sums over 32 or 64 lanes 24, over 16 lanes 20 (the first projection has two of them)
+// here; 8 for every token of the largest group and 3 for every group there, and 120 ahead (176 by least squares: the points scatter by 2.7 us).
+// Taken: 6 of 48 of 56 x 92, 6 tokens, 15.4 / 21.8, 8 of 64 + 2 of 100 x 24, 4 tokens, 14.8 / 22.8.  Left, few pairs on wide rows and many rounds: 1 of 8
+// of 240 x 164, 7 tokens, 19.9 / 15.7, 2 of 16 of 88 x 172, 3 tokens, 17.0 / 14.9, 1 of 32 of 228 x 244, 12 tokens, 23.6 / 19.8, 4 of 16 of 192 x
+// 112, 64 tokens, 36.4 / 32.7.  Of 3239 points, 1.23x in the mean, none is more than 1.1 % slower than without the one launch.
 //   Behind a routing launch, counted in thirds of an fp32 step (a bf16 step has four): two steps, in bf16 only for one token, and a third
 // more for every 32 pairs, and for every 4 tokens of the largest group that have 64 pieces of a row of W_g or W_d to add up.  us per call,
 // a token's workgroup / per expert: bf16, 2 steps, 1 / 8 / 64 / 256 tokens 12.9 / 16.4 / 19.6 / 25.8 and 15.7 / 18.7 / 33 / 74; 3 steps
@@ -509,15 +507,12 @@ bool ffn_token_supported(int pool_layout, int dtype, int batch, int K, int n_sha
   if (pool_layout != MOE_LAYOUT_ROWMAJOR) return false;
   const int KS = K + n_shared, elem = dtype == MOE_DTYPE_FP32 ? 4 : 2, V = 16 / elem;
   if (f % V != 0 || KS > kTokenThreads || token_lds(KS, d, f) > kTokenLds || (int64_t)KS * 3 * d * f * elem > kTokenMost) return false;
-  const int64_t steps_h = token_steps((int64_t)KS * f, d / V), steps_o = token_steps((int64_t)KS * d, f / V), steps = steps_h + steps_o;
+  const int64_t steps = token_steps((int64_t)KS * f, d / V) + token_steps((int64_t)KS * d, f / V);
   const int64_t pairs = (int64_t)batch * K, largest8 = n_shared > 0 ? 8 * (int64_t)batch : 8 * pairs / std::min<int64_t>(pairs, E);     // (in the mean)
-  if (whole && steps <= kLayerSteps) return true;
   if (whole) {
-    const auto sums = [&](int64_t rows, int pieces) { return token_rounds(rows, pieces) * (token_lanes(pieces) > 16 ? 3 : 1); };
-    const int64_t cost = 4 * (2 * steps_h + steps_o) + 2 * sums((int64_t)KS * f, d / V) + sums((int64_t)KS * d, f / V) - kLayerCost;
-    const int64_t others = 2 * std::min<int64_t>(batch, 32 + 6 * pairs / std::min<int64_t>(pairs, E)) + std::max(K - 2, 0);
-    const int64_t beyond = steps - kLayerSteps;
-    if (beyond * beyond * 3 <= 4 * batch && (n_shared > 0 || cost <= 0 || cost * cost <= 76 * others)) return true;
+    const auto sums = [&](int64_t rows, int pieces) { return token_rounds(rows, pieces) * (token_lanes(pieces) > 16 ? 24 : 20); };
+    const int64_t others = 120 + largest8 + 3 * std::min<int64_t>(pairs, E);
+    if (steps <= kLayerSteps || 2 * sums((int64_t)KS * f, d / V) + sums((int64_t)KS * d, f / V) <= others) return true;
   }
   const int64_t rounds = ((int64_t)batch + 255) / 256;
   const int64_t pieces64 = (d / V + 63) / 64 + (f / V + 63) / 64;
