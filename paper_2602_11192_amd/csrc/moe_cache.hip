@@ -45,9 +45,12 @@ int fail(int code, const char* fmt, ...) {
 // whose experts are all resident the GEMM may take over earlier, from 4 tokens (INT4: 5), where
 //   - bf16: the call reads enough weights (every pair on an expert of its own) to outweigh the second launch: 350 MB (4
 //     tokens, the kernel / the GEMM: 8 experts of 1024 x 4096, 201 MB, 32 / 59 us, 32 of 2048 x 512, 100 MB, 27 / 38);
-//   - INT4, where more pairs cost the kernel more than more bytes: the experts of all pairs, once each, are 95 MB, and 120 f / d.  Kernel /
+//   - INT4, where more pairs cost the kernel more than more bytes: the experts of all pairs, once each, are 100 MB (125 for one expert a token), and 120 f / d.  Kernel /
 //     GEMM: 12 experts of 3072 x 1024, 8 tokens (85) 31.8 / 34.1, 10 (106) 36 / 34.5, 16 of 2048 x 1024, 12 (85) 30.6 / 31.8, 16 (113) 33.2 / 32.3,
-//     32 of 4096 x 512, 8 (113) 40.9 / 36.7, but one of 16 of 2048 x 2048, 16 (113) 35.9 / 38.6; and
+//     32 of 4096 x 512, 8 (113) 40.9 / 36.7, but one of 8 of 3072 x 1536, 12 (96) 31.9 / 35.3, 6 of 60 of 2560 x 544, 7 (99) 35.2 / 38.3, one of 16
+//     of 2048 x 2048, 16 (113) 35.9 / 38.6, of 3072 x 2016, 10 (105) 36.3 / 38.1.  On many experts of few columns, which the second term leaves out,
+//     the tokens of all pairs decide, 64000 columns of them: 8 of 64 + 2 of 768 x 1696, 15 (115200) 55.0 / 50.3, 8 of 64 of 1024 x 7136, 8 (65536)
+//     139.9 / 135.7, 4 of 64 of 1024 x 4736, 13 (53248) 86.9 / 91.1; and
 //   - its down pass has workgroups enough - groups x blocks of 128 (INT4: 256) rows - to fill the units, each of them working
 //     through all of d_ff, in proportion to what more tokens cost the other kernel: 160 (INT4 96) and 1000 / tokens of them.
 //     Kernel / GEMM, bf16: 4 Phi-3.5-MoE-like tokens (256 workgroups) 182 / 172, 4 Mixtral-like (256) 275 / 266, 6 on 16
@@ -63,8 +66,9 @@ FfnPlan plan_ffn(int pool_layout, int d, int f, int batch, int K, bool resident,
   const bool shape = p.q4 || (p.tiled && ffn_fused_supported(d, f, 1));
   const int64_t down_wgs = (int64_t)groups * (p.q4 ? (d + 255) / 256 : (d + 127) / 128);
   const uint64_t pair_bytes = (uint64_t)batch * K * expert_bytes;
-  const bool weighty = p.q4 ? pair_bytes >= 95000000ull && pair_bytes / f >= 120000000ull / d : groups * expert_bytes >= 350000000ull;
-  const bool heavy = resident && weighty && down_wgs >= (p.q4 ? 96 : 160) && down_wgs * batch >= 1000;
+  const bool weighty = p.q4 ? pair_bytes >= (K > 1 ? 100000000ull : 125000000ull) && pair_bytes / f >= 120000000ull / d : groups * expert_bytes >= 350000000ull;
+  const bool wide = p.q4 && groups * expert_bytes >= 120000000ull && (int64_t)batch * (K + n_shared) * d >= 64000 && down_wgs >= 192;
+  const bool heavy = resident && (wide || (weighty && down_wgs >= (p.q4 ? 96 : 160) && down_wgs * batch >= 1000));
   const int most = heavy ? (p.q4 ? 4 : 3) : p.q4 ? 16 : fused_max_tokens(f);
   p.fused = shape && batch <= most;
   p.gemm = !p.fused && (shape || (p.tiled && batch > fused_max_tokens(f)));
