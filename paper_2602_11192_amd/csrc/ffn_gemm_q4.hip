@@ -269,23 +269,26 @@ __global__ void __launch_bounds__(64 * kWaves * KG, MINW) ffn_gemm_q4_kernel(Ffn
 //   tiles of 32: 8 experts of 4096 x 14336 (2016 + 144) 239 / 205 / 189, 16 of 4096 x 1024 (288 + 288) 49 / 42.5 / 41, 24 of 2048 x 768 (348
 //     + 232) 37.4 / 35.9 / 37.5, 32 of 2048 x 512 (456 + 456; 200 tokens) 46.5 / 45.4 / 57, 64 of 2048 x 1024 (1280 + 640; 64 tokens)
 //     59 / 60.5 / 62.
-//   Four need four steps each: 16 of 1024 x 512 (144 + 72) 27.6 / 26.1 / 27.  Two need two each, and beyond 320 workgroups four: 64 of 768 x 288, 63 tokens (395
+//   Four need four steps each: 16 of 1024 x 512 (144 + 72) 27.6 / 26.1 / 27; and, as they fill a unit, a unit for every workgroup that finds a tile:
+//     40 of 2560 x 448, 62 tokens (280 + 400) 39.9 / 38.2 / 45.1.  Two need two each, and beyond 320 workgroups four: 64 of 768 x 288, 63 tokens (395
 //     with 6 steps, 237 with 4.5) 27.9 / 28.9, 60 of 1280 x 288, 241 tokens (450 with 10, 450 with 4.5) 35.9 / 37.9, tiles of 64, 8 of 256 x 128, 385 tokens
 //     (2 steps) 23.1 / 24.6.
 //   tiles of 64: 8 of 4096 x 14336, 400 tokens (4480 + 320) 571 / 534, 8 of 2048 x 1024, 300 (272 + 136) 58.3 / 52, 600 (416 + 208) 66.8 / 68.3.
-constexpr int kSplit4 = 320, kSplitSteps = 4, kSplitFew = 2, kSplit2 = 512, kSplitLarge = 352;
+constexpr int kUnits = 256, kSplit4 = 320, kSplitSteps = 4, kSplitFew = 2, kSplit2 = 512, kSplitLarge = 352;
 constexpr int kSmallTile = 5, kLargeTile = 6, kStreamedTile = 7;     // log2 of the tokens per tile
 bool small_tile(int64_t load, int groups) { return load <= (int64_t)56 * groups; }
 
 }  // namespace
 
-Q4Split split_ffn_gemm_q4(int batch, int KS, int groups, int d, int f) {
-  const int64_t load = (int64_t)batch * KS;
+Q4Split split_ffn_gemm_q4(int batch, int KS, int n_shared, int groups, int d, int f) {
+  const int64_t load = (int64_t)batch * KS, routed = groups - n_shared, tile = 1 << kSmallTile;
   const bool small = small_tile(load, groups);
   const int64_t items = groups + (load >> (small ? kSmallTile : kLargeTile));     // upper bound
+  // (even loads)
+  const int64_t tiles = routed * ((load - (int64_t)batch * n_shared + routed * tile - 1) / (routed * tile)) + n_shared * ((batch + tile - 1) / tile);
   const auto pass = [&](int units, int kblocks, int step) {
-    const int64_t wgs = items * ((units + kWaves - 1) / kWaves);
-    if (small && wgs <= kSplit4 && kblocks >= 4 * kSplitSteps * step) return 4;
+    const int64_t blocks = (units + kWaves - 1) / kWaves, wgs = items * blocks;
+    if (small && wgs <= kSplit4 && tiles * blocks <= kUnits && kblocks >= 4 * kSplitSteps * step) return 4;
     return wgs <= (small ? kSplit2 : kSplitLarge) && kblocks >= 2 * (wgs <= kSplit4 ? kSplitFew : kSplitSteps) * step ? 2 : 1;
   };
   return {pass(f / 16, d / 32, 4), pass(d / 64, f / 32, 2)};

@@ -73,7 +73,7 @@ FfnPlan plan_ffn(int pool_layout, int d, int f, int batch, int K, bool resident,
   p.fused = shape && batch <= most;
   p.gemm = !p.fused && (shape || (p.tiled && batch > fused_max_tokens(f)));
   // (from the whole call and the experts, neither the wave nor the spare buffers: however a call is run, a token's sums are the same)
-  p.split = split_ffn_gemm_q4(call_batch, K + n_shared, (int)std::min<int64_t>((int64_t)call_batch * K, E) + n_shared, d, f);
+  p.split = split_ffn_gemm_q4(call_batch, K + n_shared, n_shared, (int)std::min<int64_t>((int64_t)call_batch * K, E) + n_shared, d, f);
   return p;
 }
 
@@ -986,7 +986,7 @@ int moe_layer_prefill(moe_cache_t* c, int32_t layer, const void* x_dev, const fl
   // Tiles for experts that cross the link, unless all are known to be resident (8 / 33 / 512 INT4 tokens through a resident
   // OLMoE-like layer: 142 / 173 / 353 us with them, 50 / 67 / 191 with the tiles of resident calls).
   const bool streamed = !c->full[layer];
-  const Q4Split split = streamed ? Q4Split{1, 1} : split_ffn_gemm_q4(n_tokens, KS, g_max, d, cf.d_ff);
+  const Q4Split split = streamed ? Q4Split{1, 1} : split_ffn_gemm_q4(n_tokens, KS, cf.n_shared, g_max, d, cf.d_ff);
   a.work = q4 ? plan_ffn_gemm_q4(n_tokens, KS, g_max, streamed, split) : plan_ffn_gemm(n_tokens, KS, g_max, d, cf.d_ff, streamed);
   HIPCHK(launch_route_cache(s, cf.dtype, ra, state_of(c, layer), c->t, a, RouteScratch{c->o, c->o_bytes, c->n_arrive}, KernelEvents{}));
 

@@ -219,7 +219,7 @@ bool ffn_fused_q4_supported(int d, int f, int max_count);
 hipError_t launch_ffn_fused_q4(hipStream_t s, const FfnArgs& a, KernelEvents ev);
 // Groups of waves that split the contraction of either pass of the INT4 grouped GEMM (1, 2 or 4); part of the order in which a token's sums are formed.
 struct Q4Split { int gate_up, down; };
-Q4Split split_ffn_gemm_q4(int batch, int KS, int groups, int d, int f);
+Q4Split split_ffn_gemm_q4(int batch, int KS, int n_shared, int groups, int d, int f);
 WorkPlan plan_ffn_gemm_q4(int batch, int KS, int g_max, bool streamed, const Q4Split& split);
 hipError_t launch_ffn_gemm_q4(hipStream_t s, const FfnArgs& a, const Q4Split& split, KernelEvents gate_up, KernelEvents down);
 // Which expert-FFN kernels run a call of `batch` tokens on experts of the given layout and shape.
