@@ -1134,6 +1134,15 @@ int moe_test_share_blind(moe_cache_t* c, int32_t which) {
   return MOE_OK;
 }
 
+// What runs the experts of a call on an INT4 layer that is all in memory: 0, the fused kernel; else the grouped GEMM, 10 x the groups of waves that split
+// the contraction of its gate/up pass + those of its down pass.
+int moe_test_int4_plan(int32_t d, int32_t f, int32_t E, int32_t K, int32_t n_shared, int32_t batch) {
+  const int groups = std::min(batch * K, E) + n_shared;
+  const uint64_t expert_bytes = (uint64_t)d * f * 3 * 9 / 16;
+  const FfnPlan p = plan_ffn(MOE_LAYOUT_TILED_INT4, d, f, batch, K, true, groups, expert_bytes, batch, E, n_shared);
+  return p.gemm ? 10 * p.split.gate_up + p.split.down : 0;
+}
+
 // The recency a layer's table holds, after all enqueued work: per expert the time of its last lookup (0: not resident) and its discounted count
 // (tick, score: host, [n_experts]); the number of lookups so far.
 int moe_test_recency(moe_cache_t* c, int32_t layer, uint64_t* tick, double* score, int64_t* clock) {
